@@ -98,7 +98,7 @@ def draw(rng):
     if kind == "qwen30":
         weights = rng.choice(("bf16", "bf16", "bf16", "fp8"))
         tp = rng.choice((1, 1, 2, 4, 8)) if weights == "bf16" else rng.choice((1, 2))
-        return _layer(QWEN30, _log_int(rng, 1, 65536), tp=tp, weights=weights)
+        return _layer(QWEN30, _log_int(rng, 1, 65536 if weights == "bf16" else 49152), tp=tp, weights=weights)
     if kind == "qwen235":
         weights = rng.choice(("bf16", "bf16", "fp8"))
         return _layer(QWEN235, _log_int(rng, 1, 32768), ep_rank=rng.randint(0, 7), weights=weights,
@@ -106,7 +106,7 @@ def draw(rng):
     if kind == "deepseek":
         weights = rng.choice(("bf16", "fp8", "fp8"))
         fp8_acts = weights == "fp8" and rng.random() < 0.4
-        tokens = _log_int(rng, 256 if fp8_acts else 1, 32768)
+        tokens = _log_int(rng, 256 if fp8_acts else 1, 24576)
         zipf = rng.choice((0.0, 0.0, 0.0, 1.2)) if tokens <= 1024 else 0.0
         return _layer(DEEPSEEK, tokens, weights=weights, fp8_acts=fp8_acts, zipf=zipf,
                       ep_rank=rng.randint(0, 7), tp=rng.choice((1, 2, 2, 4)))
