@@ -1118,83 +1118,142 @@ __global__ __launch_bounds__(256) void ffn_skinny_kernel(
 }
 
 // ------------------------------------------------------------ fp32 GEMM
-// Plain VALU kernel for the fp32 configuration: 64x64 tile, 16x16 threads,
-// 4x4 outputs per thread, K step 32; the next step's operands are fetched into
-// registers while the current step is computed from LDS.
+// fp32 layers on v_mfma_f32_32x32x2_f32 (fp32 products and sums).  Tile 32 rows x
+// 32 output columns (DUAL: with the matching up rows).  Operands go global -> LDS
+// directly in chunks of 128 K values (512-byte rows: whole cache lines) into a
+// ring of as many chunks as 144 KB hold; the four wavefronts each multiply a
+// quarter of every chunk and their sums are added in a fixed order at the end.
+// These layers are small (64 tokens, hidden 256, 8 experts, I 512), so a launch is
+// one workgroup's latency chain: small tiles put it on as many CUs as there are,
+// the K split makes the arithmetic a quarter as long, and a short K is in flight
+// as a whole before the first wait.  The fp32 matrix rate (128 multiply-adds per
+// cycle and CU) needs 24 bytes per cycle even with this small tile, so long
+// launches are not bound by the loads either.
+// Measured against 64 x 64 tiles of VALU arithmetic (64-token layer, GEMM-1 / -2):
+// 30.2 / 30.6 -> 7.0 / 5.9 us; 2048 rows, hidden = I = 512: 58 / 34 -> 36 / 22 us;
+// 8192 rows, hidden 2048, I 1024 (84 TFLOP/s): 1050 / 546 -> 813 / 500 us.  The same
+// tile without LDS (lanes reading 16 bytes of 32 rows each) was slower: 13 / 15 us
+// on the small layer, 2033 / 1447 us on the large one.
+// LDS row r keeps its 16-byte piece p at slot p ^ (r & 15).
+constexpr int kF32Chunk = 128;                        // K values per chunk
+template <bool DUAL> struct F32Ring {
+  static constexpr int kRows = DUAL ? 96 : 64;        // activation rows | weight rows
+  static constexpr int kSlots = kRows * (kF32Chunk / 4);
+  static constexpr int kStages = DUAL ? 3 : 4;        // 144 KB / 128 KB
+  static constexpr int kLds = kStages * kSlots * 16;
+};
+
+template <bool DUAL>
+__device__ __forceinline__ void ffn_f32_body(const float* __restrict__ A,
+                                             const float* __restrict__ Be0,
+                                             const float* __restrict__ Be1, float* __restrict__ C,
+                                             int N, int K, int row0, int row1, int n0, uint4* smem) {
+  constexpr int NB = DUAL ? 2 : 1, NS = F32Ring<DUAL>::kStages, SLOTS = F32Ring<DUAL>::kSlots;
+  constexpr int NLD = F32Ring<DUAL>::kRows / 8;       // load instructions per wavefront and chunk
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = lane >> 5, l31 = lane & 31;
+  const int brows = N - n0 < 32 ? N - n0 : 32;
+  auto rsrc = [&](const float* p, int rows) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, int(size_t(rows) * K * 4), 0x00020000);
+  };
+  const __amdgpu_buffer_rsrc_t ra = rsrc(A + size_t(row0) * K, row1 - row0);
+  const __amdgpu_buffer_rsrc_t rb0 = rsrc(Be0 + size_t(n0) * K, brows);
+  const __amdgpu_buffer_rsrc_t rb1 = rsrc((DUAL ? Be1 : Be0) + size_t(n0) * K, brows);
+  // One instruction fills two LDS rows; instruction i of wavefront w: rows
+  // (i*4 + w)*2 + lane/32, the lane that owns slot s of row r fetches piece s ^ (r&15).
+  // Rows past the tile (or past N) and pieces past K are out of range: zeros.
+  auto issue = [&](int c) {
+    uint4* const st = smem + (c % NS) * SLOTS;
+#pragma unroll
+    for (int i = 0; i < NLD; ++i) {
+      const int pair = i * 4 + wave, row = pair * 2 + h, local = row & 31;
+      const int k = c * kF32Chunk + ((l31 ^ (row & 15)) * 4);
+      const int off = k < K ? (local * K + k) * 4 : 0x7fffffff;
+      lptr_t const dst = (lptr_t)(st + pair * 64);
+      if (i < 4) __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, dst, 16, off, 0, 0, 0);
+      else if (i < 8) __builtin_amdgcn_raw_ptr_buffer_load_lds(rb0, dst, 16, off, 0, 0, 0);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(rb1, dst, 16, off, 0, 0, 0);
+    }
+  };
+  f32x16 acc[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) acc[j][q] = 0.f;
+  const int nch = (K + kF32Chunk - 1) / kF32Chunk;
+#pragma unroll
+  for (int c = 0; c < NS; ++c)
+    if (c < nch) issue(c);
+  for (int c = 0; c < nch; ++c) {
+    // chunk c must have landed; up to NS-1 younger ones stay in flight
+    const int younger = nch - 1 - c;
+    if (younger >= NS - 1) wait_vmcnt<(NS - 1) * NLD>();
+    else if (NS > 3 && younger == 2) wait_vmcnt<2 * NLD>();
+    else if (younger == 1) wait_vmcnt<NLD>();
+    else wait_vmcnt<0>();
+    asm volatile("s_barrier" ::: "memory");
+    const uint4* const st = smem + (c % NS) * SLOTS;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      // MFMA i of lane half h multiplies element i of the same piece of both operands
+      const int p = (wave * 8 + h * 4 + q) ^ (l31 & 15);
+      const float4 a = __builtin_bit_cast(float4, st[l31 * 32 + p]);
+      float4 b[NB];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) b[j] = __builtin_bit_cast(float4, st[((j + 1) * 32 + l31) * 32 + p]);
+      const float av[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+          const float bv[4] = {b[j].x, b[j].y, b[j].z, b[j].w};
+          acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[i], acc[j], 0, 0, 0);
+        }
+    }
+    if (c + NS < nch) {
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the stage has been read by all
+      issue(c + NS);
+    }
+  }
+  // add the four partial sums in a fixed order: wavefront w finishes registers 4w..4w+3
+  __syncthreads();
+  float* const red = reinterpret_cast<float*>(smem);   // [4][NB][16][64]
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) red[((wave * NB + j) * 16 + q) * 64 + lane] = acc[j][q];
+  __syncthreads();
+#pragma unroll
+  for (int qq = 0; qq < 4; ++qq) {
+    const int q = wave * 4 + qq;
+    float v[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      auto part = [&](int w) { return red[((w * NB + j) * 16 + q) * 64 + lane]; };
+      v[j] = ((part(0) + part(1)) + part(2)) + part(3);
+    }
+    // D layout: lane l, register q -> row (q/4)*8 + (l/32)*4 + q%4, col l%32
+    const int row = row0 + (q >> 2) * 8 + h * 4 + (q & 3), col = n0 + l31;
+    if (row >= row1 || col >= N) continue;
+    if constexpr (DUAL) v[0] = v[0] / (1.0f + expf(-v[0])) * v[NB - 1];
+    C[size_t(row) * N + col] = v[0];
+  }
+}
+
 template <bool DUAL>
 __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ A,
                                                      const float* __restrict__ B0,
                                                      const float* __restrict__ B1,
                                                      float* __restrict__ C, int N, int K,
                                                      const int32_t* __restrict__ tiles) {
-  constexpr int TB = 64, TK = 32, PER = TB * TK / 256;
-  __shared__ __align__(16) float As[TK][TB + 4];
-  __shared__ __align__(16) float Bg[TK][TB + 4];
-  __shared__ __align__(16) float Bu[DUAL ? TK : 1][TB + 4];
-  const int n_ntiles = (N + TB - 1) / TB;
-  const int mtile = blockIdx.x / n_ntiles, ntile = blockIdx.x % n_ntiles;
+  extern __shared__ uint4 smem[];
+  const int n_ntiles = (N + 31) / 32;
+  const int mtile = blockIdx.x / n_ntiles, ntile = blockIdx.x - mtile * n_ntiles;
   if (mtile >= tiles[0]) return;
   const int e = tiles[1 + kTileRec * mtile], row0 = tiles[2 + kTileRec * mtile],
             row1 = tiles[3 + kTileRec * mtile];
-  const int n0 = ntile * TB;
-  const float* Be0 = B0 + size_t(e) * N * K;
-  const float* Be1 = DUAL ? B1 + size_t(e) * N * K : nullptr;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float g[4][4] = {}, u[4][4] = {};
-  float ra[PER], rg[PER], ru[PER];
-  auto fetch = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int idx = threadIdx.x + i * 256;
-      const int r = idx / TK, k = k0 + idx % TK;
-      int ar = row0 + r; ar = ar < row1 ? ar : row1 - 1;
-      int bn = n0 + r;   bn = bn < N ? bn : N - 1;
-      ra[i] = k < K ? A[size_t(ar) * K + k] : 0.f;
-      rg[i] = k < K ? Be0[size_t(bn) * K + k] : 0.f;
-      if (DUAL) ru[i] = k < K ? Be1[size_t(bn) * K + k] : 0.f;
-    }
-  };
-  fetch(0);
-  for (int k0 = 0; k0 < K; k0 += TK) {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int idx = threadIdx.x + i * 256;
-      const int r = idx / TK, kk = idx % TK;
-      As[kk][r] = ra[i];
-      Bg[kk][r] = rg[i];
-      if (DUAL) Bu[kk][r] = ru[i];
-    }
-    __syncthreads();
-    if (k0 + TK < K) fetch(k0 + TK);
-#pragma unroll
-    for (int kk = 0; kk < TK; ++kk) {
-      // rows of the LDS tiles are 68 floats, so groups of four stay 16-byte aligned
-      const float4 a4 = *reinterpret_cast<const float4*>(&As[kk][ty * 4]);
-      const float4 g4 = *reinterpret_cast<const float4*>(&Bg[kk][tx * 4]);
-      const float4 u4 = DUAL ? *reinterpret_cast<const float4*>(&Bu[kk][tx * 4]) : make_float4(0.f, 0.f, 0.f, 0.f);
-      const float a[4] = {a4.x, a4.y, a4.z, a4.w}, bg[4] = {g4.x, g4.y, g4.z, g4.w},
-                  bu[4] = {u4.x, u4.y, u4.z, u4.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          g[i][j] = fmaf(a[i], bg[j], g[i][j]);
-          if (DUAL) u[i][j] = fmaf(a[i], bu[j], u[i][j]);
-        }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = row0 + ty * 4 + i, col = n0 + tx * 4 + j;
-      if (row < row1 && col < N) {
-        float v = g[i][j];
-        if (DUAL) v = v / (1.0f + expf(-v)) * u[i][j];
-        C[size_t(row) * N + col] = v;
-      }
-    }
+  ffn_f32_body<DUAL>(A, B0 + size_t(e) * N * K, DUAL ? B1 + size_t(e) * N * K : nullptr, C, N, K,
+                     row0, row1, ntile * 32, smem);
 }
 
 template <int BM, int BN1, int WM, int WN1, int BN2, int WN2>
@@ -1328,18 +1387,22 @@ hipError_t launch_expert_ffn(const moe_config& c, int n_experts, const void* xs,
                              hipStream_t s) {
   const int H = c.hidden, I = c.inter_local;
   if (c.act_dtype == MOE_F32) {
-    const int BM = 64;
-    const int max_mt = rows_capacity / BM + n_experts;
-    MOE_LAUNCH(MOE_K_FFN_TILES, ffn_tiles_kernel, dim3(1), dim3(256), 0, s, offsets, n_experts, BM,
-                       rows_capacity, ws.tiles, max_mt < ws.max_tiles ? max_mt : ws.max_tiles, 0, 0,
-             (int32_t*)nullptr, (int32_t*)nullptr);
-    MOE_LAUNCH(MOE_K_FFN_GEMM1, ffn_f32_kernel<true>, dim3(size_t(max_mt) * ((I + 63) / 64)), dim3(256), 0,
-                       s, static_cast<const float*>(xs), static_cast<const float*>(w_gate),
-                       static_cast<const float*>(w_up), static_cast<float*>(ws.hmid), I, H,
-                       ws.tiles);
-    MOE_LAUNCH(MOE_K_FFN_GEMM2, ffn_f32_kernel<false>, dim3(size_t(max_mt) * ((H + 63) / 64)), dim3(256), 0,
-                       s, static_cast<const float*>(ws.hmid), static_cast<const float*>(w_down),
-                       nullptr, static_cast<float*>(ys), H, I, ws.tiles);
+    const int max_mt = rows_capacity / 32 + n_experts;
+    MOE_LAUNCH(MOE_K_FFN_TILES, ffn_tiles_kernel, dim3(1), dim3(256), 0, s, offsets, n_experts, 32,
+               rows_capacity, ws.tiles, max_mt < ws.max_tiles ? max_mt : ws.max_tiles, 0, 0,
+               (int32_t*)nullptr, (int32_t*)nullptr);
+    auto k1 = ffn_f32_kernel<true>;
+    auto k2 = ffn_f32_kernel<false>;
+    static uint64_t opted1 = 0, opted2 = 0;
+    lds_opt_in(reinterpret_cast<const void*>(k1), F32Ring<true>::kLds, opted1);
+    lds_opt_in(reinterpret_cast<const void*>(k2), F32Ring<false>::kLds, opted2);
+    MOE_LAUNCH(MOE_K_FFN_GEMM1, k1, dim3(size_t(max_mt) * ((I + 31) / 32)), dim3(256),
+               F32Ring<true>::kLds, s, static_cast<const float*>(xs), static_cast<const float*>(w_gate),
+               static_cast<const float*>(w_up), static_cast<float*>(ws.hmid), I, H, ws.tiles);
+    MOE_LAUNCH(MOE_K_FFN_GEMM2, k2, dim3(size_t(max_mt) * ((H + 31) / 32)), dim3(256),
+               F32Ring<false>::kLds, s, static_cast<const float*>(ws.hmid),
+               static_cast<const float*>(w_down), (const float*)nullptr, static_cast<float*>(ys), H, I,
+               ws.tiles);
     return hipGetLastError();
   }
   // rows per expert can only be bounded from above on the host; pick the M
