@@ -17,7 +17,7 @@
 // per workgroup, operands global -> LDS directly, LDS rings; GEMM-2 of short groups
 // of many experts: up to 128 rows x 512 weight rows), ffn_skinny_kernel
 // (decode and fp8 weights: weight streaming, K split across wavefronts, no LDS
-// staging) and the register-staged ffn_gemm_kernel for the shapes in between.
+// staging) and ffn_shortk_kernel (GEMM-2 of narrow TP slices: K up to 128).
 // fp8 weights: the weight-streaming kernel widens the e4m3 codes to bf16 in
 // registers (exact) and multiplies the fp32 partial sum of each 128-deep K block
 // by the 128x128 block scale; the tall-tile kernel keeps the codes in its LDS
@@ -33,10 +33,17 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int BK = 64;
-
-__device__ __forceinline__ int swz(int row, int piece) { return row * 8 + (piece ^ (row & 7)); }
+// Two values rounded to bf16 (nearest even), low | high half: v_cvt_pk_bf16_f32.  Left
+// to the compiler and not written as inline assembly: it knows how long a matrix
+// instruction's result takes to arrive and keeps that distance, which it does not do
+// for the operands of an asm statement.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  const f32x2 v = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
 
 __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
   return __builtin_bit_cast(uint16_t, (__bf16)f);   // round to nearest even
@@ -73,18 +80,18 @@ static_assert(size_t(kPartFloats) * 4 == kFfnPartBytes, "partial-sum slot size")
 #ifndef MOE_RING_EXTRA_A
 #define MOE_RING_EXTRA_A 2
 #endif
-// `balance`: an expert's rows are cut into ceil(M/bm) tiles of equal height
-// (rounded up to 32 rows) instead of full tiles plus a short tail.
+// An expert's rows are cut into ceil(M/bm) tiles of equal height (rounded up to 32
+// rows) instead of full tiles plus a short tail.
 __global__ __launch_bounds__(256) void ffn_tiles_kernel(const int32_t* __restrict__ offsets,
                                                        int n_experts, int bm, int rows_capacity,
                                                        int32_t* __restrict__ tiles, int max_tiles,
-                                                       int balance, int bm_second,
+                                                       int bm_second,
                                                        int32_t* __restrict__ tiles_second,
                                                        int32_t* __restrict__ tickets) {
   __shared__ int32_t start[513];
   __shared__ int32_t off[513];
   // arrival counters of the K-split tiles of the two GEMM launches that follow
-  if (blockIdx.x == 0 && tickets)
+  if (blockIdx.x == 0)
     for (int i = threadIdx.x; i < 2 * kSplitTickets; i += blockDim.x) tickets[i] = 0;
   // a second workgroup, when launched, builds a second table with its own tile height
   if (blockIdx.x == 1) {
@@ -133,11 +140,8 @@ __global__ __launch_bounds__(256) void ffn_tiles_kernel(const int32_t* __restric
       if (start[mid] <= t) e = mid; else e_hi = mid;
     }
     const int lo = off[e], hi = off[e + 1];
-    int step = bm;
-    if (balance) {
-      const int nt = (hi - lo + bm - 1) / bm;
-      step = (((hi - lo + nt - 1) / nt) + 31) / 32 * 32;
-    }
+    const int nt = (hi - lo + bm - 1) / bm;
+    const int step = (((hi - lo + nt - 1) / nt) + 31) / 32 * 32;
     const int r = lo + (t - start[e]) * step;
     tiles[1 + kTileRec * t] = e;
     tiles[2 + kTileRec * t] = r;
@@ -145,137 +149,6 @@ __global__ __launch_bounds__(256) void ffn_tiles_kernel(const int32_t* __restric
     tiles[4 + kTileRec * t] = start[e];
     tiles[5 + kTileRec * t] = (hi - lo + step - 1) / step;
   }
-}
-
-// ------------------------------------------------------------ MFMA GEMM
-// C[rows, N] = A[rows, K] * B_e[N, K]^T over the M tiles of the table.
-// DUAL: B0 = gate, B1 = up, C = silu(A B0^T) .* (A B1^T).
-// Register-staged variant for bf16 shapes whose K is not a multiple of 64 (it
-// zero-fills the K tail).
-template <int BM, int BN, int WM, int WN, bool DUAL>
-__global__ __launch_bounds__(256) void ffn_gemm_kernel(
-    const uint16_t* __restrict__ A, const void* __restrict__ B0, const void* __restrict__ B1,
-    uint16_t* __restrict__ C, int N, int K, const int32_t* __restrict__ tiles) {
-  constexpr int BROWS = DUAL ? 2 * BN : BN;
-  constexpr int WGN = BN / WN;
-  constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int NACC = DUAL ? 2 : 1;
-  static_assert((BM / WM) * WGN == 4, "four wavefronts");
-  constexpr int A_PER = BM * 8 / 256;
-  constexpr int B_PER = BROWS * 8 / 256;
-
-  // dynamic LDS: A double buffer, then B double buffer
-  extern __shared__ uint4 smem[];
-  uint4 (*As)[BM * 8] = reinterpret_cast<uint4 (*)[BM * 8]>(smem);
-  uint4 (*Bs)[BROWS * 8] = reinterpret_cast<uint4 (*)[BROWS * 8]>(smem + 2 * BM * 8);
-
-  const int n_ntiles = (N + BN - 1) / BN;
-  const int mtile = blockIdx.x / n_ntiles, ntile = blockIdx.x % n_ntiles;
-  if (mtile >= tiles[0]) return;
-  const int e = tiles[1 + kTileRec * mtile], row0 = tiles[2 + kTileRec * mtile],
-            row1 = tiles[3 + kTileRec * mtile];
-  const int n0 = ntile * BN;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WGN, wn = wave % WGN;
-  const int ksteps = (K + BK - 1) / BK;
-  const size_t wbytes = 2;
-  const char* Be0 = static_cast<const char*>(B0) + size_t(e) * N * K * wbytes;
-  const char* Be1 = DUAL ? static_cast<const char*>(B1) + size_t(e) * N * K * wbytes : nullptr;
-
-  uint4 ra[A_PER], rb[B_PER];
-  auto gload = [&](int ks) {
-    {
-      const int lrow = tid >> 3, piece = tid & 7;
-      const int kcol = ks * BK + piece * 8;
-#pragma unroll
-      for (int i = 0; i < A_PER; ++i) {
-        int r = row0 + lrow + 32 * i;
-        r = r < row1 ? r : row1 - 1;
-        ra[i] = kcol < K ? *reinterpret_cast<const uint4*>(A + size_t(r) * K + kcol)
-                         : make_uint4(0, 0, 0, 0);
-      }
-    }
-    {
-      const int lrow = tid >> 3, piece = tid & 7;
-      const int kcol = ks * BK + piece * 8;
-#pragma unroll
-      for (int i = 0; i < B_PER; ++i) {
-        const int lr = lrow + 32 * i;
-        const char* base = (DUAL && lr >= BN) ? Be1 : Be0;
-        int n = n0 + ((DUAL && lr >= BN) ? lr - BN : lr);
-        n = n < N ? n : N - 1;
-        rb[i] = kcol < K ? *reinterpret_cast<const uint4*>(base + (size_t(n) * K + kcol) * 2)
-                         : make_uint4(0, 0, 0, 0);
-      }
-    }
-  };
-  auto lstore = [&](int buf) {
-    {
-      const int lrow = tid >> 3, piece = tid & 7;
-#pragma unroll
-      for (int i = 0; i < A_PER; ++i) As[buf][swz(lrow + 32 * i, piece)] = ra[i];
-    }
-    {
-      const int lrow = tid >> 3, piece = tid & 7;
-#pragma unroll
-      for (int i = 0; i < B_PER; ++i) Bs[buf][swz(lrow + 32 * i, piece)] = rb[i];
-    }
-  };
-
-  f32x16 acc[NACC][TM][TN];
-#pragma unroll
-  for (int a = 0; a < NACC; ++a)
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[a][i][j][q] = 0.f;
-
-  gload(0);
-  lstore(0);
-  __syncthreads();
-  for (int ks = 0; ks < ksteps; ++ks) {
-    const int buf = ks & 1;
-    if (ks + 1 < ksteps) gload(ks + 1);
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const int piece = kk * 2 + (lane >> 5);
-      bf16x8 af[TM];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        af[i] = __builtin_bit_cast(bf16x8, As[buf][swz(wm * WM + i * 32 + (lane & 31), piece)]);
-#pragma unroll
-      for (int a = 0; a < NACC; ++a)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const bf16x8 bf = __builtin_bit_cast(
-              bf16x8, Bs[buf][swz(a * BN + wn * WN + j * 32 + (lane & 31), piece)]);
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-            acc[a][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bf, acc[a][i][j], 0, 0, 0);
-        }
-    }
-    if (ks + 1 < ksteps) lstore(buf ^ 1);
-    __syncthreads();
-  }
-
-  // D layout: lane l, register q -> row (q/4)*8 + (l/32)*4 + q%4, col l%32
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int col = n0 + wn * WN + j * 32 + (lane & 31);
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int row = row0 + wm * WM + i * 32 + (q >> 2) * 8 + (lane >> 5) * 4 + (q & 3);
-        float v;
-        if (DUAL) v = silu_mul(acc[0][i][j][q], acc[NACC - 1][i][j][q]);
-        else v = acc[0][i][j][q];
-        if (row < row1 && col < N) C[size_t(row) * N + col] = f32_to_bf16_bits(v);
-      }
-    }
 }
 
 typedef const __attribute__((address_space(1))) void* gptr_t;
@@ -396,7 +269,11 @@ __device__ __forceinline__ void gemm8w_body(const uint16_t* __restrict__ A,
   uint4* const ringB = smem + SA * AS;
   const int lane = threadIdx.x & 63;
   const int wn = BR == 512 ? wave : wave & 3;        // column block of this wavefront
-  const int ksteps = klen / KS;                      // this workgroup's K window starts at kbeg
+  const int ksteps = (klen + KS - 1) / KS;           // this workgroup's K window starts at kbeg
+  // A K that is not a multiple of the step ends in a short step (bf16 only): its
+  // pieces past K are sent out of the descriptors' range and land as zeros.
+  const int tail = F8 ? 0 : klen % KS;
+  constexpr int kOut = 0x7fffffff;
 
   // LDS row r keeps its piece p at slot p ^ f(r): f = (r/2)&7 for 128-byte rows,
   // (r/4)&3 for 64-byte rows; both keep the 16 lanes the LDS serves per cycle
@@ -431,43 +308,57 @@ __device__ __forceinline__ void gemm8w_body(const uint16_t* __restrict__ A,
   const __amdgpu_buffer_rsrc_t rsrcB1 = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<char*>((DUAL ? Be1 : Be0) + (size_t(n0) * K + kbeg) * WB), 0,
       int((size_t(brows - 1) * K + klen) * WB), 0x00020000);
+  auto piece_a = [&](int q) { return (lane % PPR) ^ (((q * 8 + wave) * 4 + (lane >> 4)) & (PPR - 1)); };
+  auto piece_b = [&](int q) { return (lane % PPRB) ^ (((q * 8 + wave) * 4 + (lane >> 4)) & (PPRB - 1)); };
   int aoff[NAQ + 1], boff[NBQ];
 #pragma unroll
-  for (int q = 0; q < NAQ + 1; ++q) {
-    const int rg = q * 8 + wave;
-    const int piece = (lane % PPR) ^ ((rg * 4 + (lane >> 4)) & (PPR - 1));
-    aoff[q] = ((rg * RPI + lrow) * K + piece * 8) * 2;
-  }
+  for (int q = 0; q < NAQ + 1; ++q) aoff[q] = (((q * 8 + wave) * RPI + lrow) * K + piece_a(q) * 8) * 2;
 #pragma unroll
   for (int q = 0; q < NBQ; ++q) {
-    const int rg = q * 8 + wave;
-    const int piece = (lane % PPRB) ^ ((rg * 4 + (lane >> 4)) & (PPRB - 1));
-    const int br = rg * RPIB + lane / PPRB;
+    const int br = (q * 8 + wave) * RPIB + lane / PPRB;
     const int bl = (DUAL && br >= HALF) ? br - HALF : br;     // row inside its matrix' tile
-    boff[q] = bl * K * WB + piece * 16;
+    boff[q] = bl * K * WB + piece_b(q) * 16;
   }
   // weight row groups q: rows q*8*RPIB .. of the stage; the upper half is the up matrix
   auto b_is_up = [](int q) { return DUAL && q * 8 * RPIB >= HALF; };
-#define MOE_LOAD_A(q, kcol, dst) \
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcA, (lptr_t)(dst), 16, aoff[q], (kcol) * 2, 0, 0)
-#define MOE_LOAD_B(q, kcolb, dst)                                                                  \
-  do {                                                                                             \
-    if (b_is_up(q)) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcB1, (lptr_t)(dst), 16, boff[q], (kcolb), 0, 0); \
-    else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcB0, (lptr_t)(dst), 16, boff[q], (kcolb), 0, 0);            \
+#define MOE_LOAD_A_AT(off, kcol, dst) \
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcA, (lptr_t)(dst), 16, off, (kcol) * 2, 0, 0)
+#define MOE_LOAD_B_AT(q, off, kcolb, dst)                                                        \
+  do {                                                                                           \
+    if (b_is_up(q)) __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcB1, (lptr_t)(dst), 16, off, (kcolb), 0, 0); \
+    else __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcB0, (lptr_t)(dst), 16, off, (kcolb), 0, 0);            \
   } while (0)
+#define MOE_LOAD_A(q, kcol, dst) MOE_LOAD_A_AT(aoff[q], kcol, dst)
+#define MOE_LOAD_B(q, kcolb, dst) MOE_LOAD_B_AT(q, boff[q], kcolb, dst)
   const bool extra = AREM > 0 && wave < AREM;        // this wavefront loads one more A row group
   auto issue_a = [&](int ks) {
     const int kcol = ks * KS;
     uint4* st = ringA + (ks % SA) * AS;
+    const int lim = tail != 0 && ks == ksteps - 1 ? tail : KS;
 #pragma unroll
-    for (int q = 0; q < NAQ; ++q) MOE_LOAD_A(q, kcol, st + (q * 8 + wave) * 64);
-    if (extra) MOE_LOAD_A(NAQ, kcol, st + (NAQ * 8 + wave) * 64);
+    for (int q = 0; q < NAQ; ++q)
+      MOE_LOAD_A_AT(piece_a(q) * 8 < lim ? aoff[q] : kOut, kcol, st + (q * 8 + wave) * 64);
+    if (extra) MOE_LOAD_A_AT(piece_a(NAQ) * 8 < lim ? aoff[NAQ] : kOut, kcol, st + (NAQ * 8 + wave) * 64);
   };
   auto issue_b = [&](int ks) {
     const int kcol = ks * KS * WB;
     uint4* st = ringB + (ks % SB) * BS;
+    const int lim = tail != 0 && ks == ksteps - 1 ? tail : KS;
 #pragma unroll
-    for (int q = 0; q < NBQ; ++q) MOE_LOAD_B(q, kcol, st + (q * 8 + wave) * 64);
+    for (int q = 0; q < NBQ; ++q)
+      MOE_LOAD_B_AT(q, F8 || piece_b(q) * 8 < lim ? boff[q] : kOut, kcol, st + (q * 8 + wave) * 64);
+  };
+  // the same for a step that is known to be a whole one
+  auto issue_a_whole = [&](int ks) {
+    uint4* st = ringA + (ks % SA) * AS;
+#pragma unroll
+    for (int q = 0; q < NAQ; ++q) MOE_LOAD_A(q, ks * KS, st + (q * 8 + wave) * 64);
+    if (extra) MOE_LOAD_A(NAQ, ks * KS, st + (NAQ * 8 + wave) * 64);
+  };
+  auto issue_b_whole = [&](int ks) {
+    uint4* st = ringB + (ks % SB) * BS;
+#pragma unroll
+    for (int q = 0; q < NBQ; ++q) MOE_LOAD_B(q, ks * KS * WB, st + (q * 8 + wave) * 64);
   };
   // Issue group of step g (after its barrier): weights of step g+SB-1, then
   // activations of step g+SA-1 (SA >= SB).  Loads return in order, so at the
@@ -581,14 +472,16 @@ __device__ __forceinline__ void gemm8w_body(const uint16_t* __restrict__ A,
     constexpr bool ST = decltype(steady_c)::value;      // this step issues both of its load groups
     const int kb = ks + SB - 1, ka = ks + SA - 1;
     __builtin_amdgcn_sched_barrier(0);
-    if (ST || kb < ksteps) issue_b(kb);
+    if (ST) issue_b_whole(kb);
+    else if (kb < ksteps) issue_b(kb);
     read_half(ks, 0);
     __builtin_amdgcn_sched_barrier(0);
     phase_end(no_drain);
     mma_half();
     __builtin_amdgcn_sched_barrier(0);
     phase_end(no_drain);
-    if (ST) issue_a(ka);
+    if (ST) issue_a_whole(ka);
+    else if (ka < ksteps) issue_a(ka);
     read_half(ks, 1);
     __builtin_amdgcn_sched_barrier(0);
     if (WM == 1) wait_step(ST);
@@ -603,7 +496,7 @@ __device__ __forceinline__ void gemm8w_body(const uint16_t* __restrict__ A,
   wait_step(SA - 2 < ksteps);                                 // step 0 has landed
   phase_end(no_drain);
   if (WM == 1) phase_end(no_drain);                          // one phase behind row half 0
-  const int steady_steps = ksteps - (SA - 1);
+  const int steady_steps = ksteps - (SA - 1) - (tail != 0);
   int ks = 0;
   for (; ks < steady_steps; ++ks) step(ks, std::true_type{});
   for (; ks < ksteps; ++ks) step(ks, std::false_type{});
@@ -709,7 +602,7 @@ __device__ __forceinline__ void gemm8w_body(const uint16_t* __restrict__ A,
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  const int spread_steps = ksteps - (SA - 1);
+  const int spread_steps = ksteps - (SA - 1) - (tail != 0);
   int ks = 0;
   for (; ks < spread_steps; ++ks) turn(ks, std::true_type{});
   for (; ks < ksteps; ++ks) turn(ks, std::false_type{});
@@ -787,8 +680,7 @@ __device__ __forceinline__ void gemm8w_body(const uint16_t* __restrict__ A,
     const int valid = row1 - row0 - lrow;                        // rows r (tile-relative to lrow) < valid exist
     uint16_t* const cl = C + size_t(row0 + lrow) * N + n0 + (lane & 31);
     auto put2 = [&](uint16_t* p, float v0, float v1, bool ok0, bool ok1) {
-      uint32_t pk;   // bf16(v0) | bf16(v1) << 16, round to nearest even
-      asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(pk) : "v"(v0), "v"(v1));
+      const uint32_t pk = pack_bf16(v0, v1);
       if (ok0) p[0] = uint16_t(pk);
       if (ok1) p[N] = uint16_t(pk >> 16);
     };
@@ -800,13 +692,13 @@ __device__ __forceinline__ void gemm8w_body(const uint16_t* __restrict__ A,
         const bool ok0 = !PRED || r < valid, ok1 = !PRED || r + 1 < valid;
         uint16_t* const p = cl + size_t(r) * N;
         if (DUAL) {
-          if (n0 + wn * 32 < N)
+          if (n0 + wn * 32 + (lane & 31) < N)
             put2(p + wn * 32, silu_mul_fast(acc[i][0][q], acc[i][1][q]),
                  silu_mul_fast(acc[i][0][q + 1], acc[i][1][q + 1]), ok0, ok1);
         } else {
 #pragma unroll
           for (int j = 0; j < 2; ++j)
-            if (n0 + wn * 64 + j * 32 < N)
+            if (n0 + wn * 64 + j * 32 + (lane & 31) < N)
               put2(p + wn * 64 + j * 32, acc[i][j][q], acc[i][j][q + 1], ok0, ok1);
         }
       }
@@ -822,6 +714,8 @@ __device__ __forceinline__ void gemm8w_body(const uint16_t* __restrict__ A,
 
 #undef MOE_LOAD_A
 #undef MOE_LOAD_B
+#undef MOE_LOAD_A_AT
+#undef MOE_LOAD_B_AT
 
 template <bool DUAL, int NB, bool F8, bool WIDE>
 __device__ __forceinline__ void gemm8w_tile(const uint16_t* A, const char* Be0, const char* Be1,
@@ -859,7 +753,7 @@ __global__ __launch_bounds__(512) void ffn_gemm8w_kernel(
   extern __shared__ uint4 smem[];
   const int n_ntiles = (N + BN - 1) / BN;
   const int total = tiles[0] * n_ntiles;
-  const int ksteps_all = K / 64;
+  const int ksteps_all = (K + 63) / 64;
   const int pid = blockIdx.x;
   const int left = total % kCUs;
   int parts = 1;
@@ -933,7 +827,7 @@ __global__ __launch_bounds__(512) void ffn_gemm8w_kernel(
   }
 #define MOE_TILE_(NBV)                                                                        \
   gemm8w_tile<DUAL, NBV, F8, WIDE>(A, Be0, Be1, Se0, Se1, C, N, K, row0, row1, n0, smem, wave,   \
-                                   kb * 64, (ke - kb) * 64, job)
+                                   kb * 64, (ke * 64 < K ? ke * 64 : K) - kb * 64, job)
   if constexpr (WIDE) {
     switch ((row1 - row0 + 31) >> 5) {   // valid 32-row blocks of the tile: at most four
       case 1: MOE_TILE_(1); break;
@@ -1020,6 +914,19 @@ __global__ __launch_bounds__(256) void ffn_skinny_kernel(
   struct Slice { uint4 a[NKK]; uint4 b[2][BL]; };
   auto load = [&](int sl, Slice& r) {
     const int k0 = sl * W;
+    if (!FP8 && k0 + W > K) {                // the last slice of a K that is no multiple of 64
+#pragma unroll
+      for (int kk = 0; kk < NKK; ++kk) {
+        const bool in = k0 + h * (W / 2) + kk * 8 < K;
+        const uint4 zero = make_uint4(0, 0, 0, 0);
+        r.a[kk] = in && a_valid ? *reinterpret_cast<const uint4*>(arow + k0 + kk * 8) : zero;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          if (kk < BL)
+            r.b[j][kk] = in ? *reinterpret_cast<const uint4*>(brow[j] + size_t(k0) * wb + kk * 16) : zero;
+      }
+      return;
+    }
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk)
       if (a_valid) r.a[kk] = *reinterpret_cast<const uint4*>(arow + k0 + kk * 8);
@@ -1072,7 +979,7 @@ __global__ __launch_bounds__(256) void ffn_skinny_kernel(
     }
   };
 
-  const int nslices = K / W;
+  const int nslices = (K + W - 1) / W;
   Slice r0, r1;
 #pragma unroll
   for (int kk = 0; kk < NKK; ++kk) r0.a[kk] = r1.a[kk] = make_uint4(0, 0, 0, 0);
@@ -1115,6 +1022,185 @@ __global__ __launch_bounds__(256) void ffn_skinny_kernel(
       }
     }
   }
+}
+
+// -------------------------------------------------- MFMA GEMM-2, short K
+// The down projection of a narrow TP slice (K = I_loc up to 128): a tile is a
+// handful of K steps, so what counts is streaming w_down in and ys out without a
+// gap, not the K loop.  A workgroup of four wavefronts takes 128 rows, keeps their
+// activation fragments in registers (the whole K) and walks a run of 128-column
+// blocks: the weights of the next block are in flight (global -> LDS, two stages)
+// while the current block is multiplied and stored.  Small workgroups (52 KB of LDS
+// at K = 96), so that three of them share a CU and fill each other's waits; the
+// tall-tile kernel pays 6 us per tile beyond its K steps and has a CU to itself.
+// The weights are the first MFMA operand, so a lane holds four neighbouring columns
+// of one row, which go through LDS once more to be stored as whole 128-byte lines.
+// LDS rows have an odd pitch in 16-byte pieces (the padding piece is loaded out of
+// range: zeros), which keeps the operand reads free of bank conflicts.
+// Bound by the output write and the weights at prefill sizes.  128 experts, hidden
+// 2048, I_loc 96, against 128 x 128 tiles with register staging and 2-byte stores:
+// 3001 tokens (24 008 rows: 98 MB out, 50 MB of weights, 30 us at the copy rate) 60 ->
+// 34 us, 16 000 tokens (524 MB out) 254 -> 117 us; storing from the accumulators
+// instead (16 bytes per lane, 32 contiguous bytes per row) took 39 / 187 us, two
+// workgroups per CU instead of three 37 / 141 us.
+constexpr int kShortKMax = 128;
+
+template <int NKS> struct ShortK {
+  static constexpr int kLoaded = 128 * (NKS * 2 + 1);
+  static constexpr int kStage = kLoaded > 4 * 32 * 9 ? kLoaded : 4 * 32 * 9;
+};
+
+template <int NKS>                                   // K sub-steps of 16: K <= 16 * NKS
+__device__ __forceinline__ void shortk_body(const uint16_t* __restrict__ A,
+                                            const uint16_t* __restrict__ Be,
+                                            uint16_t* __restrict__ C, int N, int K, int row0,
+                                            int row1, int nb0, int nb1, uint4* smem) {
+  constexpr int P = NKS * 2 + 1;                     // pieces per LDS row
+  constexpr int kTurn = 32 * 9;                      // slots in which a wavefront turns 32 x 64 outputs around
+  constexpr int STAGE = ShortK<NKS>::kStage;         // 16-byte slots of a stage
+  constexpr int NINST = 2 * P, NLD = (NINST + 3) / 4;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = lane >> 5, l31 = lane & 31;
+  const int wm = wave & 1, wn = wave >> 1;
+  constexpr int kOut = 0x7fffffff;
+
+  const int rows = row1 - row0;
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(A + size_t(row0) * K), 0, int(size_t(rows) * K * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(Be), 0, int(size_t(N) * K * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+      C + size_t(row0) * N, 0, int(size_t(rows) * N * 2), 0x00020000);
+
+  int boff[NLD];                                     // this lane's piece of load i, relative to the block
+#pragma unroll
+  for (int i = 0; i < NLD; ++i) {
+    const int slot = (i * 4 + wave) * 64 + lane, row = slot / P, piece = slot - row * P;
+    boff[i] = piece * 8 < K ? (row * K + piece * 8) * 2 : kOut;
+  }
+  auto issue = [&](int nb) {
+    uint4* const st = smem + (nb & 1) * STAGE;
+    const int base = nb * 128 * K * 2;
+#pragma unroll
+    for (int i = 0; i < NLD; ++i)
+      if (i * 4 + wave < NINST)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lptr_t)(st + (i * 4 + wave) * 64), 16, boff[i], base, 0, 0);
+  };
+  issue(nb0);
+  // activation fragments: rows wm*64 + i*32 + lane%32, k = kk*16 + h*8 .. +8
+  bf16x8 af[2][NKS];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int kk = 0; kk < NKS; ++kk) {
+      const int k = kk * 16 + h * 8;
+      const int off = k < K ? ((wm * 64 + i * 32 + l31) * K + k) * 2 : kOut;
+      af[i][kk] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(ra, off, 0, 0));
+    }
+  for (int nb = nb0; nb < nb1; ++nb) {
+    // the weights of this block have landed; the eight stores of the block before
+    // it are younger and may stay in flight
+    if (nb == nb0) wait_vmcnt<0>(); else wait_vmcnt<8>();
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (nb + 1 < nb1) issue(nb + 1);                 // every wavefront is done with that stage
+    const uint4* const st = smem + (nb & 1) * STAGE;
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < NKS; ++kk) {
+      bf16x8 bf[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        bf[j] = __builtin_bit_cast(bf16x8, st[(wn * 64 + j * 32 + l31) * P + kk * 2 + h]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[j], af[i][kk], acc[i][j], 0, 0, 0);
+    }
+    // Lane l holds row l%32 of block i, columns (q/4)*8 + (l/32)*4 + q%4 of block j.
+    // The stage has served its purpose: each wavefront turns its 32-row halves
+    // around in a slice of it, so that a store writes whole 128-byte lines.
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    uint4* const turn = smem + (nb & 1) * STAGE + wave * kTurn;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const uint2 v = make_uint2(pack_bf16(acc[i][j][g * 4], acc[i][j][g * 4 + 1]),
+                                     pack_bf16(acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]));
+          reinterpret_cast<uint2*>(turn + l31 * 9 + j * 4 + g)[h] = v;
+        }
+      asm volatile("" ::: "memory");                 // the reads below see the writes above (same wavefront)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int row = t * 8 + (lane >> 3), piece = lane & 7;
+        const u32x4 v = __builtin_bit_cast(u32x4, turn[row * 9 + piece]);
+        const int col = nb * 128 + wn * 64 + piece * 8;
+        const int off = col < N ? ((wm * 64 + i * 32 + row) * N + col) * 2 : kOut;
+        __builtin_amdgcn_raw_buffer_store_b128(v, rc, off, 0, 0);
+      }
+      asm volatile("" ::: "memory");
+    }
+  }
+}
+
+// `split` workgroups share an M tile's column blocks.  Inside an expert the M
+// tiles are neighbours (they stream the same weights), and every XCD walks a
+// contiguous run of workgroups.
+template <int NKS>
+__global__ __launch_bounds__(256, NKS <= 6 ? 3 : 2) void ffn_shortk_kernel(const uint16_t* __restrict__ A,
+                                                        const uint16_t* __restrict__ B,
+                                                        uint16_t* __restrict__ C, int N, int K,
+                                                        const int32_t* __restrict__ tiles, int split) {
+  extern __shared__ uint4 smem[];
+  const int total = tiles[0] * split, per_xcd = (total + 7) >> 3;
+  const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (int(blockIdx.x >> 3) >= per_xcd || logical >= total) return;
+  const int at = logical / split;                    // a tile of the same expert
+  const int first = tiles[4 + kTileRec * at], cnt = tiles[5 + kTileRec * at];
+  const int local = logical - first * split, part = local / cnt, mtile = first + local - part * cnt;
+  const int e = tiles[1 + kTileRec * mtile], row0 = tiles[2 + kTileRec * mtile],
+            row1 = tiles[3 + kTileRec * mtile];
+  const int blocks = (N + 127) / 128;
+  const int nb0 = part * blocks / split, nb1 = (part + 1) * blocks / split;
+  if (nb0 >= nb1) return;
+  shortk_body<NKS>(A, B + size_t(e) * N * K, C, N, K, row0, row1, nb0, nb1, smem);
+}
+
+void launch_shortk(const void* hmid, const void* w_down, void* ys, int N, int K, const int32_t* tiles,
+                   int max_mt, hipStream_t s) {
+  // about four rounds of three workgroups per CU, each with at least four column
+  // blocks to overlap, unless that leaves CUs without a workgroup (decode sizes)
+  const int blocks = (N + 127) / 128;
+  int most = (blocks + 3) / 4;
+  while (most < blocks && long(max_mt) * most < 2 * kCUs) most *= 2;
+  most = most < blocks ? most : blocks;
+  int split = (12 * kCUs + max_mt - 1) / max_mt;
+  split = split < most ? split : most;
+  const int grid = (max_mt * split + 7) / 8 * 8;
+#define MOE_SHORTK(NKS)                                                                            \
+  do {                                                                                             \
+    constexpr int lds = 2 * ShortK<NKS>::kStage * 16;                                              \
+    static uint64_t opted = 0;                                                                     \
+    auto k = ffn_shortk_kernel<NKS>;                                                               \
+    lds_opt_in(reinterpret_cast<const void*>(k), lds, opted);                                      \
+    MOE_LAUNCH(MOE_K_FFN_GEMM2, k, dim3(grid), dim3(256), lds, s, static_cast<const uint16_t*>(hmid), \
+               static_cast<const uint16_t*>(w_down), static_cast<uint16_t*>(ys), N, K, tiles, split);   \
+  } while (0)
+  const int ks = (K + 15) / 16;
+  if (ks <= 2) MOE_SHORTK(2);
+  else if (ks <= 4) MOE_SHORTK(4);
+  else if (ks <= 6) MOE_SHORTK(6);
+  else MOE_SHORTK(8);
+#undef MOE_SHORTK
 }
 
 // ------------------------------------------------------------ fp32 GEMM
@@ -1256,126 +1342,92 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
                      row0, row1, ntile * 32, smem);
 }
 
-template <int BM, int BN1, int WM, int WN1, int BN2, int WN2>
-void launch_mfma_pair(const moe_config& c, int n_experts, const void* xs, const int32_t* offsets,
-                      int rows_capacity, const void* w_gate, const void* w_up, const void* w_down,
-                      const float* s_gate, const float* s_up, const float* s_down, void* ys,
-                      const FfnWs& ws, hipStream_t s) {
-  const int H = c.hidden, I = c.inter_local;
-  const int max_mt = rows_capacity / BM + n_experts;
-  MOE_LAUNCH(MOE_K_FFN_TILES, ffn_tiles_kernel, dim3(1), dim3(256), 0, s, offsets, n_experts, BM,
-                     rows_capacity, ws.tiles, max_mt < ws.max_tiles ? max_mt : ws.max_tiles, 0, 0,
-             (int32_t*)nullptr, (int32_t*)nullptr);
-  const int nt1 = (I + BN1 - 1) / BN1, nt2 = (H + BN2 - 1) / BN2;
-  auto k1 = ffn_gemm_kernel<BM, BN1, WM, WN1, true>;
-  auto k2 = ffn_gemm_kernel<BM, BN2, WM, WN2, false>;
-  constexpr int lds1 = 2 * (BM + 2 * BN1) * 8 * 16, lds2 = 2 * (BM + BN2) * 8 * 16;
-  static uint64_t opted1 = 0, opted2 = 0;
-  lds_opt_in(reinterpret_cast<const void*>(k1), lds1, opted1);
-  lds_opt_in(reinterpret_cast<const void*>(k2), lds2, opted2);
-  MOE_LAUNCH(MOE_K_FFN_GEMM1, k1, dim3(size_t(max_mt) * nt1), dim3(256), lds1, s,
-                     static_cast<const uint16_t*>(xs), w_gate, w_up,
-                     static_cast<uint16_t*>(ws.hmid), I, H, ws.tiles);
-  MOE_LAUNCH(MOE_K_FFN_GEMM2, k2, dim3(size_t(max_mt) * nt2), dim3(256), lds2, s,
-                     static_cast<const uint16_t*>(ws.hmid), w_down, (const void*)nullptr,
-                     static_cast<uint16_t*>(ys), H, I, ws.tiles);
+// Which kernel runs each GEMM of a call, and the height of its M tiles.
+enum GemmKind { kGemmF32, kGemmStream, kGemmTall, kGemmWide, kGemmShortK };
+struct FfnPlan {
+  GemmKind g1, g2;
+  int bm1, bm2;
+};
+
+// Rows per expert can only be bounded from above on the host; the kernels are
+// picked by that bound (`avg`).
+FfnPlan plan_ffn(const moe_config& c, int n_experts, int rows_capacity) {
+  const int H = c.hidden, I = c.inter_local, avg = rows_capacity / n_experts;
+  if (c.act_dtype == MOE_F32) return {kGemmF32, kGemmF32, 32, 32};
+  const bool fp8 = c.weight_dtype == MOE_FP8_E4M3_B128;
+  FfnPlan p;
+  // GEMM-1 (K = H long): the weight-streaming kernel at decode sizes, then the LDS
+  // rings of the tall-tile kernel, which stream the weights faster as soon as a tile
+  // holds a few rows: measured on the 128-expert layer (hidden 2048, I 768) with the
+  // switch at two rows per expert.  e4m3 weights switch at twelve: up to there the
+  // block scale multiplies fp32 partial sums, above it code * scale is rounded to bf16.
+  p.g1 = avg <= (fp8 ? 12 : 2) ? kGemmStream : kGemmTall;
+  // Few rows per expert mean that the weights are streamed about once: tiles of at
+  // most 160 rows there, which leaves room for a three-stage ring.
+  p.bm1 = p.g1 == kGemmStream ? 32 : (avg <= 320 ? 160 : 256);
+  // GEMM-2 (K = I_loc short, N = H wide):
+  //  - K up to 128 (a layer cut over many TP ranks): the short-K kernel at every size.
+  //    128 experts, hidden 2048, I_loc 96: 12 us at 2 and 8 rows per expert, where the
+  //    weight-streaming kernel (three K slices per wavefront pair) takes 27 / 30 us; at K =
+  //    192 the tall-tile kernel is the faster one (188 rows per expert: 49 against 54 us).
+  //  - up to twelve rows per expert: many small weight-streaming workgroups.
+  //  - up to 96 rows per expert, when the experts give at least one such tile per CU:
+  //    tiles of 128 rows x 512 weight rows.  128 experts, hidden 2048, I 768, bf16: 85 ->
+  //    81, 94 -> 86, 102 -> 92 us at 32 / 64 / 96 rows per expert, 110 -> 115 us at 128;
+  //    e4m3 weights at 64 rows per expert (32 experts, hidden 7168): 73 -> 61 us.
+  //    (GEMM-1 keeps the narrow tiles: its wide form was slower at every size, the
+  //    512-row bf16 stage leaves room for two ring stages only.)
+  //  - else 256-row tiles.
+  if (!fp8 && I <= kShortKMax) { p.g2 = kGemmShortK; p.bm2 = 128; }
+  else if (avg <= 12) { p.g2 = kGemmStream; p.bm2 = 32; }
+  else if (avg <= 96 && long(n_experts) * ((H + 511) / 512) >= kCUs) { p.g2 = kGemmWide; p.bm2 = 128; }
+  else { p.g2 = kGemmTall; p.bm2 = 256; }
+  return p;
 }
 
-template <bool FP8>
-void launch_skinny(const moe_config& c, int n_experts, const void* xs, const int32_t* offsets,
-                   int rows_capacity, const void* w_gate, const void* w_up, const void* w_down,
-                   const float* s_gate, const float* s_up, const float* s_down, void* ys,
-                   const FfnWs& ws, hipStream_t s) {
-  const int H = c.hidden, I = c.inter_local;
-  const int max_mt = rows_capacity / 32 + n_experts;
-  MOE_LAUNCH(MOE_K_FFN_TILES, ffn_tiles_kernel, dim3(1), dim3(256), 0, s, offsets, n_experts, 32,
-             rows_capacity, ws.tiles, max_mt < ws.max_tiles ? max_mt : ws.max_tiles, 0, 0,
-             (int32_t*)nullptr, (int32_t*)nullptr);
-  const int nt1 = (I + 31) / 32, nt2 = (H + 63) / 64;
-  MOE_LAUNCH(MOE_K_FFN_GEMM1, (ffn_skinny_kernel<true, FP8>), dim3(size_t(max_mt) * nt1), dim3(256),
-             0, s, static_cast<const uint16_t*>(xs), w_gate, w_up, s_gate, s_up,
-             static_cast<uint16_t*>(ws.hmid), I, H, ws.tiles);
-  MOE_LAUNCH(MOE_K_FFN_GEMM2, (ffn_skinny_kernel<false, FP8>), dim3(size_t(max_mt) * nt2), dim3(256),
-             0, s, static_cast<const uint16_t*>(ws.hmid), w_down, (const void*)nullptr, s_down,
-             (const float*)nullptr, static_cast<uint16_t*>(ys), H, I, ws.tiles);
-}
-
-template <bool F8>
-void launch_mfma256(const moe_config& c, int n_experts, const void* xs, const int32_t* offsets,
-                    int rows_capacity, const void* w_gate, const void* w_up, const void* w_down,
-                    const float* s_gate, const float* s_up, const float* s_down, void* ys,
-                    const FfnWs& ws, hipStream_t s) {
-  const int H = c.hidden, I = c.inter_local;
-  // Few rows per expert means the weights are streamed about once: cap the tile
-  // height at 160 rows there, which leaves room for a three-stage ring.
-  // GEMM-2 (K = I_loc is short, N = H wide) is best with 256-row tiles throughout
-  // (measured); when the two heights differ a second workgroup of the table
-  // kernel builds GEMM-2's table.
-  // GEMM-2 of short groups (at most 96 rows per expert on average: a decode batch or
-  // a cold EP share) takes 128-row tiles x 512 weight rows when the experts still
-  // give at least one such tile per CU; otherwise the narrower tiles keep more CUs
-  // streaming.  Measured on the 128-expert layer (hidden 2048, I 768, bf16): 85 ->
-  // 81, 94 -> 86, 102 -> 92 us at 32 / 64 / 96 rows per expert, 110 -> 115 us at 128;
-  // e4m3 weights at 64 rows per expert (32 experts, hidden 7168): 73 -> 61 us.
-  // GEMM-1 keeps the narrow tiles: its wide form was slower at every size (the
-  // 512-row bf16 stage leaves room for two ring stages only).
-  const bool wide2 = rows_capacity / n_experts <= 96 && long(n_experts) * ((H + 511) / 512) >= kCUs;
-  const int bm = rows_capacity / n_experts <= 320 ? 160 : 256;
-  const int bm2 = wide2 ? 128 : 256;
-  const int max_mt = rows_capacity / bm + n_experts;
-  const int max_mt2 = rows_capacity / bm2 + n_experts;
-  // one bound for both tables: the one with the shorter tiles can hold more
-  const int most = max_mt > max_mt2 ? max_mt : max_mt2;
-  const int cap = most < ws.max_tiles ? most : ws.max_tiles;
-  int32_t* const tiles2 = bm2 == bm ? ws.tiles : ws.tiles2;
-  MOE_LAUNCH(MOE_K_FFN_TILES, ffn_tiles_kernel, dim3(bm2 == bm ? 1 : 2), dim3(256), 0, s, offsets,
-             n_experts, bm, rows_capacity, ws.tiles, cap, 1, bm2, tiles2, ws.tickets);
-  const int nt1 = (I + 127) / 128, nt2 = wide2 ? (H + 511) / 512 : (H + 255) / 256;
+// One GEMM of the call: C[rows, N] = A[rows, K] B^T (DUAL: the gate|up pair with SwiGLU).
+template <bool DUAL, bool F8>
+void launch_gemm(GemmKind kind, int bm, const uint16_t* A, const void* B0, const void* B1,
+                 const float* S0, const float* S1, uint16_t* C, int N, int K, int n_experts,
+                 int rows_capacity, const int32_t* tiles, const FfnWs& ws, hipStream_t s) {
+  constexpr int id = DUAL ? MOE_K_FFN_GEMM1 : MOE_K_FFN_GEMM2;
+  const int max_mt = rows_capacity / bm + (n_experts < rows_capacity ? n_experts : rows_capacity);
+  if (kind == kGemmStream) {
+    constexpr int BN = DUAL ? 32 : 64;
+    MOE_LAUNCH(id, (ffn_skinny_kernel<DUAL, F8>), dim3(size_t(max_mt) * ((N + BN - 1) / BN)), dim3(256),
+               0, s, A, B0, B1, S0, S1, C, N, K, tiles);
+    return;
+  }
+  if (!DUAL && !F8 && kind == kGemmShortK) {
+    launch_shortk(A, B0, C, N, K, tiles, max_mt, s);
+    return;
+  }
   constexpr int lds = 160 * 1024;         // all of a CU's LDS: the rings of the tallest tile fill it
+  const bool wide = !DUAL && kind == kGemmWide;
+  const int BN = DUAL ? 128 : (wide ? 512 : 256);
   // room for the parts of the leftover tiles behind the whole tiles
-  const int g1 = (max_mt * nt1 + 7) / 8 * 8 + kCUs, g2 = (max_mt2 * nt2 + 7) / 8 * 8 + kCUs;
-  auto k1 = ffn_gemm8w_kernel<true, F8, false>;
-  auto k2 = wide2 ? ffn_gemm8w_kernel<false, F8, true> : ffn_gemm8w_kernel<false, F8, false>;
-  static uint64_t opted1 = 0, opted2 = 0, opted2w = 0;
-  lds_opt_in(reinterpret_cast<const void*>(k1), lds, opted1);
-  lds_opt_in(reinterpret_cast<const void*>(k2), lds, wide2 ? opted2w : opted2);
-  MOE_LAUNCH(MOE_K_FFN_GEMM1, k1, dim3(g1), dim3(512), lds, s, static_cast<const uint16_t*>(xs),
-             w_gate, w_up, s_gate, s_up, static_cast<uint16_t*>(ws.hmid), I, H, ws.tiles, 1,
-             ws.partial, ws.tickets);
-  MOE_LAUNCH(MOE_K_FFN_GEMM2, k2, dim3(g2), dim3(512), lds, s,
-             static_cast<const uint16_t*>(ws.hmid), w_down, (const void*)nullptr, s_down,
-             (const float*)nullptr, static_cast<uint16_t*>(ys), H, I, tiles2, 1, ws.partial,
-             ws.tickets + kSplitTickets);
+  const int grid = (max_mt * ((N + BN - 1) / BN) + 7) / 8 * 8 + kCUs;
+  auto k = ffn_gemm8w_kernel<DUAL, F8, false>;
+  if constexpr (!DUAL) {
+    if (wide) k = ffn_gemm8w_kernel<false, F8, true>;
+  }
+  static uint64_t opted = 0, opted_wide = 0;
+  lds_opt_in(reinterpret_cast<const void*>(k), lds, wide ? opted_wide : opted);
+  MOE_LAUNCH(id, k, dim3(grid), dim3(512), lds, s, A, B0, B1, S0, S1, C, N, K, tiles, 1, ws.partial,
+             ws.tickets + (DUAL ? 0 : kSplitTickets));
 }
 
-// Between the two: a handful of rows per expert.  GEMM-1 (K = H long) streams its
-// weights fastest through the LDS rings of the tall-tile kernel even when a tile
-// holds one or two row blocks; GEMM-2 (K = I_loc short, N = H wide) is best as
-// many small weight-streaming workgroups.  Each kernel gets its own tile table.
 template <bool F8>
-void launch_mixed(const moe_config& c, int n_experts, const void* xs, const int32_t* offsets,
-                  int rows_capacity, const void* w_gate, const void* w_up, const void* w_down,
-                  const float* s_gate, const float* s_up, const float* s_down, void* ys,
-                  const FfnWs& ws, hipStream_t s) {
+void launch_pair(const FfnPlan& p, const moe_config& c, int n_experts, const void* xs,
+                 int rows_capacity, const void* w_gate, const void* w_up, const void* w_down,
+                 const float* s_gate, const float* s_up, const float* s_down, void* ys,
+                 const int32_t* tiles2, const FfnWs& ws, hipStream_t s) {
   const int H = c.hidden, I = c.inter_local;
-  const int bm = 160, bm2 = 32;
-  const int max_mt = rows_capacity / bm + n_experts;
-  const int max_mt2 = rows_capacity / bm2 + n_experts;
-  const int cap = max_mt2 < ws.max_tiles ? max_mt2 : ws.max_tiles;
-  MOE_LAUNCH(MOE_K_FFN_TILES, ffn_tiles_kernel, dim3(2), dim3(256), 0, s, offsets, n_experts, bm,
-             rows_capacity, ws.tiles, cap, 1, bm2, ws.tiles2, ws.tickets);
-  const int nt1 = (I + 127) / 128, nt2 = (H + 63) / 64;
-  constexpr int lds = 160 * 1024;
-  const int g1 = (max_mt * nt1 + 7) / 8 * 8 + kCUs;
-  auto k1 = ffn_gemm8w_kernel<true, F8>;
-  static uint64_t opted1 = 0;
-  lds_opt_in(reinterpret_cast<const void*>(k1), lds, opted1);
-  MOE_LAUNCH(MOE_K_FFN_GEMM1, k1, dim3(g1), dim3(512), lds, s, static_cast<const uint16_t*>(xs),
-             w_gate, w_up, s_gate, s_up, static_cast<uint16_t*>(ws.hmid), I, H, ws.tiles, 1,
-             ws.partial, ws.tickets);
-  MOE_LAUNCH(MOE_K_FFN_GEMM2, (ffn_skinny_kernel<false, F8>), dim3(size_t(max_mt2) * nt2), dim3(256),
-             0, s, static_cast<const uint16_t*>(ws.hmid), w_down, (const void*)nullptr, s_down,
-             (const float*)nullptr, static_cast<uint16_t*>(ys), H, I, ws.tiles2);
+  uint16_t* const hmid = static_cast<uint16_t*>(ws.hmid);
+  launch_gemm<true, F8>(p.g1, p.bm1, static_cast<const uint16_t*>(xs), w_gate, w_up, s_gate, s_up, hmid,
+                        I, H, n_experts, rows_capacity, ws.tiles, ws, s);
+  launch_gemm<false, F8>(p.g2, p.bm2, hmid, w_down, nullptr, s_down, nullptr,
+                         static_cast<uint16_t*>(ys), H, I, n_experts, rows_capacity, tiles2, ws, s);
 }
 
 }  // namespace
@@ -1386,11 +1438,13 @@ hipError_t launch_expert_ffn(const moe_config& c, int n_experts, const void* xs,
                              const float* s_up, const float* s_down, void* ys, const FfnWs& ws,
                              hipStream_t s) {
   const int H = c.hidden, I = c.inter_local;
-  if (c.act_dtype == MOE_F32) {
-    const int max_mt = rows_capacity / 32 + n_experts;
-    MOE_LAUNCH(MOE_K_FFN_TILES, ffn_tiles_kernel, dim3(1), dim3(256), 0, s, offsets, n_experts, 32,
-               rows_capacity, ws.tiles, max_mt < ws.max_tiles ? max_mt : ws.max_tiles, 0, 0,
-               (int32_t*)nullptr, (int32_t*)nullptr);
+  const FfnPlan p = plan_ffn(c, n_experts, rows_capacity);
+  // when the two GEMMs cut the rows differently a second workgroup builds a second table
+  int32_t* const tiles2 = p.bm1 == p.bm2 ? ws.tiles : ws.tiles2;
+  MOE_LAUNCH(MOE_K_FFN_TILES, ffn_tiles_kernel, dim3(p.bm1 == p.bm2 ? 1 : 2), dim3(256), 0, s, offsets,
+             n_experts, p.bm1, rows_capacity, ws.tiles, ws.max_tiles, p.bm2, tiles2, ws.tickets);
+  if (p.g1 == kGemmF32) {
+    const int max_mt = rows_capacity / 32 + (n_experts < rows_capacity ? n_experts : rows_capacity);
     auto k1 = ffn_f32_kernel<true>;
     auto k2 = ffn_f32_kernel<false>;
     static uint64_t opted1 = 0, opted2 = 0;
@@ -1403,38 +1457,14 @@ hipError_t launch_expert_ffn(const moe_config& c, int n_experts, const void* xs,
                F32Ring<false>::kLds, s, static_cast<const float*>(ws.hmid),
                static_cast<const float*>(w_down), (const float*)nullptr, static_cast<float*>(ys), H, I,
                ws.tiles);
-    return hipGetLastError();
-  }
-  // rows per expert can only be bounded from above on the host; pick the M
-  // tile from that bound (decode batches get the short tiles)
-  const int avg = rows_capacity / n_experts;
-  const bool fp8 = c.weight_dtype == MOE_FP8_E4M3_B128;
-#define MOE_FFN_ARGS c, n_experts, xs, offsets, rows_capacity, w_gate, w_up, w_down, s_gate, s_up, s_down, ys, ws, s
-  if (fp8 && H % 128 == 0 && I % 128 == 0 && avg > 12) {
-    // e4m3 weight tiles in the LDS rings of the tall-tile kernel (the scaled weight
-    // is rounded to bf16 there; below, the scale multiplies fp32 partial sums)
-    launch_mfma256<true>(MOE_FFN_ARGS);
-  } else if (fp8) {
-    // the configuration check admits fp8 weights only with hidden and intermediate
-    // sizes that are multiples of 128
-    launch_skinny<true>(MOE_FFN_ARGS);
-  } else if (H % BK == 0 && I % BK == 0) {
-    // measured on the 128-expert layer (hidden 2048, I 768): with at most two rows
-    // per expert the weight-streaming kernel wins both GEMMs, from about twelve on
-    // the tall-tile kernel does, in between each takes the GEMM it is better at
-    if (avg <= 2) launch_skinny<false>(MOE_FFN_ARGS);
-    else if (avg <= 12) launch_mixed<false>(MOE_FFN_ARGS);
-    else launch_mfma256<false>(MOE_FFN_ARGS);
-  } else if (avg <= 32) {
-    launch_mfma_pair<32, 128, 32, 32, 256, 64>(MOE_FFN_ARGS);
-  } else if (avg <= 64) {
-    launch_mfma_pair<64, 128, 64, 32, 256, 64>(MOE_FFN_ARGS);
+  } else if (c.weight_dtype == MOE_FP8_E4M3_B128) {
+    launch_pair<true>(p, c, n_experts, xs, rows_capacity, w_gate, w_up, w_down, s_gate, s_up, s_down, ys,
+                      tiles2, ws, s);
   } else {
-    launch_mfma_pair<128, 64, 64, 32, 128, 64>(MOE_FFN_ARGS);
+    launch_pair<false>(p, c, n_experts, xs, rows_capacity, w_gate, w_up, w_down, nullptr, nullptr, nullptr,
+                       ys, tiles2, ws, s);
   }
-#undef MOE_FFN_ARGS
   return hipGetLastError();
 }
 
 }  // namespace moe
-

@@ -37,3 +37,29 @@ def check_ffn(counts, H, I, tol, **changes):
 @pytest.mark.parametrize("H,I", [(8, 8), (136, 40), (384, 512), (520, 640), (1032, 264)])
 def test_fp32_tiles(H, I):
     check_ffn([1, 31, 32, 33, 0, 70], H, I, TOL["f32"], act_dtype="f32", weight_dtype="f32", x_std=0.02)
+
+
+# GEMM-2 with K = I up to 128: one to eight K sub-steps, the last one partly filled,
+# column blocks of 128 with a remainder, fewer blocks than one, 32-row blocks of the
+# 128-row tiles on both sides of a border.  bf16 bar of the layer.
+@pytest.mark.parametrize("H,I", [(64, 8), (136, 16), (392, 40), (1032, 72), (520, 96), (256, 104), (8, 128)])
+@pytest.mark.parametrize("counts", [[1, 31, 33, 0, 2], [127, 128, 129, 300]])
+def test_bf16_short_k(counts, H, I):
+    check_ffn(counts, H, I, TOL["bf16"])
+
+
+# K that is no multiple of 64 on the tall-tile kernel: full tiles (alternating loop) and
+# short ones (rotated loop) whose last step is partly filled, columns that end inside a
+# 32-column block, fewer steps than the rings have stages, and leftover tiles split
+# along a K that ends in a short step (49 steps of GEMM-1).
+@pytest.mark.parametrize("counts,H,I", [([256, 520, 40], 328, 200), ([300, 257], 72, 136),
+                                        ([512, 97], 1032, 264), ([300], 3080, 136)])
+def test_bf16_ragged_k_tall_tiles(counts, H, I):
+    check_ffn(counts, H, I, TOL["bf16"])
+
+
+# K that is no multiple of 64 on the weight-streaming kernel (at most two rows per
+# expert on average, and GEMM-2 at up to twelve).
+@pytest.mark.parametrize("counts", [[1, 2, 0, 3], [9, 1, 14, 8]])
+def test_bf16_ragged_k_weight_streaming(counts):
+    check_ffn(counts, 328, 200, TOL["bf16"])
