@@ -38,16 +38,18 @@ __device__ __forceinline__ void fma8(float (&acc)[8], float w, const uint4& v) {
   acc[7] = fmaf(w, bf16_hi(v.w), acc[7]);
 }
 
-// bf16 rows: a piece is 8 elements (16 B in, 32 B out).
+// bf16 rows: a piece is 8 elements (16 B in, 32 B out).  A wavefront owns 64 pieces of
+// one token's row (a row of hidden 2048 is shared out over four) and fetches up to kRows
+// expert rows at once, so its chain is one round of loads for top-8 and not one per
+// expert.  Against 256 pieces per wavefront and one row at a time: one token, hidden
+// 2048, 5.8 -> 2.9 us; 65 536 tokens x 8 rows (2.7 GB) 497 -> 441 us.
+constexpr int kRows = 8;
 __global__ __launch_bounds__(256) void combine_bf16_kernel(
     const uint4* __restrict__ ys, const int32_t* __restrict__ inv, const float* __restrict__ w,
     const uint4* __restrict__ shared_ys, float4* __restrict__ out, int T, int k, int row8,
     int accumulate) {
   const int lane = threadIdx.x & 63;
-  constexpr int P = 4;                          // pieces per lane in flight
-  // a wavefront owns one segment of 64*P pieces of one token's row: wide rows are
-  // shared out over several wavefronts, each with one round of loads and stores
-  const int nseg = (row8 + 64 * P - 1) / (64 * P);
+  const int nseg = (row8 + 63) / 64;
   const int gw = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int t = gw / nseg;
   if (t >= T) return;
@@ -57,58 +59,42 @@ __global__ __launch_bounds__(256) void combine_bf16_kernel(
     pos = inv[size_t(t) * k + lane];
     wt = w[size_t(t) * k + lane];
   }
-  const uint64_t have = __ballot(pos >= 0);
-  // every lane of the wavefront runs the body (the shuffles below need all of them)
-  {
-    const int cb = (gw - t * nseg) * 64 * P;
-    const int c0 = cb + lane;
-    float acc[P][8];
+  // every lane runs the body (the shuffles below need all of them); lanes past the row's
+  // end read its last piece and store nothing
+  const int c = (gw - t * nseg) * 64 + lane, cc = min(c, row8 - 1);
+  float acc[8];
 #pragma unroll
-    for (int i = 0; i < P; ++i)
+  for (int q = 0; q < 8; ++q) acc[q] = 0.f;
+  uint64_t m = __ballot(pos >= 0);            // the same in every lane
+  while (m) {                                 // ascending j
+    uint4 v[kRows];
+    float wj[kRows];
+    int n = 0;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) acc[i][q] = 0.f;
-    uint64_t m = have;
-    while (m) {                               // ascending j
-      const int j = __ffsll((unsigned long long)m) - 1;
-      m &= m - 1;
-      const int p = __shfl(pos, j);
-      const float wj = __shfl(wt, j);
-      const uint4* row = ys + size_t(p) * row8;
-      uint4 v[P];
-#pragma unroll
-      for (int i = 0; i < P; ++i)
-        if (c0 + 64 * i < row8) v[i] = nt_load16(row + c0 + 64 * i);
-#pragma unroll
-      for (int i = 0; i < P; ++i)
-        if (c0 + 64 * i < row8) fma8(acc[i], wj, v[i]);
-    }
-    if (shared_ys) {
-      const uint4* row = shared_ys + size_t(t) * row8;
-      uint4 v[P];
-#pragma unroll
-      for (int i = 0; i < P; ++i)
-        if (c0 + 64 * i < row8) v[i] = nt_load16(row + c0 + 64 * i);
-#pragma unroll
-      for (int i = 0; i < P; ++i)
-        if (c0 + 64 * i < row8) fma8(acc[i], 1.0f, v[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < P; ++i) {
-      const int c = c0 + 64 * i;
-      if (c < row8) {
-        float4* o = out + (size_t(t) * row8 + c) * 2;
-        if (accumulate) {                     // Y <- Y + (weighted sum of this stage)
-          const float4 o0 = o[0], o1 = o[1];
-          acc[i][0] += o0.x; acc[i][1] += o0.y; acc[i][2] += o0.z; acc[i][3] += o0.w;
-          acc[i][4] += o1.x; acc[i][5] += o1.y; acc[i][6] += o1.z; acc[i][7] += o1.w;
-        }
-        nt_store16(o, make_uint4(__float_as_uint(acc[i][0]), __float_as_uint(acc[i][1]),
-                                 __float_as_uint(acc[i][2]), __float_as_uint(acc[i][3])));
-        nt_store16(o + 1, make_uint4(__float_as_uint(acc[i][4]), __float_as_uint(acc[i][5]),
-                                     __float_as_uint(acc[i][6]), __float_as_uint(acc[i][7])));
+    for (int u = 0; u < kRows; ++u)
+      if (m) {
+        const int j = __ffsll((unsigned long long)m) - 1;
+        m &= m - 1;
+        wj[u] = __shfl(wt, j);
+        v[u] = nt_load16(ys + size_t(__shfl(pos, j)) * row8 + cc);
+        n = u + 1;
       }
-    }
+#pragma unroll
+    for (int u = 0; u < kRows; ++u)
+      if (u < n) fma8(acc, wj[u], v[u]);
   }
+  if (shared_ys) fma8(acc, 1.0f, nt_load16(shared_ys + size_t(t) * row8 + cc));
+  if (c >= row8) return;
+  float4* o = out + (size_t(t) * row8 + c) * 2;
+  if (accumulate) {                           // Y <- Y + (weighted sum of this stage)
+    const float4 o0 = o[0], o1 = o[1];
+    acc[0] += o0.x; acc[1] += o0.y; acc[2] += o0.z; acc[3] += o0.w;
+    acc[4] += o1.x; acc[5] += o1.y; acc[6] += o1.z; acc[7] += o1.w;
+  }
+  nt_store16(o, make_uint4(__float_as_uint(acc[0]), __float_as_uint(acc[1]),
+                           __float_as_uint(acc[2]), __float_as_uint(acc[3])));
+  nt_store16(o + 1, make_uint4(__float_as_uint(acc[4]), __float_as_uint(acc[5]),
+                               __float_as_uint(acc[6]), __float_as_uint(acc[7])));
 }
 
 // fp32 rows: a piece is 4 elements.
@@ -168,7 +154,7 @@ hipError_t launch_combine(const moe_config& c, int T, const void* ys, const int3
   const dim3 block(256);
   dim3 grid((T + 3) / 4);
   if (c.act_dtype == MOE_BF16) {
-    const size_t nseg = (size_t(width / 8) + 255) / 256;      // wavefronts per token row
+    const size_t nseg = (size_t(width / 8) + 63) / 64;        // wavefronts per token row
     grid = dim3(unsigned((size_t(T) * nseg + 3) / 4));
     MOE_LAUNCH(MOE_K_COMBINE, combine_bf16_kernel, grid, block, 0, s, static_cast<const uint4*>(ys), inv,
                        w, static_cast<const uint4*>(shared_ys), reinterpret_cast<float4*>(out), T,
