@@ -1,16 +1,13 @@
 // Dispatch: build the expert-contiguous send buffer (Sec. II "EP"; Alg. 2).
 //
-// A stable counting sort of the local assignments by expert, with no atomics
-// anywhere (so the permutation is unique and repeatable):
-//   1. count   one wavefront per sub-chunk of 64 consecutive assignments counts
-//              them per local expert with ballots (one per bit of the expert
-//              index, no atomics) and notes every
-//              assignment's rank among its expert's assignments of the sub-chunk
-//   2. scan    per expert (a workgroup of four wavefronts each) an exclusive scan over the
-//              sub-chunks -> counts; offsets = exclusive scan over experts,
-//              rebuilt in LDS by every scatter workgroup
-//   3. place   position = offsets[e] + start of the sub-chunk's run + rank
-//   4. gather  one wavefront per token reads the row ONCE (16 B per lane,
+// A stable counting sort of the local assignments by expert (the permutation is
+// unique and repeatable):
+//   1. count   per chunk of assignments the count of every local expert and every
+//              assignment's rank among its expert's assignments of the chunk
+//   2. place   counts, offsets = exclusive scan over experts (rebuilt by every
+//              workgroup from the chunks' counts); position = offsets[e] + count in
+//              the chunks before + rank
+//   3. gather  one wavefront per token reads the row ONCE (16 B per lane,
 //              coalesced) and writes it to each of its local positions
 #include "moe_internal.h"
 
@@ -49,109 +46,121 @@ __device__ __forceinline__ uint64_t same_expert_lanes(int e, int E_loc) {
   return same;
 }
 
-// One wavefront per sub-chunk of 64 consecutive flat assignments.  The lanes
-// that go to the same local expert find each other with ballots, which yields,
-// without atomics, the count per expert
-// and the rank of every assignment among its expert's assignments of the
-// sub-chunk.  Counts go to hist[E_loc][n_sub] (built in a wavefront-private LDS
-// row, so absent experts get their zero), ranks are parked in inv[].
-__global__ __launch_bounds__(256) void dispatch_count_kernel(
-    const int32_t* __restrict__ ids, int A, int e_lo, int E_loc, int n_sub,
+// The index, in two launches over chunks of whole runs of 1024 assignments (a
+// workgroup of sixteen wavefronts, one per 64 assignments of the run).
+//
+// count: the lanes of a wavefront that go to the same local expert find each other with
+// ballots; one thread per expert then orders the wavefronts, which yields, without
+// atomics, the rank of every assignment among its expert's assignments of the chunk
+// (parked in inv[]) and the chunk's count per expert (hist[chunk][E_loc]).
+constexpr int kRun = 1024;
+constexpr int kIndexWgs = 256;                 // chunks at most (longer ones instead)
+inline int index_chunk(int A) { return ((A + kIndexWgs - 1) / kIndexWgs + kRun - 1) / kRun * kRun; }
+
+__global__ __launch_bounds__(kRun) void dispatch_count_kernel(
+    const int32_t* __restrict__ ids, int A, int e_lo, int E_loc, int chunk,
     int32_t* __restrict__ hist, int32_t* __restrict__ inv) {
-  __shared__ int32_t cnt[4][512];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int sub = blockIdx.x * 4 + wave;
-  if (sub >= n_sub) return;
-  const int a = sub * kSub + lane;
-  int e = -1;
-  if (a < A) {
-    e = ids[a] - e_lo;
-    if (e < 0 || e >= E_loc) e = -1;
+  extern __shared__ int32_t cnt[];             // [16][E_loc]
+  const int tid = threadIdx.x, wave = tid >> 6;
+  const int a0 = blockIdx.x * chunk, a1 = min(A - a0, chunk) + a0;
+  int at = 0;                                  // thread e: assignments of expert e so far
+  for (int p = a0; p < a1; p += kRun) {
+    for (int i = tid; i < 16 * E_loc; i += kRun) cnt[i] = 0;
+    const int a = p + tid;
+    int e = -1;
+    if (a < a1) {
+      e = ids[a] - e_lo;
+      if (e < 0 || e >= E_loc) e = -1;
+    }
+    const uint64_t same = same_expert_lanes(e, E_loc);
+    const int rank = __popcll(same & lanemask_lt());
+    __syncthreads();
+    if (e >= 0 && rank == 0) cnt[wave * E_loc + e] = __popcll(same);   // the lowest lane of each expert present
+    __syncthreads();
+    if (tid < E_loc) {                         // E_loc <= 512
+#pragma unroll
+      for (int w = 0; w < 16; ++w) {
+        const int n = cnt[w * E_loc + tid];
+        cnt[w * E_loc + tid] = at;
+        at += n;
+      }
+    }
+    __syncthreads();
+    if (a < a1) inv[a] = e >= 0 ? cnt[wave * E_loc + e] + rank : -1;   // -1: expert not local
+    __syncthreads();                           // before cnt[] is cleared again
   }
-  int32_t* row = cnt[wave];                    // same-wavefront LDS accesses execute in order
-  for (int x = lane; x < E_loc; x += 64) row[x] = 0;
-  const uint64_t same = same_expert_lanes(e, E_loc);
-  int rank = -1;
-  if (e >= 0) {
-    rank = __popcll(same & lanemask_lt());
-    if (rank == 0) row[e] = __popcll(same);    // the lowest lane of each expert present
-  }
-  if (a < A) inv[a] = rank;                    // -1: expert not local
-  for (int x = lane; x < E_loc; x += 64) hist[size_t(x) * n_sub + sub] = row[x];
+  if (tid < E_loc) hist[size_t(blockIdx.x) * E_loc + tid] = at;
 }
 
-// Position of every local assignment: offsets[e] + start of its sub-chunk's run
-// inside the expert's segment + its rank (left in inv[] by the count kernel).
-// Every workgroup rebuilds offsets = exclusive scan of counts in LDS (E_loc <=
-// 512 values, one wavefront); workgroup 0 also stores them.
-__global__ __launch_bounds__(256) void dispatch_place_kernel(
-    const int32_t* __restrict__ ids, int A, int e_lo, int E_loc, int n_sub,
-    const int32_t* __restrict__ hist, const int32_t* __restrict__ counts,
-    int32_t* __restrict__ offsets_out, int32_t* __restrict__ perm, int32_t* __restrict__ inv) {
-  __shared__ int32_t offsets[513];
-  if (threadIdx.x < 64) {
-    const int l = threadIdx.x;
+// place: every workgroup adds up the chunks' counts per expert, those before its own
+// chunk apart from the rest (the threads share out experts and chunks; integer sums, so
+// the order of the LDS atomics does not matter), and scans the totals into offsets;
+// position = offsets[e] + count before the chunk + rank.  Workgroup 0 stores counts and
+// offsets.
+__global__ __launch_bounds__(kRun) void dispatch_place_kernel(
+    const int32_t* __restrict__ ids, int A, int e_lo, int E_loc, int chunk, int n_chunks,
+    const int32_t* __restrict__ hist, int32_t* __restrict__ counts, int32_t* __restrict__ offsets_out,
+    int32_t* __restrict__ perm, int32_t* __restrict__ inv) {
+  __shared__ int32_t before[512], total[512];  // before: becomes the chunk's first position of each expert
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int mine = blockIdx.x;
+  const int a0 = mine * chunk, a1 = min(A - a0, chunk) + a0;
+  const int a_first = a0 + tid;
+  int e = -1, rank = -1;                       // of this thread's first assignment: on their way meanwhile
+  if (a_first < a1) {
+    e = ids[a_first] - e_lo;
+    rank = inv[a_first];
+  }
+  if (tid < E_loc) before[tid] = total[tid] = 0;
+  __syncthreads();
+  const int groups = kRun / E_loc;             // threads per expert
+  if (tid < groups * E_loc) {
+    const int x = tid % E_loc, g = tid / E_loc;
+    int lo = 0, all = 0;
+#pragma unroll 4
+    for (int ch = g; ch < n_chunks; ch += groups) {
+      const int n = hist[size_t(ch) * E_loc + x];
+      all += n;
+      lo += ch < mine ? n : 0;
+    }
+    atomicAdd(&total[x], all);
+    atomicAdd(&before[x], lo);
+  }
+  __syncthreads();
+  if (tid < 64) {
     const int per = (E_loc + 63) / 64;
-    const int x0 = l * per, x1 = (x0 + per < E_loc) ? x0 + per : E_loc;
+    const int x0 = min(E_loc, lane * per), x1 = min(E_loc, x0 + per);
     int sum = 0;
-    for (int x = x0; x < x1; ++x) sum += counts[x];
+    for (int x = x0; x < x1; ++x) sum += total[x];
     int incl = sum;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
       const int o = __shfl_up(incl, off);
-      if (l >= off) incl += o;
+      if (lane >= off) incl += o;
     }
-    int run = incl - sum;
+    int at = incl - sum;
     for (int x = x0; x < x1; ++x) {
-      offsets[x] = run;
-      if (blockIdx.x == 0) offsets_out[x] = run;
-      run += counts[x];
+      const int n = total[x];
+      before[x] += at;
+      if (mine == 0) {
+        counts[x] = n;
+        offsets_out[x] = at;
+      }
+      at += n;
     }
-    if (l == 63) {
-      offsets[E_loc] = incl;
-      if (blockIdx.x == 0) offsets_out[E_loc] = incl;
-    }
+    if (lane == 63 && mine == 0) offsets_out[E_loc] = incl;
   }
   __syncthreads();
-  const int a = blockIdx.x * 256 + threadIdx.x;
-  if (a >= A) return;
-  const int rank = inv[a];
-  if (rank < 0) return;                        // inv[a] stays -1
-  const int e = ids[a] - e_lo;
-  const int pos = offsets[e] + hist[size_t(e) * n_sub + a / kSub] + rank;
-  perm[pos] = a;
-  inv[a] = pos;
-}
-
-// One workgroup of four wavefronts per local expert: exclusive scan of the
-// expert's row of counts (thread i owns a contiguous run of sub-chunks; a scan over
-// the lanes of each wavefront, then over the four wavefront totals), counts[e] =
-// the row's total.  Integer sums: the result does not depend on the split.
-__global__ __launch_bounds__(256) void dispatch_scan_kernel(int32_t* __restrict__ hist, int n_sub,
-                                                           int32_t* __restrict__ counts) {
-  __shared__ int32_t wave_total[4];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, e = blockIdx.x;
-  int32_t* row = hist + size_t(e) * n_sub;
-  const int per = (n_sub + 255) / 256;
-  const int s0 = min(n_sub, tid * per), s1 = min(n_sub, s0 + per);
-  int sum = 0;
-  for (int sb = s0; sb < s1; ++sb) sum += row[sb];
-  int incl = sum;                               // inclusive scan over the lanes of the wavefront
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int o = __shfl_up(incl, off);
-    if (lane >= off) incl += o;
+  for (int a = a_first; a < a1; a += kRun) {
+    if (a != a_first) {
+      e = ids[a] - e_lo;
+      rank = inv[a];
+    }
+    if (rank < 0) continue;                    // inv[a] stays -1
+    const int pos = before[e] + rank;
+    perm[pos] = a;
+    inv[a] = pos;
   }
-  if (lane == 63) wave_total[wave] = incl;
-  __syncthreads();
-  int run = incl - sum;
-  for (int w = 0; w < wave; ++w) run += wave_total[w];
-  for (int sb = s0; sb < s1; ++sb) {
-    const int c = row[sb];
-    row[sb] = run;
-    run += c;
-  }
-  if (tid == 255) counts[e] = run;
 }
 
 // One wavefront per token: read the row once, write it to every local position.
@@ -319,15 +328,22 @@ __global__ __launch_bounds__(256) void dispatch_small_kernel(
 
 // Per-row block scales follow their rows: out[kb][pos] = in[kb][token of pos] for
 // the valid positions (both arrays are block-major: one row of the array per
-// 128-column block).
+// 128-column block).  blockIdx.y takes kScaleRun blocks: one thread walking all 56
+// blocks of hidden 7168 was a chain of dependent loads on a quarter of the chip.
+constexpr int kScaleRun = 8;
 __global__ __launch_bounds__(256) void dispatch_scales_kernel(
     const float* __restrict__ in, int in_pitch, const int32_t* __restrict__ perm,
     const int32_t* __restrict__ offsets, int E_loc, int k, int n_blocks, float* __restrict__ out,
     int out_pitch) {
   const int pos = blockIdx.x * 256 + threadIdx.x;
   if (pos >= offsets[E_loc] || pos >= out_pitch) return;
-  const int t = perm[pos] / k;
-  for (int kb = 0; kb < n_blocks; ++kb) out[size_t(kb) * out_pitch + pos] = in[size_t(kb) * in_pitch + t];
+  const int t = perm[pos] / k, kb0 = blockIdx.y * kScaleRun;
+  float v[kScaleRun];
+#pragma unroll
+  for (int i = 0; i < kScaleRun; ++i) v[i] = in[size_t(min(kb0 + i, n_blocks - 1)) * in_pitch + t];
+#pragma unroll
+  for (int i = 0; i < kScaleRun; ++i)
+    if (kb0 + i < n_blocks) out[size_t(kb0 + i) * out_pitch + pos] = v[i];
 }
 
 }  // namespace
@@ -335,7 +351,8 @@ __global__ __launch_bounds__(256) void dispatch_scales_kernel(
 hipError_t launch_dispatch_scales(const float* in, int in_pitch, const int32_t* perm,
                                   const int32_t* offsets, int E_loc, int k, int n_blocks, float* out,
                                   int out_pitch, hipStream_t s) {
-  MOE_LAUNCH(MOE_K_DISPATCH_GATHER, dispatch_scales_kernel, dim3((out_pitch + 255) / 256), dim3(256), 0, s,
+  MOE_LAUNCH(MOE_K_DISPATCH_GATHER, dispatch_scales_kernel,
+             dim3((out_pitch + 255) / 256, (n_blocks + kScaleRun - 1) / kScaleRun), dim3(256), 0, s,
              in, in_pitch, perm, offsets, E_loc, k, n_blocks, out, out_pitch);
   return hipGetLastError();
 }
@@ -360,13 +377,11 @@ hipError_t launch_dispatch(const moe_config& c, int T, const void* x, const int3
                tp_rank * row16, row16);
     return hipGetLastError();
   }
-  const dim3 grid_idx((n_sub + 3) / 4), block_idx(256);
-  MOE_LAUNCH(MOE_K_DISPATCH_HIST, dispatch_count_kernel, grid_idx, block_idx, 0, s, ids, A,
-             c.expert_lo, E_loc, n_sub, ws.block_hist, inv);
-  MOE_LAUNCH(MOE_K_DISPATCH_SCAN, dispatch_scan_kernel, dim3(E_loc), dim3(256), 0, s, ws.block_hist,
-             n_sub, counts);
-  MOE_LAUNCH(MOE_K_DISPATCH_SCATTER, dispatch_place_kernel, dim3((A + 255) / 256), block_idx, 0, s,
-             ids, A, c.expert_lo, E_loc, n_sub, ws.block_hist, counts, offsets, perm, inv);
+  const int chunk = index_chunk(A), n_chunks = (A + chunk - 1) / chunk;
+  MOE_LAUNCH(MOE_K_DISPATCH_HIST, dispatch_count_kernel, dim3(n_chunks), dim3(kRun),
+             size_t(16) * E_loc * sizeof(int32_t), s, ids, A, c.expert_lo, E_loc, chunk, ws.block_hist, inv);
+  MOE_LAUNCH(MOE_K_DISPATCH_SCATTER, dispatch_place_kernel, dim3(n_chunks), dim3(kRun), 0, s, ids, A,
+             c.expert_lo, E_loc, chunk, n_chunks, ws.block_hist, counts, offsets, perm, inv);
   MOE_LAUNCH(MOE_K_DISPATCH_GATHER, dispatch_gather_kernel<8>, dim3((T + 3) / 4), dim3(256), 0, s,
              static_cast<const uint4*>(x), inv, static_cast<uint4*>(xs), T, k, src16,
              tp_rank * row16, row16);

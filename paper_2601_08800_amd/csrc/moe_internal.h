@@ -48,9 +48,8 @@ RouteWs carve_route(void* ws, int T, int E);
 // dispatch
 constexpr int kDispatchChunk = 64;            // assignments per histogram column (one wavefront)
 struct DispatchWs {
-  int32_t* block_hist; // [E_loc, n_blocks] counts per expert and sub-chunk of 64
-                       // assignments -> after the scan: start of the sub-chunk's
-                       // run inside the expert's segment
+  int32_t* block_hist; // [chunks, E_loc] counts per expert and chunk of assignments; sized
+                       // for one chunk per 64 assignments (n_blocks), the chunks are longer
   int n_blocks;
   size_t bytes;
 };

@@ -1,15 +1,34 @@
-"""Index kernels at the edges of their tiles: the combine's batches of eight rows."""
+"""Index kernels at the edges of their tiles: the two launches of the dispatch index
+around their chunk of 1024 assignments, and the combine's batches of eight rows."""
 import numpy as np
 import pytest
 import torch
 
 import oracle
-from helpers import dev, make_layer
+from helpers import check_dispatch, dev, make_layer
 from workloads import gen
 
 pytestmark = pytest.mark.gpu
 
 NO_WEIGHTS = {"w_gate": None, "w_up": None, "w_down": None}
+
+
+# one run, whole and ragged runs, more than 256 runs (chunks of two); one local expert,
+# 512 of them, an expert count that does not divide the workgroup
+@pytest.mark.parametrize("T,k,E,lo,hi", [
+    (4097, 1, 512, 0, 512), (4097, 1, 512, 511, 512), (2560, 2, 300, 0, 300), (1366, 3, 96, 5, 42),
+    (33000, 8, 64, 0, 64), (262145, 1, 32, 3, 32), (32768, 8, 8, 0, 8)])
+def test_dispatch_index_runs(T, k, E, lo, hi):
+    w = gen.CONFIGS["c2d"].replace(T=T, H=8, E=E, k=k, I=8, expert_lo=lo, expert_hi=hi)
+    rng = np.random.default_rng(T + E)
+    ids = rng.random((T, E), dtype=np.float32).argpartition(k - 1, axis=1)[:, :k].astype(np.int32)
+    ids[: T // 3, 0] = lo                                    # a hot expert (a token may hold it twice)
+    d = {"x": gen.make_x(w), "gate": gen.make_gate(w), "experts": NO_WEIGHTS, "shared": None}
+    L = make_layer(w, d)
+    L.topk_ids = dev(ids)
+    L.dispatch(dev(d["x"]))
+    torch.cuda.synchronize()
+    check_dispatch(L, ids, w, d["x"])
 
 
 # rows of one piece, of one wavefront's 64 pieces and one more; 1, 8, 9 and 32 experts a
