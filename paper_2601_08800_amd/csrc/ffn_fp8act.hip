@@ -105,33 +105,46 @@ __global__ __launch_bounds__(256) void fp8act_quant_kernel(const uint16_t* __res
 }
 
 // ------------------------------------------------------------- tile table
-// tiles[0] = number of M tiles, then (expert, first row, end row, 0) per tile of
-// up to FBM rows.  One thread per expert; experts have few tiles.
+// tiles[0] = number of M tiles, then (expert, first row, end row, 0) per tile.  An
+// expert's rows are cut into ceil(M / FBM) tiles of equal height (rounded up to 32 rows):
+// the GEMM skips the 32-row blocks a tile does not have.  One thread per expert; one
+// wavefront scans the tile counts.
 __global__ __launch_bounds__(512) void fp8act_tiles_kernel(const int32_t* __restrict__ offsets,
                                                           int n_experts, int rows_capacity,
                                                           int32_t* __restrict__ tiles, int max_tiles) {
-  __shared__ int32_t start[513];
+  __shared__ int32_t start[512];
   const int e = threadIdx.x;
   int lo = 0, hi = 0;
   if (e < n_experts) {
     lo = min(max(offsets[e], 0), rows_capacity);
     hi = min(max(offsets[e + 1], lo), rows_capacity);
   }
-  const int nt = (hi - lo + FBM - 1) / FBM;
-  if (e < 513) start[e] = nt;
+  const int full = (hi - lo + FBM - 1) / FBM;
+  const int step = full ? ((hi - lo + full - 1) / full + 31) / 32 * 32 : FBM;
+  start[e] = (hi - lo + step - 1) / step;       // experts past n_experts: no tiles
   __syncthreads();
-  if (threadIdx.x == 0) {                      // n_experts <= 512: a serial scan is a few hundred adds
-    int run = 0;
-    for (int i = 0; i < n_experts; ++i) { const int c = start[i]; start[i] = run; run += c; }
-    tiles[0] = run < max_tiles ? run : max_tiles;
+  if (e < 64) {
+    int n[8], sum = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum += n[i] = start[e * 8 + i];
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(incl, o);
+      if (e >= o) incl += v;
+    }
+    int run = incl - sum;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { start[e * 8 + i] = run; run += n[i]; }
+    if (e == 63) tiles[0] = incl < max_tiles ? incl : max_tiles;
   }
   __syncthreads();
   if (e >= n_experts) return;
   int t = start[e];
-  for (int r = lo; r < hi && t < max_tiles; r += FBM, ++t) {
+  for (int r = lo; r < hi && t < max_tiles; r += step, ++t) {
     tiles[1 + kTileRec * t] = e;
     tiles[2 + kTileRec * t] = r;
-    tiles[3 + kTileRec * t] = r + FBM < hi ? r + FBM : hi;
+    tiles[3 + kTileRec * t] = r + step < hi ? r + step : hi;
     tiles[4 + kTileRec * t] = 0;
   }
 }
@@ -163,8 +176,14 @@ __device__ __forceinline__ void fp8act_gemm_body(
   const int e = tiles[1 + kTileRec * mtile], row0 = tiles[2 + kTileRec * mtile],
             row1 = tiles[3 + kTileRec * mtile];
   const int n0 = ntile * CN;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // Wavefront (wm, wn) computes the 32-row blocks wm and wm + 2, as far as the tile has
+  // them.  Of a tile of one or three blocks the wm = 0 wavefronts do one block more; the
+  // workgroups that come to a CU second (the hardware deals the ids out over all 256 CUs)
+  // swap the roles, so the work is even over the SIMDs.
+  const int wm = (wave ^ (blockIdx.x >> 8)) & 1, wn = wave >> 1;
+  const int nblk = (row1 - row0 + 31) >> 5;       // 32-row blocks of the tile: 1..4
+  const int nbw = (nblk - wm + 1) >> 1;           // ... of this wavefront: 0..2
   const int h = lane >> 5, l31 = lane & 31;
   const int nkb = K / kQBlock, nnb = N / 128;
 
@@ -194,7 +213,7 @@ __device__ __forceinline__ void fp8act_gemm_body(
     rs = sA_t[size_t(kb) * rows_capacity + srow];          // first: the oldest load of the group
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      __builtin_amdgcn_global_load_lds((gptr_t)(ap[i] + size_t(kb) * kQBlock),
+      if (i < nblk) __builtin_amdgcn_global_load_lds((gptr_t)(ap[i] + size_t(kb) * kQBlock),
                                        (lptr_t)(As + st * FBM * 8 + (i * 4 + wave) * 64), 16, 0, 0);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -232,7 +251,8 @@ __device__ __forceinline__ void fp8act_gemm_body(
       i32x8 fa[2], fb[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const int r = wm * 64 + i * 32 + l31;
+        if (i >= nbw) break;
+        const int r = i * 64 + wm * 32 + l31;
         const uint4 lo = Ab[swz(r, p)], hi = Ab[swz(r, p + 1)];
         fa[i] = i32x8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
       }
@@ -243,7 +263,8 @@ __device__ __forceinline__ void fp8act_gemm_body(
         fb[j] = i32x8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
       }
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 2; ++i) {
+        if (i >= nbw) break;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           f32x16 c;
@@ -256,16 +277,18 @@ __device__ __forceinline__ void fp8act_gemm_body(
           part[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[i], fb[j], c, 0, 0, 0,
                                                                       0x7f7f7f7f, 0, 0x7f7f7f7f);
         }
+      }
     }
     // promote the block's sums: acc += part * sA[row] * sB
     const float sb0 = s0p[kb];
     const float sb1 = DUAL ? s1p[kb] : sb0;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
+      if (i >= nbw) break;
       float sa[16];
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
-        const float4 v = *reinterpret_cast<const float4*>(Ss + buf * FBM + wm * 64 + i * 32 + q4 * 8 + h * 4);
+        const float4 v = *reinterpret_cast<const float4*>(Ss + buf * FBM + i * 64 + wm * 32 + q4 * 8 + h * 4);
         sa[q4 * 4 + 0] = v.x; sa[q4 * 4 + 1] = v.y; sa[q4 * 4 + 2] = v.z; sa[q4 * 4 + 3] = v.w;
       }
 #pragma unroll
@@ -281,7 +304,7 @@ __device__ __forceinline__ void fp8act_gemm_body(
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-      const int row = row0 + wm * 64 + i * 32 + (q >> 2) * 8 + h * 4 + (q & 3);
+      const int row = row0 + i * 64 + wm * 32 + (q >> 2) * 8 + h * 4 + (q & 3);
       if (row >= row1) continue;
       if (DUAL) {
         const float g = acc[i][0][q], u = acc[i][1][q];
