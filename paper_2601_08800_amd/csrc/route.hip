@@ -13,8 +13,8 @@
 //   3. re-score    one workgroup per listed token: the experts whose key
 //                  interval reaches the selection get an fp64 dot product and
 //                  the selection is redone in fp64
-// Decode-sized batches (T*E*H up to 2^28) skip all three: one kernel computes
-// every logit in fp64 and selects on fp64 keys.
+// Short batches (and fp32 rows) skip all three: every logit is computed in fp64 on the
+// fp64 matrix instructions and the selection works on fp64 keys.
 // Error model of stage 1 for a chain of n bf16 products (exact in fp32) added
 // in fp32: every addition is off by at most one ulp of the running sum, so
 // |error| <= 2n * 2^-24 * sum|x_h w_h| <= 2n * 2^-24 * |x|_2 |w|_2.
@@ -78,10 +78,6 @@ __device__ __forceinline__ double read_lane(double v, int l) {
   return __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
 }
 
-__device__ __forceinline__ int lane_id() {
-  return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-}
-
 // Sum over the wave in a fixed order, the same in every lane: a butterfly inside
 // each row of 16 lanes, then (row0 + row1) + (row2 + row3) from the row results
 // read as scalars.
@@ -106,30 +102,17 @@ __device__ __forceinline__ T wave_max(T v) {
   return b > a ? b : a;
 }
 
-__device__ __forceinline__ int wave_min(int v) {
-#define STEP_(S) { const int o = lane_xchg<S>(v); v = o < v ? o : v; }
-  MOE_ALL_STEPS(STEP_)
-#undef STEP_
-  return v;
-}
-
-// Largest value over the wave, ties to the lowest index; idx == INT_MAX marks
-// "no candidate".  Result is the same in every lane.  The maximum is a plain
-// wave_max; the lanes that hold it answer a ballot, and the usual single winner's
-// index is read from its lane (a minimum over the tied lanes otherwise).
+// Largest value over the wave, ties to the lowest index, which must not fall from one
+// lane to the next: the first lane that holds the maximum has it.  idx == INT_MAX marks
+// "no candidate".  Result is the same in every lane.
 template <typename T>
 __device__ __forceinline__ void wave_argmax(T& v, int& idx) {
   const bool cand = idx != INT_MAX;
   const T vv = cand ? v : (T)-INFINITY;
   const T m = wave_max(vv);
   const uint64_t tie = __ballot(cand && vv == m);
-  int win = INT_MAX;
-  if (tie != 0) {
-    if ((tie & (tie - 1)) == 0) win = read_lane(idx, __ffsll((unsigned long long)tie) - 1);
-    else win = wave_min((tie >> lane_id() & 1) ? idx : INT_MAX);
-  }
+  idx = tie != 0 ? read_lane(idx, __ffsll((unsigned long long)tie) - 1) : INT_MAX;
   v = tie != 0 ? m : (T)0;
-  idx = win;
 }
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t hi16) {
@@ -148,7 +131,7 @@ __device__ __forceinline__ float piece_sumsq(const uint4& a, float acc) {
   return acc;
 }
 
-// fp64 dot product of two 16-byte pieces (8 bf16 or 4 fp32), added to acc.
+// fp64 dot product (exact products) of two 16-byte pieces, 8 bf16 or 4 fp32, added to acc.
 template <bool BF16>
 __device__ __forceinline__ double piece_dot64(const uint4& a, const uint4& b, double acc) {
   const uint32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
@@ -164,79 +147,9 @@ __device__ __forceinline__ double piece_dot64(const uint4& a, const uint4& b, do
   return acc;
 }
 
-// fp64 dot product of one token row with one gate row, one wavefront, fixed
-// order (lane-strided partial sums, then a butterfly): exact products, fp64 sums.
-template <bool BF16>
-__device__ __forceinline__ double wave_dot64(const void* xrow, const void* wrow, int H, int lane) {
-  double acc = 0.0;
-  if (BF16) {
-    const uint4* xa = static_cast<const uint4*>(xrow);
-    const uint4* wa = static_cast<const uint4*>(wrow);
-#pragma unroll 4
-    for (int c = lane; c < H / 8; c += 64) {
-      const uint4 a = xa[c], b = wa[c];
-      const uint32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        acc = fma((double)bf16_bits_to_f32(av[i] & 0xffffu), (double)bf16_bits_to_f32(bv[i] & 0xffffu), acc);
-        acc = fma((double)bf16_bits_to_f32(av[i] >> 16), (double)bf16_bits_to_f32(bv[i] >> 16), acc);
-      }
-    }
-  } else {
-    const float4* xa = static_cast<const float4*>(xrow);
-    const float4* wa = static_cast<const float4*>(wrow);
-#pragma unroll 4
-    for (int c = lane; c < H / 4; c += 64) {
-      const float4 a = xa[c], b = wa[c];
-      acc = fma((double)a.x, (double)b.x, acc);
-      acc = fma((double)a.y, (double)b.y, acc);
-      acc = fma((double)a.z, (double)b.z, acc);
-      acc = fma((double)a.w, (double)b.w, acc);
-    }
-  }
-  return wave_sum(acc);
-}
-
-// ------------------------------------------------- stage 0: gate row norms
-// One wavefront per gate row: wnorm2[e] = sum_h w[e,h]^2.  Also clears the
-// re-score counter (a fill kernel rather than a memset, so the call can be
-// captured in a graph).
-template <bool BF16>
-__global__ __launch_bounds__(256) void gate_wnorm_kernel(const void* __restrict__ gate_w, int E,
-                                                        int H, float* __restrict__ wnorm2,
-                                                        int32_t* __restrict__ counters) {
-  if (blockIdx.x == 0 && threadIdx.x < 64) counters[threadIdx.x] = 0;
-  if (!gate_w) return;
-  const int lane = threadIdx.x & 63;
-  const int e = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (e >= E) return;
-  const size_t rb = size_t(e) * H * (BF16 ? 2 : 4);
-  const char* row = static_cast<const char*>(gate_w) + rb;
-  const double s = wave_dot64<BF16>(row, row, H, lane);
-  if (lane == 0) wnorm2[e] = (float)(s * (1.0 + 1e-6));
-}
-
-// ------------------------ stage 1 (fp32 inputs, many tokens): fp64 VALU gate
-// One workgroup per token; each wavefront takes every 4th expert.  Exact
-// products, fp64 sums: the logits are good to the fp32 store.
-template <bool BF16>
-__global__ __launch_bounds__(256) void gate_f64_kernel(const void* __restrict__ x,
-                                                      const void* __restrict__ gate_w, int T,
-                                                      int H, int E, float* __restrict__ logits,
-                                                      float* __restrict__ xnorm2) {
-  const int t = blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const size_t eb = BF16 ? 2 : 4;
-  const char* xr = static_cast<const char*>(x) + size_t(t) * H * eb;
-  for (int e = wave; e < E; e += 4) {
-    const double z = wave_dot64<BF16>(xr, static_cast<const char*>(gate_w) + size_t(e) * H * eb, H, lane);
-    if (lane == 0) logits[size_t(t) * E + e] = (float)z;
-  }
-  if (wave == 0) {
-    const double s = wave_dot64<BF16>(xr, xr, H, lane);
-    if (lane == 0) xnorm2[t] = (float)(s * (1.0 + 1e-6));
-  }
-}
+// Clears the re-score counter where no gate GEMM does (logits given by the caller): a
+// kernel rather than a memset, so the call can be captured in a graph.
+__global__ void clear_counters_kernel(int32_t* __restrict__ counters) { counters[threadIdx.x] = 0; }
 
 // ------------------------------------------ stage 1 (bf16): MFMA gate GEMM
 // Register-staged variant, used when H is not a multiple of 64 (it zero-fills
@@ -541,29 +454,63 @@ struct SelCfg {
   float scale;
   float chain_err;   // 2n * 2^-24 of the gate accumulation (0 when logits are given)
   int have_norms;
-  int nsplit;        // K splits of the gate GEMM: logits and row norms are sums of this many slabs
-  int wsplit;        // slabs of the gate rows' sums of squares (stride E)
+  int nsplit;        // K splits of the gate GEMM: logits, token-row and gate-row norms are sums of this many slabs
   int T;             // tokens: slab strides are T*E (logits) and T (row norms)
 };
+
+// The gate's form, fixed at compile time for the two forms that layers are served with.
+// The routing kernels are short: much of their time is fetching their own code, one
+// cache line after the other on every CU, so a kernel holds what its gate executes.
+enum GateForm {
+  kGateSoftmax,    // softmax scores, no group limit
+  kGateGrouped,    // sigmoid scores, group limit over aligned runs of whole lanes (aligned_groups)
+  kGateAny         // everything else: decided at run time
+};
+template <int FORM> __device__ __forceinline__ bool is_softmax(const SelCfg& c) {
+  return FORM == kGateSoftmax || (FORM == kGateAny && c.score_fn == MOE_SCORE_SOFTMAX);
+}
+template <int FORM> __device__ __forceinline__ bool has_groups(const SelCfg& c) {
+  return FORM == kGateGrouped || (FORM == kGateAny && c.G > 1);
+}
+// Groups that are aligned runs of 1, 2, 4 .. 64 whole lanes, scored by one or two keys.
+template <int EPL> __host__ __device__ __forceinline__ bool aligned_groups(const SelCfg& c) {
+  const int gs = c.E / c.G;
+  return gs % EPL == 0 && 64 % (gs / EPL) == 0 && c.gn <= 2;
+}
+// Group of the lane's expert i.
+template <int EPL, int FORM> __device__ __forceinline__ int lane_group(const SelCfg& c, int lane, int i) {
+  return (lane * EPL + (FORM == kGateGrouped ? 0 : i)) / (c.E / c.G);
+}
+template <int EPL> inline GateForm gate_form(const SelCfg& c) {
+  if (c.G <= 1 && c.score_fn == MOE_SCORE_SOFTMAX) return kGateSoftmax;
+  if (c.G > 1 && c.score_fn == MOE_SCORE_SIGMOID && aligned_groups<EPL>(c)) return kGateGrouped;
+  return kGateAny;
+}
+
+// Sum of element p of `ns` (1..kGateMaxSplit) slabs `stride` apart, in slab order.  The
+// loads do not wait for one another: a slab loop that adds as it goes is one memory
+// latency per slab, and a wavefront has EPL of them for the logits and as many for the
+// gate norms.  The slabs past the last are read again from the first and left out.
+__device__ __forceinline__ float slab_sum(const float* __restrict__ p, size_t stride, int ns) {
+  float v[kGateMaxSplit];
+#pragma unroll
+  for (int i = 0; i < kGateMaxSplit; ++i) v[i] = p[i < ns ? i * stride : 0];
+  float s = v[0];
+#pragma unroll
+  for (int i = 1; i < kGateMaxSplit; ++i) s = i < ns ? s + v[i] : s;
+  return s;
+}
 
 // Norm of token t's row from the per-split sums of squares.
 __device__ __forceinline__ float token_norm(const SelCfg& c, const float* __restrict__ xnorm2, int t) {
   if (!c.have_norms) return 0.f;
-  float s = xnorm2[t];
-  for (int i = 1; i < c.nsplit; ++i) s += xnorm2[t + size_t(i) * c.T];
-  return sqrtf(s);
-}
-
-// Norm of gate row e from the per-split sums of squares.
-__device__ __forceinline__ float gate_norm(const SelCfg& c, const float* __restrict__ wnorm2, int e) {
-  float s = wnorm2[e];
-  for (int i = 1; i < c.wsplit; ++i) s += wnorm2[e + i * c.E];
-  return sqrtf(s);
+  return sqrtf(c.nsplit == 1 ? xnorm2[t] : slab_sum(xnorm2 + t, c.T, c.nsplit));
 }
 
 // Fast key of one expert from its stage-1 logit z (the slabs already added up):
 // key, the bound eps on |key - exact key|, and the value sc the weight is made of.
 // wn = norm of the gate row (unused without norms).
+template <int FORM>
 __device__ __forceinline__ void fast_key_one(const SelCfg& c, float z, float xn, float wn,
                                              const float* __restrict__ logit_bias,
                                              const float* __restrict__ select_bias, int e,
@@ -574,7 +521,7 @@ __device__ __forceinline__ void fast_key_one(const SelCfg& c, float z, float xn,
     z += logit_bias[e];
     ez += kUlp * fabsf(z);
   }
-  if (c.score_fn == MOE_SCORE_SOFTMAX) {
+  if (is_softmax<FORM>(c)) {
     key = z; eps = ez; sc = z;
   } else {
     const float s = 1.0f / (1.0f + expf(-z));
@@ -587,7 +534,8 @@ __device__ __forceinline__ void fast_key_one(const SelCfg& c, float z, float xn,
   }
 }
 
-// Per-lane view of one token's experts: expert e = slot*64 + lane.
+// Per-lane view of one token's experts: lane l holds experts l*EPL .. l*EPL + EPL-1, so that a
+// group of experts is a run of lanes and what its lanes hold is first combined in registers.
 template <typename FT, int EPL>
 struct Keys {
   FT key[EPL];   // selection key
@@ -611,46 +559,68 @@ struct Picks {
   bool certain;  // every comparison held with the error intervals apart
 };
 
-// Fast keys of token t from the stage-1 logits.
-template <int EPL>
+// Fast keys of token t from the stage-1 logits.  All loads come first.
+template <int EPL, int FORM>
 __device__ __forceinline__ void fast_keys(const SelCfg& c, const float* __restrict__ logits_row,
                                           const float* __restrict__ logit_bias,
                                           const float* __restrict__ select_bias, float xn,
                                           const float* __restrict__ wnorm2, int lane,
                                           Keys<float, EPL>& K) {
+  float z[EPL], wn2[EPL];
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) { z[i] = 0.f; wn2[i] = 0.f; }
+  if (c.nsplit == 1) {
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+      const int e = lane * EPL + i;
+      if (e < c.E) {
+        z[i] = logits_row[e];
+        if (c.have_norms) wn2[i] = wnorm2[e];
+      }
+    }
+  } else {                                     // only the gate GEMM's slabs: norms are there too
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) {
+      const int e = min(lane * EPL + i, c.E - 1);
+      z[i] = slab_sum(logits_row + e, size_t(c.T) * c.E, c.nsplit);
+      wn2[i] = slab_sum(wnorm2 + e, c.E, c.nsplit);
+    }
+  }
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
-    const int e = i * 64 + lane;
+    const int e = lane * EPL + i;
     float key = -INFINITY, eps = 0.f, sc = 0.f;
-    if (e < c.E) {
-      float z = logits_row[e];
-      for (int sp = 1; sp < c.nsplit; ++sp) z += logits_row[e + size_t(sp) * c.T * c.E];
-      const float wn = c.have_norms ? gate_norm(c, wnorm2, e) : 0.f;
-      fast_key_one(c, z, xn, wn, logit_bias, select_bias, e, key, eps, sc);
-    }
+    if (e < c.E)
+      fast_key_one<FORM>(c, z[i], xn, c.have_norms ? sqrtf(wn2[i]) : 0.f, logit_bias, select_bias, e, key, eps, sc);
     K.key[i] = key; K.eps[i] = eps; K.sc[i] = sc;
   }
 }
 
 // Group limit: keep the Kg groups with the largest sum of their gn largest
 // keys; ties go to the lowest group.  Lane g ends up holding group g's score.
-template <typename FT, int EPL>
+template <typename FT, int EPL, int FORM>
 __device__ __forceinline__ void group_stage(const SelCfg& c, const Keys<FT, EPL>& K, int lane,
                                             Groups<FT>& Gp) {
   const int gs = c.E / c.G;
   FT gsum = 0, gerr = 0;          // lane g: score of group g and the bound on its error
   uint32_t need = 0;
-  if (64 % gs == 0 && c.gn <= 2 && c.E % 64 == 0) {
-    // groups are aligned runs of gs lanes inside a slot: butterfly (max1, max2,
-    // max eps, min lower bound of the two largest) over each run, all groups at once
-    const int per_slot = 64 / gs;
+  if (FORM == kGateGrouped || aligned_groups<EPL>(c)) {
+    // (max1, max2, max eps, two largest lower bounds) of the lane's own keys, then a
+    // butterfly over the lanes of each group, all groups at once
+    const int gl = gs / EPL;
+    FT m1 = -INFINITY, m2 = -INFINITY, me = 0, l1 = -INFINITY, l2 = -INFINITY;
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
-      if (i * 64 >= c.E) break;
-      FT m1 = K.key[i], m2 = -INFINITY, me = K.eps[i];
-      FT l1 = K.key[i] - K.eps[i], l2 = -INFINITY;      // two largest lower bounds
+      const FT k = K.key[i], l = k - K.eps[i];
+      const FT klo = k < m1 ? k : m1, llo = l < l1 ? l : l1;
+      m1 = k > m1 ? k : m1;
+      m2 = klo > m2 ? klo : m2;
+      l1 = l > l1 ? l : l1;
+      l2 = llo > l2 ? llo : l2;
+      me = K.eps[i] > me ? K.eps[i] : me;
+    }
 #define STEP_(S)                                                                   \
-  if ((1 << S) < gs) {                                                             \
+  if ((1 << S) < gl) {                                                             \
     const FT o1 = lane_xchg<S>(m1), o2 = lane_xchg<S>(m2), oe = lane_xchg<S>(me);  \
     const FT p1 = lane_xchg<S>(l1), p2 = lane_xchg<S>(l2);                         \
     const FT lo = m1 < o1 ? m1 : o1, hi2 = m2 > o2 ? m2 : o2;                      \
@@ -661,24 +631,24 @@ __device__ __forceinline__ void group_stage(const SelCfg& c, const Keys<FT, EPL>
     l1 = l1 > p1 ? l1 : p1;                                                        \
     l2 = ql > qh ? ql : qh;                                                        \
   }
-      MOE_ALL_STEPS(STEP_)
+    MOE_ALL_STEPS(STEP_)
 #undef STEP_
-      const FT sum = c.gn == 2 ? m1 + m2 : m1;
-      const FT nth_low = c.gn == 2 ? l2 : l1;            // <= the gn-th largest exact key
+    const FT sum = c.gn == 2 ? m1 + m2 : m1;
+    const FT nth_low = c.gn == 2 ? l2 : l1;              // <= the gn-th largest exact key
+#pragma unroll
+    for (int i = 0; i < EPL; ++i)
       if (K.key[i] + K.eps[i] >= nth_low) need |= 1u << i;
-      // lane g fetches its group's values from the first lane of the run
-      const int g0 = i * per_slot;
-      const int src = (lane >= g0 && lane < g0 + per_slot) ? (lane - g0) * gs : 0;
-      const FT s_ = __shfl(sum, src), e_ = __shfl(me, src);
-      if (lane >= g0 && lane < g0 + per_slot) { gsum = s_; gerr = e_ * (FT)c.gn; }
-    }
+    // lane g fetches its group's values from the first lane of the run
+    const int src = lane < c.G ? lane * gl : 0;
+    gsum = __shfl(sum, src);
+    gerr = __shfl(me, src) * (FT)c.gn;
   } else {
     for (int g = 0; g < c.G; ++g) {
       uint32_t taken = 0;
       FT sum = 0, me = 0, nth_low = INFINITY;
 #pragma unroll
       for (int i = 0; i < EPL; ++i) {
-        const int e = i * 64 + lane;
+        const int e = lane * EPL + i;
         if (e < c.E && e / gs == g) me = K.eps[i] > me ? K.eps[i] : me;
       }
       me = wave_max(me);
@@ -686,7 +656,7 @@ __device__ __forceinline__ void group_stage(const SelCfg& c, const Keys<FT, EPL>
         FT v = 0; int idx = INT_MAX;
 #pragma unroll
         for (int i = 0; i < EPL; ++i) {
-          const int e = i * 64 + lane;
+          const int e = lane * EPL + i;
           if (e < c.E && e / gs == g && !(taken >> i & 1) && (idx == INT_MAX || K.key[i] > v)) {
             v = K.key[i]; idx = e;
           }
@@ -694,11 +664,11 @@ __device__ __forceinline__ void group_stage(const SelCfg& c, const Keys<FT, EPL>
         wave_argmax(v, idx);
         sum += v;
         nth_low = v - me;       // keys come in descending order; me bounds every eps
-        if ((idx & 63) == lane) taken |= 1u << (idx >> 6);
+        if (idx / EPL == lane) taken |= 1u << (idx % EPL);
       }
 #pragma unroll
       for (int i = 0; i < EPL; ++i) {
-        const int e = i * 64 + lane;
+        const int e = lane * EPL + i;
         if (e < c.E && e / gs == g && K.key[i] + K.eps[i] >= nth_low) need |= 1u << i;
       }
       if (lane == g) { gsum = sum; gerr = me * (FT)c.gn; }
@@ -728,14 +698,13 @@ __device__ __forceinline__ void group_stage(const SelCfg& c, const Keys<FT, EPL>
 }
 
 // Eligibility bits per slot: valid expert whose group is kept.
-template <int EPL>
+template <int EPL, int FORM>
 __device__ __forceinline__ uint32_t eligible_mask(const SelCfg& c, uint64_t kept, int lane) {
   uint32_t elig = 0;
-  const int gs = c.E / c.G;
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
-    const int e = i * 64 + lane;
-    if (e < c.E && (c.G <= 1 || (kept >> (e / gs) & 1))) elig |= 1u << i;
+    const int e = lane * EPL + i;
+    if (e < c.E && (!has_groups<FORM>(c) || (kept >> lane_group<EPL, FORM>(c, lane, i) & 1))) elig |= 1u << i;
   }
   return elig;
 }
@@ -753,11 +722,11 @@ __device__ __forceinline__ void topk_stage(const SelCfg& c, const Keys<FT, EPL>&
 #pragma unroll
     for (int i = 0; i < EPL; ++i) {
       if ((elig >> i & 1) && !(taken >> i & 1) && (idx == INT_MAX || K.key[i] > v)) {
-        v = K.key[i]; idx = i * 64 + lane;
+        v = K.key[i]; idx = lane * EPL + i;
       }
     }
     wave_argmax(v, idx);
-    const int owner = idx & 63, slot = idx >> 6;
+    const int owner = (idx / EPL) & 63, slot = idx % EPL;
     FT oe = 0, os = 0;
 #pragma unroll
     for (int i = 0; i < EPL; ++i)
@@ -786,12 +755,12 @@ __device__ __forceinline__ void topk_stage(const SelCfg& c, const Keys<FT, EPL>&
 }
 
 // Weights of the picked experts; lane j < k returns w[t,j].
-template <typename FT, int EPL>
+template <typename FT, int EPL, int FORM>
 __device__ __forceinline__ FT pick_weight(const SelCfg& c, const Keys<FT, EPL>& K,
                                           const Picks<FT>& P, int lane) {
   const bool mine = lane < c.k;
   FT num, den;
-  if (c.score_fn == MOE_SCORE_SOFTMAX) {
+  if (is_softmax<FORM>(c)) {
     if (c.renormalize) {
       const FT m = wave_max(mine ? P.sc : (FT)-INFINITY);
       num = mine ? (FT)exp((FT)(P.sc - m)) : (FT)0;
@@ -800,12 +769,12 @@ __device__ __forceinline__ FT pick_weight(const SelCfg& c, const Keys<FT, EPL>& 
       FT m = -INFINITY;
 #pragma unroll
       for (int i = 0; i < EPL; ++i)
-        if (i * 64 + lane < c.E) m = K.sc[i] > m ? K.sc[i] : m;
+        if (lane * EPL + i < c.E) m = K.sc[i] > m ? K.sc[i] : m;
       m = wave_max(m);
       FT s = 0;
 #pragma unroll
       for (int i = 0; i < EPL; ++i)
-        if (i * 64 + lane < c.E) s += (FT)exp((FT)(K.sc[i] - m));
+        if (lane * EPL + i < c.E) s += (FT)exp((FT)(K.sc[i] - m));
       den = wave_sum(s);
       num = mine ? (FT)exp((FT)(P.sc - m)) : (FT)0;
     }
@@ -816,7 +785,7 @@ __device__ __forceinline__ FT pick_weight(const SelCfg& c, const Keys<FT, EPL>& 
   return num / den * (FT)c.scale;
 }
 
-template <int EPL>
+template <int EPL, int FORM>
 __global__ __launch_bounds__(256) void route_select_kernel(
     SelCfg c, int T, const float* __restrict__ logits, const float* __restrict__ logit_bias,
     const float* __restrict__ select_bias, const float* __restrict__ xnorm2,
@@ -828,14 +797,14 @@ __global__ __launch_bounds__(256) void route_select_kernel(
   if (t >= T) return;
   Keys<float, EPL> K;
   const float xn = token_norm(c, xnorm2, t);
-  fast_keys<EPL>(c, logits + size_t(t) * c.E, logit_bias, select_bias, xn, wnorm2, lane, K);
+  fast_keys<EPL, FORM>(c, logits + size_t(t) * c.E, logit_bias, select_bias, xn, wnorm2, lane, K);
   Groups<float> Gp;
   Gp.kept = 0; Gp.certain = true; Gp.need = 0; Gp.open = 0;
-  if (c.G > 1) group_stage<float, EPL>(c, K, lane, Gp);
+  if (has_groups<FORM>(c)) group_stage<float, EPL, FORM>(c, K, lane, Gp);
   Picks<float> P;
-  topk_stage<float, EPL>(c, K, eligible_mask<EPL>(c, Gp.kept, lane), lane, P);
+  topk_stage<float, EPL>(c, K, eligible_mask<EPL, FORM>(c, Gp.kept, lane), lane, P);
   if (P.certain && Gp.certain) {
-    const float wt = pick_weight<float, EPL>(c, K, P, lane);
+    const float wt = pick_weight<float, EPL, FORM>(c, K, P, lane);
     if (lane < c.k) {
       ids[size_t(t) * c.k + lane] = P.id;
       w[size_t(t) * c.k + lane] = wt;
@@ -850,47 +819,45 @@ __global__ __launch_bounds__(256) void route_select_kernel(
 }
 
 // --------------------------------------------------------- stage 3: re-score
-// One wavefront per listed token (four independent tokens per workgroup, no
-// workgroup barrier).  Phase 1 (only when the group cut is in doubt): the
+// One workgroup per listed token, or one wavefront when the list is longer than the
+// grid (known here only; the whole grid takes the same side).  Phase 0 (only when the group cut is in doubt): the
 // experts that may be among their group's largest get exact keys and the groups
-// are chosen in fp64.  Phase 2: with the groups fixed, the experts whose key
+// are chosen in fp64.  Phase 1: with the groups fixed, the experts whose key
 // interval reaches the picks get exact keys and the top-k is taken in fp64.
 // Experts outside those sets keep their fast keys: by construction they cannot
-// change either decision.  A wavefront's candidate list and exact logits live
-// in its own slice of LDS; LDS operations of one wavefront execute in order.
-// COOP (short lists: few tokens in the batch): one token per workgroup.  The four
-// wavefronts run the same selection steps on the same data (so their control
-// flow is identical and the barriers below are reached by all of them) and share
-// out each exact dot product, a quarter of the token row each: the chain of
-// dependent load rounds, which is all this kernel's time, is four times shorter.
-template <int EPL, bool BF16, bool COOP>
-__global__ __launch_bounds__(256, 2) void route_recheck_kernel(
+// change either decision.  The four wavefronts of a shared token run the same selection
+// steps on the same data (so their control flow is identical and the barriers are reached
+// by all of them) and share out each exact dot product, a quarter of the token row each.  A
+// wavefront's candidate list and exact logits live in its own slice of LDS; LDS
+// operations of one wavefront execute in order.
+// What bounds it is one token's chain: dependent loads, and the fetch of the code, which
+// every CU does afresh.  Hence one form of the dot products (two experts at a time: the
+// usual list is two picks whose order is in doubt), one copy of each step for both
+// phases, and the gate's form fixed at compile time.
+template <int EPL, int FORM>
+__global__ __launch_bounds__(256, EPL <= 1 ? 3 : 2) void route_recheck_kernel(
     SelCfg c, int H, const void* __restrict__ x, const void* __restrict__ gate_w,
     const float* __restrict__ logits_in, const float* __restrict__ logits,
     const float* __restrict__ logit_bias, const float* __restrict__ select_bias,
     const float* __restrict__ xnorm2, const float* __restrict__ wnorm2, int32_t* __restrict__ ids,
     float* __restrict__ w, const int32_t* __restrict__ counters,
     const int32_t* __restrict__ recheck, const float* __restrict__ recheck_low) {
+  constexpr int CB = 2;                          // experts per walk over the token row
+  constexpr int U = 4;                           // pieces per thread and row in flight
   __shared__ int xlist_all[4][EPL * 64];
   __shared__ double zx_all[4][EPL * 64];
-  __shared__ float2 rint_all[4][EPL * 64];     // key intervals of the listed experts
-  __shared__ double part_all[COOP ? 4 : 1][4]; // COOP: partial dot products of the wavefronts (up to 4 experts)
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ float2 rint_all[4][EPL * 64];       // key intervals of the listed experts
+  __shared__ double part_all[4][CB];             // partial dot products of the wavefronts
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int* const xlist = xlist_all[wave];
   double* const zx = zx_all[wave];
   float2* const rint = rint_all[wave];
   const int n_list = counters[0];
-  const size_t eb = BF16 ? 2 : 4;
+  const bool coop = n_list <= int(gridDim.x);    // a workgroup per token
+  const int team = coop ? 256 : 64, me = coop ? tid : lane;
+  const int n16 = H / 8;                         // pieces of a bf16 row (fp32 rows have exact logits to begin with)
 
-  // exact logits of the experts in xlist[0..n) -> zx[e].  The wavefront walks the
-  // token row once per batch of CB experts, lane-strided 16-byte pieces, four
-  // pieces per lane and expert in flight; the lane sums are combined by a fixed
-  // butterfly.
-  // CB experts per walk over the token row.  6 and 8 measured slower (register
-  // pressure); a second instance of this code with CB = 2 for the usual short list
-  // (two picks whose order is in doubt) made the kernel slower as a whole
-  // (re-score 46 -> 64 us on the 256-expert gate at 16384 tokens).
-  constexpr int CB = 4;
+  // exact logits of the experts in xlist[0..n) -> zx[e]
   auto exact_logits = [&](int t, int n) {
     if (logits_in) {
       for (int q = lane; q < n; q += 64) {
@@ -901,8 +868,8 @@ __global__ __launch_bounds__(256, 2) void route_recheck_kernel(
       }
       return;
     }
-    const char* xrow = static_cast<const char*>(x) + size_t(t) * H * eb;
-    const int n16 = int(H * eb / 16);
+    const char* xrow = static_cast<const char*>(x) + size_t(t) * H * 2;
+#pragma unroll 1
     for (int q0 = 0; q0 < n; q0 += CB) {
       double acc[CB];
       const char* wrow[CB];
@@ -911,59 +878,44 @@ __global__ __launch_bounds__(256, 2) void route_recheck_kernel(
       for (int i = 0; i < CB; ++i) {
         acc[i] = 0.0;
         ex[i] = xlist[q0 + i < n ? q0 + i : n - 1];
-        wrow[i] = static_cast<const char*>(gate_w) + size_t(ex[i]) * H * eb;
+        wrow[i] = static_cast<const char*>(gate_w) + size_t(ex[i]) * H * 2;
       }
-      // U pieces per lane and expert in flight (the tail pieces are clamped to the
-      // last one and masked out of the sum)
-      constexpr int U = 4;
-      // COOP: wavefront w walks the pieces w*64*U .. of every run of 4*64*U
-      for (int p0 = COOP ? wave * 64 * U : 0; p0 < n16; p0 += (COOP ? 4 : 1) * 64 * U) {
+#pragma unroll 1
+      for (int p0 = me; p0 < n16; p0 += team * U) {
         uint4 a[U], b[CB][U];
-        bool in[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          int p = p0 + u * 64 + lane;
-          in[u] = p < n16;
-          p = in[u] ? p : n16 - 1;
+          const int p = min(p0 + u * team, n16 - 1);
           a[u] = *reinterpret_cast<const uint4*>(xrow + size_t(p) * 16);
 #pragma unroll
           for (int i = 0; i < CB; ++i) b[i][u] = *reinterpret_cast<const uint4*>(wrow[i] + size_t(p) * 16);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
+          if (p0 + u * team < n16) {
 #pragma unroll
-          for (int i = 0; i < CB; ++i) {
-            const double d = piece_dot64<BF16>(a[u], b[i][u], 0.0);
-            acc[i] += in[u] ? d : 0.0;
+            for (int i = 0; i < CB; ++i) acc[i] = piece_dot64<true>(a[u], b[i][u], acc[i]);
           }
       }
-      if constexpr (COOP) {
+      double z[CB];
+#pragma unroll
+      for (int i = 0; i < CB; ++i) z[i] = wave_sum(acc[i]);
+      if (coop) {
         // the four partial sums of each expert, added in wavefront order by everyone
 #pragma unroll
-        for (int i = 0; i < CB; ++i) {
-          const double zp = wave_sum(acc[i]);
-          if (lane == 0) part_all[wave][i] = zp;
-        }
+        for (int i = 0; i < CB; ++i)
+          if (lane == 0) part_all[wave][i] = z[i];
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < CB; ++i) {
-          double z = ((part_all[0][i] + part_all[1][i]) + part_all[2][i]) + part_all[3][i];
-          if (q0 + i < n && lane == 0) {
-            if (logit_bias) z += (double)logit_bias[ex[i]];
-            zx[ex[i]] = z;
-          }
-        }
-        __syncthreads();                    // before the next batch overwrites the partial sums
-      } else {
-#pragma unroll
-        for (int i = 0; i < CB; ++i) {
-          double z = wave_sum(acc[i]);
-          if (q0 + i < n && lane == 0) {
-            if (logit_bias) z += (double)logit_bias[ex[i]];
-            zx[ex[i]] = z;
-          }
-        }
+        for (int i = 0; i < CB; ++i) z[i] = ((part_all[0][i] + part_all[1][i]) + part_all[2][i]) + part_all[3][i];
+        __syncthreads();                  // before the next batch overwrites the partial sums
       }
+#pragma unroll
+      for (int i = 0; i < CB; ++i)
+        if (q0 + i < n && lane == 0) {
+          if (logit_bias) z[i] += (double)logit_bias[ex[i]];
+          zx[ex[i]] = z[i];
+        }
     }
   };
   // list the experts flagged in `want`; returns how many
@@ -973,27 +925,87 @@ __global__ __launch_bounds__(256, 2) void route_recheck_kernel(
     for (int i = 0; i < EPL; ++i) {
       const bool in = want >> i & 1;
       const uint64_t m = __ballot(in);
-      if (in) xlist[n + __popcll(m & ((uint64_t(1) << lane) - 1))] = i * 64 + lane;
+      if (in) xlist[n + __popcll(m & ((uint64_t(1) << lane) - 1))] = lane * EPL + i;
       n += __popcll(m);
     }
     return n;
   };
 
-  for (int li = COOP ? int(blockIdx.x) : int(blockIdx.x) * 4 + wave; li < n_list;
-       li += COOP ? int(gridDim.x) : int(gridDim.x) * 4) {
+  for (int li = coop ? blockIdx.x : blockIdx.x * 4 + wave; li < n_list; li += coop ? gridDim.x : gridDim.x * 4) {
     const int t = recheck[li];
     Keys<float, EPL> K;
     Keys<double, EPL> D;
     Groups<float> Gf;
     Gf.kept = 0; Gf.certain = true; Gf.need = 0; Gf.open = 0;
-    uint32_t exact = 0;          // slots of this lane that hold exact keys
-    auto adopt = [&](uint32_t want) {   // pull exact logits into D
+    const float xn = token_norm(c, xnorm2, t);
+    fast_keys<EPL, FORM>(c, logits + size_t(t) * c.E, logit_bias, select_bias, xn, wnorm2, lane, K);
 #pragma unroll
-      for (int i = 0; i < EPL; ++i) {
+    for (int i = 0; i < EPL; ++i) {
+      D.key[i] = (double)K.key[i]; D.sc[i] = (double)K.sc[i]; D.eps[i] = 0.0;
+    }
+    if (has_groups<FORM>(c)) group_stage<float, EPL, FORM>(c, K, lane, Gf);
+    uint64_t kept = Gf.kept;
+    uint32_t exact = 0;          // slots of this lane that hold exact keys
+#pragma unroll 1
+    for (int phase = has_groups<FORM>(c) && !Gf.certain ? 0 : 1; phase < 2; ++phase) {
+      uint32_t want = 0;
+      if (has_groups<FORM>(c) && phase == 0) {
+        // settle the groups in fp64: exact keys only where they can matter, the possible
+        // largest members of the groups on whose scores the cut still depends.  The
+        // other groups keep their fast scores, which the intervals already order
+        // against every open group.
+#pragma unroll
+        for (int i = 0; i < EPL; ++i)
+          if ((Gf.need >> i & 1) && (Gf.open >> lane_group<EPL, FORM>(c, lane, i) & 1)) want |= 1u << i;
+      } else {
+        // candidates of the top-k.  The smallest lower bound of the fast picks comes
+        // from the selection pass unless the groups had to be settled here.
+        const uint32_t elig = eligible_mask<EPL, FORM>(c, kept, lane);
+        Picks<float> P;
+        P.low = recheck_low[li];
+        if (has_groups<FORM>(c) && !(P.low == P.low)) topk_stage<float, EPL>(c, K, elig, lane, P);
+        // Only experts whose upper bound reaches the smallest lower bound of a pick can
+        // be among the picks.  Of those, an expert whose interval is apart from every
+        // other's is ordered against all of them by its fast key already; the ones whose
+        // intervals meet another's get exact keys.
+        uint32_t region = 0;
+        float lo[EPL], hi[EPL];
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) {
+          lo[i] = K.key[i] - K.eps[i];
+          hi[i] = K.key[i] + K.eps[i];
+          if ((elig >> i & 1) && hi[i] >= P.low) region |= 1u << i;
+        }
+        int nr = 0;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) {
+          const bool in = region >> i & 1;
+          const uint64_t m = __ballot(in);
+          if (in) {
+            const int pos = nr + __popcll(m & ((uint64_t(1) << lane) - 1));
+            xlist[pos] = lane * EPL + i;
+            rint[pos] = make_float2(lo[i], hi[i]);
+          }
+          nr += __popcll(m);
+        }
+#pragma unroll 1
+        for (int q = 0; q < nr; ++q) {
+          const int m = xlist[q];
+          const float2 iv = rint[q];
+#pragma unroll
+          for (int i = 0; i < EPL; ++i)
+            if ((region >> i & 1) && lane * EPL + i != m && lo[i] <= iv.y && iv.x <= hi[i]) want |= 1u << i;
+        }
+        want &= ~exact;
+      }
+      const int n = make_list(want);
+      exact_logits(t, n);
+#pragma unroll
+      for (int i = 0; i < EPL; ++i) {       // pull the exact logits into D
         if (!(want >> i & 1)) continue;
-        const int e = i * 64 + lane;
+        const int e = lane * EPL + i;
         const double z = zx[e];
-        if (c.score_fn == MOE_SCORE_SOFTMAX) {
+        if (is_softmax<FORM>(c)) {
           D.key[i] = z; D.sc[i] = z;
         } else {
           const double sg = 1.0 / (1.0 + exp(-z));
@@ -1002,91 +1014,31 @@ __global__ __launch_bounds__(256, 2) void route_recheck_kernel(
         }
       }
       exact |= want;
-    };
-    const float xn = token_norm(c, xnorm2, t);
-    fast_keys<EPL>(c, logits + size_t(t) * c.E, logit_bias, select_bias, xn, wnorm2, lane, K);
-#pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-      D.key[i] = (double)K.key[i]; D.sc[i] = (double)K.sc[i]; D.eps[i] = 0.0;
-    }
-    if (c.G > 1) group_stage<float, EPL>(c, K, lane, Gf);
-    uint64_t kept = Gf.kept;
-    if (c.G > 1 && !Gf.certain) {       // phase 1: settle the groups in fp64
-      // exact keys only where they can matter: the possible largest members of the
-      // groups on whose scores the cut still depends.  The other groups keep their
-      // fast scores, which the intervals already order against every open group.
-      uint32_t want1 = 0;
-      const int gs = c.E / c.G;
-#pragma unroll
-      for (int i = 0; i < EPL; ++i)
-        if ((Gf.need >> i & 1) && (Gf.open >> ((i * 64 + lane) / gs) & 1)) want1 |= 1u << i;
-      const int n = make_list(want1);
-      exact_logits(t, n);
-      adopt(want1);
-      Groups<double> Gd;
-      group_stage<double, EPL>(c, D, lane, Gd);
-      kept = Gd.kept;
-    }
-    // phase 2: candidates of the top-k.  The smallest lower bound of the fast picks
-    // comes from the selection pass unless the groups had to be settled here.
-    const uint32_t elig = eligible_mask<EPL>(c, kept, lane);
-    Picks<float> P;
-    P.low = recheck_low[li];
-    if (!(P.low == P.low)) topk_stage<float, EPL>(c, K, elig, lane, P);
-    // Only experts whose upper bound reaches the smallest lower bound of a pick can
-    // be among the picks.  Of those, an expert whose interval is apart from every
-    // other's is ordered against all of them by its fast key already; the ones whose
-    // intervals meet another's get exact keys.
-    uint32_t region = 0;
-    float lo[EPL], hi[EPL];
-#pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-      lo[i] = K.key[i] - K.eps[i];
-      hi[i] = K.key[i] + K.eps[i];
-      if ((elig >> i & 1) && hi[i] >= P.low) region |= 1u << i;
-    }
-    int nr = 0;
-#pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-      const bool in = region >> i & 1;
-      const uint64_t m = __ballot(in);
-      if (in) {
-        const int pos = nr + __popcll(m & ((uint64_t(1) << lane) - 1));
-        xlist[pos] = i * 64 + lane;
-        rint[pos] = make_float2(lo[i], hi[i]);
+      if (has_groups<FORM>(c) && phase == 0) {
+        Groups<double> Gd;
+        group_stage<double, EPL, FORM>(c, D, lane, Gd);
+        kept = Gd.kept;
       }
-      nr += __popcll(m);
     }
-    uint32_t want = 0;
-    for (int q = 0; q < nr; ++q) {
-      const int m = xlist[q];
-      const float2 iv = rint[q];
-#pragma unroll
-      for (int i = 0; i < EPL; ++i)
-        if ((region >> i & 1) && i * 64 + lane != m && lo[i] <= iv.y && iv.x <= hi[i]) want |= 1u << i;
-    }
-    want &= ~exact;
-    const int n = make_list(want);
-    exact_logits(t, n);
-    adopt(want);
     Picks<double> Q;
-    topk_stage<double, EPL>(c, D, elig, lane, Q);
-    const double wt = pick_weight<double, EPL>(c, D, Q, lane);
-    if (lane < c.k && (!COOP || wave == 0)) {
+    topk_stage<double, EPL>(c, D, eligible_mask<EPL, FORM>(c, kept, lane), lane, Q);
+    const double wt = pick_weight<double, EPL, FORM>(c, D, Q, lane);
+    if (lane < c.k && (!coop || wave == 0)) {
       ids[size_t(t) * c.k + lane] = Q.id;
       w[size_t(t) * c.k + lane] = (float)wt;
     }
   }
 }
 
-// -------------------- few tokens: gate, scores and top-k of a token in one pass
+// ------------- a small fp32 layer: gate, scores and top-k of a token in one pass
 // One workgroup of sixteen wavefronts per token.  The wavefronts share out the experts and
 // compute every logit exactly (fp64 sums of exact products, CB experts per walk
 // over the token row); the first wavefront then builds fp64 keys for all experts
-// and takes the group limit, the top-k and the weights in fp64.  No fast pass,
-// no error intervals and nothing to re-score: at decode sizes the T*E*H fused
-// multiply-adds cost less than the launches they replace.
-template <int EPL, bool BF16>
+// and takes the group limit, the top-k and the weights in fp64.  One launch less than
+// the matrix form below, which is what counts while there is at most one workgroup per
+// CU (8 experts, hidden 256, 64 tokens: 8.4 against 10.5 us; 128 experts, hidden 2048:
+// 14.8 against 13.7 us).
+template <int EPL, int FORM>
 __global__ __launch_bounds__(1024) void route_exact_kernel(
     SelCfg c, int H, const void* __restrict__ x, const void* __restrict__ gate_w,
     const float* __restrict__ logit_bias, const float* __restrict__ select_bias,
@@ -1095,9 +1047,8 @@ __global__ __launch_bounds__(1024) void route_exact_kernel(
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int t = blockIdx.x;
   if (t == 0 && threadIdx.x < 64) counters[threadIdx.x] = 0;   // nothing is re-scored
-  const size_t eb = BF16 ? 2 : 4;
-  const char* xrow = static_cast<const char*>(x) + size_t(t) * H * eb;
-  const int n16 = int(H * eb / 16);
+  const char* xrow = static_cast<const char*>(x) + size_t(t) * H * 4;
+  const int n16 = H / 4;
   const int per = (c.E + 15) / 16;
   const int e_begin = min(c.E, wave * per), e_end = min(c.E, e_begin + per);
   constexpr int CB = 4, U = 4;   // experts per walk, pieces per lane and row in flight (8: spills)
@@ -1107,7 +1058,7 @@ __global__ __launch_bounds__(1024) void route_exact_kernel(
 #pragma unroll
     for (int i = 0; i < CB; ++i) {
       acc[i] = 0.0;
-      wrow[i] = static_cast<const char*>(gate_w) + size_t(min(e0 + i, e_end - 1)) * H * eb;
+      wrow[i] = static_cast<const char*>(gate_w) + size_t(min(e0 + i, e_end - 1)) * H * 4;
     }
     for (int p0 = 0; p0 < n16; p0 += 64 * U) {
       uint4 a[U], b[CB][U];
@@ -1125,7 +1076,7 @@ __global__ __launch_bounds__(1024) void route_exact_kernel(
       for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int i = 0; i < CB; ++i) {
-          const double d = piece_dot64<BF16>(a[u], b[i][u], 0.0);
+          const double d = piece_dot64<false>(a[u], b[i][u], 0.0);
           acc[i] += in[u] ? d : 0.0;
         }
     }
@@ -1143,11 +1094,11 @@ __global__ __launch_bounds__(1024) void route_exact_kernel(
   Keys<double, EPL> D;
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
-    const int e = i * 64 + lane;
+    const int e = lane * EPL + i;
     D.key[i] = -INFINITY; D.sc[i] = 0.0; D.eps[i] = 0.0;
     if (e < c.E) {
       const double z = zx[e];
-      if (c.score_fn == MOE_SCORE_SOFTMAX) {
+      if (is_softmax<FORM>(c)) {
         D.key[i] = z; D.sc[i] = z;
       } else {
         const double sg = 1.0 / (1.0 + exp(-z));
@@ -1157,79 +1108,91 @@ __global__ __launch_bounds__(1024) void route_exact_kernel(
     }
   }
   uint64_t kept = 0;
-  if (c.G > 1) {
+  if (has_groups<FORM>(c)) {
     Groups<double> Gd;
-    group_stage<double, EPL>(c, D, lane, Gd);
+    group_stage<double, EPL, FORM>(c, D, lane, Gd);
     kept = Gd.kept;
   }
-  const uint32_t elig = eligible_mask<EPL>(c, kept, lane);
+  const uint32_t elig = eligible_mask<EPL, FORM>(c, kept, lane);
   Picks<double> Q;
   topk_stage<double, EPL>(c, D, elig, lane, Q);
-  const double wt = pick_weight<double, EPL>(c, D, Q, lane);
+  const double wt = pick_weight<double, EPL, FORM>(c, D, Q, lane);
   if (lane < c.k) {
     ids[size_t(t) * c.k + lane] = Q.id;
     w[size_t(t) * c.k + lane] = (float)wt;
   }
 }
 
-// ---------- few tokens, long gate rows: exact logits and selection as two kernels
-// When a token's E*H multiply-adds are many (256 experts x hidden 7168), one
-// workgroup per token is a chain of sixteen dependent load rounds per wavefront.
-// Here a workgroup of four wavefronts takes sixteen experts of one token (a
-// wavefront: four gate rows, eight 16-byte pieces per lane and row in flight), so
-// a token is shared out over E/16 workgroups and the fp64 logits go to the
-// workspace; a second kernel, one wavefront per token, selects on the fp64 keys.
+// ------------- few tokens: exact logits on fp64 matrix instructions, then selection
+// A workgroup of sixteen wavefronts computes 16 tokens x 16 experts with
+// v_mfma_f64_16x16x4_f64 (exact products, fp64 sums): the wavefronts share out K and
+// their sums are added in a fixed order.  Per instruction (1024 multiply-adds) a lane
+// widens one element of each operand, where the dot products of one token on the
+// vector unit widen an element per multiply-add.  K runs in the order that makes a
+// lane's load one 16-byte piece of its row, the same for both operands: piece 4g + q of
+// the row for lanes 16q..16q+15, group g of four pieces going to wavefront g % 16.  The
+// fp64 logits go to the workspace; a second kernel, one wavefront per token, selects.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
 template <bool BF16>
-__global__ __launch_bounds__(256) void gate_exact_kernel(
-    int H, int E, const void* __restrict__ x, const void* __restrict__ gate_w,
+__global__ __launch_bounds__(1024) void gate_exact_kernel(
+    int T, int H, int E, const void* __restrict__ x, const void* __restrict__ gate_w,
     const float* __restrict__ logit_bias, double* __restrict__ zx, int32_t* __restrict__ counters) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int t = blockIdx.y;
-  if (blockIdx.x == 0 && t == 0 && threadIdx.x < 64) counters[threadIdx.x] = 0;   // nothing is re-scored
-  constexpr int CB = 4, U = 8;
-  const int e0 = (blockIdx.x * 4 + wave) * CB;
-  if (e0 >= E) return;
-  const size_t eb = BF16 ? 2 : 4;
-  const char* xrow = static_cast<const char*>(x) + size_t(t) * H * eb;
-  const int n16 = int(H * eb / 16);
-  double acc[CB];
-  const char* wrow[CB];
-#pragma unroll
-  for (int i = 0; i < CB; ++i) {
-    acc[i] = 0.0;
-    wrow[i] = static_cast<const char*>(gate_w) + size_t(min(e0 + i, E - 1)) * H * eb;
-  }
-  for (int p0 = 0; p0 < n16; p0 += 64 * U) {
-    uint4 a[U], b[CB][U];
-    bool in[U];
+  __shared__ double red[16][256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (blockIdx.x == 0 && tid < 64) counters[tid] = 0;   // nothing is re-scored
+  const int n_etiles = (E + 15) / 16;
+  const int ttile = blockIdx.x / n_etiles, e0 = (blockIdx.x - ttile * n_etiles) * 16, t0 = ttile * 16;
+  const size_t row_bytes = size_t(H) * (BF16 ? 2 : 4);
+  const int n16 = int(row_bytes / 16), groups = (n16 + 3) / 4;
+  const char* const xrow = static_cast<const char*>(x) + size_t(min(t0 + (lane & 15), T - 1)) * row_bytes;
+  const char* const wrow = static_cast<const char*>(gate_w) + size_t(min(e0 + (lane & 15), E - 1)) * row_bytes;
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  constexpr int U = 4;                       // groups in flight
+  for (int g0 = wave; g0 < groups; g0 += 16 * U) {
+    uint4 a[U], b[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      int p = p0 + u * 64 + lane;
-      in[u] = p < n16;
-      p = in[u] ? p : n16 - 1;
-      a[u] = *reinterpret_cast<const uint4*>(xrow + size_t(p) * 16);
-#pragma unroll
-      for (int i = 0; i < CB; ++i) b[i][u] = *reinterpret_cast<const uint4*>(wrow[i] + size_t(p) * 16);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int i = 0; i < CB; ++i) {
-        const double d = piece_dot64<BF16>(a[u], b[i][u], 0.0);
-        acc[i] += in[u] ? d : 0.0;
+      const int p = (g0 + 16 * u) * 4 + (lane >> 4);
+      a[u] = b[u] = make_uint4(0, 0, 0, 0);
+      if (p < n16) {
+        a[u] = *reinterpret_cast<const uint4*>(xrow + size_t(p) * 16);
+        b[u] = *reinterpret_cast<const uint4*>(wrow + size_t(p) * 16);
       }
-  }
-#pragma unroll
-  for (int i = 0; i < CB; ++i) {
-    double z = wave_sum(acc[i]);
-    if (e0 + i < E && lane == 0) {
-      if (logit_bias) z += (double)logit_bias[e0 + i];
-      zx[size_t(t) * E + e0 + i] = z;
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (g0 + 16 * u >= groups) break;      // the same in every lane
+      const uint32_t av[4] = {a[u].x, a[u].y, a[u].z, a[u].w}, bv[4] = {b[u].x, b[u].y, b[u].z, b[u].w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (BF16) {
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)bf16_bits_to_f32(av[i] & 0xffffu),
+                                                     (double)bf16_bits_to_f32(bv[i] & 0xffffu), acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)bf16_bits_to_f32(av[i] >> 16),
+                                                     (double)bf16_bits_to_f32(bv[i] >> 16), acc, 0, 0, 0);
+        } else {
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)__uint_as_float(av[i]),
+                                                     (double)__uint_as_float(bv[i]), acc, 0, 0, 0);
+        }
+      }
+    }
+  }
+  // D layout: lane l, element i -> token 4i + l/16, expert l%16
+#pragma unroll
+  for (int i = 0; i < 4; ++i) red[wave][(i * 4 + (lane >> 4)) * 16 + (lane & 15)] = acc[i];
+  __syncthreads();
+  const int t = t0 + (tid >> 4), e = e0 + (tid & 15);
+  if (tid < 256 && t < T && e < E) {
+    double z = red[0][tid];
+#pragma unroll
+    for (int w = 1; w < 16; ++w) z += red[w][tid];
+    if (logit_bias) z += (double)logit_bias[e];
+    zx[size_t(t) * E + e] = z;
   }
 }
 
-template <int EPL>
+template <int EPL, int FORM>
 __global__ __launch_bounds__(256) void select_exact_kernel(
     SelCfg c, int T, const double* __restrict__ zx, const float* __restrict__ select_bias,
     int32_t* __restrict__ ids, float* __restrict__ w) {
@@ -1239,11 +1202,11 @@ __global__ __launch_bounds__(256) void select_exact_kernel(
   Keys<double, EPL> D;
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
-    const int e = i * 64 + lane;
+    const int e = lane * EPL + i;
     D.key[i] = -INFINITY; D.sc[i] = 0.0; D.eps[i] = 0.0;
     if (e < c.E) {
       const double z = zx[size_t(t) * c.E + e];
-      if (c.score_fn == MOE_SCORE_SOFTMAX) {
+      if (is_softmax<FORM>(c)) {
         D.key[i] = z; D.sc[i] = z;
       } else {
         const double sg = 1.0 / (1.0 + exp(-z));
@@ -1253,73 +1216,62 @@ __global__ __launch_bounds__(256) void select_exact_kernel(
     }
   }
   uint64_t kept = 0;
-  if (c.G > 1) {
+  if (has_groups<FORM>(c)) {
     Groups<double> Gd;
-    group_stage<double, EPL>(c, D, lane, Gd);
+    group_stage<double, EPL, FORM>(c, D, lane, Gd);
     kept = Gd.kept;
   }
-  const uint32_t elig = eligible_mask<EPL>(c, kept, lane);
+  const uint32_t elig = eligible_mask<EPL, FORM>(c, kept, lane);
   Picks<double> Q;
   topk_stage<double, EPL>(c, D, elig, lane, Q);
-  const double wt = pick_weight<double, EPL>(c, D, Q, lane);
+  const double wt = pick_weight<double, EPL, FORM>(c, D, Q, lane);
   if (lane < c.k) {
     ids[size_t(t) * c.k + lane] = Q.id;
     w[size_t(t) * c.k + lane] = (float)wt;
   }
 }
 
-template <int EPL>
+// 16 x 16 tiles of the exact gate: workgroups of gate_exact_kernel
+inline long exact_tiles(int T, int E) { return long((T + 15) / 16) * ((E + 15) / 16); }
+
+template <int EPL, int FORM>
 void launch_route_exact2(const SelCfg& sc, const moe_config& c, int T, const void* x,
                          const void* gate_w, const float* logit_bias, const float* select_bias,
                          int32_t* ids, float* w, const RouteWs& ws, hipStream_t s) {
   // the logits area holds at least two floats per (token, expert): room for one double
   double* zx = reinterpret_cast<double*>(ws.logits);
-  const dim3 grid((c.n_experts + 15) / 16, T);
+  const dim3 grid(unsigned(exact_tiles(T, c.n_experts)));
   if (c.act_dtype == MOE_BF16)
-    MOE_LAUNCH(MOE_K_GATE_GEMM, gate_exact_kernel<true>, grid, dim3(256), 0, s, c.hidden, c.n_experts, x,
-               gate_w, logit_bias, zx, ws.counters);
+    MOE_LAUNCH(MOE_K_GATE_GEMM, gate_exact_kernel<true>, grid, dim3(1024), 0, s, T, c.hidden, c.n_experts,
+               x, gate_w, logit_bias, zx, ws.counters);
   else
-    MOE_LAUNCH(MOE_K_GATE_GEMM, gate_exact_kernel<false>, grid, dim3(256), 0, s, c.hidden, c.n_experts, x,
-               gate_w, logit_bias, zx, ws.counters);
-  MOE_LAUNCH(MOE_K_SELECT, select_exact_kernel<EPL>, dim3((T + 3) / 4), dim3(256), 0, s, sc, T, zx,
+    MOE_LAUNCH(MOE_K_GATE_GEMM, gate_exact_kernel<false>, grid, dim3(1024), 0, s, T, c.hidden, c.n_experts,
+               x, gate_w, logit_bias, zx, ws.counters);
+  MOE_LAUNCH(MOE_K_SELECT, (select_exact_kernel<EPL, FORM>), dim3((T + 3) / 4), dim3(256), 0, s, sc, T, zx,
              select_bias, ids, w);
 }
 
-template <int EPL>
+template <int EPL, int FORM>
 void launch_route_exact(const SelCfg& sc, const moe_config& c, int T, const void* x,
                         const void* gate_w, const float* logit_bias, const float* select_bias,
                         int32_t* ids, float* w, const RouteWs& ws, hipStream_t s) {
-  if (c.act_dtype == MOE_BF16)
-    MOE_LAUNCH(MOE_K_GATE_GEMM, (route_exact_kernel<EPL, true>), dim3(T), dim3(1024), 0, s, sc,
-               c.hidden, x, gate_w, logit_bias, select_bias, ids, w, ws.counters);
-  else
-    MOE_LAUNCH(MOE_K_GATE_GEMM, (route_exact_kernel<EPL, false>), dim3(T), dim3(1024), 0, s, sc,
-               c.hidden, x, gate_w, logit_bias, select_bias, ids, w, ws.counters);
+  MOE_LAUNCH(MOE_K_GATE_GEMM, (route_exact_kernel<EPL, FORM>), dim3(T), dim3(1024), 0, s, sc, c.hidden, x,
+             gate_w, logit_bias, select_bias, ids, w, ws.counters);
 }
 
-template <int EPL>
+template <int EPL, int FORM>
 void launch_select_and_recheck(const SelCfg& sc, const moe_config& c, int T, const void* x,
                                const void* gate_w, const float* logit_bias,
                                const float* select_bias, const float* logits_in,
                                const float* logits, int32_t* ids, float* w, const RouteWs& ws,
                                hipStream_t s) {
-  MOE_LAUNCH(MOE_K_SELECT, route_select_kernel<EPL>, dim3((T + 3) / 4), dim3(256), 0, s, sc, T, logits,
+  MOE_LAUNCH(MOE_K_SELECT, (route_select_kernel<EPL, FORM>), dim3((T + 3) / 4), dim3(256), 0, s, sc, T, logits,
              logit_bias, select_bias, ws.xnorm2, ws.wnorm2, ids, w, ws.counters, ws.recheck,
              ws.recheck_low);
-  // short batches have short lists: a workgroup per listed token, its wavefronts
-  // sharing each dot product; otherwise four tokens per workgroup at a time
-  const bool coop = T <= 1024 && !logits_in;
-  const int grid = coop ? T : (T < 4096 ? (T + 3) / 4 : 1024);
-#define MOE_RECHECK(BF, CO)                                                                       \
-  MOE_LAUNCH(MOE_K_RESCORE, (route_recheck_kernel<EPL, BF, CO>), dim3(grid), dim3(256), 0, s, sc, \
-             c.hidden, x, gate_w, logits_in, logits, logit_bias, select_bias, ws.xnorm2,          \
-             ws.wnorm2, ids, w, ws.counters, ws.recheck, ws.recheck_low)
-  if (c.act_dtype == MOE_BF16) {
-    if (coop) MOE_RECHECK(true, true); else MOE_RECHECK(true, false);
-  } else {
-    if (coop) MOE_RECHECK(false, true); else MOE_RECHECK(false, false);
-  }
-#undef MOE_RECHECK
+  const int grid = T < 1024 ? T : 1024;
+  MOE_LAUNCH(MOE_K_RESCORE, (route_recheck_kernel<EPL, FORM>), dim3(grid), dim3(256), 0, s, sc, c.hidden, x,
+             gate_w, logits_in, logits, logit_bias, select_bias, ws.xnorm2, ws.wnorm2, ids, w, ws.counters,
+             ws.recheck, ws.recheck_low);
 }
 
 }  // namespace
@@ -1334,96 +1286,81 @@ hipError_t launch_route(const moe_config& c, int T, const void* x, const void* g
   SelCfg sc;
   sc.E = E; sc.k = c.top_k; sc.score_fn = c.score_fn; sc.renormalize = c.renormalize;
   sc.G = c.n_groups; sc.Kg = c.topk_groups; sc.gn = c.group_score_n; sc.scale = c.routed_scale;
-  sc.chain_err = 0.f; sc.have_norms = 0; sc.nsplit = 1; sc.wsplit = 1; sc.T = T;
+  sc.chain_err = 0.f; sc.have_norms = 0; sc.nsplit = 1; sc.T = T;
   const int epl = (E + 63) / 64;
-  // decode-sized batches: the exact gate costs T*E*H fp64 fused multiply-adds,
-  // about 0.24 us per 2^20 of them, in one kernel for the whole stage (a workgroup
-  // per token: not for long batches of tiny layers).  The bf16 pipeline of four
-  // kernels takes 45-50 us at these sizes (measured on the 128-expert layer, hidden
-  // 2048: 51 us exact against 46 us tiled at 768 tokens), which puts the crossover
-  // near 5 * 2^25; the fp32 pipeline starts with an fp64 VALU gate of its own and is
-  // never faster below 2^28.
-  const size_t small_limit = bf16 ? size_t(5) << 25 : size_t(1) << 28;
-  const bool small = size_t(T) * E * H <= small_limit && T <= 4096;
-  // long gate rows and few tokens: the same arithmetic as two kernels.  Measured on
-  // 256 experts x hidden 7168: 37 / 53 / 81 us at 16 / 64 / 128 tokens, where one
-  // workgroup per token takes 84 us and the bf16 pipeline 92 us; the fp64 work grows
-  // with the token count (135 us at 256), so the switch back sits at 2^28.
-  const bool long_rows = size_t(E) * H > (size_t(1) << 19) && T <= 4096 &&
-                         size_t(T) * E * H <= (size_t(1) << 28);
-  if (!logits_in && long_rows) {
-    if (epl <= 1) launch_route_exact2<1>(sc, c, T, x, gate_w, logit_bias, select_bias, ids, w, ws, s);
-    else if (epl <= 2) launch_route_exact2<2>(sc, c, T, x, gate_w, logit_bias, select_bias, ids, w, ws, s);
-    else if (epl <= 4) launch_route_exact2<4>(sc, c, T, x, gate_w, logit_bias, select_bias, ids, w, ws, s);
-    else launch_route_exact2<8>(sc, c, T, x, gate_w, logit_bias, select_bias, ids, w, ws, s);
+  // The exact gate (fp64 matrix instructions, two launches) against the bf16 pipeline of
+  // three: it costs about 8 us + 6.5 us for every 256 tiles at hidden 2048, the pipeline
+  // 24-33 us for up to 128 experts.  Measured us, exact / pipeline: 128 experts, hidden 2048,
+  // 64 tokens 14 / -, 1024 tokens 21 / 26, 1536 tokens 29 / 27; hidden 4096, 512 tokens 21 / 30,
+  // 768 tokens 34 / 33; hidden 1024, 2048 tokens 24 / 26; hidden 512, 4096 tokens 29 / 24 (the
+  // selection on fp64 keys costs more per token: hence the limit on tiles).  The grouped
+  // gate of 256 experts, hidden 7168, has the longer pipeline: 256 tokens 36 / 62, 512 tokens 57 /
+  // 64, 768 tokens 78 / 66.  fp32 rows have no other gate.
+  const long tiles = exact_tiles(T, E);
+  const size_t limit = size_t(1) << (c.n_groups > 1 ? 22 : 20);
+  const bool exact = !bf16 || (tiles <= 1024 && size_t(tiles) * H <= limit);
+  const bool small_f32 = !bf16 && T <= 256 && size_t(E) * H <= (size_t(1) << 17);
+  // experts per lane and form of the gate -> one instance of the selection kernels
+#define MOE_BY_FORM(F, EPL, ...)                                                      \
+  switch (gate_form<EPL>(sc)) {                                                            \
+    case kGateSoftmax: F<EPL, kGateSoftmax>(__VA_ARGS__); break;                      \
+    case kGateGrouped: F<EPL, kGateGrouped>(__VA_ARGS__); break;                      \
+    default: F<EPL, kGateAny>(__VA_ARGS__); break;                                    \
+  }
+#define MOE_BY_GATE(F, ...)                                                           \
+  do {                                                                                \
+    if (epl <= 1) { MOE_BY_FORM(F, 1, __VA_ARGS__) }                                  \
+    else if (epl <= 2) { MOE_BY_FORM(F, 2, __VA_ARGS__) }                             \
+    else if (epl <= 4) { MOE_BY_FORM(F, 4, __VA_ARGS__) }                             \
+    else { MOE_BY_FORM(F, 8, __VA_ARGS__) }                                           \
+  } while (0)
+  if (!logits_in && exact && !small_f32) {
+    MOE_BY_GATE(launch_route_exact2, sc, c, T, x, gate_w, logit_bias, select_bias, ids, w, ws, s);
     return hipGetLastError();
   }
-  if (!logits_in && small) {
-    if (epl <= 1) launch_route_exact<1>(sc, c, T, x, gate_w, logit_bias, select_bias, ids, w, ws, s);
-    else if (epl <= 2) launch_route_exact<2>(sc, c, T, x, gate_w, logit_bias, select_bias, ids, w, ws, s);
-    else if (epl <= 4) launch_route_exact<4>(sc, c, T, x, gate_w, logit_bias, select_bias, ids, w, ws, s);
-    else launch_route_exact<8>(sc, c, T, x, gate_w, logit_bias, select_bias, ids, w, ws, s);
+  if (!logits_in && small_f32) {
+    MOE_BY_GATE(launch_route_exact, sc, c, T, x, gate_w, logit_bias, select_bias, ids, w, ws, s);
     return hipGetLastError();
   }
-  // The bf16 gate GEMM sums the gate rows' squares and clears the counter itself
-  // (its first token tile); the fp32 gate and the given-logits path use this kernel.
-  if (logits_in || !bf16) {
-    const void* gw_for_norm = logits_in ? nullptr : gate_w;
-    if (bf16)
-      MOE_LAUNCH(MOE_K_GATE_NORMS, gate_wnorm_kernel<true>, dim3((E + 3) / 4), dim3(256), 0, s, gw_for_norm,
-                 E, H, ws.wnorm2, ws.counters);
-    else
-      MOE_LAUNCH(MOE_K_GATE_NORMS, gate_wnorm_kernel<false>, dim3((E + 3) / 4), dim3(256), 0, s, gw_for_norm,
-                 E, H, ws.wnorm2, ws.counters);
-  }
-  if (!logits_in) {
+  if (logits_in) {
+    MOE_LAUNCH(MOE_K_GATE_NORMS, clear_counters_kernel, dim3(1), dim3(kRouteCounterBytes / 4), 0, s, ws.counters);
+  } else {
+    // the bf16 gate GEMM sums the gate rows' squares and clears the counter itself
     logits = ws.logits;
     sc.have_norms = 1;
-    if (bf16) {
-      // few tiles: split K so that about two workgroups per CU run (one workgroup is
-      // one wavefront per SIMD, which hides no latency); each split keeps at least 8
-      // K steps
-      const int blocks = ((T + GBM - 1) / GBM) * ((E + GBN - 1) / GBN);
-      const int ksteps = (H + GBK - 1) / GBK;
-      int nsplit = 1;
-      const int cap = gate_split_cap(T, E);
-      while (nsplit < cap && blocks * nsplit * 2 <= kGateWgTarget && ksteps / (nsplit * 2) >= 8) nsplit *= 2;
-      const dim3 grid((T + GBM - 1) / GBM, (E + GBN - 1) / GBN, nsplit);
-      if (H % GBK == 0) {
-        // two stages (48 KB): three workgroups share a CU, which measured faster than
-        // deeper rings with fewer workgroups, and than 128-token tiles
-        constexpr int NS = 2;
-        constexpr int lds = NS * (GBM + GBN) * 8 * 16;
-        MOE_LAUNCH(MOE_K_GATE_GEMM, (gate_dma_kernel<GBM, NS, kGateChainSteps>), grid, dim3(512), lds, s,
-                   static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(gate_w), T, H, E,
-                   ws.logits, ws.xnorm2, ws.wnorm2, ws.counters);
-      } else {
-        MOE_LAUNCH(MOE_K_GATE_GEMM, gate_mfma_kernel<kGateChainSteps>, grid, dim3(512), 0, s,
-                   static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(gate_w), T, H, E,
-                   ws.logits, ws.xnorm2, ws.wnorm2, ws.counters);
-      }
-      sc.nsplit = nsplit;
-      sc.wsplit = nsplit;
-      // chains of kGateChainSteps*64 products; +2 for the flush and the store.  The
-      // partial dot products of the splits obey sum_s |x_s||w_s| <= |x||w|, so the
-      // chain term is unchanged; summing the slabs in fp32 adds one ulp of that
-      // product per addition and per slab store
-      sc.chain_err = (2.f * kGateChainSteps * GBK + 2.f + 2.f * (nsplit - 1)) * kUlp;
+    // few tiles: split K so that about two workgroups per CU run (one workgroup is
+    // one wavefront per SIMD, which hides no latency); each split keeps at least 8
+    // K steps
+    const int blocks = ((T + GBM - 1) / GBM) * ((E + GBN - 1) / GBN);
+    const int ksteps = (H + GBK - 1) / GBK;
+    int nsplit = 1;
+    const int cap = gate_split_cap(T, E);
+    while (nsplit < cap && blocks * nsplit * 2 <= kGateWgTarget && ksteps / (nsplit * 2) >= 8) nsplit *= 2;
+    const dim3 grid((T + GBM - 1) / GBM, (E + GBN - 1) / GBN, nsplit);
+    if (H % GBK == 0) {
+      // two stages (48 KB): three workgroups share a CU, which measured faster than
+      // deeper rings with fewer workgroups, and than 128-token tiles
+      constexpr int NS = 2;
+      constexpr int lds = NS * (GBM + GBN) * 8 * 16;
+      MOE_LAUNCH(MOE_K_GATE_GEMM, (gate_dma_kernel<GBM, NS, kGateChainSteps>), grid, dim3(512), lds, s,
+                 static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(gate_w), T, H, E,
+                 ws.logits, ws.xnorm2, ws.wnorm2, ws.counters);
     } else {
-      MOE_LAUNCH(MOE_K_GATE_GEMM, gate_f64_kernel<false>, dim3(T), dim3(256), 0, s, x, gate_w, T,
-                 H, E, ws.logits, ws.xnorm2);
-      // fp64 sums: the only error is the fp32 store, covered by the 2 ulp term
-      sc.chain_err = 1e-12f;
+      MOE_LAUNCH(MOE_K_GATE_GEMM, gate_mfma_kernel<kGateChainSteps>, grid, dim3(512), 0, s,
+                 static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(gate_w), T, H, E,
+                 ws.logits, ws.xnorm2, ws.wnorm2, ws.counters);
     }
+    sc.nsplit = nsplit;
+    // chains of kGateChainSteps*64 products; +2 for the flush and the store.  The
+    // partial dot products of the splits obey sum_s |x_s||w_s| <= |x||w|, so the
+    // chain term is unchanged; summing the slabs in fp32 adds one ulp of that
+    // product per addition and per slab store
+    sc.chain_err = (2.f * kGateChainSteps * GBK + 2.f + 2.f * (nsplit - 1)) * kUlp;
   }
-  if (epl <= 1)
-    launch_select_and_recheck<1>(sc, c, T, x, gate_w, logit_bias, select_bias, logits_in, logits, ids, w, ws, s);
-  else if (epl <= 2)
-    launch_select_and_recheck<2>(sc, c, T, x, gate_w, logit_bias, select_bias, logits_in, logits, ids, w, ws, s);
-  else if (epl <= 4)
-    launch_select_and_recheck<4>(sc, c, T, x, gate_w, logit_bias, select_bias, logits_in, logits, ids, w, ws, s);
-  else
-    launch_select_and_recheck<8>(sc, c, T, x, gate_w, logit_bias, select_bias, logits_in, logits, ids, w, ws, s);
+  MOE_BY_GATE(launch_select_and_recheck, sc, c, T, x, gate_w, logit_bias, select_bias, logits_in, logits, ids,
+              w, ws, s);
+#undef MOE_BY_GATE
+#undef MOE_BY_FORM
   return hipGetLastError();
 }
 

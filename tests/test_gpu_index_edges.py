@@ -1,16 +1,40 @@
-"""Index kernels at the edges of their tiles: the two launches of the dispatch index
-around their chunk of 1024 assignments, and the combine's batches of eight rows."""
+"""Routing and index kernels at the edges of their tiles and of the rules that pick
+them: the exact gate's 16 x 16 tiles and K groups, the two launches of the dispatch
+index around their chunk of 1024 assignments, and the combine's batches of eight rows."""
 import numpy as np
 import pytest
 import torch
 
 import oracle
-from helpers import check_dispatch, dev, make_layer
+from helpers import check_dispatch, check_routing, dev, host, make_layer, oracle_route
 from workloads import gen
 
 pytestmark = pytest.mark.gpu
 
 NO_WEIGHTS = {"w_gate": None, "w_up": None, "w_down": None}
+
+
+# tokens and experts one below, at and one above a tile; rows of one piece, of a partial
+# group of pieces, and of more groups than a workgroup has wavefronts; fp32 layers on
+# either side of the one-launch route (256 tokens, E*H = 2^17); grouped gates
+@pytest.mark.parametrize("act,T,E,H,k,G", [
+    ("bf16", 1, 1, 8, 1, 1), ("bf16", 15, 17, 40, 3, 1), ("bf16", 16, 16, 264, 16, 1),
+    ("bf16", 17, 33, 2056, 5, 1), ("bf16", 333, 128, 520, 8, 1), ("bf16", 500, 512, 72, 32, 1),
+    ("bf16", 49, 64, 1024, 6, 8), ("bf16", 50, 48, 136, 5, 4), ("bf16", 21, 256, 4104, 8, 8),
+    ("f32", 256, 8, 264, 2, 1), ("f32", 257, 8, 264, 2, 1), ("f32", 31, 130, 1032, 8, 1),
+    ("f32", 5000, 16, 8, 3, 1), ("f32", 65, 96, 2048, 4, 6)])
+def test_exact_route_tiles(act, T, E, H, k, G):
+    base = gen.CONFIGS["c4" if G > 1 else "c1"]
+    w = base.replace(name="exact_tiles", T=T, E=E, H=H, k=k, I=8, act_dtype=act, weight_dtype=act, tp=1,
+                     expert_lo=0, expert_hi=E, shared_expert=False, n_groups=G,
+                     topk_groups=max(1, G // 2), group_score_n=2 if G > 1 else 0, seed=T + E)
+    x, gate = gen.make_x(w), gen.make_gate(w)
+    L = make_layer(w, {"gate": gate, "experts": NO_WEIGHTS, "shared": None})
+    L.route(dev(x))
+    torch.cuda.synchronize()
+    assert int(L.ws[:4].view(torch.int32).item()) == 0          # exact keys: nothing to re-score
+    ids_ref, w_ref, margin = oracle_route(w, x, gate)
+    check_routing(host(L.topk_ids), host(L.topk_w), ids_ref, w_ref, margin, w.routed_scale, "exact_tiles")
 
 
 # one run, whole and ragged runs, more than 256 runs (chunks of two); one local expert,
