@@ -142,12 +142,14 @@ class MoELayerShare:
         """One pass of the whole path.  `forced` = (ids, w) device tensors to
         bypass the gate (forced-routing stress case)."""
         concurrent = self.shared is not None and self.overlap_shared
+        if stream is None and (concurrent or torch.cuda.is_initialized()):   # looked up once: the calls take the raw handle
+            main = torch.cuda.current_stream()
+            stream = main.cuda_stream
+        elif concurrent:
+            main = torch.cuda.ExternalStream(stream) if isinstance(stream, int) else stream
         if self.fp8_activations:
             B.moe_quant_act(self.cfg, self.T, x, self.xq, self.xq_scales, stream)
         if concurrent:
-            main = torch.cuda.current_stream() if stream is None else stream
-            if isinstance(main, int):                # a raw hipStream_t handle
-                main = torch.cuda.ExternalStream(main)
             self.side_stream.wait_stream(main)       # x ready; the previous combine has read shared_ys
             self.shared_ffn(x, self.side_stream, ws=self.ws_shared)
         if forced is None:
