@@ -232,13 +232,13 @@ moe_status moe_combine_stage(const moe_config* cfg, int32_t T, const void* ys_bl
  * not recorded.  Events are host objects; no device memory is involved.
  */
 typedef enum {
-  MOE_K_GATE_NORMS = 0,   /* gate-row norms + counter clear                 */
+  MOE_K_GATE_NORMS = 0,   /* counter clear when the logits are given        */
   MOE_K_GATE_GEMM = 1,    /* gate logits                                    */
   MOE_K_SELECT = 2,       /* wavefront top-k                                */
   MOE_K_RESCORE = 3,      /* fp64 re-scoring of doubtful tokens             */
-  MOE_K_DISPATCH_HIST = 4,
-  MOE_K_DISPATCH_SCAN = 5,
-  MOE_K_DISPATCH_SCATTER = 6,
+  MOE_K_DISPATCH_HIST = 4,    /* counts per chunk, ranks                    */
+  MOE_K_DISPATCH_SCAN = 5,    /* (no kernel: part of the next one)          */
+  MOE_K_DISPATCH_SCATTER = 6, /* offsets and positions                      */
   MOE_K_DISPATCH_GATHER = 7,
   MOE_K_FFN_TILES = 8,
   MOE_K_FFN_GEMM1 = 9,    /* gate|up projection + SwiGLU                    */

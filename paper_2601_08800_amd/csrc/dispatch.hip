@@ -93,8 +93,8 @@ __global__ __launch_bounds__(kRun) void dispatch_count_kernel(
 }
 
 // place: every workgroup adds up the chunks' counts per expert, those before its own
-// chunk apart from the rest (the threads share out experts and chunks; integer sums, so
-// the order of the LDS atomics does not matter), and scans the totals into offsets;
+// chunk apart from the rest (up to 32 threads share an expert's chunks, their sums are
+// added in LDS), and scans the totals into offsets;
 // position = offsets[e] + count before the chunk + rank.  Workgroup 0 stores counts and
 // offsets.
 __global__ __launch_bounds__(kRun) void dispatch_place_kernel(
@@ -102,6 +102,7 @@ __global__ __launch_bounds__(kRun) void dispatch_place_kernel(
     const int32_t* __restrict__ hist, int32_t* __restrict__ counts, int32_t* __restrict__ offsets_out,
     int32_t* __restrict__ perm, int32_t* __restrict__ inv) {
   __shared__ int32_t before[512], total[512];  // before: becomes the chunk's first position of each expert
+  __shared__ int32_t part_lo[kRun], part_all[kRun];
   const int tid = threadIdx.x, lane = tid & 63;
   const int mine = blockIdx.x;
   const int a0 = mine * chunk, a1 = min(A - a0, chunk) + a0;
@@ -111,9 +112,7 @@ __global__ __launch_bounds__(kRun) void dispatch_place_kernel(
     e = ids[a_first] - e_lo;
     rank = inv[a_first];
   }
-  if (tid < E_loc) before[tid] = total[tid] = 0;
-  __syncthreads();
-  const int groups = kRun / E_loc;             // threads per expert
+  const int groups = min(kRun / E_loc, 32);    // threads per expert
   if (tid < groups * E_loc) {
     const int x = tid % E_loc, g = tid / E_loc;
     int lo = 0, all = 0;
@@ -123,8 +122,19 @@ __global__ __launch_bounds__(kRun) void dispatch_place_kernel(
       all += n;
       lo += ch < mine ? n : 0;
     }
-    atomicAdd(&total[x], all);
-    atomicAdd(&before[x], lo);
+    part_lo[tid] = lo;
+    part_all[tid] = all;
+  }
+  __syncthreads();
+  if (tid < E_loc) {
+    int lo = 0, all = 0;
+#pragma unroll 4
+    for (int g = 0; g < groups; ++g) {
+      lo += part_lo[g * E_loc + tid];
+      all += part_all[g * E_loc + tid];
+    }
+    before[tid] = lo;
+    total[tid] = all;
   }
   __syncthreads();
   if (tid < 64) {
@@ -206,8 +216,10 @@ __global__ __launch_bounds__(256) void dispatch_gather_kernel(const uint4* __res
 // workgroup rebuilds the same index in its own LDS (count per sub-chunk, scan
 // per expert, scan over experts, place: the steps and the order of the kernels
 // above, so the permutation is the same), workgroup 0 stores it, and each
-// workgroup then copies the rows of its four tokens.  The redundant index work
-// is a few microseconds on otherwise idle CUs and replaces three launches.
+// workgroup then copies the rows of its four tokens, four wavefronts a row.  The
+// redundant index work is a few microseconds on otherwise idle CUs and replaces two
+// launches; it is a chain of LDS steps, so the workgroup has sixteen wavefronts and the
+// scan over the sub-chunks keeps eight counts in flight.
 // LDS: hist[n_sub][E_loc] | slot[n_sub*64] | cnt[E_loc] | offs[E_loc+1].
 constexpr int kSmallA = 4096;
 constexpr size_t kSmallLds = 60 * 1024;
@@ -216,7 +228,7 @@ inline size_t small_lds_bytes(int E_loc, int n_sub) {
 }
 
 template <int PIECES>
-__global__ __launch_bounds__(256) void dispatch_small_kernel(
+__global__ __launch_bounds__(1024) void dispatch_small_kernel(
     const int32_t* __restrict__ ids, int A, int e_lo, int E_loc, int n_sub,
     int32_t* __restrict__ counts, int32_t* __restrict__ offsets_out, int32_t* __restrict__ perm,
     int32_t* __restrict__ inv, const uint4* __restrict__ x, uint4* __restrict__ xs, int T, int k,
@@ -228,10 +240,10 @@ __global__ __launch_bounds__(256) void dispatch_small_kernel(
   int32_t* const offs = cnt + E_loc;                 // [E_loc + 1]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const bool first = blockIdx.x == 0;
-  for (int i = tid; i < n_sub * E_loc; i += 256) hist[i] = 0;
+  for (int i = tid; i < n_sub * E_loc; i += 1024) hist[i] = 0;
   __syncthreads();
   // 1. count: ballots find the lanes of a sub-chunk that share an expert
-  for (int sub = wave; sub < n_sub; sub += 4) {
+  for (int sub = wave; sub < n_sub; sub += 16) {
     const int a = sub * kSub + lane;
     int e = -1;
     if (a < A) {
@@ -248,12 +260,17 @@ __global__ __launch_bounds__(256) void dispatch_small_kernel(
   }
   __syncthreads();
   // 2. scan over the sub-chunks, one thread per expert
-  for (int e = tid; e < E_loc; e += 256) {
+  for (int e = tid; e < E_loc; e += 1024) {
     int run = 0;
-    for (int sb = 0; sb < n_sub; ++sb) {
-      const int c = hist[sb * E_loc + e];
-      hist[sb * E_loc + e] = run;
-      run += c;
+    for (int s0 = 0; s0 < n_sub; s0 += 8) {
+      int c[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) c[i] = s0 + i < n_sub ? hist[(s0 + i) * E_loc + e] : 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if (s0 + i < n_sub) hist[(s0 + i) * E_loc + e] = run;
+        run += c[i];
+      }
     }
     cnt[e] = run;
     if (first) counts[e] = run;
@@ -284,7 +301,7 @@ __global__ __launch_bounds__(256) void dispatch_small_kernel(
   }
   __syncthreads();
   // 4. place
-  for (int a = tid; a < A; a += 256) {
+  for (int a = tid; a < A; a += 1024) {
     const int sl = slot[a];
     int pos = -1;
     if (sl >= 0) {
@@ -296,19 +313,20 @@ __global__ __launch_bounds__(256) void dispatch_small_kernel(
     if (first) inv[a] = pos;
   }
   __syncthreads();
-  // 5. copy the rows of this workgroup's tokens (one wavefront per token)
-  const int t = blockIdx.x * 4 + wave;
+  // 5. copy the rows of this workgroup's tokens: wavefront w takes runs w%4, w%4 + 4, .. of
+  // 64 pieces of token w/4
+  const int t = blockIdx.x * 4 + (wave >> 2);
   if (t >= T) return;
   int pos = -1;
   if (lane < k) pos = slot[t * k + lane];
   const uint64_t have = __ballot(pos >= 0);
   if (!have) return;
   const uint4* src = x + size_t(t) * src16 + col16;
-  for (int c0 = 0; c0 < row16; c0 += 64 * PIECES) {
+  for (int c0 = (wave & 3) * 64; c0 < row16; c0 += 256 * PIECES) {
     uint4 v[PIECES];
 #pragma unroll
     for (int i = 0; i < PIECES; ++i) {
-      const int c = c0 + i * 64 + lane;
+      const int c = c0 + i * 256 + lane;
       if (c < row16) v[i] = nt_load16(src + c);
     }
     uint64_t m = have;
@@ -319,7 +337,7 @@ __global__ __launch_bounds__(256) void dispatch_small_kernel(
       uint4* dst = xs + size_t(p) * row16;
 #pragma unroll
       for (int i = 0; i < PIECES; ++i) {
-        const int c = c0 + i * 64 + lane;
+        const int c = c0 + i * 256 + lane;
         if (c < row16) nt_store16(dst + c, v[i]);
       }
     }
@@ -371,7 +389,7 @@ hipError_t launch_dispatch(const moe_config& c, int T, const void* x, const int3
   const int src16 = c.hidden * elem_bytes / 16;
   const int row16 = src16 / tp_size;
   if (A <= kSmallA && small_lds_bytes(E_loc, n_sub) <= kSmallLds) {
-    MOE_LAUNCH(MOE_K_DISPATCH_GATHER, dispatch_small_kernel<8>, dim3((T + 3) / 4), dim3(256),
+    MOE_LAUNCH(MOE_K_DISPATCH_GATHER, dispatch_small_kernel<4>, dim3((T + 3) / 4), dim3(1024),
                small_lds_bytes(E_loc, n_sub), s, ids, A, c.expert_lo, E_loc, n_sub, counts, offsets,
                perm, inv, static_cast<const uint4*>(x), static_cast<uint4*>(xs), T, k, src16,
                tp_rank * row16, row16);
