@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "moe_internal.h"
+#include "shortk_layout.h"
 
 namespace moe {
 
@@ -1043,48 +1044,42 @@ __global__ __launch_bounds__(256) void ffn_skinny_kernel(
 // 34 us, 16 000 tokens (524 MB out) 254 -> 117 us; storing from the accumulators
 // instead (16 bytes per lane, 32 contiguous bytes per row) took 39 / 187 us, two
 // workgroups per CU instead of three 37 / 141 us.
-constexpr int kShortKMax = 128;
-
-template <int NKS> struct ShortK {
-  static constexpr int kLoaded = 128 * (NKS * 2 + 1);
-  static constexpr int kStage = kLoaded > 4 * 32 * 9 ? kLoaded : 4 * 32 * 9;
-};
 
 template <int NKS>                                   // K sub-steps of 16: K <= 16 * NKS
 __device__ __forceinline__ void shortk_body(const uint16_t* __restrict__ A,
                                             const uint16_t* __restrict__ Be,
                                             uint16_t* __restrict__ C, int N, int K, int row0,
                                             int row1, int nb0, int nb1, uint4* smem) {
-  constexpr int P = NKS * 2 + 1;                     // pieces per LDS row
-  constexpr int kTurn = 32 * 9;                      // slots in which a wavefront turns 32 x 64 outputs around
+  constexpr int P = ShortK<NKS>::kPieces;            // pieces per LDS row
+  constexpr int kTurn = ShortK<NKS>::kTurn;          // slots in which a wavefront turns 32 x 64 outputs around
   constexpr int STAGE = ShortK<NKS>::kStage;         // 16-byte slots of a stage
-  constexpr int NINST = 2 * P, NLD = (NINST + 3) / 4;
+  constexpr int NINST = ShortK<NKS>::kLoads, NLD = (NINST + 3) / 4;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int h = lane >> 5, l31 = lane & 31;
   const int wm = wave & 1, wn = wave >> 1;
-  constexpr int kOut = 0x7fffffff;
+  constexpr int kOut = kShortKOut;
 
   const int rows = row1 - row0;
   const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(A + size_t(row0) * K), 0, int(size_t(rows) * K * 2), 0x00020000);
-  const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(Be), 0, int(size_t(N) * K * 2), 0x00020000);
   const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
       C + size_t(row0) * N, 0, int(size_t(rows) * N * 2), 0x00020000);
 
   int boff[NLD];                                     // this lane's piece of load i, relative to the block
 #pragma unroll
-  for (int i = 0; i < NLD; ++i) {
-    const int slot = (i * 4 + wave) * 64 + lane, row = slot / P, piece = slot - row * P;
-    boff[i] = piece * 8 < K ? (row * K + piece * 8) * 2 : kOut;
-  }
+  for (int i = 0; i < NLD; ++i) boff[i] = shortk_slot_offset<NKS>((i * 4 + wave) * 64 + lane, K);
+  // The block's place goes into the descriptor's base and its length is what the block
+  // has of w_down, so that the lanes' own offsets decide what is read: a scalar offset
+  // beside them need not count in the range check.
   auto issue = [&](int nb) {
     uint4* const st = smem + (nb & 1) * STAGE;
-    const int base = nb * 128 * K * 2;
+    const ShortKWindow win = shortk_window(nb, N, K);
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t*>(Be + win.first / 2), 0, win.bytes, 0x00020000);
 #pragma unroll
     for (int i = 0; i < NLD; ++i)
       if (i * 4 + wave < NINST)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lptr_t)(st + (i * 4 + wave) * 64), 16, boff[i], base, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lptr_t)(st + (i * 4 + wave) * 64), 16, boff[i], 0, 0, 0);
   };
   issue(nb0);
   // activation fragments: rows wm*64 + i*32 + lane%32, k = kk*16 + h*8 .. +8

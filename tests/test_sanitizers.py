@@ -1,8 +1,8 @@
 """CPU sanitizer legs (AddressSanitizer + UndefinedBehaviorSanitizer, host code
-only): the oracle's C source driven over small layers with its edge cases, and
-the library's host-side argument validation / workspace carving with the kernel
-launchers stubbed out.  Both are standalone executables built here; nothing
-runs on a GPU."""
+only): the oracle's C source driven over small layers with its edge cases, the
+library's host-side argument validation / workspace carving with the kernel
+launchers stubbed out, and the index arithmetic of the short-K kernel's loads.
+All are standalone executables built here; nothing runs on a GPU."""
 import os
 import subprocess
 
@@ -37,4 +37,12 @@ def test_host_validation_under_asan_ubsan(tmp_path):
                            os.path.join(ROOT, "paper_2601_08800_amd", "csrc", "moe_api.hip"),
                            os.path.join(ROOT, "tests", "sanitize", "api_driver.cpp"), "-o", exe],
                           stderr=subprocess.DEVNULL)
+    assert "ok" in _run(exe)
+
+
+def test_short_k_loads_stay_inside_the_expert(tmp_path):
+    exe = str(tmp_path / "shortk_san")
+    subprocess.check_call(["g++", "-O1", "-g", "-std=c++17", *SAN,
+                           "-I", os.path.join(ROOT, "paper_2601_08800_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "sanitize", "shortk_driver.cpp"), "-o", exe])
     assert "ok" in _run(exe)
