@@ -1301,7 +1301,15 @@ hipError_t launch_route(const moe_config& c, int T, const void* x, const void* g
   // 64, 768 tokens 78 / 66.  fp32 rows have no other gate.
   const long tiles = exact_tiles(T, E);
   const size_t limit = size_t(1) << (c.n_groups > 1 ? 22 : 20);
-  const bool exact = !bf16 || (tiles <= 1024 && size_t(tiles) * H <= limit);
+  // Up to 4096 tokens bf16 batches of T*E*H <= 5 * 2^25 (2^28 where a token's gate is long,
+  // E*H > 2^19) have exact logits whatever that costs: their weights are fp64 arithmetic
+  // rounded once, where the pipeline's are fp32 exponentials of fp32 logits.  This adds to the
+  // tiles short rows (128 experts, hidden 512, 2304 tokens) and the batches that only rounding
+  // up to whole tiles takes past the limit (33 tokens, 512 experts, hidden 14336).
+  const size_t teh = size_t(T) * E * H;
+  const bool fp64_band = T <= 4096 && (teh <= size_t(5) << 25 ||
+                                       (size_t(E) * H > size_t(1) << 19 && teh <= size_t(1) << 28));
+  const bool exact = !bf16 || fp64_band || (tiles <= 1024 && size_t(tiles) * H <= limit);
   const bool small_f32 = !bf16 && T <= 256 && size_t(E) * H <= (size_t(1) << 17);
   // experts per lane and form of the gate -> one instance of the selection kernels
 #define MOE_BY_FORM(F, EPL, ...)                                                      \
