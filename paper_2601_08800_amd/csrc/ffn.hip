@@ -245,7 +245,8 @@ template <int NB, bool F8 = false, int BR = 256> struct Ring {
 // the 128-row block this wavefront's weight rows lie in ([K/128] values).  The
 // scaled weight code * scale is rounded to bf16 before the MFMA (the exact
 // per-block scale would need a second set of accumulators).
-template <bool DUAL, int NB, int WM, bool F8, int BR = 256>
+// RAGGED: N or K is no multiple of 64.
+template <bool DUAL, int NB, int WM, bool F8, bool RAGGED, int BR = 256>
 __device__ __forceinline__ void gemm8w_body(const uint16_t* __restrict__ A,
                                             const char* __restrict__ Be0,
                                             const char* __restrict__ Be1,
@@ -271,9 +272,9 @@ __device__ __forceinline__ void gemm8w_body(const uint16_t* __restrict__ A,
   const int lane = threadIdx.x & 63;
   const int wn = BR == 512 ? wave : wave & 3;        // column block of this wavefront
   const int ksteps = (klen + KS - 1) / KS;           // this workgroup's K window starts at kbeg
-  // A K that is not a multiple of the step ends in a short step (bf16 only): its
-  // pieces past K are sent out of the descriptors' range and land as zeros.
-  const int tail = F8 ? 0 : klen % KS;
+  // A K that is not a multiple of the step ends in a short step: its pieces past K are
+  // sent out of the descriptors' range and land as zeros.
+  const int tail = RAGGED ? klen % KS : 0;
   constexpr int kOut = 0x7fffffff;
 
   // LDS row r keeps its piece p at slot p ^ f(r): f = (r/2)&7 for 128-byte rows,
@@ -685,6 +686,10 @@ __device__ __forceinline__ void gemm8w_body(const uint16_t* __restrict__ A,
       if (ok0) p[0] = uint16_t(pk);
       if (ok1) p[N] = uint16_t(pk >> 16);
     };
+    // Sizes that are no multiple of 64 take the division: the reciprocal is one ulp
+    // coarser, and g * u past the fp32 range times a reciprocal of zero (strongly
+    // negative g) is no number where the quotient is zero.
+    auto swiglu = [](float g, float u) { return RAGGED ? silu_mul(g, u) : silu_mul_fast(g, u); };
     auto store_block = [&](int i, auto pred_c) {
       constexpr bool PRED = decltype(pred_c)::value;
 #pragma unroll
@@ -693,13 +698,13 @@ __device__ __forceinline__ void gemm8w_body(const uint16_t* __restrict__ A,
         const bool ok0 = !PRED || r < valid, ok1 = !PRED || r + 1 < valid;
         uint16_t* const p = cl + size_t(r) * N;
         if (DUAL) {
-          if (n0 + wn * 32 + (lane & 31) < N)
-            put2(p + wn * 32, silu_mul_fast(acc[i][0][q], acc[i][1][q]),
-                 silu_mul_fast(acc[i][0][q + 1], acc[i][1][q + 1]), ok0, ok1);
+          if (n0 + wn * 32 + (RAGGED ? lane & 31 : 0) < N)
+            put2(p + wn * 32, swiglu(acc[i][0][q], acc[i][1][q]),
+                 swiglu(acc[i][0][q + 1], acc[i][1][q + 1]), ok0, ok1);
         } else {
 #pragma unroll
           for (int j = 0; j < 2; ++j)
-            if (n0 + wn * 64 + j * 32 + (lane & 31) < N)
+            if (n0 + wn * 64 + j * 32 + (RAGGED ? lane & 31 : 0) < N)
               put2(p + wn * 64 + j * 32, acc[i][j][q], acc[i][j][q + 1], ok0, ok1);
         }
       }
@@ -718,7 +723,7 @@ __device__ __forceinline__ void gemm8w_body(const uint16_t* __restrict__ A,
 #undef MOE_LOAD_A_AT
 #undef MOE_LOAD_B_AT
 
-template <bool DUAL, int NB, bool F8, bool WIDE>
+template <bool DUAL, int NB, bool F8, bool RAGGED, bool WIDE>
 __device__ __forceinline__ void gemm8w_tile(const uint16_t* A, const char* Be0, const char* Be1,
                                             const float* Se0, const float* Se1, uint16_t* C, int N,
                                             int K, int row0, int row1, int n0, uint4* smem,
@@ -726,10 +731,10 @@ __device__ __forceinline__ void gemm8w_tile(const uint16_t* A, const char* Be0, 
   if constexpr (WIDE) {
     // at most four row blocks: all eight wavefronts work on them, each on its own
     // 32 (DUAL) or 64 weight rows of a 512-row stage
-    gemm8w_body<DUAL, NB, 0, F8, 512>(A, Be0, Be1, Se0, Se1, C, N, K, row0, row1, n0, smem, wave, kbeg, klen, job);
+    gemm8w_body<DUAL, NB, 0, F8, RAGGED, 512>(A, Be0, Be1, Se0, Se1, C, N, K, row0, row1, n0, smem, wave, kbeg, klen, job);
   } else {
-    if (wave < 4) gemm8w_body<DUAL, NB, 0, F8>(A, Be0, Be1, Se0, Se1, C, N, K, row0, row1, n0, smem, wave, kbeg, klen, job);
-    else gemm8w_body<DUAL, NB, 1, F8>(A, Be0, Be1, Se0, Se1, C, N, K, row0, row1, n0, smem, wave, kbeg, klen, job);
+    if (wave < 4) gemm8w_body<DUAL, NB, 0, F8, RAGGED>(A, Be0, Be1, Se0, Se1, C, N, K, row0, row1, n0, smem, wave, kbeg, klen, job);
+    else gemm8w_body<DUAL, NB, 1, F8, RAGGED>(A, Be0, Be1, Se0, Se1, C, N, K, row0, row1, n0, smem, wave, kbeg, klen, job);
   }
 }
 
@@ -744,7 +749,7 @@ __device__ __forceinline__ void gemm8w_tile(const uint16_t* A, const char* Be0, 
 // WIDE: tiles of at most 128 rows (the table is built with that height) x 512
 // weight rows, for GEMM-2 launches whose groups are short: twice the weight bytes
 // per K step and barrier, half as many tiles.
-template <bool DUAL, bool F8, bool WIDE = false>
+template <bool DUAL, bool F8, bool RAGGED, bool WIDE>
 __global__ __launch_bounds__(512) void ffn_gemm8w_kernel(
     const uint16_t* __restrict__ A, const void* __restrict__ B0, const void* __restrict__ B1,
     const float* __restrict__ S0, const float* __restrict__ S1, uint16_t* __restrict__ C, int N,
@@ -827,7 +832,7 @@ __global__ __launch_bounds__(512) void ffn_gemm8w_kernel(
     Se1 = DUAL ? S1 + (size_t(e) * nnb + nb) * nkb + (kb >> 1) : Se0;
   }
 #define MOE_TILE_(NBV)                                                                        \
-  gemm8w_tile<DUAL, NBV, F8, WIDE>(A, Be0, Be1, Se0, Se1, C, N, K, row0, row1, n0, smem, wave,   \
+  gemm8w_tile<DUAL, NBV, F8, RAGGED, WIDE>(A, Be0, Be1, Se0, Se1, C, N, K, row0, row1, n0, smem, wave,   \
                                    kb * 64, (ke * 64 < K ? ke * 64 : K) - kb * 64, job)
   if constexpr (WIDE) {
     switch ((row1 - row0 + 31) >> 5) {   // valid 32-row blocks of the tile: at most four
@@ -1402,12 +1407,19 @@ void launch_gemm(GemmKind kind, int bm, const uint16_t* A, const void* B0, const
   const int BN = DUAL ? 128 : (wide ? 512 : 256);
   // room for the parts of the leftover tiles behind the whole tiles
   const int grid = (max_mt * ((N + BN - 1) / BN) + 7) / 8 * 8 + kCUs;
-  auto k = ffn_gemm8w_kernel<DUAL, F8, false>;
-  if constexpr (!DUAL) {
-    if (wide) k = ffn_gemm8w_kernel<false, F8, true>;
+  auto k = ffn_gemm8w_kernel<DUAL, F8, false, false>;
+  int form = 0;
+  if constexpr (!F8) {
+    if (((N | K) & 63) != 0) { k = ffn_gemm8w_kernel<DUAL, F8, true, false>; form = 1; }
   }
-  static uint64_t opted = 0, opted_wide = 0;
-  lds_opt_in(reinterpret_cast<const void*>(k), lds, wide ? opted_wide : opted);
+  if constexpr (!DUAL) {
+    if (wide) { k = ffn_gemm8w_kernel<DUAL, F8, false, true>; form = 2; }
+    if constexpr (!F8) {
+      if (wide && ((N | K) & 63) != 0) { k = ffn_gemm8w_kernel<DUAL, F8, true, true>; form = 3; }
+    }
+  }
+  static uint64_t opted[4] = {};
+  lds_opt_in(reinterpret_cast<const void*>(k), lds, opted[form]);
   MOE_LAUNCH(id, k, dim3(grid), dim3(512), lds, s, A, B0, B1, S0, S1, C, N, K, tiles, 1, ws.partial,
              ws.tickets + (DUAL ? 0 : kSplitTickets));
 }

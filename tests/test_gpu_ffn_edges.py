@@ -63,3 +63,25 @@ def test_bf16_ragged_k_tall_tiles(counts, H, I):
 @pytest.mark.parametrize("counts", [[1, 2, 0, 3], [9, 1, 14, 8]])
 def test_bf16_ragged_k_weight_streaming(counts):
     check_ffn(counts, 328, 200, TOL["bf16"])
+
+
+# SwiGLU where g * u is past the fp32 range and silu(g) is zero: g = -2^66, u = 2^66 have the
+# intermediate 0, at sizes that are no multiple of 64, on every kernel of GEMM-1 (the average
+# number of rows picks it) and on both row halves of a tile.
+@pytest.mark.parametrize("H,I", [(328, 200), (520, 136), (72, 96)])
+@pytest.mark.parametrize("rows", [2, 24, 300, 700])
+def test_bf16_ragged_swiglu_of_large_values(rows, H, I):
+    import paper_2601_08800_amd as moe
+    cfg = moe.MoEConfig(hidden=H, n_experts=1, top_k=1, score_fn=moe.MOE_SCORE_SOFTMAX, renormalize=1, routed_scale=1.0,
+                        n_groups=1, topk_groups=1, group_score_n=0, expert_lo=0, expert_hi=1, inter_local=I,
+                        act_dtype=moe.MOE_BF16, weight_dtype=moe.MOE_BF16)
+    bf = lambda *s: torch.zeros(*s, dtype=torch.bfloat16, device="cuda")
+    x, wg, wu, wd, ys = bf(rows, H), bf(1, I, H), bf(1, I, H), bf(1, H, I), bf(rows, H)
+    x[:, 0] = 2.0 ** 33
+    wg[:, :, 0], wu[:, :, 0] = -2.0 ** 33, 2.0 ** 33
+    wd.fill_(1.0)
+    offsets = torch.tensor([0, rows], dtype=torch.int32, device="cuda")
+    ws = torch.empty(moe.moe_workspace_bytes(cfg, rows), dtype=torch.uint8, device="cuda")
+    ys.fill_(1.0)
+    moe.moe_expert_ffn(cfg, 1, x, offsets, rows, wg, wu, wd, None, None, None, ys, ws)
+    assert torch.count_nonzero(ys).item() == 0 and not torch.isnan(ys).any()
