@@ -924,12 +924,14 @@ __global__ __launch_bounds__(256) void ffn_skinny_kernel(
 #pragma unroll
       for (int kk = 0; kk < NKK; ++kk) {
         const bool in = k0 + h * (W / 2) + kk * 8 < K;
-        const uint4 zero = make_uint4(0, 0, 0, 0);
-        r.a[kk] = in && a_valid ? *reinterpret_cast<const uint4*>(arow + k0 + kk * 8) : zero;
+        // (a value on the other side of the ?, not a variable: the choice of an address
+        // would put that variable into scratch memory, and every load of the slice is flat)
+        r.a[kk] = in && a_valid ? *reinterpret_cast<const uint4*>(arow + k0 + kk * 8) : make_uint4(0, 0, 0, 0);
 #pragma unroll
         for (int j = 0; j < 2; ++j)
           if (kk < BL)
-            r.b[j][kk] = in ? *reinterpret_cast<const uint4*>(brow[j] + size_t(k0) * wb + kk * 16) : zero;
+            r.b[j][kk] = in ? *reinterpret_cast<const uint4*>(brow[j] + size_t(k0) * wb + kk * 16)
+                            : make_uint4(0, 0, 0, 0);
       }
       return;
     }
