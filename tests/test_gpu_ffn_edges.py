@@ -85,3 +85,23 @@ def test_bf16_ragged_swiglu_of_large_values(rows, H, I):
     ys.fill_(1.0)
     moe.moe_expert_ffn(cfg, 1, x, offsets, rows, wg, wu, wd, None, None, None, ys, ws)
     assert torch.count_nonzero(ys).item() == 0 and not torch.isnan(ys).any()
+
+
+# An infinite gate keeps silu(g) = g (inf) on every kernel of GEMM-1, beside finite values in
+# the same tile; the intermediate is then inf, and so is every output of that row.
+@pytest.mark.parametrize("rows", [2, 24, 300])
+def test_bf16_ragged_swiglu_of_infinity(rows):
+    import paper_2601_08800_amd as moe
+    H, I = 72, 96
+    cfg = moe.MoEConfig(hidden=H, n_experts=1, top_k=1, score_fn=moe.MOE_SCORE_SOFTMAX, renormalize=1, routed_scale=1.0,
+                        n_groups=1, topk_groups=1, group_score_n=0, expert_lo=0, expert_hi=1, inter_local=I,
+                        act_dtype=moe.MOE_BF16, weight_dtype=moe.MOE_BF16)
+    full = lambda v, *s: torch.full(s, v, dtype=torch.bfloat16, device="cuda")
+    x, wg, wu, wd, ys = full(0.0, rows, H), full(0.0, 1, I, H), full(0.0, 1, I, H), full(1.0, 1, H, I), full(0.0, rows, H)
+    x[:, 0] = 1.0
+    x[rows - 1, 0] = 2.0 ** 100
+    wg[:, :, 0], wu[:, :, 0] = 2.0 ** 100, 1.0          # g = 2^100, and past the range in the last row
+    offsets = torch.tensor([0, rows], dtype=torch.int32, device="cuda")
+    ws = torch.empty(moe.moe_workspace_bytes(cfg, rows), dtype=torch.uint8, device="cuda")
+    moe.moe_expert_ffn(cfg, 1, x, offsets, rows, wg, wu, wd, None, None, None, ys, ws)
+    assert bool((ys[:-1].float() == 96 * 2.0 ** 100).all()) and bool(torch.isposinf(ys[-1].float()).all())
