@@ -1378,11 +1378,16 @@ struct FfnPlan {
 };
 
 // Rows per expert can only be bounded from above on the host; the kernels are
-// picked by that bound (`avg`).
+// picked by that bound (`avg`).  Tile counts are bounds too.
 FfnPlan plan_ffn(const moe_config& c, int n_experts, int rows_capacity) {
   const int H = c.hidden, I = c.inter_local, avg = rows_capacity / n_experts;
   if (c.act_dtype == MOE_F32) return {kGemmF32, kGemmF32, 32, 32};
   const bool fp8 = c.weight_dtype == MOE_FP8_E4M3_B128;
+  const bool ragged = ((H | I) & 63) != 0;
+  const int groups = n_experts < rows_capacity ? n_experts : rows_capacity;
+  auto tiles_of = [&](int bm, int cols, int bn) {
+    return long(rows_capacity / bm + groups) * ((cols + bn - 1) / bn);
+  };
   FfnPlan p;
   // GEMM-1 (K = H long): the weight-streaming kernel at decode sizes, then the LDS
   // rings of the tall-tile kernel, which stream the weights faster as soon as a tile
@@ -1393,10 +1398,22 @@ FfnPlan plan_ffn(const moe_config& c, int n_experts, int rows_capacity) {
   // Few rows per expert mean that the weights are streamed about once: tiles of at
   // most 160 rows there, which leaves room for a three-stage ring.
   p.bm1 = p.g1 == kGemmStream ? 32 : (avg <= 320 ? 160 : 256);
+  // Sizes that are no multiple of 64 (I: a cut that is not even, 1408 / 8) differ in two things:
+  //  - 160-row tiles also for long groups while they fit one round of the CUs, where a tall
+  //    tile's length is the launch's: one group of 512 / 1024 rows, hidden 2048, I 200: 37 -> 28 /
+  //    37 -> 33 us; 16 groups of 512: 39 -> 35; 320 tiles (128 experts, I 344): no gain.
+  //  - the weight-streaming kernel up to 16 rows per expert where one tall tile per expert and
+  //    128 columns would leave a second round of CUs less than half full: 64 experts, hidden 520,
+  //    I 520 (320 tiles), 3 / 16 rows per expert: 22.4 -> 18.1 / 22.8 -> 20.9 us, 128 experts,
+  //    hidden 2048, I 344 (384 tiles): 85 -> 68 / 91 -> 76; one whole round (128 experts, hidden 520,
+  //    I 136) 12.6 against 13.7 us.
+  const long tall = tiles_of(160, I, 128), first = long(groups) * ((I + 127) / 128);
+  if (ragged && avg > 2 && avg <= 16 && first > kCUs && 2 * first <= 3 * kCUs) { p.g1 = kGemmStream; p.bm1 = 32; }
+  if (ragged && p.bm1 == 256 && tall <= kCUs) p.bm1 = 160;
   // GEMM-2 (K = I_loc short, N = H wide):
   //  - K up to 128 (a layer cut over many TP ranks): the short-K kernel at every size.
   //    128 experts, hidden 2048, I_loc 96: 12 us at 2 and 8 rows per expert, where the
-  //    weight-streaming kernel (three K slices per wavefront pair) takes 27 / 30 us; at K =
+  //    weight-streaming kernel (a K slice each for two of its wavefronts) takes 27 / 30 us; at K =
   //    192 the tall-tile kernel is the faster one (188 rows per expert: 49 against 54 us).
   //  - up to twelve rows per expert: many small weight-streaming workgroups.
   //  - up to 96 rows per expert, when the experts give at least one such tile per CU:
@@ -1404,12 +1421,25 @@ FfnPlan plan_ffn(const moe_config& c, int n_experts, int rows_capacity) {
   //    81, 94 -> 86, 102 -> 92 us at 32 / 64 / 96 rows per expert, 110 -> 115 us at 128;
   //    e4m3 weights at 64 rows per expert (32 experts, hidden 7168): 73 -> 61 us.
   //    (GEMM-1 keeps the narrow tiles: its wide form was slower at every size, the
-  //    512-row bf16 stage leaves room for two ring stages only.)
+  //    512-row bf16 stage leaves room for two ring stages only.)  For sizes that are no
+  //    multiple of 64 from three rows per expert on if K is short, up to 384 (128 experts, hidden
+  //    2048, I 200: 36 -> 31 us at twelve rows, I 344: 52 -> 50, 64 experts, I 1000: 55 against 58 at
+  //    three), in the short-K kernel's place up to 16 rows if K is at most 48 (64 experts, I 40:
+  //    8.5 -> 7.2 us), and not where most columns of the last tile are missing and the tiles are
+  //    more than a round (hidden 1032, I 520, 128 experts: 53 against 45 us at 16 rows).
+  //  - 128-row tiles for sizes that are no multiple of 64, long groups and no more tiles than CUs
+  //    (one group of 256 / 1024 rows, hidden 2048, I 200: 13.5 -> 10.4 / 14 -> 10.8 us).
   //  - else 256-row tiles.
-  if (!fp8 && I <= kShortKMax) { p.g2 = kGemmShortK; p.bm2 = 128; }
+  const long wide_tiles = long(n_experts) * ((H + 511) / 512);
+  const bool wide = wide_tiles >= kCUs &&
+                    (!ragged || wide_tiles <= kCUs || (H + 511) / 512 * 512 * 4L <= 5L * H);
+  if (ragged && wide && (I <= 48 ? avg <= 16 : I > kShortKMax && I <= 384 && avg > 2 && avg <= 12)) {
+    p.g2 = kGemmWide;
+    p.bm2 = 128;
+  } else if (!fp8 && I <= kShortKMax) { p.g2 = kGemmShortK; p.bm2 = 128; }
   else if (avg <= 12) { p.g2 = kGemmStream; p.bm2 = 32; }
-  else if (avg <= 96 && long(n_experts) * ((H + 511) / 512) >= kCUs) { p.g2 = kGemmWide; p.bm2 = 128; }
-  else { p.g2 = kGemmTall; p.bm2 = 256; }
+  else if (avg <= 96 && wide) { p.g2 = kGemmWide; p.bm2 = 128; }
+  else { p.g2 = kGemmTall; p.bm2 = ragged && avg >= 128 && tiles_of(128, H, 256) <= kCUs ? 128 : 256; }
   return p;
 }
 

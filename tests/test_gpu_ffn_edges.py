@@ -105,3 +105,58 @@ def test_bf16_ragged_swiglu_of_infinity(rows):
     ws = torch.empty(moe.moe_workspace_bytes(cfg, rows), dtype=torch.uint8, device="cuda")
     moe.moe_expert_ffn(cfg, 1, x, offsets, rows, wg, wu, wd, None, None, None, ys, ws)
     assert bool((ys[:-1].float() == 96 * 2.0 ** 100).all()) and bool(torch.isposinf(ys[-1].float()).all())
+
+
+def _ffn(counts, H, I):
+    """moe_expert_ffn on groups of `counts` rows, and fp64 torch on the same bf16 values (the
+    intermediate rounded to bf16 as it is stored)."""
+    import paper_2601_08800_amd as moe
+    n, R = len(counts), sum(counts)
+    cfg = moe.MoEConfig(hidden=H, n_experts=n, top_k=1, score_fn=moe.MOE_SCORE_SOFTMAX, renormalize=1, routed_scale=1.0,
+                        n_groups=1, topk_groups=1, group_score_n=0, expert_lo=0, expert_hi=n, inter_local=I,
+                        act_dtype=moe.MOE_BF16, weight_dtype=moe.MOE_BF16)
+    g = torch.Generator(device="cuda").manual_seed(R + H + I)
+    bf = lambda std, *s: torch.empty(*s, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    x, wg, wu, wd = bf(1.0, R, H), bf(0.05, n, I, H), bf(0.05, n, I, H), bf(0.05, n, H, I)
+    ends = np.cumsum([0] + list(counts))
+    offsets = torch.tensor(ends, dtype=torch.int32, device="cuda")
+    ws = torch.empty(moe.moe_workspace_bytes(cfg, R), dtype=torch.uint8, device="cuda")
+    ys = [torch.full((R, H), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    for y in ys:
+        moe.moe_expert_ffn(cfg, n, x, offsets, R, wg, wu, wd, None, None, None, y, ws)
+    assert torch.equal(ys[0].view(torch.int16), ys[1].view(torch.int16))
+    ref = torch.empty(R, H, dtype=torch.float64, device="cuda")
+    for e in range(n):
+        lo, hi = int(ends[e]), int(ends[e + 1])
+        if lo == hi:
+            continue
+        xe = x[lo:hi].double()
+        gate, up = (xe @ w[e].double().t().contiguous() for w in (wg, wu))
+        h = (gate * torch.sigmoid(gate) * up).to(torch.bfloat16).double()
+        ref[lo:hi] = h @ wd[e].double().t().contiguous()
+    err = float((ys[0].double() - ref).abs().max() / ref.abs().max())
+    print("experts", n, "rows", R, "H", H, "I", I, "err %.3e" % err, flush=True)
+    # the output's rounding (2^-9), and intermediates that fall to the other side of a
+    # rounding (2^-8 of one of I terms each): well inside the layer's bar
+    assert err <= TOL["bf16"]
+
+
+def _counts(n, lo, hi):
+    c = np.random.default_rng(n * 1000 + hi).integers(lo, hi + 1, n)
+    c[n // 3] = 0
+    return c.tolist()
+
+
+# Sizes that are no multiple of 64, by the kernel that the rules pick: weight streaming in
+# both GEMMs past two rows per expert (270 tall tiles, a second round of CUs nearly empty) and at
+# one or two; 128 x 512 tiles of GEMM-2 with a K and an N remainder: K up to 48, up to 384
+# from three rows per expert, from 13 on, and 260 tiles of 53 K steps, four of them cut along K;
+# 160- and 128-row tall tiles of long groups.
+@pytest.mark.parametrize("counts,H,I", [
+    (_counts(90, 0, 33), 520, 328), (_counts(90, 1, 5), 520, 328), (_counts(130, 1, 2), 136, 520),
+    (_counts(128, 0, 9), 1000, 40), (_counts(128, 1, 20), 2056, 136), (_counts(128, 1, 70), 2056, 200),
+    (_counts(52, 20, 60), 2504, 3400),
+    ([900, 0, 513, 700], 328, 136), ([1500], 584, 264), ([300, 128, 129], 1032, 200)],
+    ids=lambda v: str(v) if isinstance(v, int) else "%dx%d" % (len(v), sum(v)))
+def test_bf16_ragged_rules(counts, H, I):
+    _ffn(counts, H, I)
