@@ -1206,11 +1206,17 @@ __global__ __launch_bounds__(256, NKS <= 6 ? 3 : 2) void ffn_shortk_kernel(const
 void launch_shortk(const void* hmid, const void* w_down, void* ys, int N, int K, const int32_t* tiles,
                    int max_mt, hipStream_t s) {
   // about four rounds of three workgroups per CU, each with at least four column
-  // blocks to overlap, unless that leaves CUs without a workgroup (decode sizes)
+  // blocks to overlap, unless that leaves CUs without a workgroup (decode sizes); with
+  // one block each there is nothing to overlap, so not where the halves of a launch that
+  // nearly fills the chip would come to a second round (8 experts, hidden 7168, I_loc 64, 144
+  // rows each: 952 workgroups 12.1 us, 476 10.8)
   const int blocks = (N + 127) / 128;
   int most = (blocks + 3) / 4;
-  while (most < blocks && long(max_mt) * most < 2 * kCUs) most *= 2;
-  most = most < blocks ? most : blocks;
+  while (most < blocks && long(max_mt) * most < 2 * kCUs) {
+    const int twice = 2 * most < blocks ? 2 * most : blocks;
+    if (2L * max_mt * twice > 7 * kCUs) break;
+    most = twice;
+  }
   int split = (12 * kCUs + max_mt - 1) / max_mt;
   split = split < most ? split : most;
   const int grid = (max_mt * split + 7) / 8 * 8;
@@ -1411,10 +1417,17 @@ FfnPlan plan_ffn(const moe_config& c, int n_experts, int rows_capacity) {
   if (ragged && avg > 2 && avg <= 16 && first > kCUs && 2 * first <= 3 * kCUs) { p.g1 = kGemmStream; p.bm1 = 32; }
   if (ragged && p.bm1 == 256 && tall <= kCUs) p.bm1 = 160;
   // GEMM-2 (K = I_loc short, N = H wide):
-  //  - K up to 128 (a layer cut over many TP ranks): the short-K kernel at every size.
-  //    128 experts, hidden 2048, I_loc 96: 12 us at 2 and 8 rows per expert, where the
-  //    weight-streaming kernel (a K slice each for two of its wavefronts) takes 27 / 30 us; at K =
+  //  - K up to 128 (a layer cut over many TP ranks): the short-K kernel.
+  //    128 experts, hidden 2048, I_loc 96: 13 / 14 us at 2 / 6 rows per expert, where the
+  //    weight-streaming kernel (a K slice each for two of its wavefronts) takes 23 / 27 us; at K =
   //    192 the tall-tile kernel is the faster one (188 rows per expert: 49 against 54 us).
+  //    At K = 128, where two of its workgroups share a CU and not three and the others have whole
+  //    steps, only launches of many 128 x 128 blocks: 32 experts, hidden 2048, 112 rows each (960
+  //    blocks) 16 against 13 us for the tall tiles, 8 experts, hidden 7168, 144 rows (952) 17
+  //    against 12, 64 experts, hidden 2048, 16 rows (1152) 12.6 against 11.0 for the wide ones;
+  //    32 experts, hidden 7168, 64 rows (2688) 20 against 24; against the weight-streaming
+  //    kernel 16 experts, hidden 7168, one row (896) 10.5 / 9.7, 128 experts, hidden 2048, 4 rows
+  //    (2112) 17 / 25 us.
   //  - up to twelve rows per expert: many small weight-streaming workgroups.
   //  - up to 96 rows per expert, when the experts give at least one such tile per CU:
   //    tiles of 128 rows x 512 weight rows.  128 experts, hidden 2048, I 768, bf16: 85 ->
@@ -1430,13 +1443,15 @@ FfnPlan plan_ffn(const moe_config& c, int n_experts, int rows_capacity) {
   //  - 128-row tiles for sizes that are no multiple of 64, long groups and no more tiles than CUs
   //    (one group of 256 / 1024 rows, hidden 2048, I 200: 13.5 -> 10.4 / 14 -> 10.8 us).
   //  - else 256-row tiles.
+  const long blocks = tiles_of(128, H, 128);
+  const bool short_k = ragged || I < kShortKMax || (avg <= 12 ? blocks > 1024 : blocks >= 2048);
   const long wide_tiles = long(n_experts) * ((H + 511) / 512);
   const bool wide = wide_tiles >= kCUs &&
                     (!ragged || wide_tiles <= kCUs || (H + 511) / 512 * 512 * 4L <= 5L * H);
   if (ragged && wide && (I <= 48 ? avg <= 16 : I > kShortKMax && I <= 384 && avg > 2 && avg <= 12)) {
     p.g2 = kGemmWide;
     p.bm2 = 128;
-  } else if (!fp8 && I <= kShortKMax) { p.g2 = kGemmShortK; p.bm2 = 128; }
+  } else if (!fp8 && I <= kShortKMax && short_k) { p.g2 = kGemmShortK; p.bm2 = 128; }
   else if (avg <= 12) { p.g2 = kGemmStream; p.bm2 = 32; }
   else if (avg <= 96 && wide) { p.g2 = kGemmWide; p.bm2 = 128; }
   else { p.g2 = kGemmTall; p.bm2 = ragged && avg >= 128 && tiles_of(128, H, 256) <= kCUs ? 128 : 256; }

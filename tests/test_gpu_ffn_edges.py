@@ -160,3 +160,13 @@ def _counts(n, lo, hi):
     ids=lambda v: str(v) if isinstance(v, int) else "%dx%d" % (len(v), sum(v)))
 def test_bf16_ragged_rules(counts, H, I):
     _ffn(counts, H, I)
+
+
+# K = 128 on either side of the launches that the short-K kernel takes: 2048 blocks (past twelve
+# rows per expert) and 1024 (up to there); K = 64 with column blocks that are not halved further.
+@pytest.mark.parametrize("counts,H,I", [
+    (_counts(128, 1, 40), 2048, 128), (_counts(128, 1, 40), 1024, 128), ([144] * 8, 7168, 128),
+    (_counts(128, 0, 7), 2048, 128), (_counts(64, 1, 1), 2048, 128), ([144] * 8, 7168, 64)],
+    ids=lambda v: str(v) if isinstance(v, int) else "%dx%d" % (len(v), sum(v)))
+def test_bf16_k128_rules(counts, H, I):
+    _ffn(counts, H, I)
