@@ -1241,8 +1241,9 @@ void launch_shortk(const void* hmid, const void* w_down, void* ys, int N, int K,
 // fp32 layers on v_mfma_f32_32x32x2_f32 (fp32 products and sums).  Tile 32 rows x
 // 32 output columns (DUAL: with the matching up rows).  Operands go global -> LDS
 // directly in chunks of 128 K values (512-byte rows: whole cache lines) into a
-// ring of as many chunks as 144 KB hold; the four wavefronts each multiply a
-// quarter of every chunk and their sums are added in a fixed order at the end.
+// ring of as many chunks as 144 KB hold (launches of more tiles than CUs: one chunk, see
+// F32Ring::stages); the four wavefronts each multiply a quarter of every chunk and their
+// sums are added in a fixed order at the end.
 // These layers are small (64 tokens, hidden 256, 8 experts, I 512), so a launch is
 // one workgroup's latency chain: small tiles put it on as many CUs as there are,
 // the K split makes the arithmetic a quarter as long, and a short K is in flight
@@ -1250,24 +1251,35 @@ void launch_shortk(const void* hmid, const void* w_down, void* ys, int N, int K,
 // cycle and CU) needs 24 bytes per cycle even with this small tile, so long
 // launches are not bound by the loads either.
 // Measured against 64 x 64 tiles of VALU arithmetic (64-token layer, GEMM-1 / -2):
-// 30.2 / 30.6 -> 7.0 / 5.9 us; 2048 rows, hidden = I = 512: 58 / 34 -> 36 / 22 us;
-// 8192 rows, hidden 2048, I 1024 (84 TFLOP/s): 1050 / 546 -> 813 / 500 us.  The same
-// tile without LDS (lanes reading 16 bytes of 32 rows each) was slower: 13 / 15 us
-// on the small layer, 2033 / 1447 us on the large one.
+// 30.2 / 30.6 -> 7.0 / 5.9 us; 8 experts of 256 rows, hidden = I = 512: 72 / 43 -> 35 / 21 us;
+// 8192 rows, hidden 2048, I 1024: 914 / 497 -> 629 / 339 us (109 TFLOP/s).  The same tile
+// without LDS (lanes reading 16 bytes of 32 rows each) was slower: 13 / 15 us on the small
+// layer, 2033 / 1447 us on the large one.
 // LDS row r keeps its 16-byte piece p at slot p ^ (r & 15).
 constexpr int kF32Chunk = 128;                        // K values per chunk
 template <bool DUAL> struct F32Ring {
   static constexpr int kRows = DUAL ? 96 : 64;        // activation rows | weight rows
   static constexpr int kSlots = kRows * (kF32Chunk / 4);
   static constexpr int kStages = DUAL ? 3 : 4;        // 144 KB / 128 KB
-  static constexpr int kLds = kStages * kSlots * 16;
+  static constexpr int kStageBytes = kSlots * 16;
+  static constexpr int kLds = kStages * kStageBytes;
+  // Stages of a launch of at most `tiles` tiles: as many as K has chunks and the ring holds
+  // while every tile has a CU to itself, else one, so that three (DUAL) or five workgroups
+  // share a CU and load while others multiply.  8192 rows, hidden = I = 512, GEMM-1 / -2: 75 / 47 ->
+  // 60 / 37 us; 1056 tiles, hidden = I = 256: 29 -> 22; below 256 tiles 7.8 against 8.5 us (K = 512).
+  static int stages(int K, long tiles) {
+    const int chunks = (K + kF32Chunk - 1) / kF32Chunk;
+    const int most = tiles > kCUs ? 1 : kStages;
+    return chunks < most ? chunks : most;
+  }
 };
 
 template <bool DUAL>
 __device__ __forceinline__ void ffn_f32_body(const float* __restrict__ A,
                                              const float* __restrict__ Be0,
                                              const float* __restrict__ Be1, float* __restrict__ C,
-                                             int N, int K, int row0, int row1, int n0, uint4* smem) {
+                                             int N, int K, int row0, int row1, int n0, int stages,
+                                             uint4* smem) {
   constexpr int NB = DUAL ? 2 : 1, NS = F32Ring<DUAL>::kStages, SLOTS = F32Ring<DUAL>::kSlots;
   constexpr int NLD = F32Ring<DUAL>::kRows / 8;       // load instructions per wavefront and chunk
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1282,8 +1294,8 @@ __device__ __forceinline__ void ffn_f32_body(const float* __restrict__ A,
   // One instruction fills two LDS rows; instruction i of wavefront w: rows
   // (i*4 + w)*2 + lane/32, the lane that owns slot s of row r fetches piece s ^ (r&15).
   // Rows past the tile (or past N) and pieces past K are out of range: zeros.
-  auto issue = [&](int c) {
-    uint4* const st = smem + (c % NS) * SLOTS;
+  auto issue = [&](int c, int stage) {
+    uint4* const st = smem + stage * SLOTS;
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
       const int pair = i * 4 + wave, row = pair * 2 + h, local = row & 31;
@@ -1303,16 +1315,17 @@ __device__ __forceinline__ void ffn_f32_body(const float* __restrict__ A,
   const int nch = (K + kF32Chunk - 1) / kF32Chunk;
 #pragma unroll
   for (int c = 0; c < NS; ++c)
-    if (c < nch) issue(c);
+    if (c < stages) issue(c, c);                     // stages <= nch
+  int stage = 0;                                     // of chunk c
   for (int c = 0; c < nch; ++c) {
-    // chunk c must have landed; up to NS-1 younger ones stay in flight
-    const int younger = nch - 1 - c;
-    if (younger >= NS - 1) wait_vmcnt<(NS - 1) * NLD>();
-    else if (NS > 3 && younger == 2) wait_vmcnt<2 * NLD>();
+    // chunk c must have landed; up to stages-1 younger ones stay in flight
+    const int younger = nch - 1 - c < stages - 1 ? nch - 1 - c : stages - 1;
+    if (NS > 3 && younger == 3) wait_vmcnt<3 * NLD>();
+    else if (younger == 2) wait_vmcnt<2 * NLD>();
     else if (younger == 1) wait_vmcnt<NLD>();
     else wait_vmcnt<0>();
     asm volatile("s_barrier" ::: "memory");
-    const uint4* const st = smem + (c % NS) * SLOTS;
+    const uint4* const st = smem + stage * SLOTS;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       // MFMA i of lane half h multiplies element i of the same piece of both operands
@@ -1330,10 +1343,11 @@ __device__ __forceinline__ void ffn_f32_body(const float* __restrict__ A,
           acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[i], acc[j], 0, 0, 0);
         }
     }
-    if (c + NS < nch) {
+    if (c + stages < nch) {
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the stage has been read by all
-      issue(c + NS);
+      issue(c + stages, stage);
     }
+    stage = stage + 1 < stages ? stage + 1 : 0;
   }
   // add the four partial sums in a fixed order: wavefront w finishes registers 4w..4w+3
   __syncthreads();
@@ -1365,7 +1379,7 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
                                                      const float* __restrict__ B0,
                                                      const float* __restrict__ B1,
                                                      float* __restrict__ C, int N, int K,
-                                                     const int32_t* __restrict__ tiles) {
+                                                     const int32_t* __restrict__ tiles, int stages) {
   extern __shared__ uint4 smem[];
   const int n_ntiles = (N + 31) / 32;
   const int mtile = blockIdx.x / n_ntiles, ntile = blockIdx.x - mtile * n_ntiles;
@@ -1373,11 +1387,91 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
   const int e = tiles[1 + kTileRec * mtile], row0 = tiles[2 + kTileRec * mtile],
             row1 = tiles[3 + kTileRec * mtile];
   ffn_f32_body<DUAL>(A, B0 + size_t(e) * N * K, DUAL ? B1 + size_t(e) * N * K : nullptr, C, N, K,
-                     row0, row1, ntile * 32, smem);
+                     row0, row1, ntile * 32, stages, smem);
+}
+
+// fp32, K up to 64 and many tiles: 64 x 64 tile of VALU arithmetic, 16x16 threads, 4x4 outputs per
+// thread, K step 32; the next step's operands are fetched into registers while the
+// current step is computed from LDS.  A tile of the kernel above is there a single chunk
+// that is half empty, so its loads, barriers and sums cost more than its arithmetic.
+template <bool DUAL>
+__global__ __launch_bounds__(256) void ffn_f32_valu_kernel(const float* __restrict__ A,
+                                                          const float* __restrict__ B0,
+                                                          const float* __restrict__ B1,
+                                                          float* __restrict__ C, int N, int K,
+                                                          const int32_t* __restrict__ tiles) {
+  constexpr int TB = 64, TK = 32, PER = TB * TK / 256;
+  __shared__ __align__(16) float As[TK][TB + 4];
+  __shared__ __align__(16) float Bg[TK][TB + 4];
+  __shared__ __align__(16) float Bu[DUAL ? TK : 1][TB + 4];
+  const int n_ntiles = (N + TB - 1) / TB;
+  const int mtile = blockIdx.x / n_ntiles, ntile = blockIdx.x % n_ntiles;
+  if (mtile >= tiles[0]) return;
+  const int e = tiles[1 + kTileRec * mtile], row0 = tiles[2 + kTileRec * mtile],
+            row1 = tiles[3 + kTileRec * mtile];
+  const int n0 = ntile * TB;
+  const float* Be0 = B0 + size_t(e) * N * K;
+  const float* Be1 = DUAL ? B1 + size_t(e) * N * K : nullptr;
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  float g[4][4] = {}, u[4][4] = {};
+  float ra[PER], rg[PER], ru[PER];
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int idx = threadIdx.x + i * 256;
+      const int r = idx / TK, k = k0 + idx % TK;
+      int ar = row0 + r; ar = ar < row1 ? ar : row1 - 1;
+      int bn = n0 + r;   bn = bn < N ? bn : N - 1;
+      ra[i] = k < K ? A[size_t(ar) * K + k] : 0.f;
+      rg[i] = k < K ? Be0[size_t(bn) * K + k] : 0.f;
+      if (DUAL) ru[i] = k < K ? Be1[size_t(bn) * K + k] : 0.f;
+    }
+  };
+  fetch(0);
+  for (int k0 = 0; k0 < K; k0 += TK) {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int idx = threadIdx.x + i * 256;
+      const int r = idx / TK, kk = idx % TK;
+      As[kk][r] = ra[i];
+      Bg[kk][r] = rg[i];
+      if (DUAL) Bu[kk][r] = ru[i];
+    }
+    __syncthreads();
+    if (k0 + TK < K) fetch(k0 + TK);
+#pragma unroll
+    for (int kk = 0; kk < TK; ++kk) {
+      // rows of the LDS tiles are 68 floats, so groups of four stay 16-byte aligned
+      const float4 a4 = *reinterpret_cast<const float4*>(&As[kk][ty * 4]);
+      const float4 g4 = *reinterpret_cast<const float4*>(&Bg[kk][tx * 4]);
+      const float4 u4 = DUAL ? *reinterpret_cast<const float4*>(&Bu[kk][tx * 4]) : make_float4(0.f, 0.f, 0.f, 0.f);
+      const float a[4] = {a4.x, a4.y, a4.z, a4.w}, bg[4] = {g4.x, g4.y, g4.z, g4.w},
+                  bu[4] = {u4.x, u4.y, u4.z, u4.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          g[i][j] = fmaf(a[i], bg[j], g[i][j]);
+          if (DUAL) u[i][j] = fmaf(a[i], bu[j], u[i][j]);
+        }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int row = row0 + ty * 4 + i, col = n0 + tx * 4 + j;
+      if (row < row1 && col < N) {
+        float v = g[i][j];
+        if (DUAL) v = v / (1.0f + expf(-v)) * u[i][j];
+        C[size_t(row) * N + col] = v;
+      }
+    }
 }
 
 // Which kernel runs each GEMM of a call, and the height of its M tiles.
-enum GemmKind { kGemmF32, kGemmStream, kGemmTall, kGemmWide, kGemmShortK };
+enum GemmKind { kGemmF32, kGemmF32Valu, kGemmStream, kGemmTall, kGemmWide, kGemmShortK };
 struct FfnPlan {
   GemmKind g1, g2;
   int bm1, bm2;
@@ -1387,7 +1481,6 @@ struct FfnPlan {
 // picked by that bound (`avg`).  Tile counts are bounds too.
 FfnPlan plan_ffn(const moe_config& c, int n_experts, int rows_capacity) {
   const int H = c.hidden, I = c.inter_local, avg = rows_capacity / n_experts;
-  if (c.act_dtype == MOE_F32) return {kGemmF32, kGemmF32, 32, 32};
   const bool fp8 = c.weight_dtype == MOE_FP8_E4M3_B128;
   const bool ragged = ((H | I) & 63) != 0;
   const int groups = n_experts < rows_capacity ? n_experts : rows_capacity;
@@ -1395,6 +1488,15 @@ FfnPlan plan_ffn(const moe_config& c, int n_experts, int rows_capacity) {
     return long(rows_capacity / bm + groups) * ((cols + bn - 1) / bn);
   };
   FfnPlan p;
+  if (c.act_dtype == MOE_F32) {
+    // 32 x 32 tiles of fp32 matrix instructions, except a K up to 64 in launches of many of them.
+    // hidden = I = 64: GEMM-1 of 32 768 rows (2112 tiles) 24 -> 21 us, 15 / 16 at 1056; hidden 1024, I 64:
+    // GEMM-2 of 8192 rows (32 experts of 256, 9216 tiles) 39 -> 30, 2304 tiles 14.2 / 14.1.
+    p = {kGemmF32, kGemmF32, 32, 32};
+    if (H <= 64 && tiles_of(32, I, 32) > 6 * kCUs) { p.g1 = kGemmF32Valu; p.bm1 = 64; }
+    if (I <= 64 && tiles_of(32, H, 32) >= 16 * kCUs) { p.g2 = kGemmF32Valu; p.bm2 = 64; }
+    return p;
+  }
   // GEMM-1 (K = H long): the weight-streaming kernel at decode sizes, then the LDS
   // rings of the tall-tile kernel, which stream the weights faster as soon as a tile
   // holds a few rows: measured on the 128-expert layer (hidden 2048, I 768) with the
@@ -1497,6 +1599,25 @@ void launch_gemm(GemmKind kind, int bm, const uint16_t* A, const void* B0, const
              ws.tickets + (DUAL ? 0 : kSplitTickets));
 }
 
+template <bool DUAL>
+void launch_f32(GemmKind kind, int bm, const float* A, const float* B0, const float* B1, float* C, int N,
+                int K, int n_experts, int rows_capacity, const int32_t* tiles, hipStream_t s) {
+  constexpr int id = DUAL ? MOE_K_FFN_GEMM1 : MOE_K_FFN_GEMM2;
+  const int bn = kind == kGemmF32Valu ? 64 : 32;
+  const int max_mt = rows_capacity / bm + (n_experts < rows_capacity ? n_experts : rows_capacity);
+  const size_t grid = size_t(max_mt) * ((N + bn - 1) / bn);
+  if (kind == kGemmF32Valu) {
+    MOE_LAUNCH(id, ffn_f32_valu_kernel<DUAL>, dim3(grid), dim3(256), 0, s, A, B0, B1, C, N, K, tiles);
+    return;
+  }
+  auto k = ffn_f32_kernel<DUAL>;
+  static uint64_t opted = 0;
+  lds_opt_in(reinterpret_cast<const void*>(k), F32Ring<DUAL>::kLds, opted);
+  const int stages = F32Ring<DUAL>::stages(K, long(grid));
+  MOE_LAUNCH(id, k, dim3(grid), dim3(256), stages * F32Ring<DUAL>::kStageBytes, s, A, B0, B1, C, N, K, tiles,
+             stages);
+}
+
 template <bool F8>
 void launch_pair(const FfnPlan& p, const moe_config& c, int n_experts, const void* xs,
                  int rows_capacity, const void* w_gate, const void* w_up, const void* w_down,
@@ -1523,20 +1644,12 @@ hipError_t launch_expert_ffn(const moe_config& c, int n_experts, const void* xs,
   int32_t* const tiles2 = p.bm1 == p.bm2 ? ws.tiles : ws.tiles2;
   MOE_LAUNCH(MOE_K_FFN_TILES, ffn_tiles_kernel, dim3(p.bm1 == p.bm2 ? 1 : 2), dim3(256), 0, s, offsets,
              n_experts, p.bm1, rows_capacity, ws.tiles, ws.max_tiles, p.bm2, tiles2, ws.tickets);
-  if (p.g1 == kGemmF32) {
-    const int max_mt = rows_capacity / 32 + (n_experts < rows_capacity ? n_experts : rows_capacity);
-    auto k1 = ffn_f32_kernel<true>;
-    auto k2 = ffn_f32_kernel<false>;
-    static uint64_t opted1 = 0, opted2 = 0;
-    lds_opt_in(reinterpret_cast<const void*>(k1), F32Ring<true>::kLds, opted1);
-    lds_opt_in(reinterpret_cast<const void*>(k2), F32Ring<false>::kLds, opted2);
-    MOE_LAUNCH(MOE_K_FFN_GEMM1, k1, dim3(size_t(max_mt) * ((I + 31) / 32)), dim3(256),
-               F32Ring<true>::kLds, s, static_cast<const float*>(xs), static_cast<const float*>(w_gate),
-               static_cast<const float*>(w_up), static_cast<float*>(ws.hmid), I, H, ws.tiles);
-    MOE_LAUNCH(MOE_K_FFN_GEMM2, k2, dim3(size_t(max_mt) * ((H + 31) / 32)), dim3(256),
-               F32Ring<false>::kLds, s, static_cast<const float*>(ws.hmid),
-               static_cast<const float*>(w_down), (const float*)nullptr, static_cast<float*>(ys), H, I,
-               ws.tiles);
+  if (c.act_dtype == MOE_F32) {
+    float* const hmid = static_cast<float*>(ws.hmid);
+    launch_f32<true>(p.g1, p.bm1, static_cast<const float*>(xs), static_cast<const float*>(w_gate),
+                     static_cast<const float*>(w_up), hmid, I, H, n_experts, rows_capacity, ws.tiles, s);
+    launch_f32<false>(p.g2, p.bm2, hmid, static_cast<const float*>(w_down), nullptr,
+                      static_cast<float*>(ys), H, I, n_experts, rows_capacity, tiles2, s);
   } else if (c.weight_dtype == MOE_FP8_E4M3_B128) {
     launch_pair<true>(p, c, n_experts, xs, rows_capacity, w_gate, w_up, w_down, s_gate, s_up, s_down, ys,
                       tiles2, ws, s);

@@ -107,24 +107,26 @@ def test_bf16_ragged_swiglu_of_infinity(rows):
     assert bool((ys[:-1].float() == 96 * 2.0 ** 100).all()) and bool(torch.isposinf(ys[-1].float()).all())
 
 
-def _ffn(counts, H, I):
-    """moe_expert_ffn on groups of `counts` rows, and fp64 torch on the same bf16 values (the
-    intermediate rounded to bf16 as it is stored)."""
+def _ffn(counts, H, I, act="bf16"):
+    """moe_expert_ffn on groups of `counts` rows, and fp64 torch on the same stored values (a bf16
+    layer's intermediate rounded to bf16 as it is stored)."""
     import paper_2601_08800_amd as moe
     n, R = len(counts), sum(counts)
     cfg = moe.MoEConfig(hidden=H, n_experts=n, top_k=1, score_fn=moe.MOE_SCORE_SOFTMAX, renormalize=1, routed_scale=1.0,
                         n_groups=1, topk_groups=1, group_score_n=0, expert_lo=0, expert_hi=n, inter_local=I,
-                        act_dtype=moe.MOE_BF16, weight_dtype=moe.MOE_BF16)
+                        act_dtype=moe.MOE_BF16 if act == "bf16" else moe.MOE_F32,
+                        weight_dtype=moe.MOE_BF16 if act == "bf16" else moe.MOE_F32)
+    dt, bits = (torch.bfloat16, torch.int16) if act == "bf16" else (torch.float32, torch.int32)
     g = torch.Generator(device="cuda").manual_seed(R + H + I)
-    bf = lambda std, *s: torch.empty(*s, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
-    x, wg, wu, wd = bf(1.0, R, H), bf(0.05, n, I, H), bf(0.05, n, I, H), bf(0.05, n, H, I)
+    draw = lambda std, *s: torch.empty(*s, dtype=dt, device="cuda").normal_(0.0, std, generator=g)
+    x, wg, wu, wd = draw(1.0, R, H), draw(0.05, n, I, H), draw(0.05, n, I, H), draw(0.05, n, H, I)
     ends = np.cumsum([0] + list(counts))
     offsets = torch.tensor(ends, dtype=torch.int32, device="cuda")
     ws = torch.empty(moe.moe_workspace_bytes(cfg, R), dtype=torch.uint8, device="cuda")
-    ys = [torch.full((R, H), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    ys = [torch.full((R, H), float("nan"), dtype=dt, device="cuda") for _ in range(2)]
     for y in ys:
         moe.moe_expert_ffn(cfg, n, x, offsets, R, wg, wu, wd, None, None, None, y, ws)
-    assert torch.equal(ys[0].view(torch.int16), ys[1].view(torch.int16))
+    assert torch.equal(ys[0].view(bits), ys[1].view(bits))
     ref = torch.empty(R, H, dtype=torch.float64, device="cuda")
     for e in range(n):
         lo, hi = int(ends[e]), int(ends[e + 1])
@@ -132,13 +134,16 @@ def _ffn(counts, H, I):
             continue
         xe = x[lo:hi].double()
         gate, up = (xe @ w[e].double().t().contiguous() for w in (wg, wu))
-        h = (gate * torch.sigmoid(gate) * up).to(torch.bfloat16).double()
+        h = gate * torch.sigmoid(gate) * up
+        if act == "bf16":
+            h = h.to(torch.bfloat16).double()
         ref[lo:hi] = h @ wd[e].double().t().contiguous()
     err = float((ys[0].double() - ref).abs().max() / ref.abs().max())
     print("experts", n, "rows", R, "H", H, "I", I, "err %.3e" % err, flush=True)
-    # the output's rounding (2^-9), and intermediates that fall to the other side of a
-    # rounding (2^-8 of one of I terms each): well inside the layer's bar
-    assert err <= TOL["bf16"]
+    # bf16: the output's rounding (2^-9), and intermediates that fall to the other side of a
+    # rounding (2^-8 of one of I terms each); fp32: sums of at most H products, sqrt(H) * 2^-24 of
+    # the largest value in the mean.  Both well inside the layer's bar.
+    assert err <= TOL[act]
 
 
 def _counts(n, lo, hi):
@@ -170,3 +175,14 @@ def test_bf16_ragged_rules(counts, H, I):
     ids=lambda v: str(v) if isinstance(v, int) else "%dx%d" % (len(v), sum(v)))
 def test_bf16_k128_rules(counts, H, I):
     _ffn(counts, H, I)
+
+
+# fp32 past one tile per CU: one ring stage per workgroup for K of one, three and five chunks, the
+# last one partly filled; and K up to 64 on the 64 x 64 tiles, GEMM-1 (1900 tiles) and GEMM-2
+# (6400), with row, column and K remainders.
+@pytest.mark.parametrize("counts,H,I", [
+    (_counts(9, 60, 200), 520, 328), (_counts(30, 1, 90), 72, 264), (_counts(36, 400, 1300), 56, 40),
+    (_counts(64, 1, 130), 1000, 24)],
+    ids=lambda v: str(v) if isinstance(v, int) else "%dx%d" % (len(v), sum(v)))
+def test_fp32_many_tiles(counts, H, I):
+    _ffn(counts, H, I, "f32")
