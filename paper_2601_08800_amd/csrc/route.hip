@@ -13,8 +13,8 @@
 //   3. re-score    one workgroup per listed token: the experts whose key
 //                  interval reaches the selection get an fp64 dot product and
 //                  the selection is redone in fp64
-// Short batches (and fp32 rows) skip all three: every logit is computed in fp64 on the
-// fp64 matrix instructions and the selection works on fp64 keys.
+// Short batches (and fp32 rows) skip all three: every logit is computed in fp64, on the
+// vector unit or the fp64 matrix instructions, and the selection works on fp64 keys.
 // Error model of stage 1 for a chain of n bf16 products (exact in fp32) added
 // in fp32: every addition is off by at most one ulp of the running sum, so
 // |error| <= 2n * 2^-24 * sum|x_h w_h| <= 2n * 2^-24 * |x|_2 |w|_2.
@@ -1033,15 +1033,14 @@ __global__ __launch_bounds__(256, EPL <= 1 ? 3 : 2) void route_recheck_kernel(
   }
 }
 
-// ------------- a small fp32 layer: gate, scores and top-k of a token in one pass
+// ------------- few tokens, small gate: gate, scores and top-k of a token in one pass
 // One workgroup of sixteen wavefronts per token.  The wavefronts share out the experts and
 // compute every logit exactly (fp64 sums of exact products, CB experts per walk
 // over the token row); the first wavefront then builds fp64 keys for all experts
 // and takes the group limit, the top-k and the weights in fp64.  One launch less than
-// the matrix form below, which is what counts while there is at most one workgroup per
-// CU (8 experts, hidden 256, 64 tokens: 8.4 against 10.5 us; 128 experts, hidden 2048:
-// 14.8 against 13.7 us).
-template <int EPL, int FORM>
+// the forms below, which is what counts while there is at most one workgroup per CU and a
+// wavefront walks few gate rows (the rule and what it measured: exact_form).
+template <int EPL, int FORM, bool BF16>
 __global__ __launch_bounds__(1024) void route_exact_kernel(
     SelCfg c, int H, const void* __restrict__ x, const void* __restrict__ gate_w,
     const float* __restrict__ logit_bias, const float* __restrict__ select_bias,
@@ -1050,8 +1049,9 @@ __global__ __launch_bounds__(1024) void route_exact_kernel(
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int t = blockIdx.x;
   if (t == 0 && threadIdx.x < 64) counters[threadIdx.x] = 0;   // nothing is re-scored
-  const char* xrow = static_cast<const char*>(x) + size_t(t) * H * 4;
-  const int n16 = H / 4;
+  const size_t row_bytes = size_t(H) * (BF16 ? 2 : 4);
+  const char* xrow = static_cast<const char*>(x) + size_t(t) * row_bytes;
+  const int n16 = int(row_bytes / 16);
   const int per = (c.E + 15) / 16;
   const int e_begin = min(c.E, wave * per), e_end = min(c.E, e_begin + per);
   constexpr int CB = 4, U = 4;   // experts per walk, pieces per lane and row in flight (8: spills)
@@ -1061,7 +1061,7 @@ __global__ __launch_bounds__(1024) void route_exact_kernel(
 #pragma unroll
     for (int i = 0; i < CB; ++i) {
       acc[i] = 0.0;
-      wrow[i] = static_cast<const char*>(gate_w) + size_t(min(e0 + i, e_end - 1)) * H * 4;
+      wrow[i] = static_cast<const char*>(gate_w) + size_t(min(e0 + i, e_end - 1)) * row_bytes;
     }
     for (int p0 = 0; p0 < n16; p0 += 64 * U) {
       uint4 a[U], b[CB][U];
@@ -1079,7 +1079,7 @@ __global__ __launch_bounds__(1024) void route_exact_kernel(
       for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int i = 0; i < CB; ++i) {
-          const double d = piece_dot64<false>(a[u], b[i][u], 0.0);
+          const double d = piece_dot64<BF16>(a[u], b[i][u], 0.0);
           acc[i] += in[u] ? d : 0.0;
         }
     }
@@ -1126,7 +1126,62 @@ __global__ __launch_bounds__(1024) void route_exact_kernel(
   }
 }
 
-// ------------- few tokens: exact logits on fp64 matrix instructions, then selection
+// ------------- few tokens, long gate rows: exact logits on the vector unit, then selection
+// A workgroup of four wavefronts takes sixteen experts of one token (a wavefront: four gate
+// rows, eight 16-byte pieces per lane and row in flight), so a token is shared out over
+// E/16 workgroups and no wavefront walks more than four rows.  The 16 x 16 tile of the matrix
+// form below does sixteen tokens' work for one, on one CU.
+template <bool BF16>
+__global__ __launch_bounds__(256) void gate_exact_rows_kernel(
+    int H, int E, const void* __restrict__ x, const void* __restrict__ gate_w,
+    const float* __restrict__ logit_bias, double* __restrict__ zx, int32_t* __restrict__ counters) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int t = blockIdx.y;
+  if (blockIdx.x == 0 && t == 0 && threadIdx.x < 64) counters[threadIdx.x] = 0;   // nothing is re-scored
+  constexpr int CB = 4, U = 8;
+  const int e0 = (blockIdx.x * 4 + wave) * CB;
+  if (e0 >= E) return;
+  const size_t row_bytes = size_t(H) * (BF16 ? 2 : 4);
+  const char* xrow = static_cast<const char*>(x) + size_t(t) * row_bytes;
+  const int n16 = int(row_bytes / 16);
+  double acc[CB];
+  const char* wrow[CB];
+#pragma unroll
+  for (int i = 0; i < CB; ++i) {
+    acc[i] = 0.0;
+    wrow[i] = static_cast<const char*>(gate_w) + size_t(min(e0 + i, E - 1)) * row_bytes;
+  }
+  for (int p0 = 0; p0 < n16; p0 += 64 * U) {
+    uint4 a[U], b[CB][U];
+    bool in[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      int p = p0 + u * 64 + lane;
+      in[u] = p < n16;
+      p = in[u] ? p : n16 - 1;
+      a[u] = *reinterpret_cast<const uint4*>(xrow + size_t(p) * 16);
+#pragma unroll
+      for (int i = 0; i < CB; ++i) b[i][u] = *reinterpret_cast<const uint4*>(wrow[i] + size_t(p) * 16);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < CB; ++i) {
+        const double d = piece_dot64<BF16>(a[u], b[i][u], 0.0);
+        acc[i] += in[u] ? d : 0.0;
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < CB; ++i) {
+    double z = wave_sum(acc[i]);
+    if (e0 + i < E && lane == 0) {
+      if (logit_bias) z += (double)logit_bias[e0 + i];
+      zx[size_t(t) * E + e0 + i] = z;
+    }
+  }
+}
+
+// ------------- exact logits on fp64 matrix instructions, then selection
 // A workgroup of sixteen wavefronts computes 16 tokens x 16 experts with
 // v_mfma_f64_16x16x4_f64 (exact products, fp64 sums): the wavefronts share out K and
 // their sums are added in a fixed order.  Per instruction (1024 multiply-adds) a lane
@@ -1234,32 +1289,63 @@ __global__ __launch_bounds__(256) void select_exact_kernel(
   }
 }
 
+// Which kernels compute exact logits.
+enum ExactForm { kExactOneLaunch, kExactRows, kExactTiles };
 // 16 x 16 tiles of the exact gate: workgroups of gate_exact_kernel
 inline long exact_tiles(int T, int E) { return long((T + 15) / 16) * ((E + 15) / 16); }
 
-template <int EPL, int FORM>
-void launch_route_exact2(const SelCfg& sc, const moe_config& c, int T, const void* x,
-                         const void* gate_w, const float* logit_bias, const float* select_bias,
-                         int32_t* ids, float* w, const RouteWs& ws, hipStream_t s) {
+// The form whose gate takes the least, from estimates in us that follow 1296 measured sizes (1 to
+// 4096 tokens, 4 to 512 experts, hidden 256 to 7168, both types; the picked form is within 1 % of
+// the best one in the mean, 16 % at worst).  Against the second launch that they save or pay:
+//   one launch  a round of 256 pieces per wavefront that has experts, on a CU per token
+//   rows        a round of 512 pieces per wavefront; past one workgroup per CU the workgroups'
+//               starts and their wavefronts' rounds add up
+//   tiles       one CU's fp64 matrix rate over the row, 256 tiles at a time
+// e.g. bf16, one launch / rows / tiles: 8 experts, hidden 2048, 64 tokens 6.9 / 8.9 / 11.5; 128 experts,
+// hidden 7168, 16 tokens 39 / 15 / 27; 64 experts, hidden 1024, 256 tokens 10.7 / 18.8 / 9.7.
+ExactForm exact_form(bool bf16, int T, int E, int H) {
+  const int pieces = H / (bf16 ? 8 : 4), per = (E + 15) / 16;
+  const float wgs = float(T) * per / 256, tiles = exact_tiles(T, E) / 256.f;
+  const int r256 = (pieces + 255) / 256, r512 = (pieces + 511) / 512;
+  const float waves = float((E + 3) / 4) / (4 * per);      // of the rows form's workgroups, with experts
+  const float one = (bf16 ? -1.f : -1.7f) + (bf16 ? .29f : .165f) * ((E + per - 1) / per) * r256;
+  const float rows_one = bf16 ? 3.1f + (pieces > 256 ? .3f : 0.f) + 3.3f * (r512 - 1) : 1.f + 1.65f * (r512 - 1);
+  const float rows_all = wgs * (bf16 ? .6f + 2.5f * waves * r512 : .3f + 1.6f * waves * r512);
+  const float rows = rows_one > rows_all ? rows_one : rows_all;
+  const float tile = (bf16 ? 2.75e-3f * H + .2f : 3.6e-3f * H + .4f) * (tiles > 1 ? tiles : 1.f);
+  if (T <= 256 && E <= 64 && one <= rows && one <= tile) return kExactOneLaunch;
+  return rows <= tile ? kExactRows : kExactTiles;
+}
+
+template <int EPL, int FORM, bool BF16>
+void launch_route_exact(ExactForm form, const SelCfg& sc, const moe_config& c, int T, const void* x,
+                        const void* gate_w, const float* logit_bias, const float* select_bias,
+                        int32_t* ids, float* w, const RouteWs& ws, hipStream_t s) {
+  const int E = c.n_experts;
+  if constexpr (EPL == 1) {
+    if (form == kExactOneLaunch) {
+      // (bf16: the general instance; the soft-max one spills at sixteen wavefronts, 7.4 against 6.5 us)
+      MOE_LAUNCH(MOE_K_GATE_GEMM, (route_exact_kernel<1, BF16 ? int(kGateAny) : FORM, BF16>), dim3(T), dim3(1024), 0,
+                 s, sc, c.hidden, x, gate_w, logit_bias, select_bias, ids, w, ws.counters);
+      return;
+    }
+  }
   // the logits area holds at least two floats per (token, expert): room for one double
   double* zx = reinterpret_cast<double*>(ws.logits);
-  const dim3 grid(unsigned(exact_tiles(T, c.n_experts)));
-  if (c.act_dtype == MOE_BF16)
-    MOE_LAUNCH(MOE_K_GATE_GEMM, gate_exact_kernel<true>, grid, dim3(1024), 0, s, T, c.hidden, c.n_experts,
-               x, gate_w, logit_bias, zx, ws.counters);
+  if (form == kExactRows)
+    MOE_LAUNCH(MOE_K_GATE_GEMM, gate_exact_rows_kernel<BF16>, dim3((E + 15) / 16, T), dim3(256), 0, s, c.hidden,
+               E, x, gate_w, logit_bias, zx, ws.counters);
   else
-    MOE_LAUNCH(MOE_K_GATE_GEMM, gate_exact_kernel<false>, grid, dim3(1024), 0, s, T, c.hidden, c.n_experts,
-               x, gate_w, logit_bias, zx, ws.counters);
+    MOE_LAUNCH(MOE_K_GATE_GEMM, gate_exact_kernel<BF16>, dim3(unsigned(exact_tiles(T, E))), dim3(1024), 0, s, T,
+               c.hidden, E, x, gate_w, logit_bias, zx, ws.counters);
   MOE_LAUNCH(MOE_K_SELECT, (select_exact_kernel<EPL, FORM>), dim3((T + 3) / 4), dim3(256), 0, s, sc, T, zx,
              select_bias, ids, w);
 }
 
-template <int EPL, int FORM>
-void launch_route_exact(const SelCfg& sc, const moe_config& c, int T, const void* x,
-                        const void* gate_w, const float* logit_bias, const float* select_bias,
-                        int32_t* ids, float* w, const RouteWs& ws, hipStream_t s) {
-  MOE_LAUNCH(MOE_K_GATE_GEMM, (route_exact_kernel<EPL, FORM>), dim3(T), dim3(1024), 0, s, sc, c.hidden, x,
-             gate_w, logit_bias, select_bias, ids, w, ws.counters);
+template <int EPL, int FORM, typename... A>
+void launch_route_exact_of(bool bf16, A&&... a) {
+  if (bf16) launch_route_exact<EPL, FORM, true>(a...);
+  else launch_route_exact<EPL, FORM, false>(a...);
 }
 
 template <int EPL, int FORM>
@@ -1310,7 +1396,6 @@ hipError_t launch_route(const moe_config& c, int T, const void* x, const void* g
   const bool fp64_band = T <= 4096 && (teh <= size_t(5) << 25 ||
                                        (size_t(E) * H > size_t(1) << 19 && teh <= size_t(1) << 28));
   const bool exact = !bf16 || fp64_band || (tiles <= 1024 && size_t(tiles) * H <= limit);
-  const bool small_f32 = !bf16 && T <= 256 && size_t(E) * H <= (size_t(1) << 17);
   // experts per lane and form of the gate -> one instance of the selection kernels
 #define MOE_BY_FORM(F, EPL, ...)                                                      \
   switch (gate_form<EPL>(sc)) {                                                            \
@@ -1325,12 +1410,9 @@ hipError_t launch_route(const moe_config& c, int T, const void* x, const void* g
     else if (epl <= 4) { MOE_BY_FORM(F, 4, __VA_ARGS__) }                             \
     else { MOE_BY_FORM(F, 8, __VA_ARGS__) }                                           \
   } while (0)
-  if (!logits_in && exact && !small_f32) {
-    MOE_BY_GATE(launch_route_exact2, sc, c, T, x, gate_w, logit_bias, select_bias, ids, w, ws, s);
-    return hipGetLastError();
-  }
-  if (!logits_in && small_f32) {
-    MOE_BY_GATE(launch_route_exact, sc, c, T, x, gate_w, logit_bias, select_bias, ids, w, ws, s);
+  if (!logits_in && exact) {
+    const ExactForm form = exact_form(bf16, T, E, H);
+    MOE_BY_GATE(launch_route_exact_of, bf16, form, sc, c, T, x, gate_w, logit_bias, select_bias, ids, w, ws, s);
     return hipGetLastError();
   }
   if (logits_in) {

@@ -14,15 +14,19 @@ pytestmark = pytest.mark.gpu
 NO_WEIGHTS = {"w_gate": None, "w_up": None, "w_down": None}
 
 
-# tokens and experts one below, at and one above a tile; rows of one piece, of a partial
-# group of pieces, and of more groups than a workgroup has wavefronts; fp32 layers on
-# either side of the one-launch route (256 tokens, E*H = 2^17); grouped gates
+# The exact gate in its three forms (one launch: up to 256 tokens and 64 experts; rows: few tokens
+# or long gate rows; tiles: the rest).  Tokens and experts one below, at and one above a tile; rows
+# of one piece, of a partial group of pieces, of a second round of 256 and 512 pieces, and of more
+# groups than a workgroup has wavefronts; grouped gates in every form.
 @pytest.mark.parametrize("act,T,E,H,k,G", [
     ("bf16", 1, 1, 8, 1, 1), ("bf16", 15, 17, 40, 3, 1), ("bf16", 16, 16, 264, 16, 1),
     ("bf16", 17, 33, 2056, 5, 1), ("bf16", 333, 128, 520, 8, 1), ("bf16", 500, 512, 72, 32, 1),
     ("bf16", 49, 64, 1024, 6, 8), ("bf16", 50, 48, 136, 5, 4), ("bf16", 21, 256, 4104, 8, 8),
+    ("bf16", 256, 8, 1032, 2, 1), ("bf16", 257, 8, 1032, 2, 1), ("bf16", 200, 64, 2056, 6, 8),
+    ("bf16", 140, 64, 2048, 6, 1), ("bf16", 3, 128, 7176, 8, 1), ("bf16", 2, 130, 4104, 6, 1),
     ("f32", 256, 8, 264, 2, 1), ("f32", 257, 8, 264, 2, 1), ("f32", 31, 130, 1032, 8, 1),
-    ("f32", 5000, 16, 8, 3, 1), ("f32", 65, 96, 2048, 4, 6)])
+    ("f32", 5000, 16, 8, 3, 1), ("f32", 65, 96, 2048, 4, 6), ("f32", 7, 61, 2056, 4, 1),
+    ("f32", 130, 64, 1024, 4, 8), ("f32", 400, 3, 2056, 1, 1)])
 def test_exact_route_tiles(act, T, E, H, k, G):
     base = gen.CONFIGS["c4" if G > 1 else "c1"]
     w = base.replace(name="exact_tiles", T=T, E=E, H=H, k=k, I=8, act_dtype=act, weight_dtype=act, tp=1,
