@@ -487,24 +487,60 @@ template <int EPL> inline GateForm gate_form(const SelCfg& c) {
   return kGateAny;
 }
 
-// Sum of element p of `ns` (1..kGateMaxSplit) slabs `stride` apart, in slab order.  The
-// loads do not wait for one another: a slab loop that adds as it goes is one memory
-// latency per slab, and a wavefront has EPL of them for the logits and as many for the
-// gate norms.  The slabs past the last are read again from the first and left out.
+// Sum of element p of `ns` (1, 2 or 4) slabs `stride` apart, in slab order.  The loads do not
+// wait for one another: a slab loop that adds as it goes is one memory latency per slab.
 __device__ __forceinline__ float slab_sum(const float* __restrict__ p, size_t stride, int ns) {
-  float v[kGateMaxSplit];
+  if (ns == 1) return p[0];
+  const float a = p[0], b = p[stride];
+  if (ns == 2) return a + b;
+  const float c = p[2 * stride], d = p[3 * stride];
+  return ((a + b) + c) + d;
+}
+
+// The lane's EPL neighbouring elements of p[0, n), zeros past the end; whole 16-byte pieces
+// where the rows keep their alignment (512 experts: two loads a lane and not eight, each of
+// which would touch 16 times the lines it needs).
+template <int EPL>
+__device__ __forceinline__ void load_run(const float* __restrict__ p, int n, int lane, float (&v)[EPL]) {
+  if (EPL % 4 == 0 && n % 4 == 0) {
 #pragma unroll
-  for (int i = 0; i < kGateMaxSplit; ++i) v[i] = p[i < ns ? i * stride : 0];
-  float s = v[0];
+    for (int i = 0; i < EPL; i += 4) {
+      const int e = lane * EPL + i;
+      const float4 q = e < n ? *reinterpret_cast<const float4*>(p + e) : make_float4(0.f, 0.f, 0.f, 0.f);
+      v[i] = q.x;
+      if (i + 1 < EPL) v[i + 1] = q.y;
+      if (i + 2 < EPL) v[i + 2] = q.z;
+      if (i + 3 < EPL) v[i + 3] = q.w;
+    }
+  } else {
 #pragma unroll
-  for (int i = 1; i < kGateMaxSplit; ++i) s = i < ns ? s + v[i] : s;
-  return s;
+    for (int i = 0; i < EPL; ++i) v[i] = lane * EPL + i < n ? p[lane * EPL + i] : 0.f;
+  }
+}
+// The same of the slabs' sum, all loads first.
+template <int EPL>
+__device__ __forceinline__ void load_slabs(const float* __restrict__ p, int n, size_t stride, int ns, int lane,
+                                           float (&v)[EPL]) {
+  load_run<EPL>(p, n, lane, v);
+  if (ns == 1) return;
+  float b[EPL];
+  load_run<EPL>(p + stride, n, lane, b);
+  if (ns == 2) {
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) v[i] += b[i];
+    return;
+  }
+  float c[EPL], d[EPL];
+  load_run<EPL>(p + 2 * stride, n, lane, c);
+  load_run<EPL>(p + 3 * stride, n, lane, d);
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) v[i] = ((v[i] + b[i]) + c[i]) + d[i];
 }
 
 // Norm of token t's row from the per-split sums of squares.
 __device__ __forceinline__ float token_norm(const SelCfg& c, const float* __restrict__ xnorm2, int t) {
   if (!c.have_norms) return 0.f;
-  return sqrtf(c.nsplit == 1 ? xnorm2[t] : slab_sum(xnorm2 + t, c.T, c.nsplit));
+  return sqrtf(slab_sum(xnorm2 + t, c.T, c.nsplit));
 }
 
 // Fast key of one expert from its stage-1 logit z (the slabs already added up):
@@ -567,24 +603,12 @@ __device__ __forceinline__ void fast_keys(const SelCfg& c, const float* __restri
                                           const float* __restrict__ wnorm2, int lane,
                                           Keys<float, EPL>& K) {
   float z[EPL], wn2[EPL];
+  load_slabs<EPL>(logits_row, c.E, size_t(c.T) * c.E, c.nsplit, lane, z);
+  if (c.have_norms) {
+    load_slabs<EPL>(wnorm2, c.E, c.E, c.nsplit, lane, wn2);
+  } else {
 #pragma unroll
-  for (int i = 0; i < EPL; ++i) { z[i] = 0.f; wn2[i] = 0.f; }
-  if (c.nsplit == 1) {
-#pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-      const int e = lane * EPL + i;
-      if (e < c.E) {
-        z[i] = logits_row[e];
-        if (c.have_norms) wn2[i] = wnorm2[e];
-      }
-    }
-  } else {                                     // only the gate GEMM's slabs: norms are there too
-#pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-      const int e = min(lane * EPL + i, c.E - 1);
-      z[i] = slab_sum(logits_row + e, size_t(c.T) * c.E, c.nsplit);
-      wn2[i] = slab_sum(wnorm2 + e, c.E, c.nsplit);
-    }
+    for (int i = 0; i < EPL; ++i) wn2[i] = 0.f;
   }
 #pragma unroll
   for (int i = 0; i < EPL; ++i) {
