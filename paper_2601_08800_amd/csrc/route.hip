@@ -877,10 +877,11 @@ __global__ __launch_bounds__(256, EPL <= 1 ? 3 : 2) void route_recheck_kernel(
   double* const zx = zx_all[wave];
   float2* const rint = rint_all[wave];
   const int n_list = counters[0];
-  // a workgroup per token, up to three quarters of the grid: past that the list takes more
-  // rounds of workgroups than it gains (256 experts, 10 000 tokens, about 980 listed, beside a
-  // shared expert: step 1236 us, with a wavefront per token 1195 us)
-  const bool coop = n_list * 4 <= int(gridDim.x) * 3;
+  // a workgroup per token while all of them run at once, two per CU; past that a wavefront per
+  // token.  Listed tokens, us with a wavefront / a workgroup each: 128 experts, hidden 2048, 430: 15.3 /
+  // 13.8, 256 grouped experts, hidden 7168, 477: 41 / 32, but 128 grouped experts, 680: 21 / 28, 512
+  // experts, 520: 26 / 35, 96 experts in six groups, 739: 34 / 50.
+  const bool coop = n_list <= 512;
   const int team = coop ? 256 : 64, me = coop ? tid : lane;
   const int n16 = H / 8;                         // pieces of a bf16 row (fp32 rows have exact logits to begin with)
 
