@@ -1402,16 +1402,16 @@ hipError_t launch_route(const moe_config& c, int T, const void* x, const void* g
   sc.G = c.n_groups; sc.Kg = c.topk_groups; sc.gn = c.group_score_n; sc.scale = c.routed_scale;
   sc.chain_err = 0.f; sc.have_norms = 0; sc.nsplit = 1; sc.T = T;
   const int epl = (E + 63) / 64;
-  // The exact gate (fp64 matrix instructions, two launches) against the bf16 pipeline of
-  // three: it costs about 8 us + 6.5 us for every 256 tiles at hidden 2048, the pipeline
-  // 24-33 us for up to 128 experts.  Measured us, exact / pipeline: 128 experts, hidden 2048,
-  // 64 tokens 14 / -, 1024 tokens 21 / 26, 1536 tokens 29 / 27; hidden 4096, 512 tokens 21 / 30,
-  // 768 tokens 34 / 33; hidden 1024, 2048 tokens 24 / 26; hidden 512, 4096 tokens 29 / 24 (the
-  // selection on fp64 keys costs more per token: hence the limit on tiles).  The grouped
-  // gate of 256 experts, hidden 7168, has the longer pipeline: 256 tokens 36 / 62, 512 tokens 57 /
-  // 64, 768 tokens 78 / 66.  fp32 rows have no other gate.
-  const long tiles = exact_tiles(T, E);
-  const size_t limit = size_t(1) << (c.n_groups > 1 ? 22 : 20);
+  // The exact gate against the bf16 pipeline of three launches, from what they take in whole
+  // rounds of 256 tiles.  bf16, exact / pipeline in us: 128 experts, hidden 2048, 1024 tokens 21 / 26, 1536
+  // tokens 29 / 27; hidden 4096, 512 tokens 21 / 30, 768 tokens 34 / 33; hidden 512, 4096 tokens 29 / 24 (the
+  // selection on fp64 keys costs more per token: hence the limit on tiles).  A gate with groups
+  // has the longer selection and re-scoring: 256 experts, hidden 7168, 288 and 400 tokens 53 / 54, 576
+  // tokens (three rounds) 75 / 55; 128 experts, hidden 4096, 2048 tokens 60 / 39; 64 experts, hidden 2048, 4096
+  // tokens 37 / 31.  fp32 rows have no other gate.
+  const long tiles = exact_tiles(T, E), rounds = (tiles + 255) / 256;
+  const bool few = tiles <= 1024 && (c.n_groups > 1 ? rounds * 256 * H < (E > 128 ? 1L << 22 : 1L << 21)
+                                                    : tiles * H <= 1L << 20);
   // Up to 4096 tokens bf16 batches of T*E*H <= 5 * 2^25 (2^28 where a token's gate is long,
   // E*H > 2^19) have exact logits whatever that costs: their weights are fp64 arithmetic
   // rounded once, where the pipeline's are fp32 exponentials of fp32 logits.  This adds to the
@@ -1420,7 +1420,7 @@ hipError_t launch_route(const moe_config& c, int T, const void* x, const void* g
   const size_t teh = size_t(T) * E * H;
   const bool fp64_band = T <= 4096 && (teh <= size_t(5) << 25 ||
                                        (size_t(E) * H > size_t(1) << 19 && teh <= size_t(1) << 28));
-  const bool exact = !bf16 || fp64_band || (tiles <= 1024 && size_t(tiles) * H <= limit);
+  const bool exact = !bf16 || fp64_band || few;
   // experts per lane and form of the gate -> one instance of the selection kernels
 #define MOE_BY_FORM(F, EPL, ...)                                                      \
   switch (gate_form<EPL>(sc)) {                                                            \

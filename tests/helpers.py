@@ -21,6 +21,20 @@ def inputs(w):
     return d
 
 
+def takes_exact_gate(w):
+    """The router's rule: fp64 logits for every token, instead of the bf16 gate GEMM with its
+    interval test and re-scoring."""
+    if w.act_dtype == "f32":
+        return True
+    teh = w.T * w.E * w.H
+    if w.T <= 4096 and (teh <= 5 << 25 or (w.E * w.H > 1 << 19 and teh <= 1 << 28)):
+        return True
+    tiles = -(-w.T // 16) * -(-w.E // 16)
+    if w.n_groups > 1:
+        return tiles <= 1024 and -(-tiles // 256) * 256 * w.H < (1 << 22 if w.E > 128 else 1 << 21)
+    return tiles <= 1024 and tiles * w.H <= 1 << 20
+
+
 def oracle_route(w, x, gate, logits_in=None):
     return oracle.route(x, gate["gate_w"], w.k, w.score_fn, w.renormalize, w.routed_scale,
                         w.n_groups, w.topk_groups, w.group_score_n, gate["logit_bias"],

@@ -7,7 +7,7 @@ import torch
 import oracle
 from workloads import gen
 from helpers import (TOL, check_dispatch, check_routing, dev, host, inputs, make_layer,
-                     oracle_out_for_tokens, oracle_route, rel_err)
+                     oracle_out_for_tokens, oracle_route, rel_err, takes_exact_gate)
 
 pytestmark = pytest.mark.gpu
 
@@ -84,7 +84,8 @@ def test_layer_share_matches_oracle(name):
 
 
 def test_route_recheck_counter_and_determinism():
-    w = SMALL["qwen_small"]
+    w = gen.CONFIGS["c2p"].replace(name="recheck_counter", T=4200, H=512, I=64, expert_lo=0, expert_hi=4)
+    assert not takes_exact_gate(w)
     d = inputs(w)
     L = make_layer(w, d)
     x = dev(d["x"])
@@ -94,15 +95,14 @@ def test_route_recheck_counter_and_determinism():
     a = (host(L.topk_ids).copy(), host(L.topk_w).copy())
     L.route(x)
     torch.cuda.synchronize()
-    assert int(L.ws[:4].view(torch.int32).item()) == n1 and 0 <= n1 <= w.T
+    assert int(L.ws[:4].view(torch.int32).item()) == n1 and 0 < n1 <= w.T
     assert np.array_equal(a[0], host(L.topk_ids)) and np.array_equal(a[1], host(L.topk_w))
 
 
-# Token counts past the decode-size threshold of the router (T*E*H > 2^28, or more
-# than 4096 tokens), so the
-# tiled bf16 gate GEMM, the interval test and the fp64 re-scoring run, at sizes
-# the oracle still scores in seconds: ragged T / E / H tails, with and without a
-# split K range, soft-max with a logit bias and sigmoid with a group limit.
+# Past the router's exact gate (helpers.takes_exact_gate), so the tiled bf16 gate GEMM, the
+# interval test and the fp64 re-scoring run, at sizes the oracle still scores in seconds:
+# ragged T / E / H tails, with and without a split K range, soft-max with a logit bias and
+# sigmoid with a group limit, one to eight experts a lane.
 TILED_GATE = {
     "softmax_ragged_splitk": gen.CONFIGS["c2p"].replace(name="softmax_ragged_splitk", T=1237, H=1096,
                                                         E=200, k=6, I=64),
@@ -111,32 +111,36 @@ TILED_GATE = {
     # many token tiles, ragged T and E, one K slab
     "tall_tile_ragged": gen.CONFIGS["c2p"].replace(name="tall_tile_ragged", T=8300, H=512, E=72, k=4,
                                                    I=64),
-    # fp32 activations past the one-kernel route: fp64 VALU gate, then select / re-score
-    "f32_many_tokens": gen.CONFIGS["c1"].replace(name="f32_many_tokens", T=4200, H=256, E=16, k=2,
-                                                 I=64),
     "sigmoid_groups_splitk": gen.CONFIGS["c4"].replace(name="sigmoid_groups_splitk", T=2100, H=1024,
                                                        E=192, k=6, I=128, n_groups=6, topk_groups=3,
                                                        expert_lo=0, expert_hi=8),
-}
-
-
-# The same pipeline at up to 1024 tokens, where the re-scoring kernel gives a listed
-# token a whole workgroup (its wavefronts share each dot product).
-TILED_GATE.update({
-    "short_list_softmax": gen.CONFIGS["c2p"].replace(name="short_list_softmax", T=777, I=64),
+    # aligned groups at one and two experts a lane, groups under soft-max, 512 experts
+    "sigmoid_groups_64": gen.CONFIGS["c4"].replace(name="sigmoid_groups_64", T=4200, H=2048, E=64, k=6, I=128,
+                                                   expert_lo=0, expert_hi=8, shared_expert=False),
+    "sigmoid_groups_128": gen.CONFIGS["c4"].replace(name="sigmoid_groups_128", T=2049, H=2048, E=128, k=8, I=128,
+                                                    n_groups=4, topk_groups=2, expert_lo=0, expert_hi=8,
+                                                    shared_expert=False),
+    "softmax_groups": gen.CONFIGS["c3"].replace(name="softmax_groups", T=2100, H=2048, E=128, k=8, I=64, n_groups=8,
+                                                topk_groups=4, group_score_n=2, expert_lo=0, expert_hi=4),
+    "softmax_512": gen.CONFIGS["c3"].replace(name="softmax_512", T=1100, H=1032, E=512, k=8, I=64, expert_lo=0,
+                                             expert_hi=4),
+    "sigmoid_510": gen.CONFIGS["c4"].replace(name="sigmoid_510", T=1100, H=1024, E=510, k=8, I=128, n_groups=1,
+                                             topk_groups=1, group_score_n=0, expert_lo=0, expert_hi=4,
+                                             shared_expert=False),
+    # about a thousand tokens and fewer: short lists, a workgroup per listed token
+    "short_list_softmax": gen.CONFIGS["c2p"].replace(name="short_list_softmax", T=777, H=4096, I=64,
+                                                     expert_lo=0, expert_hi=4),
     "short_list_softmax_1024": gen.CONFIGS["c3"].replace(name="short_list_softmax_1024", T=1024, I=64,
                                                          expert_lo=0, expert_hi=4),
-    "short_list_sigmoid_groups": gen.CONFIGS["c4"].replace(name="short_list_sigmoid_groups", T=301,
-                                                           I=128, shared_expert=False),
-    "short_list_f32": gen.CONFIGS["c1"].replace(name="short_list_f32", T=1000, H=2048, E=160, k=4,
-                                                I=64),
-})
+    "short_list_sigmoid_groups": gen.CONFIGS["c4"].replace(name="short_list_sigmoid_groups", T=600,
+                                                           I=128, expert_lo=0, expert_hi=4, shared_expert=False),
+}
 
 
 @pytest.mark.parametrize("name", list(TILED_GATE))
 def test_route_tiled_gate_matches_oracle(name):
     w = TILED_GATE[name]
-    assert w.T * w.E * w.H > 2 ** 28 or w.T > 4096 or (w.act_dtype == "bf16" and w.T * w.E * w.H > 5 * 2 ** 25)
+    assert not takes_exact_gate(w)
     print("case", name, flush=True)
     d = inputs(w)
     L = make_layer(w, d)
@@ -147,13 +151,14 @@ def test_route_tiled_gate_matches_oracle(name):
     n_amb = check_routing(host(L.topk_ids), host(L.topk_w), ids_ref, w_ref, margin,
                           w.routed_scale, name)
     print("re-scored", n_re, "of", w.T, "; fp64-ambiguous", n_amb, flush=True)
-    assert 0 <= n_re <= w.T
+    assert 0 < n_re <= w.T
 
 
 # Few tokens, long gate rows (E*H > 2^19): exact logits and selection run as two
-# kernels, a token's experts shared out over several workgroups.  Group-limited
-# sigmoid at the C4 gate shape, soft-max with 512 and with an odd number of
-# experts, fp32 inputs; one token, and token counts that are no multiple of four.
+# kernels, a token's experts shared out over several workgroups or 16 x 16 tiles of fp64 matrix
+# instructions.  Group-limited sigmoid at the C4 gate shape, soft-max with 512 and with an odd
+# number of experts, fp32 inputs (also past every limit of the bf16 rule); one token, and token
+# counts that are no multiple of four.
 LONG_ROWS = {
     "c4_gate_1_token": gen.CONFIGS["c4"].replace(name="c4_gate_1_token", T=1, I=128, shared_expert=False),
     "c4_gate_67_tokens": gen.CONFIGS["c4"].replace(name="c4_gate_67_tokens", T=67, I=128,
@@ -163,13 +168,19 @@ LONG_ROWS = {
     "softmax_130_experts": gen.CONFIGS["c3"].replace(name="softmax_130_experts", T=5, E=130, H=8192,
                                                      I=64, expert_lo=0, expert_hi=8),
     "f32_72_experts": gen.CONFIGS["c1"].replace(name="f32_72_experts", T=130, E=72, H=8192, I=64, k=4),
+    "f32_many_tokens": gen.CONFIGS["c1"].replace(name="f32_many_tokens", T=4200, H=256, E=16, k=2, I=64),
+    "f32_1000_tokens": gen.CONFIGS["c1"].replace(name="f32_1000_tokens", T=1000, H=2048, E=160, k=4, I=64),
+    "softmax_777_tokens": gen.CONFIGS["c2p"].replace(name="softmax_777_tokens", T=777, I=64, expert_lo=0,
+                                                     expert_hi=4),
+    "sigmoid_groups_301_tokens": gen.CONFIGS["c4"].replace(name="sigmoid_groups_301_tokens", T=301, I=128,
+                                                           expert_lo=0, expert_hi=4, shared_expert=False),
 }
 
 
 @pytest.mark.parametrize("name", list(LONG_ROWS))
 def test_route_long_gate_rows_matches_oracle(name):
     w = LONG_ROWS[name]
-    assert w.E * w.H > 2 ** 19 and w.T * w.E * w.H <= 2 ** 28
+    assert takes_exact_gate(w)
     print("case", name, flush=True)
     x, gate = gen.make_x(w), gen.make_gate(w)
     L = make_layer(w, {"gate": gate, "experts": gen.make_local_experts(w), "shared": None})
@@ -625,12 +636,16 @@ def test_random_ffn_families(seed):
 
 @pytest.mark.parametrize("seed", range(8))
 def test_random_routing_past_4096_tokens(seed):
-    """The random gate options of `_random_workload` at 4097..7000 tokens: tiled
-    gate GEMM (or the fp64 gate for fp32 inputs), interval test, re-scoring."""
+    """The random gate options of `_random_workload` at 4097 tokens and more: tiled gate
+    GEMM, interval test, re-scoring (few experts: as many tokens as that takes); fp32 inputs:
+    the exact gate."""
     r = np.random.default_rng(33000 + seed)
     w = _random_workload(seed).replace(T=int(r.integers(4097, 7000)), I=8, name="random_route_%d" % seed)
     if r.random() >= 0.8:
         w = w.replace(act_dtype="f32", weight_dtype="f32")
+    elif takes_exact_gate(w):
+        w = w.replace(T=16 * (1024 // -(-w.E // 16)) + 5)
+    assert takes_exact_gate(w) == (w.act_dtype == "f32")
     print("case", w, flush=True)
     d = inputs(w)
     L = make_layer(w, d)
