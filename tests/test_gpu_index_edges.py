@@ -42,8 +42,10 @@ def test_exact_route_tiles(act, T, E, H, k, G):
 
 
 # one run, whole and ragged runs, more than 256 runs (chunks of two); one local expert,
-# 512 of them, an expert count that does not divide the workgroup
+# 512 of them, an expert count that does not divide the workgroup; top-1 on either side of the
+# 2048 tokens of the one-launch form
 @pytest.mark.parametrize("T,k,E,lo,hi", [
+    (2048, 1, 40, 0, 40), (2049, 1, 40, 3, 40), (4096, 1, 8, 0, 8),
     (4097, 1, 512, 0, 512), (4097, 1, 512, 511, 512), (2560, 2, 300, 0, 300), (1366, 3, 96, 5, 42),
     (33000, 8, 64, 0, 64), (262145, 1, 32, 3, 32), (32768, 8, 8, 0, 8)])
 def test_dispatch_index_runs(T, k, E, lo, hi):
