@@ -47,10 +47,10 @@ constexpr int kRows = 8;
 __global__ __launch_bounds__(256) void combine_bf16_kernel(
     const uint4* __restrict__ ys, const int32_t* __restrict__ inv, const float* __restrict__ w,
     const uint4* __restrict__ shared_ys, float4* __restrict__ out, int T, int k, int row8,
-    int accumulate) {
+    int accumulate, int grid_row) {
   const int lane = threadIdx.x & 63;
   const int nseg = (row8 + 63) / 64;
-  const int gw = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const int gw = grid_block(grid_row) * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const int t = gw / nseg;
   if (t >= T) return;
   int pos = -1;
@@ -155,10 +155,10 @@ hipError_t launch_combine(const moe_config& c, int T, const void* ys, const int3
   dim3 grid((T + 3) / 4);
   if (c.act_dtype == MOE_BF16) {
     const size_t nseg = (size_t(width / 8) + 63) / 64;        // wavefronts per token row
-    grid = dim3(unsigned((size_t(T) * nseg + 3) / 4));
+    grid = grid_of((size_t(T) * nseg + 3) / 4, 256);
     MOE_LAUNCH(MOE_K_COMBINE, combine_bf16_kernel, grid, block, 0, s, static_cast<const uint4*>(ys), inv,
                        w, static_cast<const uint4*>(shared_ys), reinterpret_cast<float4*>(out), T,
-                       c.top_k, width / 8, accumulate);
+                       c.top_k, width / 8, accumulate, int(grid.x));
   } else {
     MOE_LAUNCH(MOE_K_COMBINE, combine_f32_kernel, grid, block, 0, s, static_cast<const float4*>(ys), inv,
                        w, static_cast<const float4*>(shared_ys), reinterpret_cast<float4*>(out), T,

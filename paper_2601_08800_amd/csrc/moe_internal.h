@@ -81,6 +81,16 @@ extern bool g_prof_on;
     if (::moe::g_prof_on) ::moe::prof_mark(id, stream, false);           \
   } while (0)
 
+// Grid of `blocks` workgroups of `threads`: a dimension holds less than 2^32 threads (more are
+// cut off without an error), so longer launches are spread over rows.  The kernel numbers its
+// workgroups with grid_block() and lets those past the last leave.
+inline dim3 grid_of(size_t blocks, unsigned threads) {
+  const size_t most = 0xffffffffu / threads, rows = (blocks + most - 1) / most;
+  return rows <= 1 ? dim3(unsigned(blocks)) : dim3(unsigned((blocks + rows - 1) / rows), unsigned(rows));
+}
+// `row`: the grid's x length, a kernel argument.
+__device__ __forceinline__ int grid_block(int row) { return int(blockIdx.y) * row + int(blockIdx.x); }
+
 // A kernel that uses more than 64 KB of dynamic LDS must opt in, once per device.
 // `done` is the call site's own record (one bit per device ordinal); a repeated
 // call from a racing thread is harmless.

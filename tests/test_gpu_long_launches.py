@@ -1,0 +1,39 @@
+"""Launches of 2^32 threads and more, which a one-dimensional grid does not take: small rows of
+very many tokens, checked on both ends and in the middle."""
+import pytest
+import torch
+
+import paper_2601_08800_amd as moe
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _give_memory_back():
+    torch.cuda.empty_cache()
+    yield
+    torch.cuda.empty_cache()
+
+
+def _cfg(H, E, k, I, act):
+    return moe.MoEConfig(hidden=H, n_experts=E, top_k=k, score_fn=moe.MOE_SCORE_SOFTMAX, renormalize=1, routed_scale=1.0,
+                         n_groups=1, topk_groups=1, group_score_n=0, expert_lo=0, expert_hi=E, inter_local=I,
+                         act_dtype=act, weight_dtype=act)
+
+
+def _sample(n):
+    return torch.cat([torch.arange(0, 300), torch.arange(n // 2, n // 2 + 300), torch.arange(n - 300, n)]).cuda()
+
+
+def test_combine_of_2_to_the_26_row_segments():
+    T, H, rows = (1 << 25) + 3, 520, 1000                 # two wavefronts a row; 70 GB of output
+    g = torch.Generator(device="cuda").manual_seed(1)
+    ys = torch.empty(rows, H, dtype=torch.bfloat16, device="cuda").normal_(generator=g)
+    inv = torch.randint(-1, rows, (T, 1), dtype=torch.int32, device="cuda", generator=g)
+    w = torch.rand(T, 1, device="cuda", generator=g)
+    out = torch.empty(T, H, device="cuda")
+    at = _sample(T)
+    out[at] = float("nan")
+    moe.moe_combine(_cfg(H, 8, 1, 128, moe.MOE_BF16), T, ys, inv, w, None, out)
+    pos = inv[at, 0].long()
+    assert torch.equal(out[at], torch.where(pos[:, None] >= 0, ys[pos.clamp(min=0)].float() * w[at], 0.0))
