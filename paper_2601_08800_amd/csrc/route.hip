@@ -1220,12 +1220,14 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 template <bool BF16>
 __global__ __launch_bounds__(1024) void gate_exact_kernel(
     int T, int H, int E, const void* __restrict__ x, const void* __restrict__ gate_w,
-    const float* __restrict__ logit_bias, double* __restrict__ zx, int32_t* __restrict__ counters) {
+    const float* __restrict__ logit_bias, double* __restrict__ zx, int32_t* __restrict__ counters, int grid_row) {
   __shared__ double red[16][256];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (blockIdx.x == 0 && tid < 64) counters[tid] = 0;   // nothing is re-scored
+  const int block = grid_block(grid_row);
+  if (block == 0 && tid < 64) counters[tid] = 0;        // nothing is re-scored
   const int n_etiles = (E + 15) / 16;
-  const int ttile = blockIdx.x / n_etiles, e0 = (blockIdx.x - ttile * n_etiles) * 16, t0 = ttile * 16;
+  const int ttile = block / n_etiles, e0 = (block - ttile * n_etiles) * 16, t0 = ttile * 16;
+  if (t0 >= T) return;                                  // the whole workgroup
   const size_t row_bytes = size_t(H) * (BF16 ? 2 : 4);
   const int n16 = int(row_bytes / 16), groups = (n16 + 3) / 4;
   const char* const xrow = static_cast<const char*>(x) + size_t(min(t0 + (lane & 15), T - 1)) * row_bytes;
@@ -1339,7 +1341,7 @@ ExactForm exact_form(bool bf16, int T, int E, int H) {
   const float rows = rows_one > rows_all ? rows_one : rows_all;
   const float tile = (bf16 ? 2.75e-3f * H + .2f : 3.6e-3f * H + .4f) * (tiles > 1 ? tiles : 1.f);
   if (T <= 256 && E <= 64 && one <= rows && one <= tile) return kExactOneLaunch;
-  return rows <= tile ? kExactRows : kExactTiles;
+  return T <= 65535 && rows <= tile ? kExactRows : kExactTiles;      // rows: tokens along the grid's y
 }
 
 template <int EPL, int FORM, bool BF16>
@@ -1357,12 +1359,14 @@ void launch_route_exact(ExactForm form, const SelCfg& sc, const moe_config& c, i
   }
   // the logits area holds at least two floats per (token, expert): room for one double
   double* zx = reinterpret_cast<double*>(ws.logits);
-  if (form == kExactRows)
+  if (form == kExactRows) {
     MOE_LAUNCH(MOE_K_GATE_GEMM, gate_exact_rows_kernel<BF16>, dim3((E + 15) / 16, T), dim3(256), 0, s, c.hidden,
                E, x, gate_w, logit_bias, zx, ws.counters);
-  else
-    MOE_LAUNCH(MOE_K_GATE_GEMM, gate_exact_kernel<BF16>, dim3(unsigned(exact_tiles(T, E))), dim3(1024), 0, s, T,
-               c.hidden, E, x, gate_w, logit_bias, zx, ws.counters);
+  } else {
+    const dim3 grid = grid_of(size_t(exact_tiles(T, E)), 1024);
+    MOE_LAUNCH(MOE_K_GATE_GEMM, gate_exact_kernel<BF16>, grid, dim3(1024), 0, s, T, c.hidden, E, x, gate_w,
+               logit_bias, zx, ws.counters, int(grid.x));
+  }
   MOE_LAUNCH(MOE_K_SELECT, (select_exact_kernel<EPL, FORM>), dim3((T + 3) / 4), dim3(256), 0, s, sc, T, zx,
              select_bias, ids, w);
 }

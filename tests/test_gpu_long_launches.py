@@ -37,3 +37,20 @@ def test_combine_of_2_to_the_26_row_segments():
     moe.moe_combine(_cfg(H, 8, 1, 128, moe.MOE_BF16), T, ys, inv, w, None, out)
     pos = inv[at, 0].long()
     assert torch.equal(out[at], torch.where(pos[:, None] >= 0, ys[pos.clamp(min=0)].float() * w[at], 0.0))
+
+
+def test_exact_gate_of_2_to_the_22_tiles():
+    T, E, H, k = (1 << 21) + 5, 512, 8, 4                 # 8.6 GB of logits
+    g = torch.Generator(device="cuda").manual_seed(2)
+    x = torch.empty(T, H, device="cuda").normal_(generator=g)
+    gate_w = torch.empty(E, H, device="cuda").normal_(generator=g)
+    cfg = _cfg(H, E, k, 128, moe.MOE_F32)
+    ids = torch.full((T, k), -1, dtype=torch.int32, device="cuda")
+    w = torch.empty(T, k, device="cuda")
+    ws = torch.empty(moe.moe_workspace_bytes(cfg, T), dtype=torch.uint8, device="cuda")
+    moe.moe_route(cfg, T, x, gate_w, None, None, None, ids, w, ws)
+    at = _sample(T)
+    top = (x[at].double() @ gate_w.double().t().contiguous()).topk(k, dim=1)
+    assert torch.equal(ids[at].long(), top.indices)
+    want = torch.softmax(top.values, dim=1)
+    assert float(((w[at].double() - want).abs() / want).max()) <= 2.0 ** -24 + 2.0 ** -35
