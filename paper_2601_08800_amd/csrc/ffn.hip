@@ -1379,10 +1379,11 @@ __global__ __launch_bounds__(256) void ffn_f32_kernel(const float* __restrict__ 
                                                      const float* __restrict__ B0,
                                                      const float* __restrict__ B1,
                                                      float* __restrict__ C, int N, int K,
-                                                     const int32_t* __restrict__ tiles, int stages) {
+                                                     const int32_t* __restrict__ tiles, int stages,
+                                                     int grid_row) {
   extern __shared__ uint4 smem[];
-  const int n_ntiles = (N + 31) / 32;
-  const int mtile = blockIdx.x / n_ntiles, ntile = blockIdx.x - mtile * n_ntiles;
+  const int n_ntiles = (N + 31) / 32, block = grid_block(grid_row);
+  const int mtile = block / n_ntiles, ntile = block - mtile * n_ntiles;
   if (mtile >= tiles[0]) return;
   const int e = tiles[1 + kTileRec * mtile], row0 = tiles[2 + kTileRec * mtile],
             row1 = tiles[3 + kTileRec * mtile];
@@ -1605,17 +1606,18 @@ void launch_f32(GemmKind kind, int bm, const float* A, const float* B0, const fl
   constexpr int id = DUAL ? MOE_K_FFN_GEMM1 : MOE_K_FFN_GEMM2;
   const int bn = kind == kGemmF32Valu ? 64 : 32;
   const int max_mt = rows_capacity / bm + (n_experts < rows_capacity ? n_experts : rows_capacity);
-  const size_t grid = size_t(max_mt) * ((N + bn - 1) / bn);
+  const size_t blocks = size_t(max_mt) * ((N + bn - 1) / bn);
   if (kind == kGemmF32Valu) {
-    MOE_LAUNCH(id, ffn_f32_valu_kernel<DUAL>, dim3(grid), dim3(256), 0, s, A, B0, B1, C, N, K, tiles);
+    MOE_LAUNCH(id, ffn_f32_valu_kernel<DUAL>, dim3(blocks), dim3(256), 0, s, A, B0, B1, C, N, K, tiles);
     return;
   }
   auto k = ffn_f32_kernel<DUAL>;
   static uint64_t opted = 0;
   lds_opt_in(reinterpret_cast<const void*>(k), F32Ring<DUAL>::kLds, opted);
-  const int stages = F32Ring<DUAL>::stages(K, long(grid));
-  MOE_LAUNCH(id, k, dim3(grid), dim3(256), stages * F32Ring<DUAL>::kStageBytes, s, A, B0, B1, C, N, K, tiles,
-             stages);
+  const int stages = F32Ring<DUAL>::stages(K, long(blocks));
+  const dim3 grid = grid_of(blocks, 256);
+  MOE_LAUNCH(id, k, grid, dim3(256), stages * F32Ring<DUAL>::kStageBytes, s, A, B0, B1, C, N, K, tiles, stages,
+             int(grid.x));
 }
 
 template <bool F8>

@@ -54,3 +54,20 @@ def test_exact_gate_of_2_to_the_22_tiles():
     assert torch.equal(ids[at].long(), top.indices)
     want = torch.softmax(top.values, dim=1)
     assert float(((w[at].double() - want).abs() / want).max()) <= 2.0 ** -24 + 2.0 ** -35
+
+
+def test_fp32_ffn_of_2_to_the_24_tiles():
+    R, H, I = 1 << 20, 72, 16384                          # 64 GB of intermediate in the workspace
+    g = torch.Generator(device="cuda").manual_seed(3)
+    draw = lambda std, *s: torch.empty(*s, device="cuda").normal_(0.0, std, generator=g)
+    x, wg, wu, wd = draw(1.0, R, H), draw(0.1, 1, I, H), draw(0.1, 1, I, H), draw(0.1, 1, H, I)
+    cfg = _cfg(H, 1, 1, I, moe.MOE_F32)
+    offsets = torch.tensor([0, R], dtype=torch.int32, device="cuda")
+    ys = torch.full((R, H), float("nan"), device="cuda")
+    ws = torch.empty(moe.moe_workspace_bytes(cfg, R), dtype=torch.uint8, device="cuda")
+    moe.moe_expert_ffn(cfg, 1, x, offsets, R, wg, wu, wd, None, None, None, ys, ws)
+    assert not torch.isnan(ys).any()
+    at = _sample(R)
+    gate, up = (x[at].double() @ m[0].double().t().contiguous() for m in (wg, wu))
+    ref = (gate * torch.sigmoid(gate) * up) @ wd[0].double().t().contiguous()
+    assert float((ys[at].double() - ref).abs().max() / ref.abs().max()) <= 1e-5
