@@ -95,8 +95,9 @@ const char* moe_status_string(moe_status s);
  * The ids are those of exact arithmetic on the stored inputs: keys are first
  * computed fast (bf16 MFMA, fp32 accumulation in short chains) and every token
  * whose decisive key gaps are within the error bound of that computation is
- * re-scored in fp64.  After the call the first int32 of `ws` holds the number
- * of tokens that were re-scored.
+ * re-scored in fp64 (short batches and fp32 rows: every key is fp64 from the
+ * start).  After the call the first int32 of `ws` holds the number of tokens that
+ * were re-scored.
  *   x          [T,H]  act dtype            gate_w [E,H] act dtype
  *   logit_bias [E] fp32 or NULL            select_bias [E] fp32 or NULL
  *   logits_in  [T,E] fp32 or NULL: when given the dot products are skipped and
@@ -132,12 +133,13 @@ moe_status moe_dispatch(const moe_config* cfg, int32_t T, const void* x,
  * moe_dispatch for callers that cannot allocate or hand over a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation.  Same arguments, outputs and errors as moe_dispatch, minus the
- * workspace: the index scratch (one int32 per local expert and sub-chunk of 64
- * assignments, E_loc * ceil(T*k / 64) * 4 bytes) lives in a fixed device array
- * inside the library, moe_dispatch_noalloc_max_bytes() = 4 MiB per GPU, held
- * until the process ends.  A call whose scratch would exceed that returns
- * MOE_ERR_WORKSPACE and enqueues nothing (the largest workload here, 65 536
- * tokens x top-8 over 128 local experts, needs exactly 4 MiB).  The call
+ * workspace: the index scratch lives in a fixed device array inside the library,
+ * moe_dispatch_noalloc_max_bytes() = 4 MiB per GPU, held until the process ends.
+ * A call for which E_loc * ceil(T*k / 64) * 4 bytes, a bound on the scratch, would
+ * exceed that returns MOE_ERR_WORKSPACE and enqueues nothing (the largest
+ * workload here, 65 536 tokens x top-8 over 128 local experts, is just within;
+ * the index itself keeps one int32 per local expert and chunk of 1024 assignments
+ * or more, 512 KiB at most).  The call
  * allocates and frees nothing and synchronises nothing; the array's device
  * address is looked up once per device on the first call there.  All calls on
  * one GPU share that GPU's array: calls that overlap in time on one GPU (two

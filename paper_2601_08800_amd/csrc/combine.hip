@@ -3,8 +3,8 @@
 // (Sec. II "Combine"; the accumulation step of Alg. 1: the rows a stage returns
 // are scaled by their top-k weights and added to the running result).
 //
-// Gather-by-token: one wavefront owns a token, walks the row in 16-byte pieces
-// and adds the token's local expert rows in ascending j, so there are no
+// Gather-by-token: a wavefront owns a token (fp32) or 64 16-byte pieces of its row
+// (bf16) and adds the token's local expert rows in ascending j, so there are no
 // atomics and the result does not depend on scheduling.  Bandwidth-bound:
 // reads A_loc*H (+T*H shared) activations, writes T*H fp32.
 #include "moe_internal.h"
@@ -42,7 +42,8 @@ __device__ __forceinline__ void fma8(float (&acc)[8], float w, const uint4& v) {
 // one token's row (a row of hidden 2048 is shared out over four) and fetches up to kRows
 // expert rows at once, so its chain is one round of loads for top-8 and not one per
 // expert.  Against 256 pieces per wavefront and one row at a time: one token, hidden
-// 2048, 5.8 -> 2.9 us; 65 536 tokens x 8 rows (2.7 GB) 497 -> 441 us.
+// 2048, 5.8 -> 2.9 us; 65 536 tokens x 8 rows (2.7 GB) 497 -> 457 us.  (Top-1 and top-2 of
+// about 512 tokens of hidden 7168: 6.2 -> 6.9 us; 200 and 1000 tokens are faster.)
 constexpr int kRows = 8;
 __global__ __launch_bounds__(256) void combine_bf16_kernel(
     const uint4* __restrict__ ys, const int32_t* __restrict__ inv, const float* __restrict__ w,

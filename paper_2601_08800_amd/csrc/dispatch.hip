@@ -26,7 +26,7 @@ __device__ __forceinline__ void nt_store16(void* p, uint4 v) {
   __builtin_nontemporal_store(t, static_cast<u32x4_t*>(p));
 }
 
-constexpr int kSub = 64;   // assignments per histogram column: one wavefront
+constexpr int kSub = 64;   // assignments per count of the one-launch form: one wavefront
 
 __device__ __forceinline__ uint64_t lanemask_lt() {
   return (uint64_t(1) << (threadIdx.x & 63)) - 1;

@@ -17,7 +17,9 @@
 // per workgroup, operands global -> LDS directly, LDS rings; GEMM-2 of short groups
 // of many experts: up to 128 rows x 512 weight rows), ffn_skinny_kernel
 // (decode and fp8 weights: weight streaming, K split across wavefronts, no LDS
-// staging) and ffn_shortk_kernel (GEMM-2 of narrow TP slices: K up to 128).
+// staging) and ffn_shortk_kernel (GEMM-2 of narrow TP slices: K up to 128).  Which one
+// runs: plan_ffn.  fp32 path: ffn_f32_kernel (matrix instructions), and for K up to 64 in
+// large launches ffn_f32_valu_kernel.
 // fp8 weights: the weight-streaming kernel widens the e4m3 codes to bf16 in
 // registers (exact) and multiplies the fp32 partial sum of each 128-deep K block
 // by the 128x128 block scale; the tall-tile kernel keeps the codes in its LDS

@@ -61,10 +61,9 @@ RouteWs carve_route(void* ws, int T, int E) {
 
 DispatchWs carve_dispatch(void* ws, int T, int k, int E_loc) {
   DispatchWs d;
-  size_t A = size_t(T) * k;
-  d.n_blocks = int((A + kDispatchChunk - 1) / kDispatchChunk);   // sub-chunks of 64 assignments
+  const size_t A = size_t(T) * k;
   d.block_hist = static_cast<int32_t*>(ws);
-  d.bytes = align_up(size_t(d.n_blocks) * E_loc * 4);
+  d.bytes = align_up((A + kDispatchSized - 1) / kDispatchSized * E_loc * 4);
   return d;
 }
 
@@ -86,10 +85,10 @@ FfnWs carve_ffn(void* ws, int rows_capacity, int n_experts, int I_loc, int abyte
 using namespace moe;
 
 // ---- moe_dispatch_noalloc: the dispatch index scratch lives in the library ----
-// The multi-kernel dispatch keeps one count per (local expert, sub-chunk of 64
-// assignments) between its kernels.  For callers that cannot provide a workspace
-// this fixed device array stands in for it; each GPU the library runs on holds
-// its own copy at its own address until the process ends.
+// The multi-kernel dispatch keeps one count per local expert and chunk of assignments
+// between its kernels.  For callers that cannot provide a workspace this fixed device
+// array stands in for it; each GPU the library runs on holds its own copy at its own
+// address until the process ends.  The size limit is that of the workspace's bound.
 constexpr size_t kNoAllocScratchBytes = size_t(4) << 20;
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 

@@ -46,11 +46,10 @@ struct RouteWs {
 RouteWs carve_route(void* ws, int T, int E);
 
 // dispatch
-constexpr int kDispatchChunk = 64;            // assignments per histogram column (one wavefront)
+constexpr int kDispatchSized = 64;            // the workspace has room for a chunk per so many assignments ...
 struct DispatchWs {
-  int32_t* block_hist; // [chunks, E_loc] counts per expert and chunk of assignments; sized
-                       // for one chunk per 64 assignments (n_blocks), the chunks are longer
-  int n_blocks;
+  int32_t* block_hist; // [chunks, E_loc] counts per expert and chunk of 1024 assignments or more:
+                       // ... a sixteenth of it at most is used; callers' sizes are what they were
   size_t bytes;
 };
 DispatchWs carve_dispatch(void* ws, int T, int k, int E_loc);
