@@ -282,8 +282,8 @@ moe_status moe_probe_mfma_rate(int32_t workgroups, int32_t iters, void* stream, 
  * (scale = max|x| / 448, 1 for an all-zero block; code = e4m3(x / scale),
  * round to nearest even after a clamp to +-448; fp32 operations), the products
  * of a 128-deep K block are summed in fp32 and multiplied by the row's and the
- * weight block's scales, and the SwiGLU intermediate, stored as bf16 in the
- * workspace, is quantised the same way before the down projection.  ys is bf16.
+ * weight block's scales, and the SwiGLU intermediate (fp32) is quantised the
+ * same way before the down projection.  ys is bf16.
  * Workspace: moe_fp8act_workspace_bytes(cfg, n_experts_here, rows_capacity)
  * bytes (0 for an unsupported configuration). */
 size_t moe_fp8act_workspace_bytes(const moe_config* cfg, int32_t n_experts_here,

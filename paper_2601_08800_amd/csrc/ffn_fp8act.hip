@@ -9,16 +9,32 @@
 //           (Aq[rows, kb] . Bq[N, kb]^T): the products of a K block are summed by
 //           the MFMA into a fresh fp32 accumulator and promoted into the running
 //           sum with the two scales (fp32 FMA), block by block
-// GEMM-1 applies SwiGLU and stores the intermediate as bf16; it is quantised by
-// the same kernel before GEMM-2.
+// GEMM-1 applies SwiGLU and quantises the intermediate by the same rule: its tile spans the
+// 128 columns of one block.
 //
-// GEMM tile: 128 rows x 128 weight rows (DUAL: 64 gate + the matching 64 up
-// rows), K step 128 bytes = one scale block, 256 threads = 4 wavefronts as 2 (M)
-// x 2 (N), each 2 x 2 MFMA tiles.  Operands go global -> LDS by DMA (two stages),
-// rows of 128 bytes with the piece index XOR-ed by (row/2)&7.  Inside a
-// K step, MFMA sub-step s of lane half h takes bytes (2s+h)*32 .. +32 of the row
-// for BOTH operands, so the pairing of A and B elements is right whatever order
-// the instruction walks K in.
+// GEMM tile: up to 192 rows x 256 weight rows (DUAL: 128 gate + the matching 128 up rows), K
+// step 128 bytes = one scale block, eight wavefronts as 2 (row halves) x 4 (64 weight rows).
+// An expert's rows are cut into tiles of equal height, in 32-row blocks (NB of them, a template
+// argument).  Operands go global -> LDS by DMA into rings of their own (Ring8), rows of 128
+// bytes with the piece index XOR-ed by (row/2)&7.  Inside a K step, MFMA sub-step s of lane
+// half h takes bytes (2s+h)*32 .. +32 of the row for BOTH operands, so the pairing of A and B
+// elements is right whatever order the instruction walks K in.  The weights are the first
+// operand: a lane then holds columns of one activation row, so that a 32 x 32 block's sums
+// have one scale per lane (one product and sixteen FMAs a block; with the rows in the
+// registers it was sixteen products more, as much time as the MFMAs take).
+//
+// What bounds it: the matrix unit would need 0.75 us for a K step of 192 rows at the clock that
+// it sustains; the step takes 1.5 us, because the LDS reads and the load instructions of a
+// step (memory phase) take longer than its MFMAs and the two row halves take turns.  Against
+// 128 x 128 tiles of four wavefronts, two workgroups per CU, all loads of a step waited for at
+// once, and passes of their own for the intermediate's quantisation (one stream, us): 6007
+// tokens of 7168, 32 of 256 experts, I 1024: routed GEMM-1 / -2 163 / 89 -> 165 / 83, one
+// expert of 6007 rows 133 / 73 -> 97 / 69, quantisation 16 -> 0; whole layer 673 -> 605; 24 576
+// tokens 2078 -> 1793, I 2048 3483 -> 2834; 256 tokens 233 -> 207.
+// Also measured (one expert of 6144 rows, GEMM-1 97): both halves in one phase with the next
+// fragments read under the last block's MFMAs 103, the same with loads spread over the row
+// blocks 111; 16 x 16 x 128 instructions 98-105; reads in front of the loads 101.
+
 #include "moe_internal.h"
 
 namespace moe {
@@ -29,13 +45,15 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kQBlock = 128;     // columns per activation scale, and K bytes per GEMM step
-constexpr int kTileRec = 4;      // tile record: expert, first row, end row, (unused)
-constexpr int FBM = 128, FBN = 128;
+constexpr int kTileRec = 4;      // tile record: expert, first row, end row, the expert's first tile
+constexpr int FBM = 192;          // rows of a tile at most
 
-__device__ __forceinline__ uint16_t f32_to_bf16_bits_rne(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+// two values rounded to bf16 (nearest even), low | high half
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  const f32x2 v = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
 __device__ __forceinline__ int swz(int row, int piece) {
@@ -105,23 +123,28 @@ __global__ __launch_bounds__(256) void fp8act_quant_kernel(const uint16_t* __res
 }
 
 // ------------------------------------------------------------- tile table
-// tiles[0] = number of M tiles, then (expert, first row, end row, 0) per tile.  An
-// expert's rows are cut into ceil(M / FBM) tiles of equal height (rounded up to 32 rows):
-// the GEMM skips the 32-row blocks a tile does not have.  One thread per expert; one
-// wavefront scans the tile counts.
+// tiles[0] = number of M tiles, then (expert, first row, end row, the expert's first tile) per
+// tile.  An expert's rows are cut into ceil(M / FBM) tiles of equal height (rounded up to 32
+// rows).  One thread per expert; one wavefront scans the tile counts.
+struct ExpertTiles { int lo, hi, step, count; };
+__device__ __forceinline__ ExpertTiles tiles_of(const int32_t* __restrict__ offsets, int e, int rows_capacity) {
+  ExpertTiles t;
+  t.lo = min(max(offsets[e], 0), rows_capacity);
+  t.hi = min(max(offsets[e + 1], t.lo), rows_capacity);
+  const int m = t.hi - t.lo, full = (m + FBM - 1) / FBM;
+  t.step = full ? ((m + full - 1) / full + 31) / 32 * 32 : FBM;
+  t.count = (m + t.step - 1) / t.step;
+  return t;
+}
+
 __global__ __launch_bounds__(512) void fp8act_tiles_kernel(const int32_t* __restrict__ offsets,
                                                           int n_experts, int rows_capacity,
                                                           int32_t* __restrict__ tiles, int max_tiles) {
   __shared__ int32_t start[512];
   const int e = threadIdx.x;
-  int lo = 0, hi = 0;
-  if (e < n_experts) {
-    lo = min(max(offsets[e], 0), rows_capacity);
-    hi = min(max(offsets[e + 1], lo), rows_capacity);
-  }
-  const int full = (hi - lo + FBM - 1) / FBM;
-  const int step = full ? ((hi - lo + full - 1) / full + 31) / 32 * 32 : FBM;
-  start[e] = (hi - lo + step - 1) / step;       // experts past n_experts: no tiles
+  ExpertTiles mine{0, 0, FBM, 0};
+  if (e < n_experts) mine = tiles_of(offsets, e, rows_capacity);
+  start[e] = mine.count;                        // experts past n_experts: no tiles
   __syncthreads();
   if (e < 64) {
     int n[8], sum = 0;
@@ -141,208 +164,342 @@ __global__ __launch_bounds__(512) void fp8act_tiles_kernel(const int32_t* __rest
   __syncthreads();
   if (e >= n_experts) return;
   int t = start[e];
-  for (int r = lo; r < hi && t < max_tiles; r += step, ++t) {
+  for (int r = mine.lo; r < mine.hi && t < max_tiles; r += mine.step, ++t) {
     tiles[1 + kTileRec * t] = e;
     tiles[2 + kTileRec * t] = r;
-    tiles[3 + kTileRec * t] = r + step < hi ? r + step : hi;
-    tiles[4 + kTileRec * t] = 0;
+    tiles[3 + kTileRec * t] = min(r + mine.step, mine.hi);
+    tiles[4 + kTileRec * t] = start[e];
   }
 }
 
 // ------------------------------------------------------------------- GEMM
 // A codes [rows, K], sA_t [K/128][rows_capacity]; B codes [n_experts][N][K] (DUAL:
-// B0 = gate, B1 = up), S [n_experts][N/128][K/128]; C bf16 [rows, N].
-// Operands go global -> LDS directly (`global_load_lds_dwordx4`) into two
-// stages: the loads of step k+1 are issued right after the barrier of step k and
-// waited for before the barrier of step k+1; two workgroups share a CU and fill
-// each other's waits.  LDS slot s of a stage holds (row s/8, piece (s%8) ^
-// (row/2)&7); the lane that owns the slot fetches that piece.
+// B0 = gate, B1 = up), S [n_experts][N/128][K/128].  DUAL: hq codes [rows, N] and
+// hs_t [N/128][rows_capacity] of the SwiGLU values; else C bf16 [rows, N].
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
-// FULL: the tile has all four row blocks.  The guards that shorter tiles need cut the loop into
-// pieces that the compiler orders each by itself, 70 ns of a K step (one expert of 256 rows,
-// hidden 7168, I 1024: GEMM-1 / -2 61.0 / 13.8 us with them, 54.4 / 13.4 without).
-template <bool DUAL, bool FULL>
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
+}
+
+// LDS of a tile of NB 32-row blocks: weight stages | activation stages | row scales.
+template <int NB> struct Ring8 {
+  static constexpr int kB = 256 * 8, kA = NB * 32 * 8;            // 16-byte slots of a stage
+  static constexpr int kS = 256;                                          // row scales of a stage (a wavefront fetches 64)
+  static constexpr int kSB = NB <= 2 ? 4 : 3;                             // weight stages
+  static constexpr int kSA = NB == 1 ? 4 : (NB <= 5 ? 3 : 2);             // activation stages: kSB or one less
+  static constexpr int kBytes = (kSB * kB + kSA * kA) * 16 + kSA * kS * 4;
+  static_assert(kBytes <= 160 * 1024, "LDS of a CU");
+};
+
+template <bool DUAL, int NB, int WM>
 __device__ __forceinline__ void fp8act_gemm_body(
     const uint8_t* __restrict__ A, const float* __restrict__ sA_t, int rows_capacity,
     const uint8_t* __restrict__ B0, const uint8_t* __restrict__ B1, const float* __restrict__ S0,
-    const float* __restrict__ S1, uint16_t* __restrict__ C, int N, int K, int e, int row0, int row1, int ntile,
-    uint4* smem) {
-  uint4* const As = smem;                         // [2][FBM * 8]
-  uint4* const Bs = smem + 2 * FBM * 8;           // [2][FBN * 8]
-  float* const Ss = reinterpret_cast<float*>(smem + 2 * FBM * 8 + 2 * FBN * 8);   // [2][FBM]
-  constexpr int CN = DUAL ? 64 : 128;             // output columns per workgroup
-  const int n0 = ntile * CN;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // Wavefront (wm, wn) computes the 32-row blocks wm and wm + 2, as far as the tile has
-  // them.  Of a tile of one or three blocks the wm = 0 wavefronts do one block more; the
-  // workgroups that come to a CU second (the hardware deals the ids out over all 256 CUs)
-  // swap the roles, so the work is even over the SIMDs.
-  const int wm = (FULL ? wave : wave ^ (blockIdx.x >> 8)) & 1, wn = wave >> 1;
-  const int nblk = FULL ? 4 : (row1 - row0 + 31) >> 5;       // 32-row blocks of the tile: 1..4
-  const int nbw = FULL ? 2 : (nblk - wm + 1) >> 1;           // ... of this wavefront: 0..2
+    const float* __restrict__ S1, uint16_t* __restrict__ C, uint8_t* __restrict__ hq, float* __restrict__ hs_t,
+    int N, int K, int e, int row0, int row1, int n0, int wave, uint4* __restrict__ smem) {
+  using R = Ring8<NB>;
+  constexpr int SA = R::kSA, SB = R::kSB;
+  constexpr int WB0 = WM == 0 ? 0 : (NB + 1) / 2;                 // first row block of this wavefront
+  constexpr int NBW = WM == 0 ? (NB + 1) / 2 : NB / 2;            // ... and their number
+  constexpr int NACC = NBW > 0 ? NBW : 1;
+  constexpr int NLB = 4, NLA = WM == 0 ? (NB + 1) / 2 : NB / 2;   // load instructions per step
+  constexpr int HALF = 128;
+  uint4* const ringB = smem;
+  uint4* const ringA = smem + SB * R::kB;
+  float* const ringS = reinterpret_cast<float*>(ringA + SA * R::kA);
+  const int lane = threadIdx.x & 63, wn = wave & 3;
   const int h = lane >> 5, l31 = lane & 31;
   const int nkb = K / kQBlock, nnb = N / 128;
-
-  // this thread's slots: tid + 256 i (i < 4) of the A stage and of the B stage: rows
-  // (tid >> 3) + 32 i, and (row / 2) & 7 does not depend on i
-  const int lrow = tid >> 3;
-  const int gpiece = (tid & 7) ^ ((lrow >> 1) & 7);
-  const uint8_t* ap[4];
-  const uint8_t* bp[4];
+  const int rows = row1 - row0;
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(A + size_t(row0) * K), 0, rows * K, 0x00020000);
+  const int brows = N - n0 < HALF * (DUAL ? 1 : 2) ? N - n0 : HALF * (DUAL ? 1 : 2);
+  const __amdgpu_buffer_rsrc_t rb0 = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>(B0 + (size_t(e) * N + n0) * K), 0, brows * K, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rb1 = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint8_t*>((DUAL ? B1 : B0) + (size_t(e) * N + n0) * K), 0, brows * K, 0x00020000);
+  // load q of a stage fills its rows q*64 + wave*8 .. +8: lane l owns slot l%8 of row l/8 and
+  // fetches the piece that belongs there
+  const int lrow = wave * 8 + (lane >> 3), lpiece = (lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7);
+  int off[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int r = row0 + lrow + 32 * i;
-    r = r < row1 ? r : row1 - 1;
-    ap[i] = A + size_t(r) * K + gpiece * 16;
-    const int br = lrow + 32 * i;                 // row of the B tile: DUAL 0..63 gate, 64..127 up
-    const uint8_t* base = (DUAL && br >= 64) ? B1 : B0;
-    const int n = n0 + ((DUAL && br >= 64) ? br - 64 : br);
-    bp[i] = base + (size_t(e) * N + n) * K + gpiece * 16;
-  }
-  const int srow = row0 + (tid & 127) < row1 ? row0 + (tid & 127) : row1 - 1;
-  const float* s0p = S0 + (size_t(e) * nnb + n0 / 128) * nkb;
-  const float* s1p = DUAL ? S1 + (size_t(e) * nnb + n0 / 128) * nkb : nullptr;
-
-  float rs;                                       // this thread's row scale of the step in flight
-  auto issue = [&](int kb) {
-    const int st = kb & 1;
-    rs = sA_t[size_t(kb) * rows_capacity + srow];          // first: the oldest load of the group
+  for (int q = 0; q < 4; ++q) off[q] = (q * 64 + lrow) * K + lpiece * 16;
+  // row scales of a stage: wavefronts w and w + 4 fetch the same 64
+  const int srow = wn * 64 + lane;
+  const float* const sp = sA_t + (row0 + srow < row1 ? row0 + srow : row1 - 1);
+  auto issue_b = [&](int kb) {
+    uint4* const st = ringB + (kb % SB) * R::kB + wave * 64;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (i < nblk) __builtin_amdgcn_global_load_lds((gptr_t)(ap[i] + size_t(kb) * kQBlock),
-                                       (lptr_t)(As + st * FBM * 8 + (i * 4 + wave) * 64), 16, 0, 0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      __builtin_amdgcn_global_load_lds((gptr_t)(bp[i] + size_t(kb) * kQBlock),
-                                       (lptr_t)(Bs + st * FBN * 8 + (i * 4 + wave) * 64), 16, 0, 0);
+    for (int q = 0; q < NLB; ++q) {
+      if (DUAL && q >= 2)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rb1, (lptr_t)(st + q * 512), 16, off[q - 2], kb * kQBlock, 0, 0);
+      else
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rb0, (lptr_t)(st + q * 512), 16, off[q], kb * kQBlock, 0, 0);
+    }
   };
-
-  f32x16 acc[2][2];
+  auto issue_a = [&](int kb) {
+    uint4* const st = ringA + (kb % SA) * R::kA + wave * 64;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int q = 0; q < NLA; ++q)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lptr_t)(st + q * 512), 16, off[q], kb * kQBlock, 0, 0);
+    __builtin_amdgcn_global_load_lds((gptr_t)(sp + size_t(kb) * rows_capacity),
+                                     (lptr_t)(ringS + (kb % SA) * R::kS + wn * 64), 4, 0, 0);
+  };
+  constexpr int NLS = NLA + 1;
+
+  f32x16 acc[NACC][2];
+#pragma unroll
+  for (int i = 0; i < NACC; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+  const int brow0 = DUAL ? wn * 32 : wn * 64;
+  const int brow1 = DUAL ? HALF + wn * 32 : wn * 64 + 32;
+  int nb0 = (n0 + (DUAL ? 0 : wn * 64)) / 128;
+  nb0 = nb0 < nnb ? nb0 : nnb - 1;
+  const float* const s0p = S0 + (size_t(e) * nnb + nb0) * nkb;
+  const float* const s1p = DUAL ? S1 + (size_t(e) * nnb + nb0) * nkb : s0p;
 
-  // B rows of this wavefront's two 32-column blocks
-  const int brow0 = DUAL ? wn * 32 : wn * 64;             // DUAL: gate block; else first block
-  const int brow1 = DUAL ? 64 + wn * 32 : wn * 64 + 32;   // DUAL: the matching up block
-
-  issue(0);
+  // The two wavefronts of a SIMD (w and w + 4, the two row halves) take turns: in one phase a
+  // wavefront issues loads and reads all fragments of a step, in the next it multiplies them; row
+  // half 1 runs one phase behind row half 0.
+  //   phase   row half 0                                       row half 1
+  //   2j      loads A(j+SA-1), B(j+SB-1), read step j          MFMAs of step j-1
+  //   2j+1    MFMAs of step j                                  loads A(j+SA-1), B(j+SB-1), read step j
+  // Step j+1 must have landed when phase 2j+1 ends: every wavefront waits for its own loads of it
+  // before that barrier.  A stage is filled again two phases after row half 0 has read it and one
+  // after row half 1 has, which therefore waits for its reads before the barrier.
+#pragma unroll
+  for (int g = 0; g < SB - 1; ++g) {
+    if (g < SA - 1 && g < nkb) issue_a(g);
+    if (g < nkb) issue_b(g);
+  }
+  // What was issued after step j+1's last load: SB-2 whole groups, or, with one activation stage
+  // less, SA-2 and the weights of the group that held the step's activations.
+  constexpr int kYounger = SA == SB ? (SB - 2) * (NLB + NLS) : NLB + (SA - 2) * (NLB + NLS);
+  // Fragment (32 rows, sub-step s): lane l reads the 16-byte pieces (2s + l/32)*2, +1 of row l%32;
+  // row blocks are multiples of 32 rows apart, which the swizzle does not see.
+  int at[2][2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) at[s][t] = swz(l31, (2 * s + h) * 2 + t);
+  auto frag = [&](const uint4* base, int s) {
+    const uint4 lo = base[at[s][0]], hi = base[at[s][1]];
+    return i32x8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+  };
+  i32x8 fb[2][2], fa[NACC][2];                     // [sub-step][column block], [row block][sub-step]
+  float sa[NACC];
+  f32x16 part[2];                                  // sums of a K block, [column block]
+  float sb0 = s0p[0], sb1 = s1p[0], f1 = 0.f;      // f1: scale of part[1], which is added up late
+#pragma unroll
+  for (int q = 0; q < 16; ++q) part[1][q] = 0.f;
+  auto mma = [&](int i, int j) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) part[j][q] = 0.f;
+    part[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[0][j], fa[i][0], part[j], 0, 0, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
+    part[j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[1][j], fa[i][1], part[j], 0, 0, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
+  };
+  auto add = [&](int i, int j, float f) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) acc[i][j][q] = fmaf(part[j][q], f, acc[i][j][q]);
+  };
+  auto phase_end = [&](bool drain) {
+    __builtin_amdgcn_sched_barrier(0);
+    if (drain) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    else asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto landed = [&](int kb) {                      // step kb + 1
+    if (kb + SB - 1 < nkb) wait_vmcnt<kYounger>(); else wait_vmcnt<0>();
+  };
+  landed(-1);
+  phase_end(false);
+  if (WM == 1) phase_end(false);                   // one phase behind row half 0
   for (int kb = 0; kb < nkb; ++kb) {
-    const int buf = kb & 1;
-    // step kb has landed (nothing younger is in flight); park its row scales
-    __builtin_amdgcn_s_waitcnt(0x0f70);                   // vmcnt(0)
-    if (tid < FBM) Ss[buf * FBM + tid] = rs;
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    // every wavefront is done with step kb-1: refill its stage
-    if (kb + 1 < nkb) issue(kb + 1);
-    const uint4* Ab = As + buf * FBM * 8;
-    const uint4* Bb = Bs + buf * FBN * 8;
-    f32x16 part[2][2];
+    if (kb + SA - 1 < nkb) issue_a(kb + SA - 1);
+    if (kb + SB - 1 < nkb) issue_b(kb + SB - 1);
+    const float c0 = sb0, c1 = sb1;
+    if constexpr (NBW > 0) {
+      const uint4* const Bb = ringB + (kb % SB) * R::kB;
+      const uint4* const Ab = ringA + (kb % SA) * R::kA + WB0 * 256;
+      const float* const Sb = ringS + (kb % SA) * R::kS + WB0 * 32 + l31;
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int p = (2 * s + h) * 2;                  // first of the lane's two 16-byte pieces
-      i32x8 fa[2], fb[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        if (i >= nbw) break;
-        const int r = i * 64 + wm * 32 + l31;
-        const uint4 lo = Ab[swz(r, p)], hi = Ab[swz(r, p + 1)];
-        fa[i] = i32x8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+      for (int s = 0; s < 2; ++s) {
+        fb[s][0] = frag(Bb + brow0 * 8, s);
+        fa[0][s] = frag(Ab, s);
       }
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int r = (j == 0 ? brow0 : brow1) + l31;
-        const uint4 lo = Bb[swz(r, p)], hi = Bb[swz(r, p + 1)];
-        fb[j] = i32x8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w, (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
-      }
+      for (int s = 0; s < 2; ++s) fb[s][1] = frag(Bb + brow1 * 8, s);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        if (i >= nbw) break;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          f32x16 c;
-          if (s == 0) {
-#pragma unroll
-            for (int q = 0; q < 16; ++q) c[q] = 0.f;
-          } else {
-            c = part[i][j];
-          }
-          part[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[i], fb[j], c, 0, 0, 0,
-                                                                      0x7f7f7f7f, 0, 0x7f7f7f7f);
+      for (int i = 0; i < NBW; ++i) {
+        if (i > 0) {
+          fa[i][0] = frag(Ab + i * 256, 0);
+          fa[i][1] = frag(Ab + i * 256, 1);
         }
+        sa[i] = Sb[i * 32];
+      }
+      add(NBW - 1, 1, f1);
+    }
+    const int kn = kb + 1 < nkb ? kb + 1 : kb;
+    sb0 = s0p[kn];
+    sb1 = s1p[kn];
+    if (WM == 1) landed(kb);
+    phase_end(WM == 1);
+    if constexpr (NBW > 0) {
+#pragma unroll
+      for (int i = 0; i < NBW; ++i) {
+        mma(i, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (i > 0) add(i - 1, 1, f1);
+        __builtin_amdgcn_sched_barrier(0);
+        mma(i, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        add(i, 0, sa[i] * c0);
+        f1 = sa[i] * c1;
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    // promote the block's sums: acc += part * sA[row] * sB
-    const float sb0 = s0p[kb];
-    const float sb1 = DUAL ? s1p[kb] : sb0;
+    if (WM == 0) landed(kb);
+    phase_end(false);
+  }
+  if (WM == 0) phase_end(false);
+  if constexpr (NBW > 0) add(NBW - 1, 1, f1);
+
+  // D layout: lane l, register q -> weight row (q/4)*8 + (l/32)*4 + q%4, activation row l%32: a
+  // lane holds four neighbouring columns of one output row.
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the stages have been read by all
+  if constexpr (DUAL) {
+    // The tile's 128 columns are one block of the intermediate's quantisation: the largest
+    // magnitude of a row over the four wavefronts of its half, then codes, turned around in LDS
+    // so that a store writes whole 128-byte rows.
+    float* const amax = reinterpret_cast<float*>(smem + FBM * 9);    // [4][FBM], behind the codes
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      if (i >= nbw) break;
-      float sa[16];
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const float4 v = *reinterpret_cast<const float4*>(Ss + buf * FBM + i * 64 + wm * 32 + q4 * 8 + h * 4);
-        sa[q4 * 4 + 0] = v.x; sa[q4 * 4 + 1] = v.y; sa[q4 * 4 + 2] = v.z; sa[q4 * 4 + 3] = v.w;
-      }
+    for (int i = 0; i < NBW; ++i) {
+      float m = 0.f;
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
-        acc[i][0][q] = fmaf(part[i][0][q], sa[q] * sb0, acc[i][0][q]);
-        acc[i][1][q] = fmaf(part[i][1][q], sa[q] * sb1, acc[i][1][q]);
+        const float g = acc[i][0][q];
+        const float v = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * acc[i][1][q];
+        acc[i][0][q] = v;
+        m = fmaxf(m, fabsf(v));
       }
+      m = fmaxf(m, __shfl_xor(m, 32));
+      if (h == 0) amax[wn * FBM + (WB0 + i) * 32 + l31] = m;
+    }
+    __syncthreads();
+    uint32_t* const codes = reinterpret_cast<uint32_t*>(smem);       // [FBM] rows of 9 pieces
+#pragma unroll
+    for (int i = 0; i < NBW; ++i) {
+      const int r = (WB0 + i) * 32 + l31;
+      const float m = fmaxf(fmaxf(amax[r], amax[FBM + r]), fmaxf(amax[2 * FBM + r], amax[3 * FBM + r]));
+      const float scale = m > 0.f ? m / 448.0f : 1.0f;
+      if (wn == 0 && h == 0 && row0 + r < row1) hs_t[size_t(n0 / kQBlock) * rows_capacity + row0 + r] = scale;
+      // v / scale without the general division's scaling steps, for scales whose reciprocal is far
+      // from the ends of the range (the general division took 3 us of a tile)
+      const bool plain = __all(m == 0.f || (m > 0x1p-90f && m < 0x1p90f));
+      const float rs = __builtin_amdgcn_rcpf(scale);
+      auto quotient = [&](float v) {
+        if (!plain) return v / scale;
+        const float q = v * rs;
+        return fmaf(fmaf(-scale, q, v), rs, q);
+      };
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        float v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = fminf(fmaxf(quotient(acc[i][0][g * 4 + q]), -448.0f), 448.0f);
+        int c = __builtin_amdgcn_cvt_pk_fp8_f32(v[0], v[1], 0, false);        // round to nearest even
+        c = __builtin_amdgcn_cvt_pk_fp8_f32(v[2], v[3], c, true);
+        codes[r * 36 + wn * 8 + g * 2 + h] = uint32_t(c);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < (NB + 1) / 2; ++u) {
+      const int r = u * 64 + wave * 8 + (lane >> 3);
+      if (r < rows)
+        *reinterpret_cast<uint4*>(hq + size_t(row0 + r) * N + n0 + (lane & 7) * 16) = smem[r * 9 + (lane & 7)];
+    }
+  } else {
+    uint4* const turn = smem + wave * (2 * 32 * 9);
+    uint16_t* const cw = C + size_t(row0) * N + n0 + wn * 64;
+    const bool col_in = n0 + wn * 64 + (lane & 7) * 8 < N;
+#pragma unroll
+    for (int i = 0; i < NBW; ++i) {
+      uint4* const t = turn + (i & 1) * 32 * 9;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          reinterpret_cast<uint2*>(t + l31 * 9 + j * 4 + g)[h] =
+              make_uint2(pack_bf16(acc[i][j][g * 4], acc[i][j][g * 4 + 1]),
+                         pack_bf16(acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]));
+      asm volatile("" ::: "memory");               // the reads below see the writes above (same wavefront)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int r = u * 8 + (lane >> 3), row = (WB0 + i) * 32 + r;
+        const uint4 v = t[r * 9 + (lane & 7)];
+        if (row0 + row < row1 && col_in) *reinterpret_cast<uint4*>(cw + size_t(row) * N + (lane & 7) * 8) = v;
+      }
+      asm volatile("" ::: "memory");
     }
   }
-
-  // D layout: lane l, register q -> row (q/4)*8 + (l/32)*4 + q%4, col l%32
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int row = row0 + i * 64 + wm * 32 + (q >> 2) * 8 + h * 4 + (q & 3);
-      if (row >= row1) continue;
-      if (DUAL) {
-        const float g = acc[i][0][q], u = acc[i][1][q];
-        const float v = g / (1.0f + __expf(-g)) * u;
-        C[size_t(row) * N + n0 + wn * 32 + l31] = f32_to_bf16_bits_rne(v);
-      } else {
-        C[size_t(row) * N + n0 + wn * 64 + l31] = f32_to_bf16_bits_rne(acc[i][0][q]);
-        C[size_t(row) * N + n0 + wn * 64 + 32 + l31] = f32_to_bf16_bits_rne(acc[i][1][q]);
-      }
-    }
 }
 
 template <bool DUAL>
-__global__ __launch_bounds__(256, 2) void fp8act_gemm_kernel(
+__global__ __launch_bounds__(512) void fp8act_gemm_kernel(
     const uint8_t* __restrict__ A, const float* __restrict__ sA_t, int rows_capacity,
     const uint8_t* __restrict__ B0, const uint8_t* __restrict__ B1, const float* __restrict__ S0,
-    const float* __restrict__ S1, uint16_t* __restrict__ C, int N, int K,
-    const int32_t* __restrict__ tiles) {
-  extern __shared__ uint4 fsmem[];
+    const float* __restrict__ S1, uint16_t* __restrict__ C, uint8_t* __restrict__ hq, float* __restrict__ hs_t,
+    int N, int K, const int32_t* __restrict__ offsets, const int32_t* __restrict__ tiles) {
   // handed on as a generic pointer: with the LDS array named in the loop the
   // compiler drains every DMA in flight before each LDS read
-  const int n_ntiles = N / (DUAL ? 64 : 128);
-  const int mtile = blockIdx.x / n_ntiles, ntile = blockIdx.x % n_ntiles;
-  if (mtile >= tiles[0]) return;
+  extern __shared__ uint4 fsmem[];
+  constexpr int BN = DUAL ? 128 : 256;
+  const int n_ntiles = (N + BN - 1) / BN;
+  const int total = tiles[0] * n_ntiles, per_xcd = (total + 7) >> 3;
+  const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (int(blockIdx.x >> 3) >= per_xcd || logical >= total) return;
+  const int at = logical / n_ntiles;
+  const int ea = tiles[1 + kTileRec * at], first = tiles[4 + kTileRec * at];
+  const int cnt = tiles_of(offsets, ea, rows_capacity).count;
+  const int local = logical - first * n_ntiles;
+  const int gsz = 4 * n_ntiles, grp = local / gsz, rem = local - grp * gsz;
+  const int mc = min(cnt - grp * 4, 4);
+  const int ntile = rem / mc, mtile = first + grp * 4 + (rem - ntile * mc);
   const int e = tiles[1 + kTileRec * mtile], row0 = tiles[2 + kTileRec * mtile],
             row1 = tiles[3 + kTileRec * mtile];
-  if (row1 - row0 > 96)
-    fp8act_gemm_body<DUAL, true>(A, sA_t, rows_capacity, B0, B1, S0, S1, C, N, K, e, row0, row1, ntile, fsmem);
-  else
-    fp8act_gemm_body<DUAL, false>(A, sA_t, rows_capacity, B0, B1, S0, S1, C, N, K, e, row0, row1, ntile, fsmem);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#define MOE_TILE8(NB)                                                                                   \
+  case NB:                                                                                              \
+    if (wave < 4) fp8act_gemm_body<DUAL, NB, 0>(A, sA_t, rows_capacity, B0, B1, S0, S1, C, hq, hs_t, N, K, e, row0, row1, ntile * BN, wave, fsmem); \
+    else fp8act_gemm_body<DUAL, NB, 1>(A, sA_t, rows_capacity, B0, B1, S0, S1, C, hq, hs_t, N, K, e, row0, row1, ntile * BN, wave, fsmem);          \
+    break
+  switch ((row1 - row0 + 31) >> 5) {
+    MOE_TILE8(1);
+    MOE_TILE8(2);
+    MOE_TILE8(3);
+    MOE_TILE8(4);
+    MOE_TILE8(5);
+    MOE_TILE8(6);
+  }
+#undef MOE_TILE8
 }
 
 }  // namespace
 
-// workspace: tiles | x codes | x scales | hmid bf16 | hmid codes | hmid scales
+// workspace: tiles | x codes | x scales | (room for a bf16 intermediate, unused: callers' workspaces
+// keep their layout) | hmid codes | hmid scales
 struct Fp8ActWs {
   int32_t* tiles;
   uint8_t* xq;
   float* xs_t;
-  uint16_t* hmid;
   uint8_t* hq;
   float* hs_t;
   int max_tiles;
@@ -353,11 +510,11 @@ static Fp8ActWs carve_fp8act(void* ws, int rows_capacity, int n_experts, int H, 
   Fp8ActWs f;
   char* p = static_cast<char*>(ws);
   size_t off = 0;
-  f.max_tiles = rows_capacity / FBM + n_experts + 1;
+  f.max_tiles = rows_capacity / 128 + n_experts + 1;
   f.tiles = reinterpret_cast<int32_t*>(p + off); off += align_up(size_t(1 + kTileRec * f.max_tiles) * 4);
   f.xq = reinterpret_cast<uint8_t*>(p + off);    off += align_up(size_t(rows_capacity) * H);
   f.xs_t = reinterpret_cast<float*>(p + off);    off += align_up(size_t(H / kQBlock) * rows_capacity * 4);
-  f.hmid = reinterpret_cast<uint16_t*>(p + off); off += align_up(size_t(rows_capacity) * I * 2);
+  off += align_up(size_t(rows_capacity) * I * 2);
   f.hq = reinterpret_cast<uint8_t*>(p + off);    off += align_up(size_t(rows_capacity) * I);
   f.hs_t = reinterpret_cast<float*>(p + off);    off += align_up(size_t(I / kQBlock) * rows_capacity * 4);
   f.bytes = off;
@@ -399,13 +556,18 @@ static moe_status fp8act_run(const moe_config* cfg, int32_t n_experts_here, cons
   Fp8ActWs f = carve_fp8act(ws, rows_capacity, n_experts_here, H, I);
   if (ws_bytes < f.bytes) return MOE_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  constexpr int lds = (2 * FBM * 8 + 2 * FBN * 8) * 16 + 2 * FBM * 4;
+  constexpr int lds = 160 * 1024;
   auto k1 = fp8act_gemm_kernel<true>;
   auto k2 = fp8act_gemm_kernel<false>;
   static uint64_t opted1 = 0, opted2 = 0;
   lds_opt_in(reinterpret_cast<const void*>(k1), lds, opted1);
   lds_opt_in(reinterpret_cast<const void*>(k2), lds, opted2);
   const dim3 qgrid((rows_capacity + 3) / 4);
+  // as many tiles as the rows can come to, in eight equal runs.  (Lower tiles where 192 rows leave
+  // CUs without one, a shared expert of 1500 to 4500 rows, were slower: 300 -> 323 us a layer at
+  // 3000 tokens, I 512: they fetch the weights more often and take the CUs from the route beside.)
+  const int max_mt = rows_capacity / FBM + (n_experts_here < rows_capacity ? n_experts_here : rows_capacity);
+  auto grid = [&](int n_ntiles) { return dim3(unsigned((size_t(max_mt) * n_ntiles + 7) / 8 * 8)); };
   MOE_LAUNCH(MOE_K_FFN_TILES, fp8act_tiles_kernel, dim3(1), dim3(512), 0, s, offsets, n_experts_here,
              rows_capacity, f.tiles, f.max_tiles);
   const uint8_t* aq = static_cast<const uint8_t*>(xs_q);
@@ -416,14 +578,13 @@ static moe_status fp8act_run(const moe_config* cfg, int32_t n_experts_here, cons
     aq = f.xq;
     as = f.xs_t;
   }
-  MOE_LAUNCH(MOE_K_FFN_GEMM1, k1, dim3(size_t(f.max_tiles) * (I / 64)), dim3(256), lds, s, aq, as,
-             rows_capacity, static_cast<const uint8_t*>(w_gate), static_cast<const uint8_t*>(w_up),
-             s_gate, s_up, f.hmid, I, H, f.tiles);
-  MOE_LAUNCH(MOE_K_FFN_TILES, fp8act_quant_kernel, qgrid, dim3(256), 0, s, f.hmid, offsets,
-             n_experts_here, I, rows_capacity, f.hq, f.hs_t);
-  MOE_LAUNCH(MOE_K_FFN_GEMM2, k2, dim3(size_t(f.max_tiles) * (H / 128)), dim3(256), lds, s, f.hq, f.hs_t,
-             rows_capacity, static_cast<const uint8_t*>(w_down), static_cast<const uint8_t*>(nullptr),
-             s_down, static_cast<const float*>(nullptr), static_cast<uint16_t*>(ys), H, I, f.tiles);
+  MOE_LAUNCH(MOE_K_FFN_GEMM1, k1, grid(I / 128), dim3(512), lds, s, aq, as, rows_capacity,
+             static_cast<const uint8_t*>(w_gate), static_cast<const uint8_t*>(w_up), s_gate, s_up,
+             static_cast<uint16_t*>(nullptr), f.hq, f.hs_t, I, H, offsets, f.tiles);
+  MOE_LAUNCH(MOE_K_FFN_GEMM2, k2, grid((H + 255) / 256), dim3(512), lds, s, f.hq, f.hs_t, rows_capacity,
+             static_cast<const uint8_t*>(w_down), static_cast<const uint8_t*>(nullptr), s_down,
+             static_cast<const float*>(nullptr), static_cast<uint16_t*>(ys), static_cast<uint8_t*>(nullptr),
+             static_cast<float*>(nullptr), H, I, offsets, f.tiles);
   return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_DEVICE;
 }
 

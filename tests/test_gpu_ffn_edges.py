@@ -186,3 +186,15 @@ def test_bf16_k128_rules(counts, H, I):
     ids=lambda v: str(v) if isinstance(v, int) else "%dx%d" % (len(v), sum(v)))
 def test_fp32_many_tiles(counts, H, I):
     _ffn(counts, H, I, "f32")
+
+
+# Every workgroup finds its tile from the offsets, up to eight experts a lane: expert counts on
+# both sides of a lane's next expert, the first and last experts empty, one to three tiles each.
+@pytest.mark.parametrize("act", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 129, 449, 512])
+def test_tile_of_expert(n, act):
+    c = np.random.default_rng(n).integers(0, 3, n) * np.random.default_rng(n + 1).integers(1, 33, n)
+    c[n // 2] = 400
+    if n > 2:
+        c[0] = c[-1] = 0
+    _ffn(c.tolist(), 64, 72 if act == "f32" else 64, act)

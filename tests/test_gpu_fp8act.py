@@ -71,6 +71,21 @@ def test_fp8act_ffn_matches_oracle(name):
     assert np.abs(got - ref).mean() <= 1e-2 * np.abs(ref).max()
 
 
+# One to six 32-row blocks a tile, one and two tiles either side of 192 rows, row halves of unequal
+# length; one, two, three and five K blocks (fewer than the rings have stages, as many, more); one
+# and two column tiles of GEMM-2, the last one half empty.  Same bars as above.
+@pytest.mark.parametrize("H,I,counts", [
+    (128, 128, [1, 31, 32, 33]), (256, 128, [64, 65, 96, 97]), (384, 256, [128, 129, 160, 161]),
+    (640, 384, [191, 192, 193, 0]), (384, 640, [385, 3, 224, 0])])
+def test_fp8act_tile_edges(H, I, counts):
+    w = BASE.replace(name="f8a_edges", H=H, I=I, E=4, k=1, expert_lo=0, expert_hi=4, seed=76)
+    got, ref, n, _, _, _ = run_case(w, counts)
+    err = rel_err(got, ref)
+    print("H", H, "I", I, counts, "max|err|/max|ref| = %.3e" % err, flush=True)
+    assert err <= 6e-2, err
+    assert np.abs(got - ref).mean() <= 1e-2 * np.abs(ref).max()
+
+
 def test_fp8act_quantiser_is_bit_exact():
     """The first stage of the call (codes and scales of the input rows, read back
     from the workspace) against the oracle's quantiser: same fp32 decisions."""
