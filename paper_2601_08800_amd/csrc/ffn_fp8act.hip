@@ -265,6 +265,15 @@ __device__ __forceinline__ void fp8act_gemm_body(
   const float* const s0p = S0 + (size_t(e) * nnb + nb0) * nkb;
   const float* const s1p = DUAL ? S1 + (size_t(e) * nnb + nb0) * nkb : s0p;
 
+  // Weight block scales: lane l holds those of K blocks l, l + 64, ..  (A scalar load in every step
+  // misses its cache every sixteenth time, and the whole workgroup waits for memory.)
+  float sv0, sv1;
+  auto load_scales = [&](int kb) {
+    sv0 = s0p[min(kb + lane, nkb - 1)];
+    sv1 = s1p[min(kb + lane, nkb - 1)];
+  };
+  auto scale = [&](float v, int kb) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), kb & 63)); };
+  load_scales(0);
   // The two wavefronts of a SIMD (w and w + 4, the two row halves) take turns: in one phase a
   // wavefront issues loads and reads all fragments of a step, in the next it multiplies them; row
   // half 1 runs one phase behind row half 0.
@@ -296,7 +305,7 @@ __device__ __forceinline__ void fp8act_gemm_body(
   i32x8 fb[2][2], fa[NACC][2];                     // [sub-step][column block], [row block][sub-step]
   float sa[NACC];
   f32x16 part[2];                                  // sums of a K block, [column block]
-  float sb0 = s0p[0], sb1 = s1p[0], f1 = 0.f;      // f1: scale of part[1], which is added up late
+  float f1 = 0.f;      // f1: scale of part[1], which is added up late
 #pragma unroll
   for (int q = 0; q < 16; ++q) part[1][q] = 0.f;
   auto mma = [&](int i, int j) {
@@ -324,7 +333,11 @@ __device__ __forceinline__ void fp8act_gemm_body(
   for (int kb = 0; kb < nkb; ++kb) {
     if (kb + SA - 1 < nkb) issue_a(kb + SA - 1);
     if (kb + SB - 1 < nkb) issue_b(kb + SB - 1);
-    const float c0 = sb0, c1 = sb1;
+    if (kb > 0 && (kb & 63) == 0) {
+      load_scales(kb);
+      wait_vmcnt<0>();                             // here, so that no wait is needed where they are used
+    }
+    const float c0 = scale(sv0, kb), c1 = scale(sv1, kb);
     if constexpr (NBW > 0) {
       const uint4* const Bb = ringB + (kb % SB) * R::kB;
       const uint4* const Ab = ringA + (kb % SA) * R::kA + WB0 * 256;
@@ -346,9 +359,6 @@ __device__ __forceinline__ void fp8act_gemm_body(
       }
       add(NBW - 1, 1, f1);
     }
-    const int kn = kb + 1 < nkb ? kb + 1 : kb;
-    sb0 = s0p[kn];
-    sb1 = s1p[kn];
     if (WM == 1) landed(kb);
     phase_end(WM == 1);
     if constexpr (NBW > 0) {
