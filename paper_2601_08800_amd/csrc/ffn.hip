@@ -22,8 +22,9 @@
 // large launches ffn_f32_valu_kernel.
 // fp8 weights: the weight-streaming kernel widens the e4m3 codes to bf16 in
 // registers (exact) and multiplies the fp32 partial sum of each 128-deep K block
-// by the 128x128 block scale; the tall-tile kernel keeps the codes in its LDS
-// ring and rounds code * scale to bf16 on the way to the matrix unit.
+// by the 128x128 block scale; ffn_e4m3_kernel (a few dozen rows per expert) does the same up
+// to 64 rows a tile; above, and in the tall-tile kernel, which keeps the codes in its LDS
+// ring, code * scale is rounded to bf16 on the way to the matrix unit.
 #include <type_traits>
 
 #include "moe_internal.h"
@@ -226,6 +227,14 @@ __device__ __forceinline__ uint4 widen_scaled(uint2 c, float sc) {
   asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r.z) : "v"(p2[0] * sc), "v"(p2[1] * sc));
   asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r.w) : "v"(p3[0] * sc), "v"(p3[1] * sc));
   return r;
+}
+
+// Eight e4m3 codes -> eight bf16 values, exact.
+__device__ __forceinline__ uint4 widen_codes(uint2 c) {
+  return make_uint4(__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c.x, 1.0f, false)),
+                    __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c.x, 1.0f, true)),
+                    __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c.y, 1.0f, false)),
+                    __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c.y, 1.0f, true)));
 }
 
 // One part of a K-split tile: `parts` workgroups share the tile's K range, part
@@ -1239,6 +1248,359 @@ void launch_shortk(const void* hmid, const void* w_down, void* ys, int N, int K,
 #undef MOE_SHORTK
 }
 
+// --------------------------------- MFMA GEMM, e4m3 weights, up to 128 rows a tile
+// e4m3 weights with a few dozen rows per expert: the work is streaming the codes in, and a
+// tile is short of rows, not of weights.  Tile: up to 128 rows (NB 32-row blocks) x 256
+// weight rows (DUAL: 128 gate + the matching 128 up rows), K step 128 = one scale block = a
+// whole cache line of every weight row.  All eight wavefronts work on all rows: wavefront
+// (kh, wn) = (w/4, w%4) multiplies half kh of every K block with the 64 weight rows of
+// column block wn, and the two halves are added at the end.  (The tall-tile kernel leaves the
+// four wavefronts of its second row half without a row below 160 rows, and its K step of 64
+// reads half lines.)  Codes are read as 16 bytes and widened to bf16 by one instruction a
+// pair, exact; for up to 64 rows the block scale multiplies the fp32 sums of the K block,
+// above (where a second set of sums would not fit the registers) code * scale is rounded
+// to bf16 as in the tall-tile kernel.  The weights are the first operand, so a lane holds
+// columns of one row; output rows are turned around in LDS and stored whole.
+// Bound by nothing alone: 32 experts of 48 rows, hidden 7168, I 1024: GEMM-1 118, GEMM-2 62 us
+// (4.0 / 3.8 TB/s of codes) against 125 / 70; a stream of the same loads alone runs at 6 TB/s, the
+// same steps without loads take 90 us, and the two add up rather than overlap.  Whole layer
+// (us): 64 tokens 191 -> 162, 256 219 -> 209, 1531 349 -> 314, 2040 422 -> 372; hidden 4096, 16 of
+// 128 experts, I 1536, 1000 tokens 178 -> 163.  Tried: weights loaded by one half of the
+// wavefronts and activations by the other (deeper weight ring) 118 -> 125, all fragments a
+// step ahead 118 -> 122, block scales in scalar registers loaded step by step (no difference).
+template <int NB> struct RingE {
+  static constexpr int kB = 256 * 8, kA = NB * 32 * 16;            // 16-byte slots of a stage
+  static constexpr int kSB = NB == 1 ? 4 : 3;                      // weight stages
+  static constexpr int kSA = NB <= 2 ? kSB : kSB - 1;              // activation stages
+  static_assert((kSB * kB + kSA * kA) * 16 <= 160 * 1024, "LDS of a CU");
+};
+
+template <bool DUAL, int NB>
+__device__ __forceinline__ void e4m3_body(const uint16_t* __restrict__ A, const char* __restrict__ B0,
+                                          const char* __restrict__ B1, const float* __restrict__ s0p,
+                                          const float* __restrict__ s1p, uint16_t* __restrict__ C, int N,
+                                          int K, int row0, int row1, int n0, int wave, int kb0, int nkb,
+                                          const SplitJob& job, uint4* __restrict__ smem) {
+  using R = RingE<NB>;
+  constexpr int SA = R::kSA, SB = R::kSB, NLA = NB, NLB = 4, HALF = 128;
+  constexpr bool kExact = NB <= 2;
+  uint4* const ringB = smem;
+  uint4* const ringA = smem + SB * R::kB;
+  const int lane = threadIdx.x & 63, wn = wave & 3, kh = wave >> 2;
+  const int h = lane >> 5, l31 = lane & 31;
+  const int rows = row1 - row0;
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(A + size_t(row0) * K + kb0 * 128), 0, ((rows - 1) * K + nkb * 128) * 2, 0x00020000);
+  const int brows = N - n0 < HALF * (DUAL ? 1 : 2) ? N - n0 : HALF * (DUAL ? 1 : 2);
+  const __amdgpu_buffer_rsrc_t rb0 = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char*>(B0 + size_t(n0) * K + kb0 * 128), 0, (brows - 1) * K + nkb * 128, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rb1 = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char*>((DUAL ? B1 : B0) + size_t(n0) * K + kb0 * 128), 0, (brows - 1) * K + nkb * 128, 0x00020000);
+  // weights: load q fills rows q*64 + wave*8 .. +8 of the stage, lane l slot l%8 of row l/8
+  const int brow = wave * 8 + (lane >> 3), bpiece = (lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7);
+  // activations: load q fills rows q*32 + wave*4 .. +4, lane l slot l%16 of row l/16
+  const int arow = wave * 4 + (lane >> 4), apiece = (lane & 15) ^ (arow & 15);
+  int boff[4], aoff[NLA];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) boff[q] = ((DUAL ? q & 1 : q) * 64 + brow) * K + bpiece * 16;
+#pragma unroll
+  for (int q = 0; q < NLA; ++q) aoff[q] = ((q * 32 + arow) * K + apiece * 8) * 2;
+  auto issue_b = [&](int kb) {
+    uint4* const st = ringB + (kb % SB) * R::kB + wave * 64;
+#pragma unroll
+    for (int q = 0; q < NLB; ++q) {
+      if (DUAL && q >= 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(rb1, (lptr_t)(st + q * 512), 16, boff[q], kb * 128, 0, 0);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(rb0, (lptr_t)(st + q * 512), 16, boff[q], kb * 128, 0, 0);
+    }
+  };
+  auto issue_a = [&](int kb) {
+    uint4* const st = ringA + (kb % SA) * R::kA + wave * 64;
+#pragma unroll
+    for (int q = 0; q < NLA; ++q)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lptr_t)(st + q * 512), 16, aoff[q], kb * 256, 0, 0);
+  };
+  f32x16 acc[NB][2];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+  const int brow0 = DUAL ? wn * 32 : wn * 64;
+  const int brow1 = DUAL ? HALF + wn * 32 : wn * 64 + 32;
+  // weight pieces kh*4 + t*2 + h of row l%32 (sixteen codes), activation pieces twice that, +1
+  int bat[2], aat[2][2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int p = kh * 4 + t * 2 + h;
+    bat[t] = l31 * 8 + (p ^ ((l31 >> 1) & 7));
+#pragma unroll
+    for (int u = 0; u < 2; ++u) aat[t][u] = l31 * 16 + ((p * 2 + u) ^ (l31 & 15));
+  }
+  // Block scales: lane l holds those of K blocks l, l + 64, ..  (A scalar load in every step misses
+  // its cache every sixteenth time, and the whole workgroup waits for memory.)
+  float sv0 = s0p[min(lane, nkb - 1)], sv1 = s1p[min(lane, nkb - 1)];
+  auto scale = [&](float v, int kb) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), kb & 63)); };
+  auto next_scales = [&](int kb) {
+    if (kb > 0 && (kb & 63) == 0) {
+      sv0 = s0p[min(kb + lane, nkb - 1)];
+      sv1 = s1p[min(kb + lane, nkb - 1)];
+      wait_vmcnt<0>();                               // here, so that no wait is needed where they are used
+    }
+  };
+  auto read_codes = [&](int kb, uint4 (&code)[2][2]) {
+    const uint4* const Bb = ringB + (kb % SB) * R::kB;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      code[0][t] = Bb[brow0 * 8 + bat[t]];
+      code[1][t] = Bb[brow1 * 8 + bat[t]];
+    }
+  };
+#pragma unroll
+  for (int g = 0; g < SB - 1; ++g) {
+    if (g < SA - 1 && g < nkb) issue_a(g);
+    if (g < nkb) issue_b(g);
+  }
+  constexpr int kYounger = SA == SB ? (SB - 2) * (NLB + NLA) : NLB + (SA - 2) * (NLB + NLA);
+  for (int kb = 0; kb < nkb; ++kb) {
+    if (kb + SB - 2 < nkb) wait_vmcnt<kYounger>(); else wait_vmcnt<0>();
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    const uint4* const Ab = ringA + (kb % SA) * R::kA;
+    uint4 code[2][2];
+    read_codes(kb, code);
+    if (kb + SA - 1 < nkb) issue_a(kb + SA - 1);
+    if (kb + SB - 1 < nkb) issue_b(kb + SB - 1);
+    next_scales(kb);
+    const float c0 = scale(sv0, kb), c1 = scale(sv1, kb);
+    uint4 fb[2][2][2];                               // [column block][t][u]: eight bf16 codes, exact
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const uint2 lo = make_uint2(code[j][t].x, code[j][t].y), hi = make_uint2(code[j][t].z, code[j][t].w);
+        if constexpr (kExact) {
+          fb[j][t][0] = widen_codes(lo);
+          fb[j][t][1] = widen_codes(hi);
+        } else {
+          fb[j][t][0] = widen_scaled(lo, j == 0 ? c0 : c1);
+          fb[j][t][1] = widen_scaled(hi, j == 0 ? c0 : c1);
+        }
+      }
+    uint4 fa[2][2][2];                               // [set][t][u]: a row block ahead
+    auto read_a = [&](int i) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) fa[i & 1][t][u] = Ab[i * 512 + aat[t][u]];
+    };
+    read_a(0);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      if (i + 1 < NB) read_a(i + 1);
+      f32x16 part[2];
+      if constexpr (kExact) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int q = 0; q < 16; ++q) part[j][q] = 0.f;
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            f32x16& c = kExact ? part[j] : acc[i][j];
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[j][t][u]),
+                                                        __builtin_bit_cast(bf16x8, fa[i & 1][t][u]), c, 0, 0, 0);
+          }
+      if constexpr (kExact) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          acc[i][0][q] = fmaf(part[0][q], c0, acc[i][0][q]);
+          acc[i][1][q] = fmaf(part[1][q], c1, acc[i][1][q]);
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // The two wavefronts of a column block (one half of every K block each) add their sums:
+  // half kh finishes registers 8*kh .. +8.  D layout (weights first): lane l holds activation row
+  // l%32, register q weight row (q/4)*8 + (l/32)*4 + q%4.
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  // A K-split part leaves its sums in the workspace and the part that arrives last adds all
+  // parts in the order of their K windows and carries on (as in the tall-tile kernel).
+  if (job.parts > 1) {
+    uint64_t* const mine = reinterpret_cast<uint64_t*>(job.partial + size_t(job.slot) * kPartFloats) + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          __hip_atomic_store(mine + ((i * 2 + j) * 8 + q) * 512,
+                             uint64_t(__float_as_uint(acc[i][j][2 * q])) |
+                                 (uint64_t(__float_as_uint(acc[i][j][2 * q + 1])) << 32),
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    int32_t* const flag = reinterpret_cast<int32_t*>(smem);
+    if (threadIdx.x == 0) *flag = atomicAdd(job.ticket, 1);
+    __syncthreads();
+    if (*flag != job.parts - 1) return;
+    __syncthreads();                                   // the flag's place is used again below
+    const uint64_t* const all = reinterpret_cast<const uint64_t*>(job.partial + size_t(job.slot0) * kPartFloats) + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        uint64_t w[kSplitMax][8];
+#pragma unroll
+        for (int p = 0; p < kSplitMax; ++p)
+          if (p < job.parts) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+              w[p][q] = __hip_atomic_load(all + size_t(p) * (kPartFloats / 2) + ((i * 2 + j) * 8 + q) * 512,
+                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+#pragma unroll
+        for (int p = 0; p < kSplitMax; ++p)
+          if (p < job.parts) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+              acc[i][j][2 * q] += __uint_as_float(uint32_t(w[p][q]));
+              acc[i][j][2 * q + 1] += __uint_as_float(uint32_t(w[p][q] >> 32));
+            }
+          }
+      }
+  }
+  float* const red = reinterpret_cast<float*>(smem);   // [wavefront][NB][2][8][64]
+  float v[NB][2][8];
+  // (two copies: a register index that depends on kh would be an indexed access per value)
+  auto exchange = [&](auto kh_c) {
+    constexpr int Q = decltype(kh_c)::value * 8;
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          red[(((wave ^ 4) * NB + i) * 2 + j) * 512 + q * 64 + lane] = acc[i][j][8 - Q + q];
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[i][j][q] = acc[i][j][Q + q] + red[((wave * NB + i) * 2 + j) * 512 + q * 64 + lane];
+  };
+  if (kh == 0) exchange(std::integral_constant<int, 0>{});
+  else exchange(std::integral_constant<int, 1>{});
+  __syncthreads();
+  // the output tile, turned around in LDS: whole rows of it are stored
+  constexpr int CP = DUAL ? 16 : 32, P = CP + 1;      // 16-byte pieces per row, and pitch
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < (DUAL ? 1 : 2); ++j)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        float o[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = DUAL ? silu_mul_fast(v[i][0][g * 4 + q], v[i][1][g * 4 + q]) : v[i][j][g * 4 + q];
+        // columns wn*32|64 + j*32 + (2 kh + g)*8 + h*4 .. +4
+        reinterpret_cast<uint2*>(smem + (i * 32 + l31) * P + wn * (CP / 4) + j * 4 + 2 * kh + g)[h] =
+            make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
+      }
+  __syncthreads();
+  constexpr int RPT = 512 / CP;                        // rows per turn of the workgroup
+#pragma unroll
+  for (int u = 0; u < NB * 32 / RPT; ++u) {
+    const int r = u * RPT + threadIdx.x / CP, piece = threadIdx.x % CP, col = n0 + piece * 8;
+    if (r < rows && col < N) *reinterpret_cast<uint4*>(C + size_t(row0 + r) * N + col) = smem[r * P + piece];
+  }
+}
+
+template <bool DUAL>
+__global__ __launch_bounds__(512) void ffn_e4m3_kernel(
+    const uint16_t* __restrict__ A, const char* __restrict__ B0, const char* __restrict__ B1,
+    const float* __restrict__ S0, const float* __restrict__ S1, uint16_t* __restrict__ C, int N, int K,
+    const int32_t* __restrict__ tiles, float* __restrict__ partial, int32_t* __restrict__ tickets) {
+  constexpr int BN = DUAL ? 128 : 256;
+  extern __shared__ uint4 smem[];
+  const int n_ntiles = (N + BN - 1) / BN;
+  const int total = tiles[0] * n_ntiles, nkb = K / 128, pid = blockIdx.x;
+  // the leftover tiles of the last round are cut along K (see "Leftover tiles" above)
+  const int left = total % kCUs;
+  int parts = 1;
+  if (partial && left > 0 && left <= kCUs / 2) {
+    parts = kCUs / left;
+    parts = parts < kSplitMax ? parts : kSplitMax;
+    const int cap = nkb / (kSplitMinSteps / 2);
+    parts = parts < cap ? parts : cap;
+  }
+  int logical, kb0 = 0, kb1 = nkb;
+  SplitJob job{1, 0, 0, partial, tickets};
+  if (parts >= 2) {
+    const int full = total - left;
+    if (pid < full) {
+      logical = (pid & 7) * (full >> 3) + (pid >> 3);
+    } else {
+      const int q = pid - full;
+      if (q >= left * parts) return;
+      const int j = q / parts, part = q - j * parts;
+      logical = full + j;
+      kb0 = part * nkb / parts;
+      kb1 = (part + 1) * nkb / parts;
+      job = SplitJob{parts, q, j * parts, partial, tickets + j};
+    }
+  } else {
+    const int per_xcd = (total + 7) >> 3;
+    logical = (pid & 7) * per_xcd + (pid >> 3);
+    if ((pid >> 3) >= per_xcd || logical >= total) return;
+  }
+  int mtile = logical / n_ntiles;
+  const int first = tiles[4 + kTileRec * mtile], cnt = tiles[5 + kTileRec * mtile];
+  const int local = logical - first * n_ntiles;
+  const int gsz = 4 * n_ntiles, grp = local / gsz, rem = local - grp * gsz;
+  const int left_m = cnt - grp * 4, mc = left_m < 4 ? left_m : 4;
+  const int ntile = rem / mc;
+  mtile = first + grp * 4 + (rem - ntile * mc);
+  const int e = tiles[1 + kTileRec * mtile], row0 = tiles[2 + kTileRec * mtile], row1 = tiles[3 + kTileRec * mtile];
+  const int n0 = ntile * BN, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const char* const b0 = B0 + size_t(e) * N * K;
+  const char* const b1 = DUAL ? B1 + size_t(e) * N * K : nullptr;
+  const int nnb = N / 128;
+  int nb = (n0 + (DUAL ? 0 : (wave & 3) * 64)) / 128;
+  nb = nb < nnb ? nb : nnb - 1;
+  const float* const s0p = S0 + (size_t(e) * nnb + nb) * nkb + kb0;
+  const float* const s1p = DUAL ? S1 + (size_t(e) * nnb + nb) * nkb + kb0 : s0p;
+  switch ((row1 - row0 + 31) >> 5) {
+    case 1: e4m3_body<DUAL, 1>(A, b0, b1, s0p, s1p, C, N, K, row0, row1, n0, wave, kb0, kb1 - kb0, job, smem); break;
+    case 2: e4m3_body<DUAL, 2>(A, b0, b1, s0p, s1p, C, N, K, row0, row1, n0, wave, kb0, kb1 - kb0, job, smem); break;
+    case 3: e4m3_body<DUAL, 3>(A, b0, b1, s0p, s1p, C, N, K, row0, row1, n0, wave, kb0, kb1 - kb0, job, smem); break;
+    default: e4m3_body<DUAL, 4>(A, b0, b1, s0p, s1p, C, N, K, row0, row1, n0, wave, kb0, kb1 - kb0, job, smem); break;
+  }
+}
+
+template <bool DUAL>
+void launch_e4m3(const uint16_t* A, const void* B0, const void* B1, const float* S0, const float* S1, uint16_t* C,
+                 int N, int K, int n_experts, const int32_t* tiles, int max_mt, const FfnWs& ws, hipStream_t s) {
+  constexpr int lds = 160 * 1024, BN = DUAL ? 128 : 256;
+  // room for the parts of the leftover tiles behind the whole tiles
+  const int grid = (max_mt * ((N + BN - 1) / BN) + 7) / 8 * 8 + kCUs;
+  static uint64_t opted = 0;
+  auto k = ffn_e4m3_kernel<DUAL>;
+  lds_opt_in(reinterpret_cast<const void*>(k), lds, opted);
+  MOE_LAUNCH(DUAL ? MOE_K_FFN_GEMM1 : MOE_K_FFN_GEMM2, k, dim3(grid), dim3(512), lds, s, A,
+             static_cast<const char*>(B0), static_cast<const char*>(B1), S0, S1, C, N, K, tiles,
+             n_experts > 1 ? ws.partial : static_cast<float*>(nullptr),
+             ws.tickets + (DUAL ? 0 : kSplitTickets));
+}
+
 // ------------------------------------------------------------ fp32 GEMM
 // fp32 layers on v_mfma_f32_32x32x2_f32 (fp32 products and sums).  Tile 32 rows x
 // 32 output columns (DUAL: with the matching up rows).  Operands go global -> LDS
@@ -1474,7 +1836,7 @@ __global__ __launch_bounds__(256) void ffn_f32_valu_kernel(const float* __restri
 }
 
 // Which kernel runs each GEMM of a call, and the height of its M tiles.
-enum GemmKind { kGemmF32, kGemmF32Valu, kGemmStream, kGemmTall, kGemmWide, kGemmShortK };
+enum GemmKind { kGemmF32, kGemmF32Valu, kGemmStream, kGemmTall, kGemmWide, kGemmShortK, kGemmE4m3 };
 struct FfnPlan {
   GemmKind g1, g2;
   int bm1, bm2;
@@ -1560,6 +1922,18 @@ FfnPlan plan_ffn(const moe_config& c, int n_experts, int rows_capacity) {
   else if (avg <= 12) { p.g2 = kGemmStream; p.bm2 = 32; }
   else if (avg <= 96 && wide) { p.g2 = kGemmWide; p.bm2 = 128; }
   else { p.g2 = kGemmTall; p.bm2 = ragged && avg >= 128 && tiles_of(128, H, 256) <= kCUs ? 128 : 256; }
+  // e4m3 weights (I and H are multiples of 128) with up to 64 rows per expert to expect, if the
+  // rows were spread over all experts of the layer (an EP share's capacity holds them all): the
+  // kernel for short tiles.  128 experts, hidden 2048, I 768: 512 tokens (32 rows) 178 -> 173 us, 1000 (62)
+  // 209 / 209, 2000 (125) 318 / 326; 32 of 256 experts, hidden 7168, I 1024: 2040 tokens (64 rows) 422 -> 372,
+  // 4000 (125) 613 / 638.  A single expert (the shared one, which runs beside the routed path) takes
+  // it unsplit from 48 tiles on: its workgroups then leave the other CUs to the route (1531 tokens,
+  // 96 tiles: 314 us a layer, with the tiles cut along K 346; 256 tokens, 24 tiles: 233 unsplit, 222 split,
+  // 209 on the tall tiles; 512 tokens with given routing, 40 tiles: 316 unsplit, 258 split).
+  if (fp8 && avg > 12 && rows_capacity / c.n_experts <= 64) {
+    if (n_experts > 1 || tiles_of(128, I, 128) >= 48) { p.g1 = kGemmE4m3; p.bm1 = 128; }
+    if (n_experts > 1 || tiles_of(128, H, 256) >= 48) { p.g2 = kGemmE4m3; p.bm2 = 128; }
+  }
   return p;
 }
 
@@ -1580,6 +1954,11 @@ void launch_gemm(GemmKind kind, int bm, const uint16_t* A, const void* B0, const
     launch_shortk(A, B0, C, N, K, tiles, max_mt, s);
     return;
   }
+  if constexpr (F8)
+    if (kind == kGemmE4m3) {
+      launch_e4m3<DUAL>(A, B0, B1, S0, S1, C, N, K, n_experts, tiles, max_mt, ws, s);
+      return;
+    }
   constexpr int lds = 160 * 1024;         // all of a CU's LDS: the rings of the tallest tile fill it
   const bool wide = !DUAL && kind == kGemmWide;
   const int BN = DUAL ? 128 : (wide ? 512 : 256);

@@ -198,3 +198,14 @@ def test_tile_of_expert(n, act):
     if n > 2:
         c[0] = c[-1] = 0
     _ffn(c.tolist(), 64, 72 if act == "f32" else 64, act)
+
+
+# e4m3 weights, 13 to 64 rows per expert on average: one to four 32-row blocks a tile and two tiles
+# an expert, one to seven K blocks (fewer than a ring has stages, as many, more), column tiles of
+# GEMM-2 half empty; and leftover tiles cut along K (26 K blocks: two parts) in GEMM-1.
+@pytest.mark.parametrize("counts,H,I", [
+    ([1, 31, 32, 33, 0, 64, 65, 30], 128, 256), ([96, 97, 128, 129, 0, 5, 20, 2], 384, 384),
+    ([16, 200, 0, 1], 640, 896), ([40, 70, 0, 100], 3328, 128)])
+def test_e4m3_short_tiles(counts, H, I):
+    assert 12 < sum(counts) // len(counts) <= 64
+    check_ffn(counts, H, I, TOL["fp8"], weight_dtype="fp8")
