@@ -99,9 +99,11 @@ static_assert(size_t(kPartFloats) * 4 == kFfnPartBytes, "partial-sum slot size")
 // rows) instead of full tiles plus a short tail.  One thread per expert (512 at most); the
 // launch is one workgroup's latency chain in front of GEMM-1, so the scan runs in registers
 // (DPP) and an expert's thread writes its tiles by itself when no expert has more than four;
-// else one thread per tile looks its expert up.  One token (128 experts) 3.1 -> 2.2 us, 64 fp32 tokens (8)
-// 2.5 -> 1.9, 65 536 tokens (2100 tiles) 10.1 -> 6.8, behind a dispatch of a few MB 4.6 either way, against a scan by one
-// wavefront over shared memory and a look-up for every tile.
+// else one thread per tile looks its expert up.  Against a scan by one wavefront over shared
+// memory and a look-up for every tile: one token (128 experts) 3.1 -> 2.2 us, 64 fp32 tokens (8
+// experts) 2.5 -> 1.9, 65 536 tokens (2100 tiles) 10.1 -> 6.8; behind a dispatch of a few MB 4.6
+// either way.  (No table, every workgroup scanning the offsets: 0.8 us a tile, 65 536 tokens
+// 5356 -> 5452 us.)
 constexpr int kTileThreads = 512, kOwnTiles = 4;
 // Lanes' inclusive sums: shifts inside the rows of 16 lanes, then the rows' sums.
 __device__ __forceinline__ int wave_incl_sum(int v) {
@@ -167,9 +169,11 @@ __global__ __launch_bounds__(kTileThreads) void ffn_tiles_kernel(const int32_t* 
       if (i < count && first + i < n_tiles) write(first + i, e, lo, hi, first);
     return;
   }
-  start[e] = first;
-  off[e] = lo;
-  if (e == n_experts - 1) off[n_experts] = hi;
+  if (e < n_experts) {                               // (the next thread, of another wavefront, must not touch off[n_experts])
+    start[e] = first;
+    off[e] = lo;
+    if (e == n_experts - 1) off[n_experts] = hi;
+  }
   __syncthreads();
   // one thread per tile: its expert is the last one whose first tile is <= t
   for (int t = e; t < n_tiles; t += kTileThreads) {

@@ -200,6 +200,15 @@ def test_tile_of_expert(n, act):
     _ffn(c.tolist(), 64, 72 if act == "f32" else 64, act)
 
 
+# Tables in which a thread per tile looks its expert up (more than four tiles of an expert), the
+# last expert with rows of its own on both sides of a wavefront's last expert.
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 128, 192, 512])
+def test_tile_look_up_last_expert(n):
+    c = np.random.default_rng(n).integers(0, 3, n)
+    c[0], c[-1] = 170, 333
+    _ffn(c.tolist(), 64, 72, "f32")
+
+
 # e4m3 weights, 13 to 64 rows per expert on average: one to four 32-row blocks a tile and two tiles
 # an expert, one to seven K blocks (fewer than a ring has stages, as many, more), column tiles of
 # GEMM-2 half empty; and leftover tiles cut along K (26 K blocks: two parts) in GEMM-1.
