@@ -1284,7 +1284,7 @@ void launch_shortk(const void* hmid, const void* w_down, void* ys, int N, int K,
 // Bound by nothing alone: 32 experts of 48 rows, hidden 7168, I 1024: GEMM-1 118, GEMM-2 62 us
 // (4.0 / 3.8 TB/s of codes) against 125 / 70; a stream of the same loads alone runs at 6 TB/s, the
 // same steps without loads take 90 us, and the two add up rather than overlap.  Whole layer
-// (us): 64 tokens 191 -> 162, 256 219 -> 209, 1531 349 -> 314, 2040 422 -> 372; hidden 4096, 16 of
+// (us): 64 tokens 191 -> 162, 700 295 -> 283, 1531 349 -> 314, 2040 422 -> 372; hidden 4096, 16 of
 // 128 experts, I 1536, 1000 tokens 178 -> 163.  Tried: weights loaded by one half of the
 // wavefronts and activations by the other (deeper weight ring) 118 -> 125, all fragments a
 // step ahead 118 -> 122, block scales in scalar registers loaded step by step (no difference).
@@ -1950,7 +1950,11 @@ FfnPlan plan_ffn(const moe_config& c, int n_experts, int rows_capacity) {
   // it unsplit from 48 tiles on: its workgroups then leave the other CUs to the route (1531 tokens,
   // 96 tiles: 314 us a layer, with the tiles cut along K 346; 256 tokens, 24 tiles: 233 unsplit, 222 split,
   // 209 on the tall tiles; 512 tokens with given routing, 40 tiles: 316 unsplit, 258 split).
-  if (fp8 && avg > 12 && rows_capacity / c.n_experts <= 64) {
+  // From five to fifteen rows the tall tiles stay for several experts: a skewed batch then has one
+  // or two experts of full 128-row tiles, whose K loop is the launch (256 tokens, Zipf routing with 241
+  // and 140 rows in the hottest experts: 219 us a layer, 244 here; evenly routed 219 / 209).
+  const int spread = rows_capacity / c.n_experts;
+  if (fp8 && avg > 12 && spread <= 64 && (n_experts == 1 || spread <= 4 || spread >= 16)) {
     if (n_experts > 1 || tiles_of(128, I, 128) >= 48) { p.g1 = kGemmE4m3; p.bm1 = 128; }
     if (n_experts > 1 || tiles_of(128, H, 256) >= 48) { p.g2 = kGemmE4m3; p.bm2 = 128; }
   }
