@@ -22,12 +22,14 @@
 // large launches ffn_f32_valu_kernel.
 // fp8 weights: the weight-streaming kernel widens the e4m3 codes to bf16 in
 // registers (exact) and multiplies the fp32 partial sum of each 128-deep K block
-// by the 128x128 block scale; ffn_e4m3_kernel (a few dozen rows per expert) does the same up
-// to 64 rows a tile; above, and in the tall-tile kernel, which keeps the codes in its LDS
-// ring, code * scale is rounded to bf16 on the way to the matrix unit.
+// by the 128x128 block scale, and so do the short tiles of up to 64 rows that the tall-tile
+// kernel has in the place of its own for a few dozen rows per expert (e4m3_body, chosen on the
+// device: short_tile_rows); in those of up to 96 rows and in the tall ones, which keep the codes
+// in their LDS ring, code * scale is rounded to bf16 on the way to the matrix unit.
 #include <type_traits>
 
 #include "moe_internal.h"
+#include "tile_rules.h"
 #include "shortk_layout.h"
 
 namespace moe {
@@ -76,16 +78,14 @@ __device__ __forceinline__ float silu_mul_plain(float g, float u) {
 }
 
 // ------------------------------------------------------------- tile table
-// tiles[0] = number of M tiles; then per tile a record (expert, first row, end
+// tiles[0] = number of M tiles (| kShortTiles); then per tile a record (expert, first row, end
 // row, index of the expert's first tile, number of tiles of the expert).
+constexpr int kShortTiles = 1 << 30;          // the tiles are e4m3_body's
 constexpr int kTileRec = 5;
 // K-split of leftover tiles (see ffn_gemm8w_kernel): at most this many tiles are
 // split, into at most kSplitMax parts of at least kSplitMinSteps K steps, and all
-// parts together are at most one workgroup per CU.
-constexpr int kCUs = 256;
+// parts together are at most one workgroup per CU (split_parts).
 constexpr int kSplitTickets = 256;
-constexpr int kSplitMax = 4;
-constexpr int kSplitMinSteps = 24;
 constexpr int kPartFloats = 512 * 128;        // fp32 accumulators of one workgroup
 static_assert(kSplitTickets == kFfnSplitSlots && kCUs <= kFfnSplitSlots, "workspace holds one slot per part");
 static_assert(size_t(kPartFloats) * 4 == kFfnPartBytes, "partial-sum slot size");
@@ -103,7 +103,8 @@ static_assert(size_t(kPartFloats) * 4 == kFfnPartBytes, "partial-sum slot size")
 // memory and a look-up for every tile: one token (128 experts) 3.1 -> 2.2 us, 64 fp32 tokens (8
 // experts) 2.5 -> 1.9, 65 536 tokens (2100 tiles) 10.1 -> 6.8; behind a dispatch of a few MB 4.6
 // either way.  (No table, every workgroup scanning the offsets: 0.8 us a tile, 65 536 tokens
-// 5356 -> 5452 us.)
+// 5356 -> 5452 us.)  Where the GEMM has a choice of tiles, their numbers at all heights come
+// out of the same scan (0.5 us).
 constexpr int kTileThreads = 512, kOwnTiles = 4;
 // Lanes' inclusive sums: shifts inside the rows of 16 lanes, then the rows' sums.
 __device__ __forceinline__ int wave_incl_sum(int v) {
@@ -116,21 +117,25 @@ __device__ __forceinline__ int wave_incl_sum(int v) {
   return v;
 }
 
+// The table of one GEMM: tiles of bm rows, or short ones.
+struct TileJob {
+  int32_t* tiles;
+  int bm;
+  ShortTiles alt;
+};
+
 __global__ __launch_bounds__(kTileThreads) void ffn_tiles_kernel(const int32_t* __restrict__ offsets,
-                                                       int n_experts, int bm, int rows_capacity,
-                                                       int32_t* __restrict__ tiles, int max_tiles,
-                                                       int bm_second,
-                                                       int32_t* __restrict__ tiles_second,
+                                                       int n_experts, int rows_capacity, int max_tiles,
+                                                       TileJob job, TileJob second,
                                                        int32_t* __restrict__ tickets) {
   __shared__ int32_t start[kTileThreads + 1];
   __shared__ int32_t off[kTileThreads + 1];
-  __shared__ int32_t wave_sum[kTileThreads / 64];
+  __shared__ int4 wave_sum[kTileThreads / 64];
   const int e = threadIdx.x, lane = e & 63, wave = e >> 6;
-  // a second workgroup, when launched, builds a second table with its own tile height
-  if (blockIdx.x == 1) {
-    bm = bm_second;
-    tiles = tiles_second;
-  }
+  // a second workgroup, when launched, builds a second table
+  if (blockIdx.x == 1) job = second;
+  int32_t* const __restrict__ tiles = job.tiles;
+  int bm = job.bm;
   int lo = 0, hi = 0;
   if (e < n_experts) {
     lo = min(max(offsets[e], 0), rows_capacity);
@@ -139,20 +144,40 @@ __global__ __launch_bounds__(kTileThreads) void ffn_tiles_kernel(const int32_t* 
   // arrival counters of the K-split tiles of the two GEMM launches that follow
   static_assert(kTileThreads == 2 * kSplitTickets, "one counter per thread");
   if (blockIdx.x == 0) tickets[e] = 0;
-  const int count = hi > lo ? int(unsigned(hi - lo + bm - 1) / unsigned(bm)) : 0;
-  const int incl = wave_incl_sum(count);
-  if (lane == 63) wave_sum[wave] = incl;
-  const bool look_up = __syncthreads_or(count > kOwnTiles);
-  int before = 0, total = 0;
+  // The expert's tiles at the height bm and, where the GEMM has the choice, at 64 and 96 rows.
+  const int rows = max(hi - lo, 0);
+  int count = int(unsigned(rows + bm - 1) / unsigned(bm)), incl = wave_incl_sum(count);
+  const int count64 = (rows + 63) >> 6, count96 = int(unsigned(rows + 95) / 96u);
+  int incl64 = 0, incl96 = 0, many = __any(count > kOwnTiles) ? 1 : 0;
+  if (job.alt.nt) {
+    incl64 = wave_incl_sum(count64);
+    incl96 = wave_incl_sum(count96);
+    many |= (__any(count64 > kOwnTiles) ? 2 : 0) | (__any(count96 > kOwnTiles) ? 4 : 0) |
+            (__any(rows > 128 * count) ? 8 : 0) | (__any(rows > 192 * count) ? 16 : 0);
+  }
+  if (lane == 63) wave_sum[wave] = make_int4(incl, incl64, incl96, many);
+  __syncthreads();
+  int4 sum[kTileThreads / 64], all = make_int4(0, 0, 0, 0);
 #pragma unroll
   for (int w = 0; w < kTileThreads / 64; ++w) {
-    const int n = wave_sum[w];
-    before += w < wave ? n : 0;
-    total += n;
+    sum[w] = wave_sum[w];
+    all = make_int4(all.x + sum[w].x, all.y + sum[w].y, all.z + sum[w].z, all.w | sum[w].w);
   }
+  const int chosen = job.alt.nt ? short_tile_rows(job.alt, n_experts, all.y, all.z, all.x, all.w & 8, all.w & 16) : 0;
+  if (chosen) {
+    bm = chosen;
+    count = chosen == 64 ? count64 : count96;
+    incl = chosen == 64 ? incl64 : incl96;
+  }
+  const int total = chosen == 0 ? all.x : (chosen == 64 ? all.y : all.z);
+  const bool look_up = all.w & (chosen == 0 ? 1 : (chosen == 64 ? 2 : 4));
+  int before = 0;
+#pragma unroll
+  for (int w = 0; w < kTileThreads / 64; ++w)
+    before += w < wave ? (chosen == 0 ? sum[w].x : (chosen == 64 ? sum[w].y : sum[w].z)) : 0;
   const int first = before + incl - count;           // experts past the last one: `total`
   const int n_tiles = total < max_tiles ? total : max_tiles;
-  if (e == 0) tiles[0] = n_tiles;
+  if (e == 0) tiles[0] = n_tiles | (chosen ? kShortTiles : 0);
   auto write = [&](int t, int expert, int rlo, int rhi, int t0) {
     const int m = rhi - rlo, nt = int(unsigned(m + bm - 1) / unsigned(bm));
     const int step = (int(unsigned(m + nt - 1) / unsigned(nt)) + 31) / 32 * 32;
@@ -795,6 +820,302 @@ __device__ __forceinline__ void gemm8w_tile(const uint16_t* A, const char* Be0, 
   }
 }
 
+// ----------------------------- MFMA GEMM, e4m3 weights, short tiles: up to 96 rows
+// e4m3 weights with a few dozen rows per expert: the work is streaming the codes in, and a
+// tile is short of rows, not of weights.  Tile: up to 96 rows (NB 32-row blocks) x 256
+// weight rows (DUAL: 128 gate + the matching 128 up rows), K step 128 = one scale block = a
+// whole cache line of every weight row.  All eight wavefronts work on all rows: wavefront
+// (kh, wn) = (w/4, w%4) multiplies half kh of every K block with the 64 weight rows of
+// column block wn, and the two halves are added at the end.  (The tall-tile kernel leaves the
+// four wavefronts of its second row half without a row below 160 rows, and its K step of 64
+// reads half lines.)  Codes are read as 16 bytes and widened to bf16 by one instruction a
+// pair, exact; for up to 64 rows the block scale multiplies the fp32 sums of the K block,
+// above (where a second set of sums would not fit the registers) code * scale is rounded
+// to bf16 as in the tall-tile kernel.  The weights are the first operand, so a lane holds
+// columns of one row; output rows are turned around in LDS and stored whole.
+// Bound by nothing alone: 32 experts of 48 rows, hidden 7168, I 1024: GEMM-1 118, GEMM-2 62 us
+// (4.0 / 3.8 TB/s of codes) against 125 / 70; a stream of the same loads alone runs at 6 TB/s, the
+// same steps without loads take 90 us, and the two add up rather than overlap.  Where the tiles
+// are taken: short_tile_rows.  Whole layer (us), on the tall tiles and with the choice: 64 tokens 188 -> 161, 700 292 ->
+// 280, 1531 371 -> 320; Zipf-routed 160 tokens 204 -> 158, 256 207 -> 193; hidden 4096, 16 of 128 experts, I
+// 1536, 1000 tokens 178 -> 151; from 2500 tokens on unchanged.  Tried: weights loaded by one half of the
+// wavefronts and activations by the other (deeper weight ring) 118 -> 125, all fragments a
+// step ahead 118 -> 122, block scales in scalar registers loaded step by step (no difference),
+// 128 rows a tile (an expert of that many rows then is the launch: Zipf-routed 128 tokens, I 512, 111 -> 120).
+template <int NB> struct RingE {
+  static constexpr int kB = 256 * 8, kA = NB * 32 * 16;            // 16-byte slots of a stage
+  static constexpr int kSB = NB == 1 ? 4 : 3;                      // weight stages
+  static constexpr int kSA = NB <= 2 ? kSB : kSB - 1;              // activation stages
+  static_assert((kSB * kB + kSA * kA) * 16 <= 160 * 1024, "LDS of a CU");
+};
+
+template <bool DUAL, int NB>
+__device__ __forceinline__ void e4m3_body(const uint16_t* __restrict__ A, const char* __restrict__ B0,
+                                          const char* __restrict__ B1, const float* __restrict__ s0p,
+                                          const float* __restrict__ s1p, uint16_t* __restrict__ C, int N,
+                                          int K, int row0, int row1, int n0, int wave, int kb0, int nkb,
+                                          const SplitJob& job, uint4* __restrict__ smem) {
+  using R = RingE<NB>;
+  constexpr int SA = R::kSA, SB = R::kSB, NLA = NB, NLB = 4, HALF = 128;
+  constexpr bool kExact = NB <= 2;
+  uint4* const ringB = smem;
+  uint4* const ringA = smem + SB * R::kB;
+  const int lane = threadIdx.x & 63, wn = wave & 3, kh = wave >> 2;
+  const int h = lane >> 5, l31 = lane & 31;
+  const int rows = row1 - row0;
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<uint16_t*>(A + size_t(row0) * K + kb0 * 128), 0, ((rows - 1) * K + nkb * 128) * 2, 0x00020000);
+  const int brows = N - n0 < HALF * (DUAL ? 1 : 2) ? N - n0 : HALF * (DUAL ? 1 : 2);
+  const __amdgpu_buffer_rsrc_t rb0 = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char*>(B0 + size_t(n0) * K + kb0 * 128), 0, (brows - 1) * K + nkb * 128, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rb1 = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<char*>((DUAL ? B1 : B0) + size_t(n0) * K + kb0 * 128), 0, (brows - 1) * K + nkb * 128, 0x00020000);
+  // weights: load q fills rows q*64 + wave*8 .. +8 of the stage, lane l slot l%8 of row l/8
+  const int brow = wave * 8 + (lane >> 3), bpiece = (lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7);
+  // activations: load q fills rows q*32 + wave*4 .. +4, lane l slot l%16 of row l/16
+  const int arow = wave * 4 + (lane >> 4), apiece = (lane & 15) ^ (arow & 15);
+  int boff[4], aoff[NLA];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) boff[q] = ((DUAL ? q & 1 : q) * 64 + brow) * K + bpiece * 16;
+#pragma unroll
+  for (int q = 0; q < NLA; ++q) aoff[q] = ((q * 32 + arow) * K + apiece * 8) * 2;
+  auto issue_b = [&](int kb) {
+    uint4* const st = ringB + (kb % SB) * R::kB + wave * 64;
+#pragma unroll
+    for (int q = 0; q < NLB; ++q) {
+      if (DUAL && q >= 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(rb1, (lptr_t)(st + q * 512), 16, boff[q], kb * 128, 0, 0);
+      else __builtin_amdgcn_raw_ptr_buffer_load_lds(rb0, (lptr_t)(st + q * 512), 16, boff[q], kb * 128, 0, 0);
+    }
+  };
+  auto issue_a = [&](int kb) {
+    uint4* const st = ringA + (kb % SA) * R::kA + wave * 64;
+#pragma unroll
+    for (int q = 0; q < NLA; ++q)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lptr_t)(st + q * 512), 16, aoff[q], kb * 256, 0, 0);
+  };
+  f32x16 acc[NB][2];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+  const int brow0 = DUAL ? wn * 32 : wn * 64;
+  const int brow1 = DUAL ? HALF + wn * 32 : wn * 64 + 32;
+  // weight pieces kh*4 + t*2 + h of row l%32 (sixteen codes), activation pieces twice that, +1
+  int bat[2], aat[2][2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const int p = kh * 4 + t * 2 + h;
+    bat[t] = l31 * 8 + (p ^ ((l31 >> 1) & 7));
+#pragma unroll
+    for (int u = 0; u < 2; ++u) aat[t][u] = l31 * 16 + ((p * 2 + u) ^ (l31 & 15));
+  }
+  // Block scales: lane l holds those of K blocks l, l + 64, ..  (A scalar load in every step misses
+  // its cache every sixteenth time, and the whole workgroup waits for memory.)
+  float sv0 = s0p[min(lane, nkb - 1)], sv1 = s1p[min(lane, nkb - 1)];
+  auto scale = [&](float v, int kb) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), kb & 63)); };
+  auto next_scales = [&](int kb) {
+    if (kb > 0 && (kb & 63) == 0) {
+      sv0 = s0p[min(kb + lane, nkb - 1)];
+      sv1 = s1p[min(kb + lane, nkb - 1)];
+      wait_vmcnt<0>();                               // here, so that no wait is needed where they are used
+    }
+  };
+  auto read_codes = [&](int kb, uint4 (&code)[2][2]) {
+    const uint4* const Bb = ringB + (kb % SB) * R::kB;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      code[0][t] = Bb[brow0 * 8 + bat[t]];
+      code[1][t] = Bb[brow1 * 8 + bat[t]];
+    }
+  };
+#pragma unroll
+  for (int g = 0; g < SB - 1; ++g) {
+    if (g < SA - 1 && g < nkb) issue_a(g);
+    if (g < nkb) issue_b(g);
+  }
+  constexpr int kYounger = SA == SB ? (SB - 2) * (NLB + NLA) : NLB + (SA - 2) * (NLB + NLA);
+  for (int kb = 0; kb < nkb; ++kb) {
+    if (kb + SB - 2 < nkb) wait_vmcnt<kYounger>(); else wait_vmcnt<0>();
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    const uint4* const Ab = ringA + (kb % SA) * R::kA;
+    uint4 code[2][2];
+    read_codes(kb, code);
+    if (kb + SA - 1 < nkb) issue_a(kb + SA - 1);
+    if (kb + SB - 1 < nkb) issue_b(kb + SB - 1);
+    next_scales(kb);
+    const float c0 = scale(sv0, kb), c1 = scale(sv1, kb);
+    uint4 fb[2][2][2];                               // [column block][t][u]: eight bf16 codes, exact
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const uint2 lo = make_uint2(code[j][t].x, code[j][t].y), hi = make_uint2(code[j][t].z, code[j][t].w);
+        if constexpr (kExact) {
+          fb[j][t][0] = widen_codes(lo);
+          fb[j][t][1] = widen_codes(hi);
+        } else {
+          fb[j][t][0] = widen_scaled(lo, j == 0 ? c0 : c1);
+          fb[j][t][1] = widen_scaled(hi, j == 0 ? c0 : c1);
+        }
+      }
+    uint4 fa[2][2][2];                               // [set][t][u]: a row block ahead
+    auto read_a = [&](int i) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) fa[i & 1][t][u] = Ab[i * 512 + aat[t][u]];
+    };
+    read_a(0);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      if (i + 1 < NB) read_a(i + 1);
+      f32x16 part[2];
+      if constexpr (kExact) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int q = 0; q < 16; ++q) part[j][q] = 0.f;
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            f32x16& c = kExact ? part[j] : acc[i][j];
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[j][t][u]),
+                                                        __builtin_bit_cast(bf16x8, fa[i & 1][t][u]), c, 0, 0, 0);
+          }
+      if constexpr (kExact) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          acc[i][0][q] = fmaf(part[0][q], c0, acc[i][0][q]);
+          acc[i][1][q] = fmaf(part[1][q], c1, acc[i][1][q]);
+        }
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // The two wavefronts of a column block (one half of every K block each) add their sums:
+  // half kh finishes registers 8*kh .. +8.  D layout (weights first): lane l holds activation row
+  // l%32, register q weight row (q/4)*8 + (l/32)*4 + q%4.
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  // A K-split part leaves its sums in the workspace and the part that arrives last adds all
+  // parts in the order of their K windows and carries on (as in the tall-tile kernel).
+  if (job.parts > 1) {
+    uint64_t* const mine = reinterpret_cast<uint64_t*>(job.partial + size_t(job.slot) * kPartFloats) + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          __hip_atomic_store(mine + ((i * 2 + j) * 8 + q) * 512,
+                             uint64_t(__float_as_uint(acc[i][j][2 * q])) |
+                                 (uint64_t(__float_as_uint(acc[i][j][2 * q + 1])) << 32),
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    int32_t* const flag = reinterpret_cast<int32_t*>(smem);
+    if (threadIdx.x == 0) *flag = atomicAdd(job.ticket, 1);
+    __syncthreads();
+    if (*flag != job.parts - 1) return;
+    __syncthreads();                                   // the flag's place is used again below
+    const uint64_t* const all = reinterpret_cast<const uint64_t*>(job.partial + size_t(job.slot0) * kPartFloats) + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        uint64_t w[kSplitMax][8];
+#pragma unroll
+        for (int p = 0; p < kSplitMax; ++p)
+          if (p < job.parts) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+              w[p][q] = __hip_atomic_load(all + size_t(p) * (kPartFloats / 2) + ((i * 2 + j) * 8 + q) * 512,
+                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+#pragma unroll
+        for (int p = 0; p < kSplitMax; ++p)
+          if (p < job.parts) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+              acc[i][j][2 * q] += __uint_as_float(uint32_t(w[p][q]));
+              acc[i][j][2 * q + 1] += __uint_as_float(uint32_t(w[p][q] >> 32));
+            }
+          }
+      }
+  }
+  float* const red = reinterpret_cast<float*>(smem);   // [wavefront][NB][2][8][64]
+  float v[NB][2][8];
+  // (two copies: a register index that depends on kh would be an indexed access per value)
+  auto exchange = [&](auto kh_c) {
+    constexpr int Q = decltype(kh_c)::value * 8;
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          red[(((wave ^ 4) * NB + i) * 2 + j) * 512 + q * 64 + lane] = acc[i][j][8 - Q + q];
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[i][j][q] = acc[i][j][Q + q] + red[((wave * NB + i) * 2 + j) * 512 + q * 64 + lane];
+  };
+  if (kh == 0) exchange(std::integral_constant<int, 0>{});
+  else exchange(std::integral_constant<int, 1>{});
+  __syncthreads();
+  // the output tile, turned around in LDS: whole rows of it are stored
+  constexpr int CP = DUAL ? 16 : 32, P = CP + 1;      // 16-byte pieces per row, and pitch
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int j = 0; j < (DUAL ? 1 : 2); ++j)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        float o[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = DUAL ? silu_mul_fast(v[i][0][g * 4 + q], v[i][1][g * 4 + q]) : v[i][j][g * 4 + q];
+        // columns wn*32|64 + j*32 + (2 kh + g)*8 + h*4 .. +4
+        reinterpret_cast<uint2*>(smem + (i * 32 + l31) * P + wn * (CP / 4) + j * 4 + 2 * kh + g)[h] =
+            make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
+      }
+  __syncthreads();
+  constexpr int RPT = 512 / CP;                        // rows per turn of the workgroup
+#pragma unroll
+  for (int u = 0; u < NB * 32 / RPT; ++u) {
+    const int r = u * RPT + threadIdx.x / CP, piece = threadIdx.x % CP, col = n0 + piece * 8;
+    if (r < rows && col < N) *reinterpret_cast<uint4*>(C + size_t(row0 + r) * N + col) = smem[r * P + piece];
+  }
+}
+
+template <bool DUAL>
+__device__ __forceinline__ void e4m3_tile(const uint16_t* A, const char* Be0, const char* Be1, const float* S0,
+                                          const float* S1, uint16_t* C, int N, int K, int e, int row0, int row1,
+                                          int n0, int wave, int part, const SplitJob& job, uint4* smem) {
+  const int nkb = K / 128, nnb = N / 128;
+  const int k0 = part * nkb / job.parts, k1 = (part + 1) * nkb / job.parts;
+  int nb = (n0 + (DUAL ? 0 : (wave & 3) * 64)) / 128;
+  nb = nb < nnb ? nb : nnb - 1;
+  const float* const s0p = S0 + (size_t(e) * nnb + nb) * nkb + k0;
+  const float* const s1p = DUAL ? S1 + (size_t(e) * nnb + nb) * nkb + k0 : s0p;
+  switch ((row1 - row0 + 31) >> 5) {
+    case 1: e4m3_body<DUAL, 1>(A, Be0, Be1, s0p, s1p, C, N, K, row0, row1, n0, wave, k0, k1 - k0, job, smem); break;
+    case 2: e4m3_body<DUAL, 2>(A, Be0, Be1, s0p, s1p, C, N, K, row0, row1, n0, wave, k0, k1 - k0, job, smem); break;
+    default:                                         // three row blocks: GEMM-1 only
+      if constexpr (DUAL) e4m3_body<DUAL, 3>(A, Be0, Be1, s0p, s1p, C, N, K, row0, row1, n0, wave, k0, k1 - k0, job, smem);
+  }
+}
+
 // Leftover tiles.  The hardware hands workgroups to CUs in the order of their
 // ids, so when the number of tiles is not a multiple of the 256 CUs the last
 // `left` tiles run on `left` CUs while the rest idle for a whole tile time.  When
@@ -806,26 +1127,25 @@ __device__ __forceinline__ void gemm8w_tile(const uint16_t* A, const char* Be0, 
 // WIDE: tiles of at most 128 rows (the table is built with that height) x 512
 // weight rows, for GEMM-2 launches whose groups are short: twice the weight bytes
 // per K step and barrier, half as many tiles.
+// F8: or the short tiles of e4m3_body, if the table says so.  They are a branch of this kernel since
+// only the device knows the rows; a launch of their own that has nothing to do takes 2-3 us.
 template <bool DUAL, bool F8, bool RAGGED, bool WIDE>
 __global__ __launch_bounds__(512) void ffn_gemm8w_kernel(
     const uint16_t* __restrict__ A, const void* __restrict__ B0, const void* __restrict__ B1,
     const float* __restrict__ S0, const float* __restrict__ S1, uint16_t* __restrict__ C, int N,
     int K, const int32_t* __restrict__ tiles, int m_fastest, float* __restrict__ partial,
     int32_t* __restrict__ tickets) {
-  constexpr int BN = (DUAL ? 128 : 256) * (WIDE ? 2 : 1);
+  constexpr int kShortBN = DUAL ? 128 : 256;
   extern __shared__ uint4 smem[];
+  const int n_mtiles = F8 ? tiles[0] & ~kShortTiles : tiles[0];
+  const bool short_tiles = F8 && (tiles[0] & kShortTiles);
+  const int BN = WIDE && !short_tiles ? 2 * kShortBN : kShortBN;
   const int n_ntiles = (N + BN - 1) / BN;
-  const int total = tiles[0] * n_ntiles;
+  const int total = n_mtiles * n_ntiles;
   const int ksteps_all = (K + 63) / 64;
   const int pid = blockIdx.x;
   const int left = total % kCUs;
-  int parts = 1;
-  if (partial && left > 0 && left <= kCUs / 2) {
-    parts = kCUs / left;
-    parts = parts < kSplitMax ? parts : kSplitMax;
-    const int cap = ksteps_all / kSplitMinSteps;
-    parts = parts < cap ? parts : cap;
-  }
+  const int parts = partial ? split_parts(left, ksteps_all / kSplitMinSteps) : 1;
   int logical, part = 0;
   SplitJob job{1, 0, 0, partial, tickets};
   if (parts >= 2) {
@@ -878,6 +1198,15 @@ __global__ __launch_bounds__(512) void ffn_gemm8w_kernel(
   const char* Be0 = static_cast<const char*>(B0) + size_t(e) * N * K * WB;
   const char* Be1 = DUAL ? static_cast<const char*>(B1) + size_t(e) * N * K * WB : nullptr;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (F8) {
+    if (__builtin_expect(short_tiles, 0)) {
+      e4m3_tile<DUAL>(A, Be0, Be1, S0, S1, C, N, K, e, row0, row1, n0, wave, part, job, smem);
+      // The compiler lets this branch join the other one's entry.  With memory operations open
+      // here it would drain the rings there in front of their loops (tall tiles 1-2 % slower).
+      wait_vmcnt<0>();
+      return;
+    }
+  }
   // F8: the scales of the 128-row block this wavefront's weight rows lie in
   const float* Se0 = nullptr;
   const float* Se1 = nullptr;
@@ -1268,359 +1597,6 @@ void launch_shortk(const void* hmid, const void* w_down, void* ys, int N, int K,
 #undef MOE_SHORTK
 }
 
-// --------------------------------- MFMA GEMM, e4m3 weights, up to 128 rows a tile
-// e4m3 weights with a few dozen rows per expert: the work is streaming the codes in, and a
-// tile is short of rows, not of weights.  Tile: up to 128 rows (NB 32-row blocks) x 256
-// weight rows (DUAL: 128 gate + the matching 128 up rows), K step 128 = one scale block = a
-// whole cache line of every weight row.  All eight wavefronts work on all rows: wavefront
-// (kh, wn) = (w/4, w%4) multiplies half kh of every K block with the 64 weight rows of
-// column block wn, and the two halves are added at the end.  (The tall-tile kernel leaves the
-// four wavefronts of its second row half without a row below 160 rows, and its K step of 64
-// reads half lines.)  Codes are read as 16 bytes and widened to bf16 by one instruction a
-// pair, exact; for up to 64 rows the block scale multiplies the fp32 sums of the K block,
-// above (where a second set of sums would not fit the registers) code * scale is rounded
-// to bf16 as in the tall-tile kernel.  The weights are the first operand, so a lane holds
-// columns of one row; output rows are turned around in LDS and stored whole.
-// Bound by nothing alone: 32 experts of 48 rows, hidden 7168, I 1024: GEMM-1 118, GEMM-2 62 us
-// (4.0 / 3.8 TB/s of codes) against 125 / 70; a stream of the same loads alone runs at 6 TB/s, the
-// same steps without loads take 90 us, and the two add up rather than overlap.  Whole layer
-// (us): 64 tokens 191 -> 162, 700 295 -> 283, 1531 349 -> 314, 2040 422 -> 372; hidden 4096, 16 of
-// 128 experts, I 1536, 1000 tokens 178 -> 163.  Tried: weights loaded by one half of the
-// wavefronts and activations by the other (deeper weight ring) 118 -> 125, all fragments a
-// step ahead 118 -> 122, block scales in scalar registers loaded step by step (no difference).
-template <int NB> struct RingE {
-  static constexpr int kB = 256 * 8, kA = NB * 32 * 16;            // 16-byte slots of a stage
-  static constexpr int kSB = NB == 1 ? 4 : 3;                      // weight stages
-  static constexpr int kSA = NB <= 2 ? kSB : kSB - 1;              // activation stages
-  static_assert((kSB * kB + kSA * kA) * 16 <= 160 * 1024, "LDS of a CU");
-};
-
-template <bool DUAL, int NB>
-__device__ __forceinline__ void e4m3_body(const uint16_t* __restrict__ A, const char* __restrict__ B0,
-                                          const char* __restrict__ B1, const float* __restrict__ s0p,
-                                          const float* __restrict__ s1p, uint16_t* __restrict__ C, int N,
-                                          int K, int row0, int row1, int n0, int wave, int kb0, int nkb,
-                                          const SplitJob& job, uint4* __restrict__ smem) {
-  using R = RingE<NB>;
-  constexpr int SA = R::kSA, SB = R::kSB, NLA = NB, NLB = 4, HALF = 128;
-  constexpr bool kExact = NB <= 2;
-  uint4* const ringB = smem;
-  uint4* const ringA = smem + SB * R::kB;
-  const int lane = threadIdx.x & 63, wn = wave & 3, kh = wave >> 2;
-  const int h = lane >> 5, l31 = lane & 31;
-  const int rows = row1 - row0;
-  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(A + size_t(row0) * K + kb0 * 128), 0, ((rows - 1) * K + nkb * 128) * 2, 0x00020000);
-  const int brows = N - n0 < HALF * (DUAL ? 1 : 2) ? N - n0 : HALF * (DUAL ? 1 : 2);
-  const __amdgpu_buffer_rsrc_t rb0 = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<char*>(B0 + size_t(n0) * K + kb0 * 128), 0, (brows - 1) * K + nkb * 128, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rb1 = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<char*>((DUAL ? B1 : B0) + size_t(n0) * K + kb0 * 128), 0, (brows - 1) * K + nkb * 128, 0x00020000);
-  // weights: load q fills rows q*64 + wave*8 .. +8 of the stage, lane l slot l%8 of row l/8
-  const int brow = wave * 8 + (lane >> 3), bpiece = (lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7);
-  // activations: load q fills rows q*32 + wave*4 .. +4, lane l slot l%16 of row l/16
-  const int arow = wave * 4 + (lane >> 4), apiece = (lane & 15) ^ (arow & 15);
-  int boff[4], aoff[NLA];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) boff[q] = ((DUAL ? q & 1 : q) * 64 + brow) * K + bpiece * 16;
-#pragma unroll
-  for (int q = 0; q < NLA; ++q) aoff[q] = ((q * 32 + arow) * K + apiece * 8) * 2;
-  auto issue_b = [&](int kb) {
-    uint4* const st = ringB + (kb % SB) * R::kB + wave * 64;
-#pragma unroll
-    for (int q = 0; q < NLB; ++q) {
-      if (DUAL && q >= 2) __builtin_amdgcn_raw_ptr_buffer_load_lds(rb1, (lptr_t)(st + q * 512), 16, boff[q], kb * 128, 0, 0);
-      else __builtin_amdgcn_raw_ptr_buffer_load_lds(rb0, (lptr_t)(st + q * 512), 16, boff[q], kb * 128, 0, 0);
-    }
-  };
-  auto issue_a = [&](int kb) {
-    uint4* const st = ringA + (kb % SA) * R::kA + wave * 64;
-#pragma unroll
-    for (int q = 0; q < NLA; ++q)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lptr_t)(st + q * 512), 16, aoff[q], kb * 256, 0, 0);
-  };
-  f32x16 acc[NB][2];
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-  const int brow0 = DUAL ? wn * 32 : wn * 64;
-  const int brow1 = DUAL ? HALF + wn * 32 : wn * 64 + 32;
-  // weight pieces kh*4 + t*2 + h of row l%32 (sixteen codes), activation pieces twice that, +1
-  int bat[2], aat[2][2];
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const int p = kh * 4 + t * 2 + h;
-    bat[t] = l31 * 8 + (p ^ ((l31 >> 1) & 7));
-#pragma unroll
-    for (int u = 0; u < 2; ++u) aat[t][u] = l31 * 16 + ((p * 2 + u) ^ (l31 & 15));
-  }
-  // Block scales: lane l holds those of K blocks l, l + 64, ..  (A scalar load in every step misses
-  // its cache every sixteenth time, and the whole workgroup waits for memory.)
-  float sv0 = s0p[min(lane, nkb - 1)], sv1 = s1p[min(lane, nkb - 1)];
-  auto scale = [&](float v, int kb) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), kb & 63)); };
-  auto next_scales = [&](int kb) {
-    if (kb > 0 && (kb & 63) == 0) {
-      sv0 = s0p[min(kb + lane, nkb - 1)];
-      sv1 = s1p[min(kb + lane, nkb - 1)];
-      wait_vmcnt<0>();                               // here, so that no wait is needed where they are used
-    }
-  };
-  auto read_codes = [&](int kb, uint4 (&code)[2][2]) {
-    const uint4* const Bb = ringB + (kb % SB) * R::kB;
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      code[0][t] = Bb[brow0 * 8 + bat[t]];
-      code[1][t] = Bb[brow1 * 8 + bat[t]];
-    }
-  };
-#pragma unroll
-  for (int g = 0; g < SB - 1; ++g) {
-    if (g < SA - 1 && g < nkb) issue_a(g);
-    if (g < nkb) issue_b(g);
-  }
-  constexpr int kYounger = SA == SB ? (SB - 2) * (NLB + NLA) : NLB + (SA - 2) * (NLB + NLA);
-  for (int kb = 0; kb < nkb; ++kb) {
-    if (kb + SB - 2 < nkb) wait_vmcnt<kYounger>(); else wait_vmcnt<0>();
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    const uint4* const Ab = ringA + (kb % SA) * R::kA;
-    uint4 code[2][2];
-    read_codes(kb, code);
-    if (kb + SA - 1 < nkb) issue_a(kb + SA - 1);
-    if (kb + SB - 1 < nkb) issue_b(kb + SB - 1);
-    next_scales(kb);
-    const float c0 = scale(sv0, kb), c1 = scale(sv1, kb);
-    uint4 fb[2][2][2];                               // [column block][t][u]: eight bf16 codes, exact
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const uint2 lo = make_uint2(code[j][t].x, code[j][t].y), hi = make_uint2(code[j][t].z, code[j][t].w);
-        if constexpr (kExact) {
-          fb[j][t][0] = widen_codes(lo);
-          fb[j][t][1] = widen_codes(hi);
-        } else {
-          fb[j][t][0] = widen_scaled(lo, j == 0 ? c0 : c1);
-          fb[j][t][1] = widen_scaled(hi, j == 0 ? c0 : c1);
-        }
-      }
-    uint4 fa[2][2][2];                               // [set][t][u]: a row block ahead
-    auto read_a = [&](int i) {
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int u = 0; u < 2; ++u) fa[i & 1][t][u] = Ab[i * 512 + aat[t][u]];
-    };
-    read_a(0);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      if (i + 1 < NB) read_a(i + 1);
-      f32x16 part[2];
-      if constexpr (kExact) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) part[j][q] = 0.f;
-      }
-#pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            f32x16& c = kExact ? part[j] : acc[i][j];
-            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[j][t][u]),
-                                                        __builtin_bit_cast(bf16x8, fa[i & 1][t][u]), c, 0, 0, 0);
-          }
-      if constexpr (kExact) {
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          acc[i][0][q] = fmaf(part[0][q], c0, acc[i][0][q]);
-          acc[i][1][q] = fmaf(part[1][q], c1, acc[i][1][q]);
-        }
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  // The two wavefronts of a column block (one half of every K block each) add their sums:
-  // half kh finishes registers 8*kh .. +8.  D layout (weights first): lane l holds activation row
-  // l%32, register q weight row (q/4)*8 + (l/32)*4 + q%4.
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-  // A K-split part leaves its sums in the workspace and the part that arrives last adds all
-  // parts in the order of their K windows and carries on (as in the tall-tile kernel).
-  if (job.parts > 1) {
-    uint64_t* const mine = reinterpret_cast<uint64_t*>(job.partial + size_t(job.slot) * kPartFloats) + threadIdx.x;
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-          __hip_atomic_store(mine + ((i * 2 + j) * 8 + q) * 512,
-                             uint64_t(__float_as_uint(acc[i][j][2 * q])) |
-                                 (uint64_t(__float_as_uint(acc[i][j][2 * q + 1])) << 32),
-                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    int32_t* const flag = reinterpret_cast<int32_t*>(smem);
-    if (threadIdx.x == 0) *flag = atomicAdd(job.ticket, 1);
-    __syncthreads();
-    if (*flag != job.parts - 1) return;
-    __syncthreads();                                   // the flag's place is used again below
-    const uint64_t* const all = reinterpret_cast<const uint64_t*>(job.partial + size_t(job.slot0) * kPartFloats) + threadIdx.x;
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        uint64_t w[kSplitMax][8];
-#pragma unroll
-        for (int p = 0; p < kSplitMax; ++p)
-          if (p < job.parts) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-              w[p][q] = __hip_atomic_load(all + size_t(p) * (kPartFloats / 2) + ((i * 2 + j) * 8 + q) * 512,
-                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          }
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-#pragma unroll
-        for (int p = 0; p < kSplitMax; ++p)
-          if (p < job.parts) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              acc[i][j][2 * q] += __uint_as_float(uint32_t(w[p][q]));
-              acc[i][j][2 * q + 1] += __uint_as_float(uint32_t(w[p][q] >> 32));
-            }
-          }
-      }
-  }
-  float* const red = reinterpret_cast<float*>(smem);   // [wavefront][NB][2][8][64]
-  float v[NB][2][8];
-  // (two copies: a register index that depends on kh would be an indexed access per value)
-  auto exchange = [&](auto kh_c) {
-    constexpr int Q = decltype(kh_c)::value * 8;
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-          red[(((wave ^ 4) * NB + i) * 2 + j) * 512 + q * 64 + lane] = acc[i][j][8 - Q + q];
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[i][j][q] = acc[i][j][Q + q] + red[((wave * NB + i) * 2 + j) * 512 + q * 64 + lane];
-  };
-  if (kh == 0) exchange(std::integral_constant<int, 0>{});
-  else exchange(std::integral_constant<int, 1>{});
-  __syncthreads();
-  // the output tile, turned around in LDS: whole rows of it are stored
-  constexpr int CP = DUAL ? 16 : 32, P = CP + 1;      // 16-byte pieces per row, and pitch
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-#pragma unroll
-    for (int j = 0; j < (DUAL ? 1 : 2); ++j)
-#pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        float o[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = DUAL ? silu_mul_fast(v[i][0][g * 4 + q], v[i][1][g * 4 + q]) : v[i][j][g * 4 + q];
-        // columns wn*32|64 + j*32 + (2 kh + g)*8 + h*4 .. +4
-        reinterpret_cast<uint2*>(smem + (i * 32 + l31) * P + wn * (CP / 4) + j * 4 + 2 * kh + g)[h] =
-            make_uint2(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]));
-      }
-  __syncthreads();
-  constexpr int RPT = 512 / CP;                        // rows per turn of the workgroup
-#pragma unroll
-  for (int u = 0; u < NB * 32 / RPT; ++u) {
-    const int r = u * RPT + threadIdx.x / CP, piece = threadIdx.x % CP, col = n0 + piece * 8;
-    if (r < rows && col < N) *reinterpret_cast<uint4*>(C + size_t(row0 + r) * N + col) = smem[r * P + piece];
-  }
-}
-
-template <bool DUAL>
-__global__ __launch_bounds__(512) void ffn_e4m3_kernel(
-    const uint16_t* __restrict__ A, const char* __restrict__ B0, const char* __restrict__ B1,
-    const float* __restrict__ S0, const float* __restrict__ S1, uint16_t* __restrict__ C, int N, int K,
-    const int32_t* __restrict__ tiles, float* __restrict__ partial, int32_t* __restrict__ tickets) {
-  constexpr int BN = DUAL ? 128 : 256;
-  extern __shared__ uint4 smem[];
-  const int n_ntiles = (N + BN - 1) / BN;
-  const int total = tiles[0] * n_ntiles, nkb = K / 128, pid = blockIdx.x;
-  // the leftover tiles of the last round are cut along K (see "Leftover tiles" above)
-  const int left = total % kCUs;
-  int parts = 1;
-  if (partial && left > 0 && left <= kCUs / 2) {
-    parts = kCUs / left;
-    parts = parts < kSplitMax ? parts : kSplitMax;
-    const int cap = nkb / (kSplitMinSteps / 2);
-    parts = parts < cap ? parts : cap;
-  }
-  int logical, kb0 = 0, kb1 = nkb;
-  SplitJob job{1, 0, 0, partial, tickets};
-  if (parts >= 2) {
-    const int full = total - left;
-    if (pid < full) {
-      logical = (pid & 7) * (full >> 3) + (pid >> 3);
-    } else {
-      const int q = pid - full;
-      if (q >= left * parts) return;
-      const int j = q / parts, part = q - j * parts;
-      logical = full + j;
-      kb0 = part * nkb / parts;
-      kb1 = (part + 1) * nkb / parts;
-      job = SplitJob{parts, q, j * parts, partial, tickets + j};
-    }
-  } else {
-    const int per_xcd = (total + 7) >> 3;
-    logical = (pid & 7) * per_xcd + (pid >> 3);
-    if ((pid >> 3) >= per_xcd || logical >= total) return;
-  }
-  int mtile = logical / n_ntiles;
-  const int first = tiles[4 + kTileRec * mtile], cnt = tiles[5 + kTileRec * mtile];
-  const int local = logical - first * n_ntiles;
-  const int gsz = 4 * n_ntiles, grp = local / gsz, rem = local - grp * gsz;
-  const int left_m = cnt - grp * 4, mc = left_m < 4 ? left_m : 4;
-  const int ntile = rem / mc;
-  mtile = first + grp * 4 + (rem - ntile * mc);
-  const int e = tiles[1 + kTileRec * mtile], row0 = tiles[2 + kTileRec * mtile], row1 = tiles[3 + kTileRec * mtile];
-  const int n0 = ntile * BN, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const char* const b0 = B0 + size_t(e) * N * K;
-  const char* const b1 = DUAL ? B1 + size_t(e) * N * K : nullptr;
-  const int nnb = N / 128;
-  int nb = (n0 + (DUAL ? 0 : (wave & 3) * 64)) / 128;
-  nb = nb < nnb ? nb : nnb - 1;
-  const float* const s0p = S0 + (size_t(e) * nnb + nb) * nkb + kb0;
-  const float* const s1p = DUAL ? S1 + (size_t(e) * nnb + nb) * nkb + kb0 : s0p;
-  switch ((row1 - row0 + 31) >> 5) {
-    case 1: e4m3_body<DUAL, 1>(A, b0, b1, s0p, s1p, C, N, K, row0, row1, n0, wave, kb0, kb1 - kb0, job, smem); break;
-    case 2: e4m3_body<DUAL, 2>(A, b0, b1, s0p, s1p, C, N, K, row0, row1, n0, wave, kb0, kb1 - kb0, job, smem); break;
-    case 3: e4m3_body<DUAL, 3>(A, b0, b1, s0p, s1p, C, N, K, row0, row1, n0, wave, kb0, kb1 - kb0, job, smem); break;
-    default: e4m3_body<DUAL, 4>(A, b0, b1, s0p, s1p, C, N, K, row0, row1, n0, wave, kb0, kb1 - kb0, job, smem); break;
-  }
-}
-
-template <bool DUAL>
-void launch_e4m3(const uint16_t* A, const void* B0, const void* B1, const float* S0, const float* S1, uint16_t* C,
-                 int N, int K, int n_experts, const int32_t* tiles, int max_mt, const FfnWs& ws, hipStream_t s) {
-  constexpr int lds = 160 * 1024, BN = DUAL ? 128 : 256;
-  // room for the parts of the leftover tiles behind the whole tiles
-  const int grid = (max_mt * ((N + BN - 1) / BN) + 7) / 8 * 8 + kCUs;
-  static uint64_t opted = 0;
-  auto k = ffn_e4m3_kernel<DUAL>;
-  lds_opt_in(reinterpret_cast<const void*>(k), lds, opted);
-  MOE_LAUNCH(DUAL ? MOE_K_FFN_GEMM1 : MOE_K_FFN_GEMM2, k, dim3(grid), dim3(512), lds, s, A,
-             static_cast<const char*>(B0), static_cast<const char*>(B1), S0, S1, C, N, K, tiles,
-             n_experts > 1 ? ws.partial : static_cast<float*>(nullptr),
-             ws.tickets + (DUAL ? 0 : kSplitTickets));
-}
-
 // ------------------------------------------------------------ fp32 GEMM
 // fp32 layers on v_mfma_f32_32x32x2_f32 (fp32 products and sums).  Tile 32 rows x
 // 32 output columns (DUAL: with the matching up rows).  Operands go global -> LDS
@@ -1856,7 +1832,7 @@ __global__ __launch_bounds__(256) void ffn_f32_valu_kernel(const float* __restri
 }
 
 // Which kernel runs each GEMM of a call, and the height of its M tiles.
-enum GemmKind { kGemmF32, kGemmF32Valu, kGemmStream, kGemmTall, kGemmWide, kGemmShortK, kGemmE4m3 };
+enum GemmKind { kGemmF32, kGemmF32Valu, kGemmStream, kGemmTall, kGemmWide, kGemmShortK };
 struct FfnPlan {
   GemmKind g1, g2;
   int bm1, bm2;
@@ -1942,23 +1918,18 @@ FfnPlan plan_ffn(const moe_config& c, int n_experts, int rows_capacity) {
   else if (avg <= 12) { p.g2 = kGemmStream; p.bm2 = 32; }
   else if (avg <= 96 && wide) { p.g2 = kGemmWide; p.bm2 = 128; }
   else { p.g2 = kGemmTall; p.bm2 = ragged && avg >= 128 && tiles_of(128, H, 256) <= kCUs ? 128 : 256; }
-  // e4m3 weights (I and H are multiples of 128) with up to 64 rows per expert to expect, if the
-  // rows were spread over all experts of the layer (an EP share's capacity holds them all): the
-  // kernel for short tiles.  128 experts, hidden 2048, I 768: 512 tokens (32 rows) 178 -> 173 us, 1000 (62)
-  // 209 / 209, 2000 (125) 318 / 326; 32 of 256 experts, hidden 7168, I 1024: 2040 tokens (64 rows) 422 -> 372,
-  // 4000 (125) 613 / 638.  A single expert (the shared one, which runs beside the routed path) takes
-  // it unsplit from 48 tiles on: its workgroups then leave the other CUs to the route (1531 tokens,
-  // 96 tiles: 314 us a layer, with the tiles cut along K 346; 256 tokens, 24 tiles: 233 unsplit, 222 split,
-  // 209 on the tall tiles; 512 tokens with given routing, 40 tiles: 316 unsplit, 258 split).
-  // From five to fifteen rows the tall tiles stay for several experts: a skewed batch then has one
-  // or two experts of full 128-row tiles, whose K loop is the launch (256 tokens, Zipf routing with 241
-  // and 140 rows in the hottest experts: 219 us a layer, 244 here; evenly routed 219 / 209).
-  const int spread = rows_capacity / c.n_experts;
-  if (fp8 && avg > 12 && spread <= 64 && (n_experts == 1 || spread <= 4 || spread >= 16)) {
-    if (n_experts > 1 || tiles_of(128, I, 128) >= 48) { p.g1 = kGemmE4m3; p.bm1 = 128; }
-    if (n_experts > 1 || tiles_of(128, H, 256) >= 48) { p.g2 = kGemmE4m3; p.bm2 = 128; }
-  }
   return p;
+}
+
+// The choice of tiles that the GEMM of `kind` has (e4m3 weights).
+template <bool DUAL>
+ShortTiles short_tiles_of(GemmKind kind, int bm, int N, int K, int n_experts, int rows_capacity) {
+  if (kind != kGemmTall && kind != kGemmWide) return {};
+  const bool wide = kind == kGemmWide;
+  const int bn = DUAL ? 128 : 256, own = wide ? 512 : bn;
+  const int nt_own = (N + own - 1) / own;
+  return {(N + bn - 1) / bn, nt_own, (K + 63) / 64 / kSplitMinSteps,
+          tall_grid(max_row_tiles(rows_capacity, n_experts, bm), nt_own, wide), DUAL, wide};
 }
 
 // One GEMM of the call: C[rows, N] = A[rows, K] B^T (DUAL: the gate|up pair with SwiGLU).
@@ -1967,7 +1938,7 @@ void launch_gemm(GemmKind kind, int bm, const uint16_t* A, const void* B0, const
                  const float* S0, const float* S1, uint16_t* C, int N, int K, int n_experts,
                  int rows_capacity, const int32_t* tiles, const FfnWs& ws, hipStream_t s) {
   constexpr int id = DUAL ? MOE_K_FFN_GEMM1 : MOE_K_FFN_GEMM2;
-  const int max_mt = rows_capacity / bm + (n_experts < rows_capacity ? n_experts : rows_capacity);
+  const int max_mt = max_row_tiles(rows_capacity, n_experts, bm);
   if (kind == kGemmStream) {
     constexpr int BN = DUAL ? 32 : 64;
     MOE_LAUNCH(id, (ffn_skinny_kernel<DUAL, F8>), dim3(size_t(max_mt) * ((N + BN - 1) / BN)), dim3(256),
@@ -1978,16 +1949,10 @@ void launch_gemm(GemmKind kind, int bm, const uint16_t* A, const void* B0, const
     launch_shortk(A, B0, C, N, K, tiles, max_mt, s);
     return;
   }
-  if constexpr (F8)
-    if (kind == kGemmE4m3) {
-      launch_e4m3<DUAL>(A, B0, B1, S0, S1, C, N, K, n_experts, tiles, max_mt, ws, s);
-      return;
-    }
   constexpr int lds = 160 * 1024;         // all of a CU's LDS: the rings of the tallest tile fill it
   const bool wide = !DUAL && kind == kGemmWide;
   const int BN = DUAL ? 128 : (wide ? 512 : 256);
-  // room for the parts of the leftover tiles behind the whole tiles
-  const int grid = (max_mt * ((N + BN - 1) / BN) + 7) / 8 * 8 + kCUs;
+  const int grid = tall_grid(max_mt, (N + BN - 1) / BN, F8 && wide);
   auto k = ffn_gemm8w_kernel<DUAL, F8, false, false>;
   int form = 0;
   if constexpr (!F8) {
@@ -2047,10 +2012,16 @@ hipError_t launch_expert_ffn(const moe_config& c, int n_experts, const void* xs,
                              hipStream_t s) {
   const int H = c.hidden, I = c.inter_local;
   const FfnPlan p = plan_ffn(c, n_experts, rows_capacity);
-  // when the two GEMMs cut the rows differently a second workgroup builds a second table
-  int32_t* const tiles2 = p.bm1 == p.bm2 ? ws.tiles : ws.tiles2;
-  MOE_LAUNCH(MOE_K_FFN_TILES, ffn_tiles_kernel, dim3(p.bm1 == p.bm2 ? 1 : 2), dim3(kTileThreads), 0, s, offsets,
-             n_experts, p.bm1, rows_capacity, ws.tiles, ws.max_tiles, p.bm2, tiles2, ws.tickets);
+  // when the two GEMMs may cut the rows differently a second workgroup builds a second table
+  TileJob t1{ws.tiles, p.bm1, {}}, t2{ws.tiles2, p.bm2, {}};
+  if (c.weight_dtype == MOE_FP8_E4M3_B128) {
+    t1.alt = short_tiles_of<true>(p.g1, p.bm1, I, H, n_experts, rows_capacity);
+    if (n_experts > 1) t2.alt = short_tiles_of<false>(p.g2, p.bm2, H, I, n_experts, rows_capacity);
+  }
+  const bool one_table = p.bm1 == p.bm2 && !t1.alt.nt && !t2.alt.nt;
+  int32_t* const tiles2 = one_table ? ws.tiles : ws.tiles2;
+  MOE_LAUNCH(MOE_K_FFN_TILES, ffn_tiles_kernel, dim3(one_table ? 1 : 2), dim3(kTileThreads), 0, s, offsets,
+             n_experts, rows_capacity, ws.max_tiles, t1, t2, ws.tickets);
   if (c.act_dtype == MOE_F32) {
     float* const hmid = static_cast<float*>(ws.hmid);
     launch_f32<true>(p.g1, p.bm1, static_cast<const float*>(xs), static_cast<const float*>(w_gate),

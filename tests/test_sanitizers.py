@@ -1,7 +1,8 @@
 """CPU sanitizer legs (AddressSanitizer + UndefinedBehaviorSanitizer, host code
 only): the oracle's C source driven over small layers with its edge cases, the
 library's host-side argument validation / workspace carving with the kernel
-launchers stubbed out, and the index arithmetic of the short-K kernel's loads.
+launchers stubbed out, the index arithmetic of the short-K kernel's loads, and the
+choice of row tiles by the experts' rows.
 All are standalone executables built here; nothing runs on a GPU."""
 import os
 import subprocess
@@ -45,4 +46,12 @@ def test_short_k_loads_stay_inside_the_expert(tmp_path):
     subprocess.check_call(["g++", "-O1", "-g", "-std=c++17", *SAN,
                            "-I", os.path.join(ROOT, "paper_2601_08800_amd", "csrc"),
                            os.path.join(ROOT, "tests", "sanitize", "shortk_driver.cpp"), "-o", exe])
+    assert "ok" in _run(exe)
+
+
+def test_tile_rules(tmp_path):
+    exe = str(tmp_path / "tile_rules_san")
+    subprocess.check_call(["g++", "-O1", "-g", "-std=c++17", *SAN,
+                           "-I", os.path.join(ROOT, "paper_2601_08800_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "sanitize", "tile_rules_driver.cpp"), "-o", exe])
     assert "ok" in _run(exe)
