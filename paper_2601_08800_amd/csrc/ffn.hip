@@ -28,6 +28,7 @@
 // in their LDS ring, code * scale is rounded to bf16 on the way to the matrix unit.
 #include <type_traits>
 
+#include "device_util.h"
 #include "moe_internal.h"
 #include "tile_rules.h"
 #include "shortk_layout.h"
@@ -38,18 +39,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-// Two values rounded to bf16 (nearest even), low | high half: v_cvt_pk_bf16_f32.  Left
-// to the compiler and not written as inline assembly: it knows how long a matrix
-// instruction's result takes to arrive and keeps that distance, which it does not do
-// for the operands of an asm statement.
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-  const f32x2 v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
 
 __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
   return __builtin_bit_cast(uint16_t, (__bf16)f);   // round to nearest even
@@ -106,16 +96,6 @@ static_assert(size_t(kPartFloats) * 4 == kFfnPartBytes, "partial-sum slot size")
 // 5356 -> 5452 us.)  Where the GEMM has a choice of tiles, their numbers at all heights come
 // out of the same scan (0.5 us).
 constexpr int kTileThreads = 512, kOwnTiles = 4;
-// Lanes' inclusive sums: shifts inside the rows of 16 lanes, then the rows' sums.
-__device__ __forceinline__ int wave_incl_sum(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);    // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);    // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);    // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);    // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);    // row_bcast:15 into rows 1 and 3
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);    // row_bcast:31 into rows 2 and 3
-  return v;
-}
 
 // The table of one GEMM: tiles of bm rows, or short ones.
 struct TileJob {
@@ -213,12 +193,6 @@ __global__ __launch_bounds__(kTileThreads) void ffn_tiles_kernel(const int32_t* 
 
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
-}
 
 // ---------------------------------------- MFMA GEMM, 256x256 tile, 8 wavefronts
 // Prefill-sized groups.  Block tile 256 rows x 256 weight rows (DUAL: 128 gate +

@@ -35,6 +35,7 @@
 // fragments read under the last block's MFMAs 103, the same with loads spread over the row
 // blocks 111; 16 x 16 x 128 instructions 98-105; reads in front of the loads 101.
 
+#include "device_util.h"
 #include "moe_internal.h"
 
 namespace moe {
@@ -47,14 +48,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kQBlock = 128;     // columns per activation scale, and K bytes per GEMM step
 constexpr int kTileRec = 4;      // tile record: expert, first row, end row, the expert's first tile
 constexpr int FBM = 192;          // rows of a tile at most
-
-// two values rounded to bf16 (nearest even), low | high half
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-  const f32x2 v = {lo, hi};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
 
 __device__ __forceinline__ int swz(int row, int piece) {
   return row * 8 + (piece ^ ((row >> 1) & 7));
@@ -178,12 +171,6 @@ __global__ __launch_bounds__(512) void fp8act_tiles_kernel(const int32_t* __rest
 // hs_t [N/128][rows_capacity] of the SwiGLU values; else C bf16 [rows, N].
 typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
-}
 
 // LDS of a tile of NB 32-row blocks: weight stages | activation stages | row scales.
 template <int NB> struct Ring8 {
