@@ -491,8 +491,7 @@ __global__ __launch_bounds__(512) void fp8act_gemm_kernel(
 
 }  // namespace
 
-// workspace: tiles | x codes | x scales | (room for a bf16 intermediate, unused: callers' workspaces
-// keep their layout) | hmid codes | hmid scales
+// workspace: tiles | x codes | x scales | hmid codes | hmid scales
 struct Fp8ActWs {
   int32_t* tiles;
   uint8_t* xq;
@@ -511,7 +510,6 @@ static Fp8ActWs carve_fp8act(void* ws, int rows_capacity, int n_experts, int H, 
   f.tiles = reinterpret_cast<int32_t*>(p + off); off += align_up(size_t(1 + kTileRec * f.max_tiles) * 4);
   f.xq = reinterpret_cast<uint8_t*>(p + off);    off += align_up(size_t(rows_capacity) * H);
   f.xs_t = reinterpret_cast<float*>(p + off);    off += align_up(size_t(H / kQBlock) * rows_capacity * 4);
-  off += align_up(size_t(rows_capacity) * I * 2);
   f.hq = reinterpret_cast<uint8_t*>(p + off);    off += align_up(size_t(rows_capacity) * I);
   f.hs_t = reinterpret_cast<float*>(p + off);    off += align_up(size_t(I / kQBlock) * rows_capacity * 4);
   f.bytes = off;

@@ -45,6 +45,15 @@ def test_workspace_bytes():
     assert moe.moe_workspace_bytes(cfg(), -1) == 0
 
 
+@pytest.mark.parametrize("n,rows,H,I", [(1, 1, 128, 128), (32, 4096, 1024, 512), (256, 196608, 7168, 2048)])
+def test_fp8act_workspace_holds_what_the_path_uses(n, rows, H, I):
+    """Codes and fp32 block scales of the rows and of the intermediate and the tile table (records of
+    16 bytes, up to one per expert and 128 rows), each up to 256 bytes: no room for anything else."""
+    got = moe.moe_fp8act_workspace_bytes(cfg(hidden=H, inter_local=I, weight_dtype=B.MOE_FP8_E4M3_B128), n, rows)
+    used = rows * (H + I) + rows * (H + I) // 128 * 4 + 4 + 16 * (rows // 128 + n + 1)
+    assert used <= got <= used + 5 * 256
+
+
 def status_of(fn, *a):
     try:
         fn(*a)
