@@ -118,29 +118,32 @@ def border_tokens(w, offsets, perm, at_least, seed=7):
     row: for every local expert the first and the last row of its segment and the
     rows on either side of every possible M-tile border (tile heights are
     multiples of 32 rows; segments longer than 1024 rows: the borders of the
-    balanced 160- and 256-row partitions and every multiple of 256), filled up
-    with random tokens to `at_least`."""
-    rows = set()
-    for e in range(len(offsets) - 1):
-        lo, hi = int(offsets[e]), int(offsets[e + 1])
-        m = hi - lo
-        if m == 0:
-            continue
+    balanced 160- and 256-row partitions, of the 192-row one of 8-bit activations
+    and the 64-row one of e4m3 weights, and every multiple of 256); the same rows
+    of the shared expert, whose segment is the batch; filled up with random tokens
+    to `at_least`."""
+    heights = (160, 256) if w.weight_dtype != "fp8" else ((192,) if w.fp8_activations else (64, 160, 256))
+
+    def sides(lo, m):
         cuts = {0, m}
         if m <= 1024:
             cuts.update(range(32, m, 32))
         else:
             cuts.update(range(256, m, 256))
-            for bm in (160, 256):
+            for bm in heights:
                 nt = -(-m // bm)
                 step = -(-(-(-m // nt)) // 32) * 32
                 cuts.update(range(step, m, step))
-        for c in cuts:
-            if c > 0:
-                rows.add(lo + c - 1)
-            if c < m:
-                rows.add(lo + c)
+        return {lo + c - 1 for c in cuts if c > 0} | {lo + c for c in cuts if c < m}
+
+    rows = set()
+    for e in range(len(offsets) - 1):
+        lo, hi = int(offsets[e]), int(offsets[e + 1])
+        if hi > lo:
+            rows |= sides(lo, hi - lo)
     toks = set((perm[np.array(sorted(rows), np.int64)] // w.k).tolist()) if rows else set()
+    if w.shared_expert:
+        toks |= sides(0, w.T)
     rng = np.random.default_rng(seed)
     while len(toks) < min(at_least, w.T):
         toks.update(rng.integers(0, w.T, at_least).tolist())

@@ -188,8 +188,8 @@ def test_fp32_many_tiles(counts, H, I):
     _ffn(counts, H, I, "f32")
 
 
-# Every workgroup finds its tile from the offsets, up to eight experts a lane: expert counts on
-# both sides of a lane's next expert, the first and last experts empty, one to three tiles each.
+# The tile table's scan: expert counts on both sides of a wavefront's last expert and of the
+# workgroup's, the first and last experts empty, up to one tile each but for one of several.
 @pytest.mark.parametrize("act", ["f32", "bf16"])
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 129, 449, 512])
 def test_tile_of_expert(n, act):
@@ -209,9 +209,9 @@ def test_tile_look_up_last_expert(n):
     _ffn(c.tolist(), 64, 72, "f32")
 
 
-# e4m3 weights, 13 to 64 rows per expert on average: one to four 32-row blocks a tile and two tiles
-# an expert, one to seven K blocks (fewer than a ring has stages, as many, more), column tiles of
-# GEMM-2 half empty; and leftover tiles cut along K (26 K blocks: two parts) in GEMM-1.
+# e4m3 weights, 13 to 64 rows per expert on average: short tiles of one and two 32-row blocks, up to
+# four tiles an expert, one to seven K blocks (fewer than a ring has stages, as many, more), column
+# tiles of GEMM-2 half empty; and, in the last case, GEMM-1 on tall tiles cut along K.
 @pytest.mark.parametrize("counts,H,I", [
     ([1, 31, 32, 33, 0, 64, 65, 30], 128, 256), ([96, 97, 128, 129, 0, 5, 20, 2], 384, 384),
     ([16, 200, 0, 1], 640, 896), ([40, 70, 0, 100], 3328, 128)])

@@ -349,8 +349,8 @@ def test_ffn_degenerate_loads(counts):
 def test_fp8_weights_on_both_sides_of_the_kernel_switch(rows_per_expert):
     """e4m3 weights: up to twelve rows per expert (rows_capacity / n_experts) the
     weight-streaming kernel applies the block scale to fp32 partial sums, above it
-    the tall-tile kernel rounds code * scale to bf16.  Both must meet the fp8
-    tolerance against the exact product on the same kind of load."""
+    the short tiles do the same (one round of them here) and tall ones round code *
+    scale to bf16.  Both must meet the fp8 tolerance against the exact product on the same kind of load."""
     E = 8
     counts = [rows_per_expert] * E
     counts[0] += 5                          # ragged, and one expert above the average
@@ -472,14 +472,16 @@ def test_ffn_wide_tiles_of_short_groups(weight_dtype):
     assert np.array_equal(out, again)
 
 
-@pytest.mark.parametrize("weight_dtype", ["bf16", "fp8"])
-def test_ffn_k_split_beside_wide_tiles(weight_dtype):
+@pytest.mark.parametrize("weight_dtype,rows,long_rows", [("bf16", 50, 200), ("fp8", 50, 200), ("fp8", 70, 300)])
+def test_ffn_k_split_beside_wide_tiles(weight_dtype, rows, long_rows):
     """64 experts, hidden 3072, intermediate 1024: GEMM-1 (70 row tiles x 8 column
     tiles = 560, 48 more than two rounds of CUs) cuts the 48 leftover tiles along its
-    48 K steps into two parts each; GEMM-2 takes its wide tiles."""
-    counts = [50] * 64
+    48 K steps into two parts each; GEMM-2 takes its wide tiles.  e4m3 weights have
+    these tiles with 70 and 300 rows per expert; with 50 and 200 GEMM-1 takes the short
+    tiles of 64 rows (82 x 8)."""
+    counts = [rows] * 64
     for e in (3, 17, 20, 33, 48, 60):
-        counts[e] = 200
+        counts[e] = long_rows
     w, ids, tw = _forced_counts_case(counts, H=3072, I=1024, seed=5)
     w = w.replace(name="wide_split", weight_dtype=weight_dtype)
     d = inputs(w)

@@ -39,12 +39,15 @@ def _quantised(v):
     return (q.double() * s.double()[:, :, None]).view(r, k)
 
 
-def run_ffn(counts, H, I, fp8_acts=False, loose=1, gate_scale=1.0):
+def run_ffn(counts, H, I, fp8_acts=False, loose=1, row_scale=None):
     """One expert-FFN call on rows of given experts; returns (outputs, 64-bit reference, workspace)."""
     n, rows = len(counts), int(sum(counts))
     g = torch.Generator(device="cuda").manual_seed(H + I + rows)
     cfg = config_from_workload(BASE.replace(name="tile_choice", H=H, I=I, E=n, k=1, expert_lo=0, expert_hi=n))
-    x = torch.empty(rows * loose, H, device="cuda").normal_(0, 1, generator=g).bfloat16()
+    x = torch.empty(rows * loose, H, device="cuda").normal_(0, 1, generator=g)
+    if row_scale is not None:
+        x *= torch.tensor(row_scale, device="cuda")[torch.arange(len(x), device="cuda") % len(row_scale), None]
+    x = x.bfloat16()
     (wg, sg, dg), (wu, su, du), (wd, sd, dd) = (_weights(g, n, *s) for s in ((I, H), (I, H), (H, I)))
     ends = np.concatenate([[0], np.cumsum(counts)])
     offsets = torch.tensor(ends, dtype=torch.int32, device="cuda")
@@ -122,3 +125,33 @@ def test_e4m3_tiles(counts, H, I, loose, want):
     for (short, tallest), height in zip(tables(ws, sum(counts) * loose, len(counts)), want):
         assert short == (height is not None), (short, tallest)
         assert height is None or tallest <= height
+
+
+# K past 64 blocks of 128: each GEMM loads its block scales again at block 64.  e4m3 weights on short
+# tiles, GEMM-1 (one expert, 180 tiles) and GEMM-2 (80 experts, 4 column tiles), and on tall tiles
+# of few rows, cut along K; 8-bit activations with one, two and six row blocks a tile.
+@pytest.mark.parametrize("counts,H,I,want", [
+    ([11520], 8448, 128, [64, None]), ([14] * 80, 1024, 8448, [64, 64]),
+    ([40, 17], 8448, 128, [None, 64]), ([40, 17], 128, 8448, [64, None])],
+    ids=lambda v: str(v) if isinstance(v, int) else "")
+def test_e4m3_scales_past_64_blocks(counts, H, I, want):
+    got, ref, ws = run_ffn(counts, H, I)
+    check(got, ref, 1.5e-2, 6e-2)
+    for (short, _), height in zip(tables(ws, sum(counts), len(counts)), want):
+        assert short == (height is not None)
+
+
+@pytest.mark.parametrize("counts,H,I", [([33, 1, 64], 8320, 128), ([40, 192], 256, 8448), ([5], 16512, 128)])
+def test_fp8act_scales_past_64_blocks(counts, H, I):
+    got, ref, _ = run_ffn(counts, H, I, fp8_acts=True)
+    check(got, ref, 1.5e-2, 6e-2)
+
+
+# Intermediates past 2^90 and below 2^-90 take the quantiser's general division, all 32 rows of a
+# block or some of them; every row is compared at its own magnitude.
+@pytest.mark.parametrize("row_scale", [[2.0**50], [2.0**-50], [1.0, 2.0**50, 2.0**-50, 2.0**20]])
+def test_fp8act_quotients_near_the_ends_of_the_range(row_scale):
+    got, ref, _ = run_ffn([40, 0, 200, 31], 256, 256, fp8_acts=True, row_scale=row_scale)
+    norm = ref.abs().amax(1, keepdim=True)
+    assert bool((norm > 0).all())
+    check(got / norm, ref / norm, 1.5e-2, 6e-2)
