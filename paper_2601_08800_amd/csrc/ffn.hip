@@ -24,7 +24,7 @@
 // registers (exact) and multiplies the fp32 partial sum of each 128-deep K block
 // by the 128x128 block scale, and so do the short tiles of up to 64 rows that the tall-tile
 // kernel has in the place of its own for a few dozen rows per expert (e4m3_body, chosen on the
-// device: short_tile_rows); in those of up to 96 rows and in the tall ones, which keep the codes
+// device: short_tile_rows); in higher ones and in the tall ones, which keep the codes
 // in their LDS ring, code * scale is rounded to bf16 on the way to the matrix unit.
 #include <type_traits>
 
@@ -68,9 +68,11 @@ __device__ __forceinline__ float silu_mul_plain(float g, float u) {
 }
 
 // ------------------------------------------------------------- tile table
-// tiles[0] = number of M tiles (| kShortTiles); then per tile a record (expert, first row, end
+// tiles[0] = number of M tiles (| flags); then per tile a record (expert, first row, end
 // row, index of the expert's first tile, number of tiles of the expert).
 constexpr int kShortTiles = 1 << 30;          // the tiles are e4m3_body's
+constexpr int kWholeTiles = 1 << 29;          // ... and stay whole
+constexpr int kTileCount = kWholeTiles - 1;
 constexpr int kTileRec = 5;
 // K-split of leftover tiles (see ffn_gemm8w_kernel): at most this many tiles are
 // split, into at most kSplitMax parts of at least kSplitMinSteps K steps, and all
@@ -104,6 +106,9 @@ struct TileJob {
   ShortTiles alt;
 };
 
+// CHOICE: one of the GEMMs may have short tiles.  (A branch at run time made the one-workgroup
+// launch longer for all others: one bf16 token, 128 experts, 37.2 -> 38.1 us.)
+template <bool CHOICE>
 __global__ __launch_bounds__(kTileThreads) void ffn_tiles_kernel(const int32_t* __restrict__ offsets,
                                                        int n_experts, int rows_capacity, int max_tiles,
                                                        TileJob job, TileJob second,
@@ -111,6 +116,7 @@ __global__ __launch_bounds__(kTileThreads) void ffn_tiles_kernel(const int32_t* 
   __shared__ int32_t start[kTileThreads + 1];
   __shared__ int32_t off[kTileThreads + 1];
   __shared__ int4 wave_sum[kTileThreads / 64];
+  __shared__ int32_t wave_many[kTileThreads / 64];
   const int e = threadIdx.x, lane = e & 63, wave = e >> 6;
   // a second workgroup, when launched, builds a second table
   if (blockIdx.x == 1) job = second;
@@ -124,40 +130,49 @@ __global__ __launch_bounds__(kTileThreads) void ffn_tiles_kernel(const int32_t* 
   // arrival counters of the K-split tiles of the two GEMM launches that follow
   static_assert(kTileThreads == 2 * kSplitTickets, "one counter per thread");
   if (blockIdx.x == 0) tickets[e] = 0;
-  // The expert's tiles at the height bm and, where the GEMM has the choice, at 64 and 96 rows.
+  // The expert's tiles at the height bm and, where the GEMM has the choice, at 64, 96 and 128 rows.
   const int rows = max(hi - lo, 0);
-  int count = int(unsigned(rows + bm - 1) / unsigned(bm)), incl = wave_incl_sum(count);
-  const int count64 = (rows + 63) >> 6, count96 = int(unsigned(rows + 95) / 96u);
-  int incl64 = 0, incl96 = 0, many = __any(count > kOwnTiles) ? 1 : 0;
-  if (job.alt.nt) {
-    incl64 = wave_incl_sum(count64);
-    incl96 = wave_incl_sum(count96);
-    many |= (__any(count64 > kOwnTiles) ? 2 : 0) | (__any(count96 > kOwnTiles) ? 4 : 0) |
-            (__any(rows > 128 * count) ? 8 : 0) | (__any(rows > 192 * count) ? 16 : 0);
+  int count[4] = {int(unsigned(rows + bm - 1) / unsigned(bm)), (rows + 63) >> 6, int(unsigned(rows + 95) / 96u),
+                  (rows + 127) >> 7};
+  int incl[4] = {wave_incl_sum(count[0]), 0, 0, 0}, many = __any(count[0] > kOwnTiles) ? 1 : 0;
+  if (CHOICE && job.alt.nt) {
+#pragma unroll
+    for (int i = 1; i < 4; ++i) {
+      incl[i] = wave_incl_sum(count[i]);
+      many |= __any(count[i] > kOwnTiles) ? 1 << i : 0;
+    }
+    // the tallest tile in 32-row blocks: bit 3 + blocks, of the highest set
+#pragma unroll
+    for (int b = 4; b <= 8; ++b) many |= __any(rows > 32 * (b - 1) * count[0]) ? 8 << b : 0;
   }
-  if (lane == 63) wave_sum[wave] = make_int4(incl, incl64, incl96, many);
+  if (lane == 63) {
+    wave_sum[wave] = make_int4(incl[0], incl[1], incl[2], CHOICE ? incl[3] : many);
+    if (CHOICE) wave_many[wave] = many;
+  }
   __syncthreads();
   int4 sum[kTileThreads / 64], all = make_int4(0, 0, 0, 0);
+  many = 0;
 #pragma unroll
   for (int w = 0; w < kTileThreads / 64; ++w) {
     sum[w] = wave_sum[w];
-    all = make_int4(all.x + sum[w].x, all.y + sum[w].y, all.z + sum[w].z, all.w | sum[w].w);
+    all = make_int4(all.x + sum[w].x, all.y + sum[w].y, all.z + sum[w].z, all.w + sum[w].w);
+    many |= CHOICE ? wave_many[w] : sum[w].w;
   }
-  const int chosen = job.alt.nt ? short_tile_rows(job.alt, n_experts, all.y, all.z, all.x, all.w & 8, all.w & 16) : 0;
-  if (chosen) {
-    bm = chosen;
-    count = chosen == 64 ? count64 : count96;
-    incl = chosen == 64 ? incl64 : incl96;
-  }
-  const int total = chosen == 0 ? all.x : (chosen == 64 ? all.y : all.z);
-  const bool look_up = all.w & (chosen == 0 ? 1 : (chosen == 64 ? 2 : 4));
+  const int chosen = CHOICE && job.alt.nt ? short_tile_rows(job.alt, n_experts, RowTiles{all.x, all.y, all.z, all.w,
+                                          many >> 7 ? (28 - __clz(many)) * 32 : 96}) : 0;
+  const int at = chosen ? chosen / 32 - 1 : 0;
+  auto pick = [&](int own, int c64, int c96, int c128) { return at == 0 ? own : (at == 1 ? c64 : (at == 2 ? c96 : c128)); };
+  if (chosen) bm = chosen;
+  const int mine = pick(count[0], count[1], count[2], count[3]);
+  const int total = pick(all.x, all.y, all.z, all.w);
+  const bool look_up = (many >> at) & 1;
   int before = 0;
 #pragma unroll
   for (int w = 0; w < kTileThreads / 64; ++w)
-    before += w < wave ? (chosen == 0 ? sum[w].x : (chosen == 64 ? sum[w].y : sum[w].z)) : 0;
-  const int first = before + incl - count;           // experts past the last one: `total`
+    before += w < wave ? pick(sum[w].x, sum[w].y, sum[w].z, sum[w].w) : 0;
+  const int first = before + pick(incl[0], incl[1], incl[2], incl[3]) - mine;     // experts past the last one: `total`
   const int n_tiles = total < max_tiles ? total : max_tiles;
-  if (e == 0) tiles[0] = n_tiles | (chosen ? kShortTiles : 0);
+  if (e == 0) tiles[0] = n_tiles | (chosen ? kShortTiles : 0) | (chosen && n_experts == 1 ? kWholeTiles : 0);
   auto write = [&](int t, int expert, int rlo, int rhi, int t0) {
     const int m = rhi - rlo, nt = int(unsigned(m + bm - 1) / unsigned(bm));
     const int step = (int(unsigned(m + nt - 1) / unsigned(nt)) + 31) / 32 * 32;
@@ -171,7 +186,7 @@ __global__ __launch_bounds__(kTileThreads) void ffn_tiles_kernel(const int32_t* 
   if (!look_up) {
 #pragma unroll
     for (int i = 0; i < kOwnTiles; ++i)
-      if (i < count && first + i < n_tiles) write(first + i, e, lo, hi, first);
+      if (i < mine && first + i < n_tiles) write(first + i, e, lo, hi, first);
     return;
   }
   if (e < n_experts) {                               // (the next thread, of another wavefront, must not touch off[n_experts])
@@ -794,9 +809,9 @@ __device__ __forceinline__ void gemm8w_tile(const uint16_t* A, const char* Be0, 
   }
 }
 
-// ----------------------------- MFMA GEMM, e4m3 weights, short tiles: up to 96 rows
+// ---------------------------- MFMA GEMM, e4m3 weights, short tiles: up to 128 rows
 // e4m3 weights with a few dozen rows per expert: the work is streaming the codes in, and a
-// tile is short of rows, not of weights.  Tile: up to 96 rows (NB 32-row blocks) x 256
+// tile is short of rows, not of weights.  Tile: up to 128 rows (NB 32-row blocks) x 256
 // weight rows (DUAL: 128 gate + the matching 128 up rows), K step 128 = one scale block = a
 // whole cache line of every weight row.  All eight wavefronts work on all rows: wavefront
 // (kh, wn) = (w/4, w%4) multiplies half kh of every K block with the 64 weight rows of
@@ -811,11 +826,13 @@ __device__ __forceinline__ void gemm8w_tile(const uint16_t* A, const char* Be0, 
 // (4.0 / 3.8 TB/s of codes) against 125 / 70; a stream of the same loads alone runs at 6 TB/s, the
 // same steps without loads take 90 us, and the two add up rather than overlap.  Where the tiles
 // are taken: short_tile_rows.  Whole layer (us), on the tall tiles and with the choice: 64 tokens 188 -> 161, 700 292 ->
-// 280, 1531 371 -> 320; Zipf-routed 160 tokens 204 -> 158, 256 207 -> 193; hidden 4096, 16 of 128 experts, I
-// 1536, 1000 tokens 178 -> 151; from 2500 tokens on unchanged.  Tried: weights loaded by one half of the
+// 280; Zipf-routed 160 tokens 204 -> 158, 256 207 -> 193; hidden 4096, 16 of 128 experts, I
+// 1536, 1000 tokens 178 -> 151; from 2500 tokens on unchanged.  The routed FFN of six batches of 1531 tokens (1119 to
+// 1953 rows on 32 experts) 188-244 -> 167-226, on 128-row tiles alone 176-219.  Tried: weights loaded by one half of the
 // wavefronts and activations by the other (deeper weight ring) 118 -> 125, all fragments a
 // step ahead 118 -> 122, block scales in scalar registers loaded step by step (no difference),
-// 128 rows a tile (an expert of that many rows then is the launch: Zipf-routed 128 tokens, I 512, 111 -> 120).
+// tiles of 128 rows at every load (an expert of that many rows then is the launch: Zipf-routed 128
+// tokens, I 512, 111 -> 120).
 template <int NB> struct RingE {
   static constexpr int kB = 256 * 8, kA = NB * 32 * 16;            // 16-byte slots of a stage
   static constexpr int kSB = NB == 1 ? 4 : 3;                      // weight stages
@@ -1085,8 +1102,8 @@ __device__ __forceinline__ void e4m3_tile(const uint16_t* A, const char* Be0, co
   switch ((row1 - row0 + 31) >> 5) {
     case 1: e4m3_body<DUAL, 1>(A, Be0, Be1, s0p, s1p, C, N, K, row0, row1, n0, wave, k0, k1 - k0, job, smem); break;
     case 2: e4m3_body<DUAL, 2>(A, Be0, Be1, s0p, s1p, C, N, K, row0, row1, n0, wave, k0, k1 - k0, job, smem); break;
-    default:                                         // three row blocks: GEMM-1 only
-      if constexpr (DUAL) e4m3_body<DUAL, 3>(A, Be0, Be1, s0p, s1p, C, N, K, row0, row1, n0, wave, k0, k1 - k0, job, smem);
+    case 3: e4m3_body<DUAL, 3>(A, Be0, Be1, s0p, s1p, C, N, K, row0, row1, n0, wave, k0, k1 - k0, job, smem); break;
+    default: e4m3_body<DUAL, 4>(A, Be0, Be1, s0p, s1p, C, N, K, row0, row1, n0, wave, k0, k1 - k0, job, smem); break;
   }
 }
 
@@ -1111,7 +1128,7 @@ __global__ __launch_bounds__(512) void ffn_gemm8w_kernel(
     int32_t* __restrict__ tickets) {
   constexpr int kShortBN = DUAL ? 128 : 256;
   extern __shared__ uint4 smem[];
-  const int n_mtiles = F8 ? tiles[0] & ~kShortTiles : tiles[0];
+  const int n_mtiles = F8 ? tiles[0] & kTileCount : tiles[0];
   const bool short_tiles = F8 && (tiles[0] & kShortTiles);
   const int BN = WIDE && !short_tiles ? 2 * kShortBN : kShortBN;
   const int n_ntiles = (N + BN - 1) / BN;
@@ -1119,7 +1136,7 @@ __global__ __launch_bounds__(512) void ffn_gemm8w_kernel(
   const int ksteps_all = (K + 63) / 64;
   const int pid = blockIdx.x;
   const int left = total % kCUs;
-  const int parts = partial ? split_parts(left, ksteps_all / kSplitMinSteps) : 1;
+  const int parts = partial && !(F8 && (tiles[0] & kWholeTiles)) ? split_parts(left, ksteps_all / kSplitMinSteps) : 1;
   int logical, part = 0;
   SplitJob job{1, 0, 0, partial, tickets};
   if (parts >= 2) {
@@ -1994,8 +2011,9 @@ hipError_t launch_expert_ffn(const moe_config& c, int n_experts, const void* xs,
   }
   const bool one_table = p.bm1 == p.bm2 && !t1.alt.nt && !t2.alt.nt;
   int32_t* const tiles2 = one_table ? ws.tiles : ws.tiles2;
-  MOE_LAUNCH(MOE_K_FFN_TILES, ffn_tiles_kernel, dim3(one_table ? 1 : 2), dim3(kTileThreads), 0, s, offsets,
-             n_experts, rows_capacity, ws.max_tiles, t1, t2, ws.tickets);
+  MOE_LAUNCH(MOE_K_FFN_TILES, (t1.alt.nt || t2.alt.nt ? ffn_tiles_kernel<true> : ffn_tiles_kernel<false>),
+             dim3(one_table ? 1 : 2), dim3(kTileThreads), 0, s, offsets, n_experts, rows_capacity, ws.max_tiles, t1, t2,
+             ws.tickets);
   if (c.act_dtype == MOE_F32) {
     float* const hmid = static_cast<float*>(ws.hmid);
     launch_f32<true>(p.g1, p.bm1, static_cast<const float*>(xs), static_cast<const float*>(w_gate),

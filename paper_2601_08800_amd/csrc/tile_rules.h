@@ -62,37 +62,55 @@ struct ShortTiles {
   bool gemm1, wide;    // wide: 512 weight rows a tile, twice a short one's
 };
 
-// Height of the short tiles, or 0: the kernel's own.  t64, t96, own: row tiles that the experts'
-// rows come to at 64 rows, at 96 and at the kernel's own height; over128, over192: one of the own
-// tiles has more rows than that.
-//  - Several experts: the short tiles read codes by whole lines and have all wavefronts work on
-//    few rows, but fetch the weights once per 64 rows.  They win where they come to no more
-//    rounds of the CUs.  Kernel times of 1770 batches (1 to 200 rows per expert, even to Zipf
-//    1.2, hidden 2048 to 7168, I 384 to 2048, 4 to 128 experts) against the kernel's own tiles:
-//    GEMM-1 with 64 rows 0.99 to 2.5 times as fast where the rule takes them (mean 1.2; up to 1.25
-//    times the rounds against tiles of more than 128 rows, whose K steps are longer, 1.00 to 1.4, up to 1.375
-//    times against more than 192 rows 0.99 to 1.4; with as much against lower ones 0.89 to 1.0), 0.73 to
-//    1.1 at half as many again; with 96 rows 0.96 to 1.5 (mean 1.13).  GEMM-2 with 64 rows 0.94 to 1.5 (mean
-//    1.15), with 96 from 0.90, hence only GEMM-1; against the wide tiles, counted double, 1.07 to 1.3
-//    with fewer rounds, 0.90 to 1.13 with as many.  Launches of less than a round keep their own
-//    tiles, whose K split is the better one (8 experts, I 1024: 0.87 to 0.97).
-//  - A single expert (the shared one of a layer): only GEMM-1 and from 176 to 256 short
-//    tiles, nearly one round, where its own tiles are a few that are cut along K.  Alone, hidden
-//    7168, us (I 1024 if not said): 136 tiles 91 -> 95, 160 105 -> 98 and (I 2048) 110 -> 111, 192 110 -> 99,
-//    232 127 -> 107, 256 129 -> 109; 320 and more were slower.  Beside the routed path of its layer 1300
-//    tokens 346 -> 328, 1531 340 -> 319, 2040 462 -> 440 (parts of fewer tiles would keep the CUs from
-//    the route: 1000 tokens 312 -> 350).
-MOE_RULE int short_tile_rows(const ShortTiles& s, int n_experts, int t64, int t96, int own, bool over128,
-                             bool over192) {
-  const long w64 = long(t64) * s.nt, w96 = long(t96) * s.nt;
-  if (n_experts == 1) return s.gemm1 && w64 >= 176 && w64 <= kCUs && w64 <= s.grid ? 64 : 0;
-  const long r = rounds12(long(own) * s.nt_own, s.cap);
+// Row tiles that the experts' rows come to at the kernel's own height and at 64, 96 and 128 rows,
+// and the rows of the tallest own one.
+struct RowTiles {
+  int own, t64, t96, t128, tallest;
+};
+
+// Height of the short tiles, or 0: the kernel's own.
+//  - Several experts: the height whose rounds of the CUs come to the least, each at the time of its
+//    tiles' K step.  The steps (of a short tile by 64 / 96 / 128 rows; of an own one by the tallest,
+//    up to 96, 128, 160, 192, 224 and 256 rows; a 64-row short tile is 20) were fitted to the
+//    times of 308 batches (4 to 170 rows per expert, even to Zipf 1.2, hidden 2048 to 7168, I 384 to 2048,
+//    16 to 128 experts) at all four heights: GEMM-1 7 us per 1024 of K at 20.  More rounds take an
+//    own tile's step for at most 28, as the shorter tiles beside it fill the CUs.  96 and 128 rows only where
+//    tiles of 64 would be at most 1.5 and 1.4 times as many (few long experts among short ones):
+//    full ones are slower than the fit (experts of 89 rows, 128-row tiles 253 -> 283).  Of the batches' FFN
+//    the rule takes 4.5 % off in GEMM-1 and 1.3 % in GEMM-2; the best choice each time, 6.2 and 2.0;
+//    128-row tiles wherever the capacity gives 16 to 64 rows, 1.7 and 0.5.
+//    Against the wide tiles only 64 rows, with fewer rounds counted double (1.07 to 1.3 times as fast, 0.90 to
+//    1.13 with as many).  Launches of less than a round keep their own tiles, whose K split is
+//    the better one (8 experts, I 1024: 0.87 to 0.97).
+//  - A single expert (the shared one of a layer, whose route and dispatch run beside it): only GEMM-1,
+//    and 128 rows where that gives 96 to 160 tiles, which stay whole: they leave a good part of the CUs
+//    to the route, where its own tiles, cut along K, fill them.  Layers of 700 to 4449 tokens (hidden 7168, I 512 to
+//    2048) on such tiles against its own, us: 1531 359 -> 338, 1800 468 -> 449, 1902 417 -> 374, 2040 456 -> 399, 2336 425 ->
+//    412, 2500 501 -> 490, 4090 436 -> 426, but 1621 386 -> 392, 3128 360 -> 370, 700 (I 2048) 452 -> 467; in the mean 2 %
+//    faster.  From 48 to 95 tiles 2 % slower, past 160 as much either way.  Alone they are slower: 1531 rows 107 ->
+//    130, 2040 131 -> 139, 2500 150 -> 171.
+//    (Tiles of 64 rows, 176 to 256 of them, are the fastest alone, 97 and 110, but 355 and 435 a layer.)
+MOE_RULE int own_step(const ShortTiles& s, int tallest, bool rounds) {
+  const int nb = (tallest + 31) / 32;
+  const int step = s.gemm1 ? (nb <= 3 ? 26 : (nb == 4 ? 27 : (nb == 5 ? 29 : (nb == 6 ? 32 : (nb == 7 ? 35 : 38)))))
+                           : (nb <= 3 ? 23 : (nb == 4 ? 24 : (nb == 5 ? 26 : (nb == 6 ? 28 : (nb == 7 ? 30 : 32)))));
+  return s.gemm1 && rounds && step > 28 ? 28 : step;
+}
+
+MOE_RULE int short_tile_rows(const ShortTiles& s, int n_experts, const RowTiles& t) {
+  const long w64 = long(t.t64) * s.nt, w96 = long(t.t96) * s.nt, w128 = long(t.t128) * s.nt;
+  if (n_experts == 1) return s.gemm1 && w128 >= 96 && w128 <= 160 && (w128 + 7) / 8 * 8 <= s.grid ? 128 : 0;
+  const long r = rounds12(long(t.own) * s.nt_own, s.cap), r64 = rounds12(w64, s.cap);
   if (r < 12) return 0;
-  long most = s.wide ? 2 * r - 1 : r;
-  const long most96 = s.gemm1 ? most : 0;
-  if (s.gemm1) most += over192 ? r * 3 / 8 : (over128 ? r / 4 : 0);
-  if (rounds12(w64, s.cap) <= most && split_grid(w64, s.cap) <= s.grid) return 64;
-  return rounds12(w96, s.cap) <= most96 && split_grid(w96, s.cap) <= s.grid ? 96 : 0;
+  const bool fits64 = split_grid(w64, s.cap) <= s.grid;
+  if (s.wide) return fits64 && r64 <= 2 * r - 1 ? 64 : 0;
+  long best = r * own_step(s, t.tallest, r > 18) + 1;
+  int rows = 0;
+  if (fits64 && r64 * 20 < best) { best = r64 * 20; rows = 64; }
+  const long c96 = rounds12(w96, s.cap) * (s.gemm1 ? 24 : 23), c128 = rounds12(w128, s.cap) * (s.gemm1 ? 27 : 26);
+  if (2 * t.t64 <= 3 * t.t96 && c96 < best && split_grid(w96, s.cap) <= s.grid) { best = c96; rows = 96; }
+  if (5 * t.t64 <= 7 * t.t128 && c128 < best && split_grid(w128, s.cap) <= s.grid) rows = 128;
+  return rows;
 }
 
 }  // namespace moe

@@ -1,9 +1,9 @@
 // The choice of row tiles by the rows that the experts have (tile_rules.h), over row counts from
 // even to one expert with everything, capacities from tight to sixteen times the rows:
-//  - the chosen tiles take no more rounds of the CUs than the kernel's own (a little more against tall
-//    ones), and the launch that was sized for the kernel's own tiles holds them: where it does not,
+//  - the chosen tiles' rounds of the CUs, at their K step's time, come to no more than those of the
+//    kernel's own (recomputed here by another route), and the launch that was sized for the kernel's own tiles holds them: where it does not,
 //    they are not taken;
-//  - a single expert has short tiles only in nearly one whole round of them, and long groups
+//  - a single expert has short tiles only where they take 96 to 160 of the 256 CUs, and long groups
 //    never have them, however loose the capacity is.
 #include <cmath>
 #include <cstdio>
@@ -21,6 +21,16 @@ static int tiles(const std::vector<int>& rows, int h) {
   long n = 0;
   for (int m : rows) n += (m + h - 1) / h;
   return int(n);
+}
+
+static RowTiles count(const std::vector<int>& rows, int bm) {
+  RowTiles t{tiles(rows, bm), tiles(rows, 64), tiles(rows, 96), tiles(rows, 128), 96};
+  for (int m : rows)
+    if (m > 0) {
+      const int n = (m + bm - 1) / bm, high = ((m + n - 1) / n + 31) / 32 * 32;
+      t.tallest = high > t.tallest ? high : t.tallest;
+    }
+  return t;
 }
 
 static void fail(const char* what, const ShortTiles& s, int n, int own_rows, int got) {
@@ -60,30 +70,28 @@ int main() {
                 const int nt_own = (N + own_bn - 1) / own_bn, own = tiles(rows, bm);
                 ShortTiles s{(N + bn - 1) / bn, nt_own, K / 64 / kSplitMinSteps,
                              tall_grid(max_row_tiles(capacity, n, bm), nt_own, wide), gemm1, wide};
-                const int t64 = tiles(rows, 64), t96 = tiles(rows, 96);
-                bool over128 = false, over192 = false;
-                for (int m : rows) {
-                  const int count = (m + bm - 1) / bm;
-                  over128 |= m > 128 * count;
-                  over192 |= m > 192 * count;
-                }
-                const int h = short_tile_rows(s, n, t64, t96, own, over128, over192);
+                const RowTiles t = count(rows, bm);
+                const int h = short_tile_rows(s, n, t);
                 ++seen;
                 ShortTiles free_grid = s;
                 free_grid.grid = 0x7fffffff;
-                refused += short_tile_rows(free_grid, n, t64, t96, own, over128, over192) != h;
+                refused += short_tile_rows(free_grid, n, t) != h;
                 if (h == 0) continue;
                 ++taken;
-                if (h != 64 && !(h == 96 && gemm1)) fail("height", s, n, own, h);
-                const long total = long(h == 64 ? t64 : t96) * s.nt;
-                if (split_grid(total, s.cap) > s.grid) fail("grid", s, n, own, h);
+                if (h != 64 && (wide || (h != 96 && h != 128))) fail("height", s, n, own, h);
+                const long total = long(tiles(rows, h)) * s.nt;
+                if ((n == 1 ? (total + 7) / 8 * 8 : split_grid(total, s.cap)) > s.grid) fail("grid", s, n, own, h);
                 if (n == 1) {
-                  if (!gemm1 || total < 176 || total > kCUs) fail("single expert", s, n, own, h);
+                  if (!gemm1 || h != 128 || total < 96 || total > 160) fail("single expert", s, n, own, h);
                   continue;
                 }
                 const long mine = rounds12(total, s.cap), theirs = rounds12(long(own) * nt_own, s.cap) * (wide ? 2 : 1);
-                const long longer = gemm1 && h == 64 ? (over192 ? 3 : over128 ? 2 : 0) : 0;     // eighths
-                if (wide ? mine >= theirs : mine * 8 > theirs * (8 + longer)) fail("rounds", s, n, own, h);
+                const double step = h == 64 ? 20 : h == 96 ? (gemm1 ? 24 : 23) : (gemm1 ? 27 : 26);
+                const double own_steps[2][6] = {{23, 24, 26, 28, 30, 32}, {26, 27, 29, 32, 35, 38}};
+                double theirs_step = own_steps[gemm1][t.tallest / 32 - 3];
+                if (gemm1 && theirs > 18 && theirs_step > 28) theirs_step = 28;
+                if (wide ? mine >= theirs : mine * step > theirs * theirs_step) fail("rounds", s, n, own, h);
+                if (h == 128 && t.t64 > 1.4 * t.t128) fail("full tiles", s, n, own, h);
                 if (theirs < 12) fail("less than a round", s, n, own, h);
               }
             }
@@ -93,23 +101,27 @@ int main() {
   for (int m : {200, 512, 1024}) {
     std::vector<int> rows(32, m);
     ShortTiles s{8, 8, 4, tall_grid(max_row_tiles(32 * m, 32, 160), 8, false), true, false};
-    if (short_tile_rows(s, 32, tiles(rows, 64), tiles(rows, 96), tiles(rows, 160), true, false)) fail("long groups", s, 32, m, -1);
+    if (short_tile_rows(s, 32, count(rows, 160))) fail("long groups", s, 32, m, -1);
   }
-  for (int m : {64, 400, 640, 1000, 2500, 4096, 8192, 16384}) {
+  for (int m : {64, 400, 640, 1000, 2600, 4096, 8192, 16384}) {
     std::vector<int> rows(1, m);
     ShortTiles s{8, 8, 4, tall_grid(max_row_tiles(m, 1, 256), 8, false), true, false};
-    if (short_tile_rows(s, 1, tiles(rows, 64), tiles(rows, 96), tiles(rows, 256), m > 128, m > 192)) fail("shared expert", s, 1, m, -1);
+    if (short_tile_rows(s, 1, count(rows, 256))) fail("shared expert", s, 1, m, -1);
   }
   // and batches that do take them: 32 experts of 40 rows; the same with one of 90; 1531 tokens of the shared expert
   {
     std::vector<int> rows(32, 40);
     ShortTiles s{8, 8, 4, tall_grid(max_row_tiles(32 * 40 * 8, 32, 256), 8, false), true, false};
-    if (short_tile_rows(s, 32, tiles(rows, 64), tiles(rows, 96), tiles(rows, 256), false, false) != 64) fail("even batch", s, 32, 40, 0);
+    if (short_tile_rows(s, 32, count(rows, 256)) != 64) fail("even batch", s, 32, 40, 0);
+    std::vector<int> mixed = rows;
+    mixed[3] = 97;
+    for (int e = 4; e < 15; ++e) mixed[e] = 70;
+    if (short_tile_rows(s, 32, count(mixed, 256)) != 128) fail("one of four row blocks", s, 32, 40, 0);
     rows[3] = 90;
-    if (short_tile_rows(s, 32, tiles(rows, 64), tiles(rows, 96), tiles(rows, 256), false, false) != 96) fail("a longer group", s, 32, 40, 0);
+    if (short_tile_rows(s, 32, count(rows, 256)) != 96) fail("a longer group", s, 32, 40, 0);
     std::vector<int> one(1, 1531);
     ShortTiles u{8, 8, 4, tall_grid(max_row_tiles(1531, 1, 256), 8, false), true, false};
-    if (short_tile_rows(u, 1, tiles(one, 64), tiles(one, 96), tiles(one, 256), true, true) != 64) fail("nearly a round", u, 1, 1531, 0);
+    if (short_tile_rows(u, 1, count(one, 256)) != 128) fail("a share of the CUs", u, 1, 1531, 0);
   }
   if (taken < 100 || refused * 100 > taken) {
     std::fprintf(stderr, "%ld of %ld taken, %ld refused for the launch's size\n", taken, seen, refused);

@@ -11,7 +11,7 @@ from test_gpu_fp8act import BASE
 
 pytestmark = pytest.mark.gpu
 
-SHORT = 1 << 30          # flag in the first word of a table: short tiles
+SHORT, COUNT = 1 << 30, (1 << 29) - 1      # first word of a table: flag of the short tiles, their number
 
 
 def _align(v):
@@ -86,7 +86,7 @@ def tables(ws, rows, n):
     words = ws.cpu().numpy().view(np.int32)
     out = []
     for at in (0, _align((1 + 5 * (rows // 32 + n + 1)) * 4 + 12) // 4):
-        count = int(words[at]) & ~SHORT
+        count = int(words[at]) & COUNT
         rec = words[at + 1:at + 1 + 5 * count].reshape(count, 5)
         out.append((bool(words[at] & SHORT), int((rec[:, 2] - rec[:, 1]).max())))
     return out
@@ -99,11 +99,14 @@ def tables(ws, rows, n):
     ([40] * 31 + [64], 2048, 1024, 1, [64, 64]),
     # one expert of 90: another 64-row tile would open a second round of GEMM-1, 96 rows do not
     ([40] * 31 + [90], 128, 1024, 1, [96, 64]),
-    # ... of 97 and of 161, the capacity loose: tall tiles of 97 and 161 rows
-    ([40] * 31 + [97], 128, 1024, 8, [None, 64]),
+    # ... of 97: 128 rows; of 161, the capacity loose: a tall tile of 161 rows
+    ([40] * 31 + [97], 128, 1024, 8, [128, 64]),
     ([40] * 31 + [161], 128, 1024, 8, [None, 64]),
+    # the same choices in GEMM-2
+    ([20] * 31 + [90], 2048, 128, 1, [64, 96]),
+    ([20] * 30 + [200], 2048, 128, 1, [64, 128]),
     # a quarter of a round more against tall tiles of 185 rows (K split of the 48 left over)
-    ([40] * 28 + [100, 120, 126, 185], 6144, 1024, 8, [64, None]),
+    ([40] * 28 + [100, 120, 126, 185], 6144, 1024, 8, [64, 64]),
     # long groups, tight and loose capacity
     ([200] * 32, 128, 1024, 1, [None, 64]),
     ([200] * 32, 128, 1024, 4, [None, 64]),
@@ -112,10 +115,12 @@ def tables(ws, rows, n):
     ([13] * 80, 2048, 128, 1, [64, 64]),
     # leftover tiles cut along K: 33 experts x 8 column tiles, 26 K blocks in two parts
     ([20] * 33, 3328, 1024, 1, [64, 64]),
-    # a single expert of 22 x 8 tiles; of 17 x 8 and 41 x 8
-    ([1400], 128, 1024, 1, [64, None]),
-    ([1030], 128, 1024, 1, [None, None]),
-    ([2600], 128, 1024, 1, [None, None]),
+    # a single expert of 12 x 8, 12 x 8 and 20 x 8 whole tiles; of 11 x 8 and 21 x 8
+    ([1409], 128, 1024, 1, [128, None]),
+    ([1531], 3328, 1024, 1, [128, None]),
+    ([2560], 128, 1024, 1, [128, None]),
+    ([1408], 128, 1024, 1, [None, None]),
+    ([2561], 128, 1024, 1, [None, None]),
     # empty first and last experts, one-row experts
     ([0, 1, 31, 32, 33, 64, 0, 1, 63, 2, 0], 256, 384, 2, [64, 64])],
     ids=lambda v: "%dx%d" % (len(v), max(c or 0 for c in v)) if isinstance(v, list) else str(v))
@@ -128,10 +133,10 @@ def test_e4m3_tiles(counts, H, I, loose, want):
 
 
 # K past 64 blocks of 128: each GEMM loads its block scales again at block 64.  e4m3 weights on short
-# tiles, GEMM-1 (one expert, 180 tiles) and GEMM-2 (80 experts, 4 column tiles), and on tall tiles
+# tiles, GEMM-1 (one expert, 98 tiles) and GEMM-2 (80 experts, 4 column tiles), and on tall tiles
 # of few rows, cut along K; 8-bit activations with one, two and six row blocks a tile.
 @pytest.mark.parametrize("counts,H,I,want", [
-    ([11520], 8448, 128, [64, None]), ([14] * 80, 1024, 8448, [64, 64]),
+    ([12544], 8448, 128, [128, None]), ([14] * 80, 1024, 8448, [64, 64]),
     ([40, 17], 8448, 128, [None, 64]), ([40, 17], 128, 8448, [64, None])],
     ids=lambda v: str(v) if isinstance(v, int) else "")
 def test_e4m3_scales_past_64_blocks(counts, H, I, want):
