@@ -28,10 +28,10 @@
 // step (memory phase) take longer than its MFMAs and the two row halves take turns.  Against
 // 128 x 128 tiles of four wavefronts, two workgroups per CU, all loads of a step waited for at
 // once, and passes of their own for the intermediate's quantisation (one stream, us): 6007
-// tokens of 7168, 32 of 256 experts, I 1024: routed GEMM-1 / -2 163 / 89 -> 165 / 83, one
-// expert of 6007 rows 133 / 73 -> 97 / 69, quantisation 16 -> 0; whole layer 673 -> 605; 24 576
+// tokens of 7168, 32 of 256 experts, I 1024: routed GEMM-1 / -2 163 / 89 -> 161 / 82, one
+// expert of 6007 rows 133 / 73 -> 92 / 67, quantisation 16 -> 0; whole layer 673 -> 605; 24 576
 // tokens 2078 -> 1793, I 2048 3483 -> 2834; 256 tokens 233 -> 207.
-// Also measured (one expert of 6144 rows, GEMM-1 97): both halves in one phase with the next
+// Also measured (one expert of 6144 rows, GEMM-1 97, with the weight block scales not yet in lanes): both halves in one phase with the next
 // fragments read under the last block's MFMAs 103, the same with loads spread over the row
 // blocks 111; 16 x 16 x 128 instructions 98-105; reads in front of the loads 101.
 
